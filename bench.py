@@ -369,7 +369,8 @@ def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
             "status_ok": int((status == 0).sum())}
 
 
-PHASES = [("load_prec", 0, 1), ("setup", 1, 2), ("initial_approx", 2, 3), ("one_wave_iters", 3, 4)]
+# the four stamps of a block of quotient limbs in the body
+BLOCK_PHASES = ["top_digits", "quotient_product", "quotient_digits", "remainder_update"]
 
 
 RT_HZ = 100e6   # rate of the real-time counter (s_memrealtime)
@@ -432,29 +433,18 @@ def phase_trace(args):
     st = np.zeros((batch, 32), dtype=np.uint64)
     assert L.mp_trace_read_divrem(st.ctypes.data, batch) == 0
     st = st.astype(np.float64)
-    full = (st[:, :9] > 0).all(axis=1) & (np.diff(st[:, :9], axis=1) >= 0).all(axis=1)
+    order = [0, 1, 2, 6, 7, 8]                       # stamps of every instance that is divided in blocks
+    full = (st[:, order] > 0).all(axis=1) & (np.diff(st[:, order], axis=1) >= 0).all(axis=1)
+    full &= (st[:, 16:20] > 0).all(axis=1) & (st[:, 16] >= st[:, 2]) & (st[:, 6] >= st[:, 19])
     rows = st[full]
-    res = {}
-    for name, a, b in PHASES:
-        res[name] = float(np.mean(rows[:, b] - rows[:, a]))
-    prev = rows[:, 4].copy()
-    last = prev.copy()
-    for i in range(16):
+    res = {"record": float(np.mean(rows[:, 1] - rows[:, 0])), "operands": float(np.mean(rows[:, 2] - rows[:, 1]))}
+    prev = rows[:, 2].copy()
+    for i in range(16):                              # four stamps per block, the last four blocks
         col = rows[:, 16 + i]
-        if not (col > 0).any():
-            continue
-        res["iter_%d" % i] = float(np.mean(col - prev))
-        prev = np.where(col > 0, col, prev)
-        last = prev
-    res["u_times_s"] = float(np.mean(rows[:, 5] - last))
-    # sub-steps of the last Refine iteration (stamps 11-13 hold its values)
-    it_end = [16 + i for i in range(16) if (rows[:, 16 + i] > 0).any()]
-    if len(it_end) >= 2 and (rows[:, [11, 12, 13]] > 0).all():
-        prev_end, end = rows[:, it_end[-2]], rows[:, it_end[-1]]
-        res["last_iter_powdiff_product"] = float(np.mean(rows[:, 11] - prev_end))
-        res["last_iter_residual"] = float(np.mean(rows[:, 12] - rows[:, 11]))
-        res["last_iter_step_product"] = float(np.mean(rows[:, 13] - rows[:, 12]))
-        res["last_iter_step_add"] = float(np.mean(end - rows[:, 13]))
+        if not (col > 0).all():
+            break
+        res["block_%d_%s" % (i // 4, BLOCK_PHASES[i % 4])] = float(np.mean(col - prev))
+        prev = col
     # the head launch (one wave per instance): its own stamps
     L.mp_trace_read_head.argtypes = [ctypes.c_void_p, ctypes.c_int]
     L.mp_trace_read_head.restype = ctypes.c_int
@@ -501,31 +491,10 @@ def phase_trace(args):
         head["record"] = float(np.mean(hr[:, 4] - prev_h))
         head["total"] = float(np.mean(hr[:, 4] - hr[:, 0]))
         head["span_all_waves"] = float(hr[:, 4].max() - hr[:, 0].min())
-    res["v_times_q"] = float(np.mean(rows[:, 6] - rows[:, 5]))
     res["corrections"] = float(np.mean(rows[:, 7] - rows[:, 6]))
     res["store"] = float(np.mean(rows[:, 8] - rows[:, 7]))
     total = float(np.mean(rows[:, 8] - rows[:, 0]))
-    # every product of the body: shape, conversion, strips of the first wave, carries
-    L.mp_trace_read_products.argtypes = [ctypes.c_void_p, ctypes.c_int]
-    L.mp_trace_read_products.restype = ctypes.c_int
-    pt = np.zeros((batch, 48, 6), dtype=np.uint64)
-    assert L.mp_trace_read_products(pt.ctypes.data, batch) == 0
-    prods = []
-    ptf = pt[full]
-    ref = ptf[0]
-    for j in range(48):
-        # the instances whose j-th product has the reference instance's shape
-        same = (ptf[:, j, 0] == ref[j, 0]) & (ptf[:, j, 1] == ref[j, 1]) & (ptf[:, j, 5] >= ptf[:, j, 2]) & \
-            (ptf[:, j, 2] > 0)
-        if ref[j, 2] == 0 or not same.any():
-            break
-        r = ptf[same][:, j, :].astype(np.float64)
-        sh0, sh1 = int(ref[j, 0]), int(ref[j, 1])
-        prods.append({"short": sh0 & 0xFFFFFFFF, "long": sh0 >> 32, "ncols": sh1 & 0xFFFFFFFF, "c0": sh1 >> 32,
-                      "instances": int(same.sum()),
-                      "operands": float(np.mean(r[:, 3] - r[:, 2])), "strips": float(np.mean(r[:, 4] - r[:, 3])),
-                      "carries": float(np.mean(r[:, 5] - r[:, 4])), "total": float(np.mean(r[:, 5] - r[:, 2]))})
-    print(json.dumps({"phase_trace": c["name"], "kernel": "k_divrem<256>", "head": head, "products": prods,
+    print(json.dumps({"phase_trace": c["name"], "kernel": "k_divrem<256>", "head": head,
                       "instances": int(full.sum()),
                       "knobs": knobs_now(), "clock": "shader cycles (s_memtime) of workgroup thread 0",
                       "body_clock": clock_stats(st[:, 0], st[:, 8], st[:, 14], st[:, 15], e0.elapsed_time(e1)),
@@ -583,7 +552,7 @@ def knobs_now():
     from paper_2606_06386_amd import binding
     sl = binding.get_knob(binding.MP_KNOB_SMALL_LIMIT)
     return {"mfma_min": binding.get_knob(binding.MP_KNOB_MFMA_MIN),
-            "small_limit": "auto (136 with several rounds of workgroups, else 96)"
+            "small_limit": "auto (136)"
             if sl == binding.MP_SMALL_LIMIT_AUTO else sl}
 
 

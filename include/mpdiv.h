@@ -62,8 +62,8 @@ mp_status_t mp_mul_batch(const uint32_t *a, int32_t na, const uint32_t *b, int32
                          uint32_t *c, int32_t batch, void *stream);
 
 /*
- * w = floor(B^h / v) for each instance, exactly (Definition 1, computed by
- * Alg. 1 and corrected to the exact value).
+ * w = floor(B^h / v) for each instance, exactly (Definition 1): the quotient
+ * of B^h by v, computed as mp_divrem_batch does.
  *   v: batch x nv limbs (1 <= nv <= mp_max_limbs()), h: 0 <= h <= mp_max_limbs(),
  *   w: batch x nw limbs, zero-padded; nw >= h - prec(v) + 2 always suffices
  *   (h + 1 for any v).
@@ -73,13 +73,13 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
                            int32_t *inst_status, int32_t batch, void *stream);
 
 /*
- * Quotient and remainder of u by v for each instance (Alg. 3: the quotient
- * q0 from the top limbs of u times the shifted inverse of v, then
- * corrections.  Theorem 2's range for q0, widened by the clipped products,
- * is q - 4 <= q0 <= q + 3, so the remainder u - v q0 reaches [0, v) after at
- * most three additions or four subtractions of v; one more of each is
- * allowed, and an instance needing more reports MP_INST_INTERNAL instead of
- * a wrong result).
+ * Quotient and remainder of u by v for each instance (Alg. 3 by
+ * blocks of quotient limbs: each block is the top of the remainder times a
+ * shifted inverse of v of one block's precision, and its product with v comes
+ * off the remainder, which stays in (-1.1 v, 2.1 v) at the block's scale; so
+ * at the end one addition or two subtractions of v reach [0, v).  Up to four
+ * are allowed, and an instance needing more reports MP_INST_INTERNAL instead
+ * of a wrong result).
  *   u: batch x nu limbs, v: batch x nv limbs, 1 <= nu, nv <= mp_max_limbs();
  *   q: batch x nq limbs, zero-padded; nq >= nu - prec(v) + 1 suffices (nu always);
  *   r: batch x nv limbs, zero-padded;
@@ -166,20 +166,17 @@ mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
  *                        limbs (>= 1) run on the int8 matrix cores as exact
  *                        balanced radix-256 digit products; shorter ones on the
  *                        vector ALU (32x32->64-bit multiply-adds).  Default 64.
- *   MP_KNOB_SMALL_LIMIT  Alg. 1's initial approximation and the Refine
- *                        iterations whose iterate has fewer than this many
- *                        limbs (0..140) run in a separate head launch, one wave
- *                        per instance, before the per-instance workgroups do
- *                        the rest; the head leaves its state in the first
- *                        limbs of the instance's q (mp_shinv_batch: w) row,
- *                        which the final result then overwrites.  0 (or an
- *                        output row shorter than 16 limbs) runs every step in
- *                        the per-instance workgroups.  MP_SMALL_LIMIT_AUTO
- *                        (the default) chooses per launch: 136 when the batch
- *                        needs more than one round of per-instance workgroups
- *                        on the device (the head runs all instances at once,
- *                        so its longer iterations are paid once and saved in
- *                        every round), 96 otherwise.
+ *   MP_KNOB_SMALL_LIMIT  the quotient is found in blocks of limbs from an
+ *                        inverse of one block's precision, which a head
+ *                        launch computes, one wave per instance, by Refine
+ *                        iterations whose iterates have fewer than this many
+ *                        limbs (0..140; below 16 counts as 16), so it bounds
+ *                        the block: 257 limbs from 133 on.  The head leaves
+ *                        the inverse in the longer of the instance's q and r
+ *                        rows (mp_shinv_batch: w), which the results then
+ *                        overwrite; instances whose rows are shorter than 27
+ *                        limbs make a small inverse in their own workgroup.
+ *                        MP_SMALL_LIMIT_AUTO (the default) is 136.
  * mp_set_knob returns MP_ERR_ARG for an unknown knob or a value out of range;
  * mp_get_knob returns the current value (-1 for an unknown knob).
  */

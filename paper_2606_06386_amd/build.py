@@ -19,7 +19,7 @@ TRACE_LIB = os.path.join(HERE, "libmpdiv_trace.so")
 # instruction issue-rate probe (calibrates the integer-multiply roofline)
 PROBE_LIB = os.path.join(HERE, "libmpprobe.so")
 PROBE_SOURCES = [os.path.join(CSRC, "probe_rates.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("mp_prims_hip.hpp", "mp_core.hpp", "mp_div.hpp", "launch.hpp")]
+HEADERS = [os.path.join(CSRC, f) for f in ("mp_prims_hip.hpp", "mp_core.hpp", "mp_div.hpp", "mp_block.hpp", "launch.hpp")]
 
 # (object name, source, defines): one object per kernel family x workgroup size
 FAMILIES = {0: "mul", 1: "shinv", 2: "divrem", 3: "ragged"}

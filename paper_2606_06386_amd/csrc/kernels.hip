@@ -19,6 +19,7 @@
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
 #include "mp_div.hpp"
+#include "mp_block.hpp"
 
 namespace mp {
 
@@ -56,24 +57,25 @@ __global__ __launch_bounds__(T) void k_mul(const uint32_t *a, int na, const uint
 
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_shinv(const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                                                          int32_t *status, Knobs kn, int head)
+                                                          int32_t *status, int head)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *wj = w + j * nw;
-    shinv_instance<T>(lds, v + j * nv, nv, h, wj, nw, status ? status + j : nullptr, kn, head ? wj : nullptr);
+    divide_instance<T>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
+                       head ? wj : nullptr);
 }
 
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, int nu, const uint32_t *v, int nv,
                                                            uint32_t *q, int nq, uint32_t *r, int32_t *status,
-                                                           Knobs kn, int head)
+                                                           int head)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
-    uint32_t *qj = q + j * nq;
-    divrem_instance<T>(lds, u + j * nu, nu, v + j * nv, nv, qj, nq, r + j * nv, status ? status + j : nullptr, kn,
-                       head ? qj : nullptr);
+    uint32_t *qj = q + j * nq, *rj = r + j * nv;
+    divide_instance<T>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
+                       head ? (nq >= nv ? qj : rj) : nullptr);
 }
 
 // persistent workgroups of one class: take the next instance of the class's
@@ -81,8 +83,7 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, in
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
                                                            const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
-                                                           int32_t *status, int32_t *ws, int cls, int count, Knobs kn,
-                                                           int head)
+                                                           int32_t *status, int32_t *ws, int cls, int count, int head)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int n = ws[cls];
@@ -98,8 +99,8 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, c
         const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off),
                       ro = uniform64(d.r_off);
         const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-        divrem_instance<T>(lds, up + uo, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j, kn,
-                           head ? qp + qo : nullptr);
+        divide_instance<T>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j,
+                           head ? (nq >= nv ? qp + qo : rp + ro) : nullptr);
     }
 }
 
@@ -114,29 +115,29 @@ hipError_t launch_mul(int grid, size_t lds, hipStream_t st, const uint32_t *a, i
 
 template <int T>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                        int32_t *status, Knobs kn, int head)
+                        int32_t *status, int head)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_shinv<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_shinv<T>, dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, kn, head);
+    hipLaunchKernelGGL(k_shinv<T>, dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, head);
     return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
-                         uint32_t *q, int nq, uint32_t *r, int32_t *status, Knobs kn, int head)
+                         uint32_t *q, int nq, uint32_t *r, int32_t *status, int head)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_divrem<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_divrem<T>, dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, kn, head);
+    hipLaunchKernelGGL(k_divrem<T>, dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, head);
     return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
-                         int count, Knobs kn, int head)
+                         int count, int head)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_ragged<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ragged<T>, dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count, kn,
+    hipLaunchKernelGGL(k_ragged<T>, dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count,
                        head);
     return hipGetLastError();
 }
@@ -147,14 +148,15 @@ hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *u
 // Heads: wave w of workgroup b owns instance b * kHeadWaves + w and the
 // `words` LDS words at lds + w * words (no workgroup barrier anywhere).
 __global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_divrem(const uint32_t *u, int nu, const uint32_t *v,
-                                                                      int nv, uint32_t *q, int nq, int batch,
-                                                                      int words, Knobs kn)
+                                                                      int nv, uint32_t *q, int nq,
+                                                                      uint32_t *r, int batch, int words, Knobs kn)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int w = (int)(threadIdx.x / kLanes);
     const size_t j = (size_t)blockIdx.x * kHeadWaves + w;
     if (j >= (size_t)batch) return;
-    head_divrem(lds + w * words, u + j * nu, nu, v + j * nv, nv, q + j * nq, nq, kn);
+    uint32_t *rec = nq >= nv ? q + j * nq : r + j * nv;
+    head_divrem(lds + w * words, u + j * nu, nu, v + j * nv, nv, rec, nq >= nv ? nq : nv, nq, kn);
 }
 
 __global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_shinv(const uint32_t *v, int nv, int h, uint32_t *w,
@@ -171,8 +173,8 @@ __global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_
 // lists (the preparation kernel's buckets, in class order)
 __global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_ragged(const uint32_t *up, const uint32_t *vp,
                                                                       const mp_desc_t *desc, uint32_t *qp,
-                                                                      const int32_t *ws, int count, int words,
-                                                                      Knobs kn)
+                                                                      uint32_t *rp, const int32_t *ws, int count,
+                                                                      int words, Knobs kn)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int w = (int)(threadIdx.x / kLanes);
@@ -181,22 +183,23 @@ __global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_
     if (c == kClasses) return;
     const int j = uniform(ws[kWsHeader + (size_t)c * count + idx]);
     const mp_desc_t &d = desc[j];
-    const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off);
+    const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off),
+                  ro = uniform64(d.r_off);
     const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-    head_divrem(lds + w * words, up + uo, nu, vp + vo, nv, qp + qo, nq, kn);
+    head_divrem(lds + w * words, up + uo, nu, vp + vo, nv, nq >= nv ? qp + qo : rp + ro, nq >= nv ? nq : nv, nq, kn);
 }
 
 // LDS words of one head wave for the current knobs
 int head_words(const Knobs &kn) { return plan_head(kn.small_limit, 0).total; }
 
 hipError_t launch_head_divrem(hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv, uint32_t *q,
-                              int nq, int batch, Knobs kn)
+                              int nq, uint32_t *r, int batch, Knobs kn)
 {
     const int words = head_words(kn);
     const size_t lds = (size_t)words * 4 * kHeadWaves;
     if (!lds_attr(reinterpret_cast<const void *>(k_head_divrem), lds)) return hipErrorInvalidValue;
     const int grid = (batch + kHeadWaves - 1) / kHeadWaves;
-    hipLaunchKernelGGL(k_head_divrem, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, u, nu, v, nv, q, nq, batch,
+    hipLaunchKernelGGL(k_head_divrem, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, u, nu, v, nv, q, nq, r, batch,
                        words, kn);
     return hipGetLastError();
 }
@@ -214,13 +217,13 @@ hipError_t launch_head_shinv(hipStream_t st, const uint32_t *v, int nv, int h, u
 }
 
 hipError_t launch_head_ragged(hipStream_t st, const uint32_t *up, const uint32_t *vp, const mp_desc_t *desc,
-                              uint32_t *qp, const int32_t *ws, int count, Knobs kn)
+                              uint32_t *qp, uint32_t *rp, const int32_t *ws, int count, Knobs kn)
 {
     const int words = head_words(kn);
     const size_t lds = (size_t)words * 4 * kHeadWaves;
     if (!lds_attr(reinterpret_cast<const void *>(k_head_ragged), lds)) return hipErrorInvalidValue;
     const int grid = (count + kHeadWaves - 1) / kHeadWaves;
-    hipLaunchKernelGGL(k_head_ragged, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, up, vp, desc, qp, ws, count,
+    hipLaunchKernelGGL(k_head_ragged, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, up, vp, desc, qp, rp, ws, count,
                        words, kn);
     return hipGetLastError();
 }
@@ -233,14 +236,14 @@ template hipError_t launch_mul<MP_KT>(int, size_t, hipStream_t, const uint32_t *
                                       uint32_t *, Knobs);
 #elif MP_KFAMILY == 1
 template hipError_t launch_shinv<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
-                                        int32_t *, Knobs, int);
+                                        int32_t *, int);
 #elif MP_KFAMILY == 2
 template hipError_t launch_divrem<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
-                                         uint32_t *, int, uint32_t *, int32_t *, Knobs, int);
+                                         uint32_t *, int, uint32_t *, int32_t *, int);
 #elif MP_KFAMILY == 3
 template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
                                          const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
-                                         Knobs, int);
+                                         int);
 #endif
 #endif
 
@@ -269,12 +272,6 @@ extern "C" int mp_trace_read_mul(uint64_t *dst, int blocks)
 extern "C" int mp_trace_read_divrem(uint64_t *dst, int blocks)
 {
     return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(mp_trace_buf), (size_t)blocks * 32 * sizeof(uint64_t), 0,
-                                    hipMemcpyDeviceToHost);
-}
-// copies the product records of the first `blocks` workgroups (48 x 6 words each)
-extern "C" int mp_trace_read_products(uint64_t *dst, int blocks)
-{
-    return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(mp_ptrace_buf), (size_t)blocks * 48 * 6 * sizeof(uint64_t), 0,
                                     hipMemcpyDeviceToHost);
 }
 #endif

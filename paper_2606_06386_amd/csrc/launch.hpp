@@ -33,23 +33,23 @@ hipError_t launch_mul(int grid, size_t lds, hipStream_t st, const uint32_t *a, i
 // body kernels: head != 0 when a head kernel ran before on the same stream
 template <int T>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                        int32_t *status, Knobs kn, int head);
+                        int32_t *status, int head);
 
 template <int T>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
-                         uint32_t *q, int nq, uint32_t *r, int32_t *status, Knobs kn, int head);
+                         uint32_t *q, int nq, uint32_t *r, int32_t *status, int head);
 
 template <int T>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
-                         int count, Knobs kn, int head);
+                         int count, int head);
 
 // head kernels (kn.small_limit > 0): records in the q (w) rows of the instances
 hipError_t launch_head_divrem(hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv, uint32_t *q,
-                              int nq, int batch, Knobs kn);
+                              int nq, uint32_t *r, int batch, Knobs kn);
 hipError_t launch_head_shinv(hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw, int batch,
                              Knobs kn);
 hipError_t launch_head_ragged(hipStream_t st, const uint32_t *up, const uint32_t *vp, const mp_desc_t *desc,
-                              uint32_t *qp, const int32_t *ws, int count, Knobs kn);
+                              uint32_t *qp, uint32_t *rp, const int32_t *ws, int count, Knobs kn);
 
 }  // namespace mp

@@ -575,7 +575,6 @@ MP_DEV int mul(uint32_t *ctl, uint32_t *p, int ncols,
         }
         strip_resolve(ctl, s, K0, lo, hi, p, c0, ncols);
     }
-    MP_PT(4);
     return add_strip_carries<T>(ctl, p, c0, ncols, nstrips, base, want_prec);
 }
 
@@ -932,58 +931,7 @@ MP_DEV int mul_mfma(uint32_t *ctl, uint32_t *p, int ncols, const uint32_t *yb, i
         for (int s = w; s < nstrips; s += 2 * W) step(s, s + W);
     }
     MP_STAMP(10);   // the first wave's strips done
-    MP_PT(4);
     return add_strip_carries<T>(ctl, p, c0, ncols, nstrips, base, want_prec);
-}
-
-// --------------------------------------------------------- short division
-
-// quotient of the n-limb number d (a view) by the single limb dv > 0:
-// qout(k, limb) for k in [0, n); returns the remainder (same on all threads).
-// Thread t divides the chunk [t*C, t*C + C): pass 1 reduces each chunk mod dv,
-// one thread chains the chunk remainders from the top (R_t-1 = R_t * B^C +
-// rem_t mod dv), pass 2 divides each chunk starting from its incoming R.
-// `scratch` holds 2*T words.
-template <int T, class FD, class FO>
-MP_DEV uint32_t shortdiv(uint32_t *ctl, uint32_t *scratch, int n, const FD &d, uint32_t dv, const FO &qout)
-{
-    bar<T>();
-    const int C = imax((n + T - 1) / T, imin(n, 64));
-    const int nch = (n + C - 1) / C;
-    const int t = tid<T>(), k0 = t * C;
-    if (t < nch) {
-        uint64_t r = 0;
-        for (int j = C - 1; j >= 0; j--) {
-            const int k = k0 + j;
-            const uint32_t x = k < n ? d(k) : 0u;
-            r = ((r << 32) | x) % dv;
-        }
-        scratch[t] = (uint32_t)r;
-    }
-    bar<T>();
-    if (t == 0) {
-        uint64_t beta = 1;
-        for (int j = 0; j < C; j++) beta = (beta << 32) % dv;   // B^C mod dv
-        uint64_t R = 0;
-        for (int c = nch - 1; c >= 0; c--) {
-            scratch[T + c] = (uint32_t)R;
-            R = ((R * beta) % dv + scratch[c]) % dv;
-        }
-        ctl[kCtlBcast] = (uint32_t)R;
-    }
-    bar<T>();
-    if (t < nch) {
-        uint64_t R = scratch[T + t];
-        for (int j = C - 1; j >= 0; j--) {
-            const int k = k0 + j;
-            if (k < n) {
-                const uint64_t num = (R << 32) | d(k);
-                qout(k, (uint32_t)(num / dv));
-                R = num % dv;
-            }
-        }
-    }
-    return ctl[kCtlBcast];
 }
 
 }  // namespace mp

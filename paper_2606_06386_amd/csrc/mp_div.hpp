@@ -47,17 +47,9 @@ enum : int32_t { kInstOk = 0, kInstDivZero = 1, kInstQWidth = 2, kInstInternal =
 MP_HD constexpr int r4(int x) { return (x + 3) & ~3; }
 MP_HD constexpr int hmax(int a, int b) { return a > b ? a : b; }
 
-// LDS layout of one division / shifted-inverse instance with h = prec(u)
-// (or the shinv precision) and k = prec(v) - 1, in 32-bit words.  Capacities
-// bound every intermediate of the method: w <= h-k+4 limbs, x <= k+8,
-// shinv <= h-k+1.  R holds the reversed digits of the shorter operand of a
-// matrix-core product (up to h/2 + 15 limbs); the window area SB doubles as
-// the long operand's digits.  P holds the columns a product forms, from its
-// first formed column on: PowDiff's close product (L <= k + 7 columns), the
-// Step's w x from column sh - 2 up (about m + 16 columns: within max(k, d) + 9
-// over a scan of random and structured operands of up to 700 limbs), u * shinv
-// from column h - 9 up (at most h - k + 11), the low k + 2 columns of v q0
-// and shinv's fix-up product (k + 4); every use is guarded.
+MP_HD constexpr int hmin(int a, int b) { return a < b ? a : b; }
+
+// LDS layout of a head's wave (32-bit words)
 struct Plan {
     int capV, capW, capX, capR, capSB, capP;
     int offV, offW, offX, offR, offSB, offP;   // offR: word 0 of the reversed digits, offSB: limb 0 of the window
@@ -67,28 +59,33 @@ struct Plan {
     int total;
 };
 
-MP_HD constexpr Plan plan_div(int h, int k)
+// A division's quotient limbs d = h - k are found in blocks (mp_block.hpp):
+// nb blocks of bi limbs, the first (top) of d - (nb - 1) bi; dp limbs of
+// precision of the inverse serve the longest of them.  bi is a multiple of 4,
+// so that every block starts at a 16-byte boundary of the remainder.
+struct BlockSplit {
+    int nb, bi, dp;
+};
+
+// longest block: the last Newton step reaches 2^j + 1 limbs, and 257 limbs is
+// the longest iterate whose steps fit one wave's head
+constexpr int kBlockMax = 257;
+constexpr int kSmallBlock = 16;   // without a head: inverses that fit one limb per lane throughout
+
+MP_HD BlockSplit block_split(int d, int bmax)
 {
-    Plan p{};
-    p.vbase = 0;
-    const int d = h - k;
-    p.capV = r4(k + 1);
-    p.capW = r4(d + 8);
-    p.capX = r4(k + 12);
-    p.capR = r4(h / 2 + 16);
-    p.capSB = r4(hmax(hmax(h, k + 12), d + 8) + 4);
-    p.capP = r4(hmax(k, d) + 24);
-    p.offV = kCtlWords;
-    p.offW = p.offV + p.capV;
-    p.offX = p.offW + p.capW;
-    p.offR = p.offX + p.capX + kXPad;
-    p.offSB = p.offR + p.capR + kXPad + kPad;
-    p.offP = p.offSB + p.capSB + kPad;
-    p.total = p.offP + p.capP + 4;
-    p.capY = 1 << 30;   // kPad covers the planes of any operand the window holds
-    p.sbLo = kPad;
-    p.sbHi = p.capSB + kPad;
-    return p;
+    if (d <= bmax) return BlockSplit{1, 0, d > 2 ? d : 2};
+    const int top = bmax & ~3, nb = 1 + (d - bmax + top - 1) / top;
+    const int even = r4((d + nb - 1) / nb), bi = even < top ? even : top, b0 = d - (nb - 1) * bi;
+    return BlockSplit{nb, bi, b0 > bi ? b0 : bi};
+}
+
+// longest block whose Newton steps all have iterates (l + 3 limbs) shorter than `limit` limbs
+MP_HD int block_limit(int limit)
+{
+    int b = 3;
+    while (2 * b - 1 <= kBlockMax && b + 3 < limit) b = 2 * b - 1;
+    return b;
 }
 
 // LDS layout of one wave's head (the Refine iterations whose iterate has fewer
@@ -109,6 +106,7 @@ MP_HD constexpr Plan plan_div(int h, int k)
 // reach 8 ((capY + 8) / 8) + 8 kYPadBlk words above its start (a longer
 // operand takes the VALU product).  Sized so that 16 heads share a compute
 // unit's LDS up to the largest limit.
+constexpr int kHeadMinLimit = 16;   // smallest small_limit (lower knob values count as this)
 constexpr int kHeadMaxLimit = 140;   // largest small_limit: every head operand then fits kHeadMaxLimbs
 constexpr int kHeadPad = kLanes + 8; // zero guard on both sides of a head's VALU window operand
 // (the longest one-wave linear operation of a head is bounded by capP, capX or
@@ -119,7 +117,7 @@ static_assert(4 * kHeadMaxLimit + 8 <= kHeadStrips * kStrip, "a head's products 
 MP_HD constexpr Plan plan_head(int limit, int vbase)
 {
     Plan p{};
-    const int L = limit < 4 ? 4 : limit > kHeadMaxLimit ? kHeadMaxLimit : limit;
+    const int L = limit < kHeadMinLimit ? kHeadMinLimit : limit > kHeadMaxLimit ? kHeadMaxLimit : limit;
     p.vbase = vbase;
     p.capV = r4(2 * L);
     p.capW = r4(2 * L + 8);
@@ -140,27 +138,18 @@ MP_HD constexpr Plan plan_head(int limit, int vbase)
     return p;
 }
 
-// Record of the head in the instance's output row (32-bit words):
-//   [0] kRecValid, or 0 when the body is to do every step itself
-//   [1] Refine iterations done   [2] l   [3] we   [4] nw   [5] h   [6] k
-//   [kRecHdr, kRecHdr + we) the limbs of the iterate W
-constexpr uint32_t kRecValid = 0x52454331u;
+// Record of the head in one of the instance's output rows (the longer of q and
+// r; w for a shifted inverse), in 32-bit words:
+//   [0] kRecValid, or 0 when there is none
+//   [1] h   [2] k   [3] limbs u and v are shifted up by (1 for a one-limb divisor)
+//   [4] limbs of W   [5] dp   [6] blocks   [7] limbs of the blocks below the first
+//   [kRecHdr, kRecHdr + [4]) the limbs of W, about B^(k + dp + 2) / v
+constexpr uint32_t kRecValid = 0x52454332u;
 constexpr int kRecHdr = 8;
+// longest inverse a record of `row` limbs can hold (dp + 3 limbs and the header)
+MP_HD int record_block(int row) { return row - kRecHdr - 3; }
 constexpr int kHeadWaves = 4;   // head instances (waves) per workgroup
 static_assert(16 * plan_head(kHeadMaxLimit, 0).total * 4 <= 160 * 1024, "16 heads must share a compute unit's LDS");
-
-// words needed by the single-limb-divisor path (quotient + chunk scratch)
-MP_HD int plan_short_words(int n, int T) { return kCtlWords + 2 * T + r4(n + 1) + 4; }
-
-// LDS words for a batch whose dividends have at most nu limbs and divisors at
-// most nv limbs (every (h, k) an instance can reach)
-MP_HD int div_lds_words(int nu, int nv, int T)
-{
-    int best = plan_short_words(nu, T);
-    const int kmax = (nv < nu ? nv : nu) - 1;
-    for (int k = 1; k <= kmax; k++) best = hmax(best, plan_div(nu, k).total);
-    return best;
-}
 
 MP_HD int mul_lds_words(int na, int nb)
 {
@@ -185,24 +174,19 @@ MP_DEV int product_views(uint32_t *ctl, uint32_t *p, int ncols, const FL &lng, i
                          uint32_t *xr, int xrcap, int mfma_min, int c0 = 0, bool want_prec = true,
                          bool sht_ready = false)
 {
-    MP_PT_BEGIN(ns, nl, ncols, c0);
     int r;
     if constexpr (MF) {
         if (ns >= mfma_min && ns + 1 <= xrcap) {
             mfma_operands<T>(ctl, lng, nl, sb, sbext, sht, ns, xr, sht_ready);
-            MP_PT(3);
             sbext = mfma_ext(nl);
             r = mul_mfma<T>(ctl, p, ncols, sb, nl, xr, ns, c0, want_prec);
-            MP_PT_END();
             return r;
         }
     }
     copy<T>(sb, nl, sbext, lng);
-    MP_PT(3);
     sbext = nl;
     if constexpr (T == kLanes) r = mul1<T>(ctl, p, ncols, sht_lds, ns, sb, nl, c0, want_prec);
     else r = mul<T>(ctl, p, ncols, sht_lds, ns, sb, nl, c0, want_prec);
-    MP_PT_END();
     return r;
 }
 
@@ -215,32 +199,6 @@ MP_DEV int product(uint32_t *ctl, uint32_t *p, int ncols, const uint32_t *x, int
     const int ns = nx >= ny ? ny : nx, nl = nx >= ny ? nx : ny;
     return product_views<T, MF>(ctl, p, ncols, Span{lng, 0, nl}, nl, lng, Span{sht, 0, ns}, ns, sht, sb, sbext,
                                 xr, xrcap, mfma_min, c0, want_prec, sht_ready);
-}
-
-// dst[0, n) = src limbs [0, e) zero-padded, where e = prec(src) must be <= n;
-// returns false (and stores nothing) when the value needs more than n limbs
-template <int T, class FS>
-MP_DEV bool store_fit(uint32_t *ctl, uint32_t *dst, int n, int ext, const FS &src)
-{
-    const int e = prec<T>(ctl, ext, src);
-    if (e > n) return false;
-    int i = tid<T>();
-    for (; i + 3 * T < n; i += 4 * T) {
-        const uint32_t y0 = i < e ? src(i) : 0u, y1 = i + T < e ? src(i + T) : 0u;
-        const uint32_t y2 = i + 2 * T < e ? src(i + 2 * T) : 0u, y3 = i + 3 * T < e ? src(i + 3 * T) : 0u;
-        dst[i] = y0;
-        dst[i + T] = y1;
-        dst[i + 2 * T] = y2;
-        dst[i + 3 * T] = y3;
-    }
-    for (; i < n; i += T) dst[i] = i < e ? src(i) : 0u;
-    return true;
-}
-
-template <int T>
-MP_DEV void store_zero(uint32_t *dst, int n)
-{
-    for (int i = tid<T>(); i < n; i += T) dst[i] = 0u;
 }
 
 // ------------------------------------------------------- Alg. 1 Refine
@@ -296,7 +254,6 @@ MP_DEV bool refine_iter(uint32_t *ctl, const Plan &pl, const Knobs &kn, uint32_t
     } else {                            // close product: P = v'w mod B^L
         if (L > pl.capP || L > pl.capX) return false;
         const int np = product<T, MF>(ctl, P, L, vp, nvp, W, nw, SB, sbext, XR, pl.capR, mm_pd);
-        MP_STAMP(11);   // (trace build: sub-steps of the latest iteration)
         MP_HEAD_SUB(i, 0);
         if (np == 0) {                  // v'w = B^hp exactly
             sign = true;
@@ -338,10 +295,8 @@ MP_DEV bool refine_iter(uint32_t *ctl, const Plan &pl, const Knobs &kn, uint32_t
         // digits from PowDiff's product are still in XR
         const bool w_ready = MF && nvp >= nw && nw < nx && nw >= mm_pd && nw + 1 <= pl.capR;
         const int mm_st = imax(nw, nx) <= pl.capY ? kn.mfma_min : (1 << 30);
-        MP_STAMP(12);
         // column c of the product goes to P[c - cs]
         product<T, MF>(ctl, P - cs, nt, W, nw, X, nx, SB, sbext, XR, pl.capR, mm_st, cs, false, w_ready);
-        MP_STAMP(13);
     }
     MP_HEAD_SUB(i, 2);
     // the sticky borrow of the negative branch (any nonzero formed column
@@ -563,16 +518,6 @@ MP_HD int refine_l(int d, int i)
     return l;
 }
 
-// number of leading Refine iterations whose iterate (l + g + 1 limbs) is
-// shorter than `limit` limbs
-MP_HD int small_iters(int d, int limit)
-{
-    const int iters = refine_iters(d);
-    int n = 0;
-    while (n < iters && refine_l(d, n) + 3 < limit) n++;
-    return n;
-}
-
 // floor(B^3 / V) for B <= V < B^2, by one wave (every lane gets the result):
 // the quotient is B^2 when V = B and below B^2 otherwise.  Its bits are found
 // six at a time from the top: in each round lane j tests whether the bits
@@ -600,35 +545,8 @@ MP_DEV void inv96_wave(uint64_t V, uint64_t &q, uint32_t &q64)
     }
 }
 
-// Alg. 1's initial approximation w = shift_g(floor(B^3 / V)), V = v_{k-1} + v_k B:
-// w0 <= B^2 has 3 limbs (65 bits when V = B).  vtop points at v_{k-1}, v_k.
-// Computed by the first wave of the T threads.
-template <int T>
-MP_DEV void refine_init(uint32_t *ctl, const uint32_t *vtop, uint32_t *W, int &we, int &nw)
-{
-    bar<T>();
-    if (T == kLanes || tid<T>() < kLanes) {
-        const uint64_t Vt = ((uint64_t)vtop[1] << 32) | vtop[0];
-        uint64_t w0;
-        uint32_t w64;
-        inv96_wave(Vt, w0, w64);
-        const uint32_t code = w64 ? 5u : (w0 >> 32) ? 4u : 3u;
-        if (lane() == 0) {
-            W[0] = 0u;
-            W[1] = 0u;
-            W[2] = (uint32_t)w0;
-            W[3] = (uint32_t)(w0 >> 32);
-            W[4] = w64;
-            if constexpr (T > kLanes) ctl[kCtlBcast + 1] = code;
-        }
-        if constexpr (T == kLanes) nw = (int)uniform(code);
-    }
-    bar<T>();
-    if constexpr (T > kLanes) nw = (int)uniform(ctl[kCtlBcast + 1]);
-    we = 5;
-}
-
-// the same for one wave (a head) from V = v_{k-1} + v_k B held in registers
+// Alg. 1's initial approximation w = shift_g(floor(B^3 / V)), V = v_{k-1} + v_k B
+// (in registers), by one wave: w0 <= B^2 has 3 limbs (65 bits when V = B)
 MP_DEV void head_init(uint64_t Vt, uint32_t *W, int &we, int &nw)
 {
     uint64_t w0;
@@ -643,41 +561,6 @@ MP_DEV void head_init(uint64_t Vt, uint32_t *W, int &we, int &nw)
     }
     nw = (int)uniform(w64 ? 5u : (w0 >> 32) ? 4u : 3u);
     we = 5;
-}
-
-// Initial approximation and the Refine loop for B^k <= v < B^(k+1), k >= 1,
-// h - k >= 1, B < v <= B^h / 2, v not a power of B.  v is in V (k+1 limbs),
-// W and the window area are zero.  With a valid head record `rec` (in global
-// memory) the iterations it covers are taken from it instead.  On return the
-// shifted inverse is the limbs of W above `shf`; W's nonzero limbs lie inside
-// [0, we) and nw = prec(W).  Returns false if a capacity guard trips or a
-// Step result turns negative (never expected).
-template <int T>
-MP_DEV bool refine(uint32_t *ctl, const Plan &pl, const Knobs &kn, uint32_t *lds, int h, int k, int &we, int &nw,
-                   int &shf, int &sbext, const uint32_t *rec)
-{
-    uint32_t *V = lds + pl.offV, *W = lds + pl.offW;
-    const int d = h - k;
-    const int iters = refine_iters(d);
-    int l = 2, i = 0;
-    if (rec) {
-        i = (int)uniform(rec[1]);
-        l = (int)uniform(rec[2]);
-        we = (int)uniform(rec[3]);
-        nw = (int)uniform(rec[4]);
-        if (we > pl.capW) return false;
-        copy<T>(W, we, 0, Span{rec + kRecHdr, 0, we});
-    } else {
-        refine_init<T>(ctl, V + k - 1, W, we, nw);
-    }
-    MP_STAMP(3);
-    MP_STAMP(4);
-    for (; i < iters; i++) {
-        if (!refine_iter<T>(ctl, pl, kn, lds, h, k, i, l, we, nw, sbext)) return false;
-        MP_STAMP(16 + (i & 15));
-    }
-    shf = d < 2 ? 4 - d : 2;
-    return true;
 }
 
 // ------------------------------------------------------------------- head
@@ -706,40 +589,48 @@ MP_DEV int wave_low(const uint32_t *x, int n)
 
 // The head of one instance with h, k = prec(v) - 1 and vlow (index of v's
 // lowest nonzero limb), by one wave in its own LDS area (plan_head words):
-// for the general case with h - k >= 2 and v not a power of B, Alg. 1's
-// initial approximation and its Refine iterations while the iterate is
-// shorter than kn.small_limit limbs, recorded in rec[0, nrec); otherwise (or
-// when the state does not fit) rec[0] = 0.  With have_top, vtop holds
-// v_{k-1} + v_k B (read by the caller), else they are read here.
+// splits the quotient's limbs into blocks and computes the inverse W they
+// need (Alg. 1's initial approximation and Refine for h' = k + dp), recorded
+// in rec[0, nrec).  rec[0] = 0 when there is nothing to divide (u < v, v a
+// power of B), the quotient cannot fit nq limbs, or the record the row.  With
+// have_top, vtop holds v_{k-1} + v_k B (read by the caller), else they are
+// read here.  A divisor of one limb is divided as v B into u B.
 MP_DEV void head_refine(uint32_t *lds, int h, int k, int vlow, const uint32_t *v, uint64_t vtop, bool have_top,
-                        uint32_t *rec, int nrec, const Knobs &kn)
+                        uint32_t *rec, int nrec, int nq, const Knobs &kn)
 {
     constexpr int T = kLanes;
     uint32_t *ctl = lds;
-    const int d = h - k, g = 2;
-    bool go = k >= 1 && d >= 2;
+    const int g = 2, sv = k == 0 ? 1 : 0;
+    bool go = k >= 0 && h > k && h - k - 1 <= nq;
     uint64_t Vt = vtop;
-    if (go && !have_top) Vt = ((uint64_t)v[k] << 32) | v[k - 1];
+    if (go && !have_top) Vt = sv ? (uint64_t)v[0] << 32 : ((uint64_t)v[k] << 32) | v[k - 1];
     if (go) go = !(vlow == k && (uint32_t)(Vt >> 32) == 1u);
-    const int ns = go ? small_iters(d, kn.small_limit) : 0;
-    const int vbase = ns ? imax(0, k - 2 * refine_l(d, ns - 1) + 1 - g) : 0;
-    const Plan pl = plan_head(kn.small_limit, vbase);
-    if (ns == 0 || k + 1 - vbase > pl.capV) {
+    const int bmax = hmin(block_limit(kn.small_limit), record_block(nrec));
+    if (!go || bmax < kSmallBlock) {
         if (lane() == 0) rec[0] = 0u;
         return;
     }
+    h += sv;
+    k += sv;
+    const BlockSplit bs = block_split(h - k, bmax);
+    const int hh = k + bs.dp, ns = refine_iters(bs.dp);
+    const int vbase = imax(0, k - 2 * refine_l(bs.dp, ns - 1) + 1 - g);
+    const Plan pl = plan_head(kn.small_limit, vbase);
     uint32_t *V = lds + pl.offV, *W = lds + pl.offW, *SB = lds + pl.offSB;
-    // the divisor limbs [vbase, k] (at most capV <= 5 T): every read in flight
-    // at once; the LDS areas are zeroed and the initial approximation (from
-    // the top limbs in registers) computed while they arrive, then they are
-    // stored
+    // the divisor limbs [vbase, k] (at most 2 l + 2 <= capV <= 5 T): every read
+    // in flight at once; the LDS areas are zeroed and the initial approximation
+    // (from the top limbs in registers) computed while they arrive, then they
+    // are stored
     int we = 0, nw = 0, sbext = 0, l = 2;
     {
         static_assert(r4(2 * kHeadMaxLimit) <= 5 * T, "a head stages its divisor limbs in one round");
-        const int nvs = k + 1 - vbase;
+        const int nvs = k + 1 - vbase, first = vbase - sv;
         uint32_t a[5];
 #pragma unroll
-        for (int j = 0; j < 5; j++) a[j] = lane() + j * T < nvs ? v[vbase + lane() + j * T] : 0u;
+        for (int j = 0; j < 5; j++) {
+            const int i = lane() + j * T;
+            a[j] = i < nvs && first + i >= 0 ? v[first + i] : 0u;
+        }
         for (int i = lane(); i < pl.capW; i += T) W[i] = 0u;
         for (int i = lane() - pl.sbLo; i < pl.sbHi; i += T) SB[i] = 0u;
         wave_sync();
@@ -750,33 +641,29 @@ MP_DEV void head_refine(uint32_t *lds, int h, int k, int vlow, const uint32_t *v
     }
     MP_WSTAMP(2);   // (trace build: staging and the initial approximation)
     MP_WSTAMP(3);
-    bool ok = true;
+    bool ok = k + 1 - vbase <= pl.capV;
     int i = 0;
-    // the first iterations in registers, one limb per lane; the rest as in the body
-    for (; i < ns && ok && iter_fits_wave(pl, h, k, l, nw, we); i++) {
-        ok = refine_iter_wave(pl, lds, h, k, i, l, we, nw);
+    // the first iterations in registers, one limb per lane; the rest through LDS
+    for (; i < ns && ok && iter_fits_wave(pl, hh, k, l, nw, we); i++) {
+        ok = refine_iter_wave(pl, lds, hh, k, i, l, we, nw);
         MP_WSTAMP(16 + (i & 15));
     }
     for (; i < ns && ok; i++) {
-        ok = refine_iter<T>(ctl, pl, kn, lds, h, k, i, l, we, nw, sbext);
+        ok = refine_iter<T>(ctl, pl, kn, lds, hh, k, i, l, we, nw, sbext);
         MP_WSTAMP(16 + (i & 15));
     }
-    ok = ok && kRecHdr + we <= nrec;
+    ok = ok && nw <= bs.dp + 3;
     wave_sync();
-    if (!ok) {
-        if (lane() == 0) rec[0] = 0u;
-        return;
-    }
-    for (int i = lane(); i < we; i += T) rec[kRecHdr + i] = W[i];
+    for (int i = lane(); ok && i < nw; i += T) rec[kRecHdr + i] = W[i];
     if (lane() == 0) {
-        rec[1] = (uint32_t)ns;
-        rec[2] = (uint32_t)l;
-        rec[3] = (uint32_t)we;
+        rec[1] = (uint32_t)h;
+        rec[2] = (uint32_t)k;
+        rec[3] = (uint32_t)sv;
         rec[4] = (uint32_t)nw;
-        rec[5] = (uint32_t)h;
-        rec[6] = (uint32_t)k;
-        rec[7] = 0u;
-        rec[0] = kRecValid;
+        rec[5] = (uint32_t)bs.dp;
+        rec[6] = (uint32_t)bs.nb;
+        rec[7] = (uint32_t)bs.bi;
+        rec[0] = ok ? kRecValid : 0u;
     }
     MP_WSTAMP(4);
     MP_WRSTAMP(15);   // (trace build: real time at the end and the start of a head)
@@ -810,12 +697,11 @@ MP_DEV bool wave_vtop(uint32_t vt, int nv, int k, uint64_t &V)
     return true;
 }
 
-// the head of a division (h = prec(u), k = prec(v) - 1): the top 64 limbs of
-// u and of v and the bottom 64 of v are read together, which settles both
-// precisions and v's lowest nonzero limb in one round trip unless a number
-// has 64 zero limbs at that end
+// the head of a division: the top 64 limbs of u and of v and the bottom 64 of
+// v are read together, which settles both precisions and v's lowest nonzero
+// limb in one round trip unless a number has 64 zero limbs at that end
 MP_DEV void head_divrem(uint32_t *lds, const uint32_t *u, int nu, const uint32_t *v, int nv, uint32_t *rec, int nrec,
-                        const Knobs &kn)
+                        int nq, const Knobs &kn)
 {
     MP_WSTAMP(0);
     MP_WRSTAMP(14);
@@ -828,10 +714,10 @@ MP_DEV void head_divrem(uint32_t *lds, const uint32_t *u, int nu, const uint32_t
     uint64_t vtop = 0;
     const bool top = wave_vtop(vt, nv, k, vtop);
     MP_WSTAMP(1);
-    head_refine(lds, h, k, vlow, v, vtop, top, rec, nrec, kn);
+    head_refine(lds, h, k, vlow, v, vtop, top, rec, nrec, nq, kn);
 }
 
-// the head of a shifted inverse floor(B^h / v)
+// the head of a shifted inverse floor(B^h / v): the division of B^h
 MP_DEV void head_shinv(uint32_t *lds, int h, const uint32_t *v, int nv, uint32_t *rec, int nrec, const Knobs &kn)
 {
     const int iv = nv - kLanes + lane(), il = lane();
@@ -840,17 +726,7 @@ MP_DEV void head_shinv(uint32_t *lds, int h, const uint32_t *v, int nv, uint32_t
     wave_vshape(v, nv, ballot(vt != 0u), ballot(vb != 0u), k, vlow);
     uint64_t vtop = 0;
     const bool top = wave_vtop(vt, nv, k, vtop);
-    head_refine(lds, h, k, vlow, v, vtop, top, rec, nrec, kn);
-}
-
-// a head record for (h, k) in the output row rec[0, nrec), or nullptr when rec
-// is absent or holds none (a valid record always fits its row)
-template <int T>
-MP_DEV const uint32_t *head_record(const uint32_t *rec, int nrec, int h, int k)
-{
-    if (!rec || nrec < kRecHdr) return nullptr;
-    if (uniform(rec[0]) != kRecValid) return nullptr;
-    return (int)uniform(rec[5]) == h && (int)uniform(rec[6]) == k ? rec : nullptr;
+    head_refine(lds, h + 1, k, vlow, v, vtop, top, rec, nrec, nrec, kn);
 }
 
 // ------------------------------------------------------------ instances
@@ -888,269 +764,6 @@ MP_DEV void mul_instance(uint32_t *lds, const uint32_t *a, int na, const uint32_
     for (int i = tid<T>(); i < na + nb; i += T) c[i] = P[i];
     MP_STAMP(5);
     MP_RSTAMP(7);
-}
-
-// w = floor(B^h / v), exactly (nw limbs).  rec: the head's record (at w), or
-// nullptr when no head ran
-template <int T>
-MP_DEV void shinv_instance(uint32_t *lds, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                           int32_t *status, const Knobs &kn, const uint32_t *rec)
-{
-    uint32_t *ctl = lds;
-    const Span Vg{v, 0, nv};
-    int32_t st = kInstOk;
-    const int nvv = prec<T>(ctl, nv, Vg);
-    if (nvv == 0) {
-        store_zero<T>(w, nw);
-        if (status && tid<T>() == 0) *status = kInstDivZero;
-        return;
-    }
-    const int k = nvv - 1;
-    const int lowz = prec<T>(ctl, k, Vg) == 0;   // limbs below k all zero
-    const uint32_t vk = v[k];
-    bool ok = true;
-    if (k == 0) {                                 // v < B: B^h quo v by short division
-        uint32_t *scratch = lds + kCtlWords, *Q = scratch + 2 * T;
-        shortdiv<T>(ctl, scratch, h + 1, PowB{h}, vk, Store{Q, 0, h + 1});
-        ok = store_fit<T>(ctl, w, nw, h + 1, Span{Q, 0, h + 1});
-    } else if (k > h || (k == h && !(lowz && vk == 1u))) {   // v > B^h
-        store_zero<T>(w, nw);
-    } else if (k == h ||                                      // v = B^h
-               (k == h - 1 && (vk > 0x80000000u || (vk == 0x80000000u && !lowz)))) {  // 2v > B^h
-        ok = nw >= 1;
-        if (ok)
-            for (int i = tid<T>(); i < nw; i += T) w[i] = i == 0 ? 1u : 0u;
-    } else if (lowz && vk == 1u) {                            // v = B^k: B^(h-k)
-        ok = nw > h - k;
-        if (ok) {
-            const int e = h - k;
-            for (int i = tid<T>(); i < nw; i += T) w[i] = i == e ? 1u : 0u;
-        }
-    } else {
-        const Plan pl = plan_div(h, k);
-        uint32_t *V = lds + pl.offV, *W = lds + pl.offW, *X = lds + pl.offX;
-        uint32_t *SB = lds + pl.offSB, *P = lds + pl.offP, *XR = lds + pl.offR;
-        copy<T>(V, k + 1, 0, Vg);
-        copy<T>(W, 0, pl.capW, Zero{});
-        copy<T>(SB - kPad, 0, pl.capSB + 2 * kPad, Zero{});
-        int we = 0, nwi = 0, shf = 0, sbext = 0;
-        if (!refine<T>(ctl, pl, kn, lds, h, k, we, nwi, shf, sbext, head_record<T>(rec, nw, h, k))) {
-            st = kInstInternal;
-        } else {
-            // exact fix-up: D = B^h - v s with s within two of floor(B^h/v), so
-            // -2v <= D < 3v.  D is formed as a signed Lr-limb number (Lr = k+3
-            // when h >= k+3: B^h vanishes mod B^Lr and |D| < B^Lr / 2), then
-            // moved into [0, v) by whole multiples of v.
-            uint32_t *S = W + shf;
-            int se = imax(we - shf, 0);
-            const int ns = imax(nwi - shf, 0);
-            const int d = h - k;
-            const int full = k + 1 + ns;
-            const int Lr = d >= 3 ? k + 3 : imax(full, h + 1) + 1;
-            const int pc = imin(Lr, full);
-            product<T>(ctl, P, pc, V, k + 1, S, ns, SB, sbext, XR, pl.capR, kn.mfma_min, 0, false);
-            addsub<T>(ctl, Lr, true, 0u, PowB{h}, Span{P, 0, pc}, Store{X, 0, Lr});
-            uint32_t *R = X, *R2 = P;
-            int adj = 0;
-            bool good = true;
-            for (int it = 0; good; it++) {         // D < 0: s too large
-                bar<T>();
-                if (!(R[Lr - 1] >> 31)) break;
-                if (it == 4) { good = false; break; }
-                addsub<T>(ctl, Lr, false, 0u, Span{R, 0, Lr}, Span{V, 0, k + 1}, Store{R, 0, Lr});
-                adj -= 1;
-            }
-            for (int it = 0; good; it++) {         // D >= v: s too small
-                if (addsub<T>(ctl, Lr, true, 0u, Span{R, 0, Lr}, Span{V, 0, k + 1}, Store{R2, 0, Lr})) break;
-                if (it == 5) { good = false; break; }
-                uint32_t *t = R;
-                R = R2;
-                R2 = t;
-                adj += 1;
-            }
-            if (good && adj != 0) {
-                addsub<T>(ctl, se + 1, adj < 0, 0u, Span{S, 0, se}, Limb0{(uint32_t)(adj < 0 ? -adj : adj)},
-                          Store{S, 0, se + 1});
-                se += 1;
-            }
-            if (!good) st = kInstInternal;
-            if (good) ok = store_fit<T>(ctl, w, nw, se, Span{S, 0, se});
-        }
-    }
-    if (st == kInstOk && !ok) st = kInstQWidth;
-    if (st != kInstOk) {
-        bar<T>();
-        store_zero<T>(w, nw);
-    }
-    if (status && tid<T>() == 0) *status = st;
-}
-
-// (q, r) with u = q v + r, 0 <= r < v  (q: nq limbs, r: nv limbs).  rec: the
-// head's record (at q), or nullptr when no head ran
-template <int T>
-MP_DEV void divrem_instance(uint32_t *lds, const uint32_t *u, int nu, const uint32_t *v, int nv,
-                            uint32_t *q, int nq, uint32_t *r, int32_t *status, const Knobs &kn,
-                            const uint32_t *rec)
-{
-    uint32_t *ctl = lds;
-    const Span Ug{u, 0, nu}, Vg{v, 0, nv};
-    int32_t st = kInstOk;
-    bool ok = true;
-    // one pass over u and v: prec(u), prec(v), and the lowest nonzero limb of v
-    uint32_t red[3] = {0u, 0u, 0u};
-    bar<T>();
-    MP_RSTAMP(14);
-    MP_PT_RESET();
-    MP_STAMP(0);
-    {
-        // eight limbs of u and of v per thread and step, all read before use;
-        // v's limbs below nu also go to LDS right after the control block, where
-        // the divisor lives in every path that uses it (the allocation always
-        // holds kCtlWords + nu words)
-        uint32_t *V0 = lds + kCtlWords;
-        const int nm = nu > nv ? nu : nv, nvs = nu < nv ? nu : nv;
-        for (int i0 = tid<T>(); i0 < nm; i0 += 8 * T) {
-            uint32_t ua[8], va[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const int i = i0 + j * T;
-                ua[j] = i < nu ? u[i] : 0u;
-                va[j] = i < nv ? v[i] : 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const int i = i0 + j * T;
-                if (i < nvs) V0[i] = va[j];
-                if (ua[j]) red[0] = (uint32_t)(i + 1);
-                if (va[j]) {
-                    red[1] = (uint32_t)(i + 1);
-                    red[2] = red[2] ? red[2] : (uint32_t)(nv - i);
-                }
-            }
-        }
-    }
-    wg_max_n<T, 3>(ctl, red);
-    MP_STAMP(1);
-    const int h = (int)red[0], nvv = (int)red[1], vlow = nv - (int)red[2];
-    if (nvv == 0) {
-        store_zero<T>(q, nq);
-        store_zero<T>(r, nv);
-        if (status && tid<T>() == 0) *status = kInstDivZero;
-        return;
-    }
-    const int c0 = h < nvv ? -1 : (h > nvv ? 1 : cmp<T>(ctl, h, Ug, Vg));
-    const int k = nvv - 1;
-    if (c0 < 0) {                                 // u < v: (0, u)
-        store_zero<T>(q, nq);
-        for (int i = tid<T>(); i < nv; i += T) r[i] = i < h ? u[i] : 0u;
-        if (status && tid<T>() == 0) *status = kInstOk;
-        return;
-    }
-    const uint32_t vk = lds[kCtlWords + k];      // k < nvv <= h <= nu: stored by the first pass
-    const bool lowz = vlow == k;                  // v = v_k B^k
-    if (k == 0) {                                 // single-limb divisor: short division of u
-        uint32_t *scratch = lds + kCtlWords, *Q = scratch + 2 * T;
-        const uint32_t rem = shortdiv<T>(ctl, scratch, h, Ug, vk, Store{Q, 0, h});
-        ok = store_fit<T>(ctl, q, nq, h, Span{Q, 0, h});
-        if (ok)
-            for (int i = tid<T>(); i < nv; i += T) r[i] = i == 0 ? rem : 0u;
-    } else if (lowz && vk == 1u) {                // v = B^k: shinv = B^(h-k), q = u >> k
-        ok = store_fit<T>(ctl, q, nq, h - k, Span{u, -k, h});
-        if (ok)
-            for (int i = tid<T>(); i < nv; i += T) r[i] = i < k ? u[i] : 0u;
-    } else {
-        const Plan pl = plan_div(h, k);
-        uint32_t *V = lds + pl.offV, *W = lds + pl.offW, *X = lds + pl.offX;
-        uint32_t *SB = lds + pl.offSB, *P = lds + pl.offP, *XR = lds + pl.offR;
-        // V = v (already there); W, X, R and the window staging area (with its guards) = 0
-        copy<T>(V + k + 1, 0, pl.offP - pl.offV - k - 1, Zero{});
-        MP_STAMP(2);
-        int we = 0, nw = 0, shf = 0, sbext = 0;
-        bool good = true;
-        if (k == h - 1 && (vk > 0x80000000u || (vk == 0x80000000u && !lowz))) {
-            bar<T>();                               // 2v > B^h: shinv = 1
-            if (tid<T>() == 0) W[0] = 1u;
-            we = 1;
-            nw = 1;
-            shf = 0;
-        } else {
-            good = refine<T>(ctl, pl, kn, lds, h, k, we, nw, shf, sbext, head_record<T>(rec, nq, h, k));
-        }
-        if (good) {
-            // q0 = shift_{-h}(u * s)
-            const uint32_t *S = W + shf;
-            const int ns = imax(nw - shf, 0);
-            good = ns <= h;
-            if (good) {
-                // only the columns from c0 = h - 2 (rounded down to a multiple of 8)
-                // up: the products below c0 sum to less than B^h, so the top
-                // limbs are floor(u s / B^h) or one less (one more on the matrix
-                // cores, whose digit products below c0 may be negative)
-                const int c0 = imax(h - 2, 0) & ~7;
-                good = h + ns - c0 <= pl.capP;
-            }
-            if (good) {
-                // column c of the product goes to P[c - c0]
-                const int c0 = imax(h - 2, 0) & ~7;
-                const int np = product_views<T, true>(ctl, P - c0, h + ns, Ug, h, nullptr, Span{S, 0, ns}, ns, S, SB,
-                                                      sbext, XR, pl.capR, kn.mfma_min, c0);
-                MP_STAMP(5);
-                const int nq0 = imax(np - h, 0);
-                copy<T>(W, nq0, we, Span{P, c0 - h, h + ns - c0});
-                we = nq0;
-                // With s within two of the shifted inverse (the Step products
-                // are clipped too), q - 4 <= q0 <= q + 3 and r0 = u - v q0 lies
-                // in [-3v, 5v): |r0| < B^(k+2) / 2, so r0 is exact as a signed
-                // (k+2)-limb number and only the low k+2 limbs of m = v q0 are
-                // needed.  The loops below allow one more step each way.
-                const int rl = k + 2;
-                product<T>(ctl, P, rl, W, nq0, V, k + 1, SB, sbext, XR, pl.capR, kn.mfma_min, 0, false);
-                MP_STAMP(6);
-                uint32_t *R = SB, *R2 = X;
-                int delta = 0;
-                addsub<T>(ctl, rl, true, 0u, Ug, Span{P, 0, rl}, Store{R, 0, rl});
-                // r0 < 0 (top bit of the signed value): add v until it is not
-                for (int it = 0; good; it++) {
-                    bar<T>();
-                    if (!(R[rl - 1] >> 31)) break;
-                    if (it == 4) { good = false; break; }
-                    addsub<T>(ctl, rl, false, 0u, Span{R, 0, rl}, Span{V, 0, k + 1}, Store{R, 0, rl});
-                    delta -= 1;
-                }
-                // now 0 <= r < 6v
-                for (int it = 0; good; it++) {
-                    if (addsub<T>(ctl, rl, true, 0u, Span{R, 0, rl}, Span{V, 0, k + 1}, Store{R2, 0, rl}))
-                        break;                    // r < v
-                    if (it == 5) { good = false; break; }
-                    uint32_t *t = R;
-                    R = R2;
-                    R2 = t;
-                    delta += 1;
-                }
-                if (good && delta != 0) {
-                    addsub<T>(ctl, we + 1, delta < 0, 0u, Span{W, 0, we}, Limb0{(uint32_t)(delta < 0 ? -delta : delta)},
-                              Store{W, 0, we + 1});
-                    we += 1;
-                }
-                MP_STAMP(7);
-                if (good) {
-                    ok = store_fit<T>(ctl, q, nq, we, Span{W, 0, we});
-                    if (ok)
-                        for (int i = tid<T>(); i < nv; i += T) r[i] = i < k + 1 ? R[i] : 0u;
-                }
-            }
-        }
-        if (!good) st = kInstInternal;
-    }
-    if (st == kInstOk && !ok) st = kInstQWidth;
-    if (st != kInstOk) {
-        bar<T>();
-        store_zero<T>(q, nq);
-        store_zero<T>(r, nv);
-    }
-    if (status && tid<T>() == 0) *status = st;
-    MP_STAMP(8);
-    MP_RSTAMP(15);
 }
 
 }  // namespace mp

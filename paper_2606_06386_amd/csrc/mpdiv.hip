@@ -4,6 +4,7 @@
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
 #include "mp_div.hpp"
+#include "mp_block.hpp"
 #include "launch.hpp"
 
 #include "../../include/mpdiv.h"
@@ -20,36 +21,21 @@ constexpr int kLdsWords = 160 * 1024 / 4;   // gfx950: 160 KB of LDS per workgro
 // run-time knobs (mp_set_knob)
 std::atomic<int32_t> g_mfma_min{64}, g_small_limit{MP_SMALL_LIMIT_AUTO};
 
-// Head limits of the automatic setting.  The head runs every instance of a
-// batch at once (one wave each), the bodies in rounds of workgroups; moving
-// the Refine iteration whose iterate is ~130 limbs into the head costs its
-// latency once and saves it in every body round, so it pays from two rounds
-// on.
-constexpr int kSmallOneRound = 96, kSmallRounds = 136;
-static_assert(kSmallRounds <= mp::kHeadMaxLimit, "automatic head limit out of range");
-
 int device_cus();
 
-// the knobs of a launch whose body workgroups of T threads use `bytes` of LDS,
-// for `count` instances (the automatic head limit resolved)
-mp::Knobs knobs_for(int T, size_t bytes, int64_t count)
+// the knobs of a launch (the automatic head limit, and limits below the
+// smallest block, resolved)
+mp::Knobs knobs_now()
 {
-    int sl = g_small_limit.load();
-    if (sl == MP_SMALL_LIMIT_AUTO) {
-        const int cus = device_cus();
-        int per_cu = 16 / (T / 64);                 // four waves per SIMD
-        const int by_lds = bytes ? (int)(160 * 1024 / bytes) : per_cu;
-        per_cu = per_cu < by_lds ? per_cu : by_lds;
-        const int64_t slots = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
-        sl = count > slots ? kSmallRounds : kSmallOneRound;
-    }
-    return mp::Knobs{g_mfma_min.load(), sl};
+    const int sl = g_small_limit.load();
+    return mp::Knobs{g_mfma_min.load(), sl == MP_SMALL_LIMIT_AUTO ? 136 : mp::hmax(sl, mp::kHeadMinLimit)};
 }
 
-// a head kernel runs first when it has iterations to do and an output row can
-// hold a record with at least a few limbs (rows too short get none and the
-// body does every step)
-int use_head(const mp::Knobs &kn, int row) { return kn.small_limit > 0 && row >= mp::kRecHdr + 8; }
+// a head kernel runs first when an output row can hold a record (otherwise the
+// instances are short and the bodies make their own inverses)
+int use_head(int row) { return mp::record_block(row) >= mp::kSmallBlock; }
+
+size_t body_bytes(int nu, int nv) { return (size_t)mp::plan_body(nu, nv).total * 4; }
 
 // ------------------------------------------------------------ ragged batches
 //
@@ -205,25 +191,18 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
 {
     const int cus = device_cus();
     if (cus <= 0) return MP_ERR_DEVICE;
-    // (the automatic head limit counts rounds of the narrowest class's workgroups)
-    static const size_t narrow_bytes = (size_t)mp::div_lds_words(kClassWidth[0], kClassWidth[0], 256) * 4;
-    const mp::Knobs kn = knobs_for(256, narrow_bytes, count);
+    const mp::Knobs kn = knobs_now();
     hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, u_limbs, v_limbs, q_limbs,
                        r_limbs, inst_status, ws);
     if (hipGetLastError() != hipSuccess) return MP_ERR_LAUNCH;
-    const int head = kn.small_limit > 0;
-    if (head && mp::launch_head_ragged(st, u_pool, v_pool, desc, q_pool, ws, count, kn) != hipSuccess)
+    if (mp::launch_head_ragged(st, u_pool, v_pool, desc, q_pool, r_pool, ws, count, kn) != hipSuccess)
         return MP_ERR_LAUNCH;
     if (fk && hipEventRecord(fk->ev_fork, st) != hipSuccess) return MP_ERR_LAUNCH;
     for (int c = 0; c < kClasses; c++) {
         hipStream_t fs = fk ? fk->fs[c] : st;
         if (fk && hipStreamWaitEvent(fs, fk->ev_fork, 0) != hipSuccess) return MP_ERR_LAUNCH;
         const int T = g_ragged.threads[c];
-        // LDS of the class's widest instance (a scan over every divisor length: computed once)
-        static size_t lds_bytes[kClasses][3];
-        const int ti = T == 256 ? 0 : T == 512 ? 1 : 2;
-        if (lds_bytes[c][ti] == 0) lds_bytes[c][ti] = (size_t)mp::div_lds_words(kClassWidth[c], kClassWidth[c], T) * 4;
-        const size_t bytes = lds_bytes[c][ti];
+        const size_t bytes = body_bytes(kClassWidth[c], kClassWidth[c]);   // the class's widest instance
         if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
         const int fit = (int)(((size_t)kLdsWords * 4) / bytes);
         const int wpc = g_ragged.wgs_per_cu[c] < fit ? g_ragged.wgs_per_cu[c] : fit;
@@ -232,15 +211,15 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
         switch (T) {
         case 256:
             e = mp::launch_ragged<256>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, kn, head);
+                                       count, 1);
             break;
         case 512:
             e = mp::launch_ragged<512>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, kn, head);
+                                       count, 1);
             break;
         default:
             e = mp::launch_ragged<1024>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                        count, kn, head);
+                                        count, 1);
             break;
         }
         if (e != hipSuccess) return MP_ERR_LAUNCH;
@@ -299,14 +278,8 @@ int64_t mp_lds_bytes(int32_t op, int32_t n1, int32_t n2)
     if (n1 <= 0 || n2 <= 0 || n1 > kMaxLimbs || n2 > kMaxLimbs) return -1;
     switch (op) {
     case MP_OP_MUL: return (int64_t)4 * mp::mul_lds_words(n1, n2);
-    case MP_OP_DIVREM: return (int64_t)4 * mp::div_lds_words(n1, n2, threads_for(n1));
-    case MP_OP_SHINV: {
-        const int T = threads_for(n2);
-        int words = mp::plan_short_words(n2 + 1, T);
-        const int kmax = (n1 < n2 ? n1 : n2) - 1;
-        for (int k = 1; k <= kmax; k++) words = mp::hmax(words, mp::plan_div(n2, k).total);
-        return (int64_t)4 * words;
-    }
+    case MP_OP_DIVREM: return (int64_t)body_bytes(n1, n2);
+    case MP_OP_SHINV: return (int64_t)body_bytes(n2 + 1, n1);
     }
     return -1;
 }
@@ -322,7 +295,7 @@ mp_status_t mp_mul_batch(const uint32_t *a, int32_t na, const uint32_t *b, int32
     if (words > kLdsWords) return MP_ERR_SIZE;
     const size_t bytes = (size_t)words * 4;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_for(threads_for((na + nb + 1) / 2), bytes, batch);
+    const mp::Knobs kn = knobs_now();
     switch (threads_for((na + nb + 1) / 2)) {
     case 256: return status_of(mp::launch_mul<256>(batch, bytes, st, a, na, b, nb, c, kn));
     case 512: return status_of(mp::launch_mul<512>(batch, bytes, st, a, na, b, nb, c, kn));
@@ -338,19 +311,16 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(h > 0 ? h : 1);
-    int words = mp::plan_short_words(h + 1, T);
-    const int kmax = (nv < h ? nv : h) - 1;
-    for (int k = 1; k <= kmax; k++) words = mp::hmax(words, mp::plan_div(h, k).total);
-    if (words > kLdsWords) return MP_ERR_SIZE;
-    const size_t bytes = (size_t)words * 4;
+    const size_t bytes = body_bytes(h + 1, nv);
+    if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_for(T, bytes, batch);
-    const int head = use_head(kn, nw);
+    const mp::Knobs kn = knobs_now();
+    const int head = use_head(nw);
     if (head && mp::launch_head_shinv(st, v, nv, h, w, nw, batch, kn) != hipSuccess) return MP_ERR_LAUNCH;
     switch (T) {
-    case 256: return status_of(mp::launch_shinv<256>(batch, bytes, st, v, nv, h, w, nw, inst_status, kn, head));
-    case 512: return status_of(mp::launch_shinv<512>(batch, bytes, st, v, nv, h, w, nw, inst_status, kn, head));
-    default: return status_of(mp::launch_shinv<1024>(batch, bytes, st, v, nv, h, w, nw, inst_status, kn, head));
+    case 256: return status_of(mp::launch_shinv<256>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
+    case 512: return status_of(mp::launch_shinv<512>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
+    default: return status_of(mp::launch_shinv<1024>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
     }
 }
 
@@ -363,20 +333,19 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(nu);
-    const int words = mp::div_lds_words(nu, nv, T);
-    if (words > kLdsWords) return MP_ERR_SIZE;
-    const size_t bytes = (size_t)words * 4;
+    const size_t bytes = body_bytes(nu, nv);
+    if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_for(T, bytes, batch);
-    const int head = use_head(kn, nq);
-    if (head && mp::launch_head_divrem(st, u, nu, v, nv, q, nq, batch, kn) != hipSuccess) return MP_ERR_LAUNCH;
+    const mp::Knobs kn = knobs_now();
+    const int head = use_head(nq > nv ? nq : nv);
+    if (head && mp::launch_head_divrem(st, u, nu, v, nv, q, nq, r, batch, kn) != hipSuccess) return MP_ERR_LAUNCH;
     switch (T) {
     case 256:
-        return status_of(mp::launch_divrem<256>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, kn, head));
+        return status_of(mp::launch_divrem<256>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
     case 512:
-        return status_of(mp::launch_divrem<512>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, kn, head));
+        return status_of(mp::launch_divrem<512>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
     default:
-        return status_of(mp::launch_divrem<1024>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, kn, head));
+        return status_of(mp::launch_divrem<1024>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
     }
 }
 
