@@ -374,7 +374,6 @@ BLOCK_PHASES = ["top_digits", "quotient_product", "quotient_digits", "remainder_
 
 
 RT_HZ = 100e6   # rate of the real-time counter (s_memrealtime)
-kHEAD_WAVES = 4  # head instances (waves) per workgroup
 
 
 def clock_stats(c0, c1, r0, r1, event_ms=None):
@@ -433,68 +432,23 @@ def phase_trace(args):
     st = np.zeros((batch, 32), dtype=np.uint64)
     assert L.mp_trace_read_divrem(st.ctypes.data, batch) == 0
     st = st.astype(np.float64)
-    order = [0, 1, 2, 6, 7, 8]                       # stamps of every instance that is divided in blocks
+    order = [0, 1, 9, 2, 6, 7, 8]                    # stamps of every instance that is divided in blocks
     full = (st[:, order] > 0).all(axis=1) & (np.diff(st[:, order], axis=1) >= 0).all(axis=1)
-    full &= (st[:, 16:20] > 0).all(axis=1) & (st[:, 16] >= st[:, 2]) & (st[:, 6] >= st[:, 19])
+    full &= (st[:, 16:18] > 0).all(axis=1) & (st[:, 16] >= st[:, 2])
     rows = st[full]
-    res = {"record": float(np.mean(rows[:, 1] - rows[:, 0])), "operands": float(np.mean(rows[:, 2] - rows[:, 1]))}
+    res = {"precisions": float(np.mean(rows[:, 1] - rows[:, 0])),
+           "divisor_digits": float(np.mean(rows[:, 9] - rows[:, 1])), "newton": float(np.mean(rows[:, 2] - rows[:, 9]))}
     prev = rows[:, 2].copy()
-    for i in range(16):                              # four stamps per block, the last four blocks
+    for i in range(16):                              # the stamps of the last blocks
         col = rows[:, 16 + i]
         if not (col > 0).all():
             break
-        res["block_%d_%s" % (i // 4, BLOCK_PHASES[i % 4])] = float(np.mean(col - prev))
+        res["block_%d_%s" % (i // len(BLOCK_PHASES), BLOCK_PHASES[i % len(BLOCK_PHASES)])] = float(np.mean(col - prev))
         prev = col
-    # the head launch (one wave per instance): its own stamps
-    L.mp_trace_read_head.argtypes = [ctypes.c_void_p, ctypes.c_int]
-    L.mp_trace_read_head.restype = ctypes.c_int
-    hs = np.zeros((batch, 32), dtype=np.uint64)
-    assert L.mp_trace_read_head(hs.ctypes.data, batch) == 0
-    hs = hs.astype(np.float64)
-    hfull = (hs[:, [0, 1, 2, 3, 4]] > 0).all(axis=1)
-    hr = hs[hfull]
-    head = {"instances": int(hfull.sum())}
-    if len(hr):
-        head["precisions"] = float(np.mean(hr[:, 1] - hr[:, 0]))
-        head["stage_v"] = float(np.mean(hr[:, 2] - hr[:, 1]))
-        head["initial_approx"] = float(np.mean(hr[:, 3] - hr[:, 2]))
-        prev_h = hr[:, 3].copy()
-        for i in range(16):
-            col = hr[:, 16 + i]
-            if not (col > 0).any():
-                continue
-            head["iter_%d" % i] = float(np.mean(np.where(col > 0, col - prev_h, 0)))
-            prev_h = np.where(col > 0, col, prev_h)
-        # sub-steps of iterations 3 and 6 (PowDiff product, residual, Step product, Step add)
-        for i, sl in ((3, 5), (6, 8)):
-            if "iter_%d" % i not in head or "iter_%d" % (i - 1) not in head:
-                continue
-            ok = (hr[:, [15 + i, sl, sl + 1, sl + 2, 16 + i]] > 0).all(axis=1)
-            if ok.any():
-                r = hr[ok]
-                t = [r[:, 15 + i], r[:, sl], r[:, sl + 1], r[:, sl + 2], r[:, 16 + i]]
-                head["iter_%d_steps" % i] = [float(np.mean(t[j + 1] - t[j])) for j in range(4)]
-        # real-time stamps (100 MHz) at each head's start and end: the spread
-        # of starts (dispatch) and of durations behind the kernel's length
-        rt = hs[hfull][:, [14, 15]]
-        if (rt > 0).all():
-            st_us, en_us = (rt[:, 0] - rt[:, 0].min()) / RT_HZ * 1e6, (rt[:, 1] - rt[:, 0].min()) / RT_HZ * 1e6
-            dur = en_us - st_us
-            head["realtime_us"] = {"start_p50": float(np.percentile(st_us, 50)), "start_max": float(st_us.max()),
-                                   "duration_p50": float(np.percentile(dur, 50)),
-                                   "duration_p90": float(np.percentile(dur, 90)), "duration_max": float(dur.max()),
-                                   "end_max": float(en_us.max())}
-            # medians per quarter of the head workgroups, in launch order
-            wgq = (np.nonzero(hfull)[0] // kHEAD_WAVES) * 4 // max(1, -(-len(hs) // kHEAD_WAVES))
-            head["realtime_us"]["duration_p50_by_wg_quarter"] = [float(np.median(dur[wgq == r])) if (wgq == r).any()
-                                                                 else None for r in range(4)]
-        head["record"] = float(np.mean(hr[:, 4] - prev_h))
-        head["total"] = float(np.mean(hr[:, 4] - hr[:, 0]))
-        head["span_all_waves"] = float(hr[:, 4].max() - hr[:, 0].min())
     res["corrections"] = float(np.mean(rows[:, 7] - rows[:, 6]))
     res["store"] = float(np.mean(rows[:, 8] - rows[:, 7]))
     total = float(np.mean(rows[:, 8] - rows[:, 0]))
-    print(json.dumps({"phase_trace": c["name"], "kernel": "k_divrem<256>", "head": head,
+    print(json.dumps({"phase_trace": c["name"], "kernel": "k_divrem<256>",
                       "instances": int(full.sum()),
                       "knobs": knobs_now(), "clock": "shader cycles (s_memtime) of workgroup thread 0",
                       "body_clock": clock_stats(st[:, 0], st[:, 8], st[:, 14], st[:, 15], e0.elapsed_time(e1)),

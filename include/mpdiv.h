@@ -162,20 +162,15 @@ mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
  * Run-time tuning knobs of the division kernels (process-wide; a change
  * applies to launches made after it).  Every setting gives the same results
  * bit for bit; only the speed differs.
- *   MP_KNOB_MFMA_MIN     products whose shorter operand has at least this many
- *                        limbs (>= 1) run on the int8 matrix cores as exact
+ *   MP_KNOB_MFMA_MIN     mp_mul_batch: products whose shorter operand has at least
+ *                        this many limbs (>= 1) run on the int8 matrix cores as exact
  *                        balanced radix-256 digit products; shorter ones on the
  *                        vector ALU (32x32->64-bit multiply-adds).  Default 64.
  *   MP_KNOB_SMALL_LIMIT  the quotient is found in blocks of limbs from an
- *                        inverse of one block's precision, which a head
- *                        launch computes, one wave per instance, by Refine
- *                        iterations whose iterates have fewer than this many
- *                        limbs (0..140; below 16 counts as 16), so it bounds
- *                        the block: 257 limbs from 133 on.  The head leaves
- *                        the inverse in the longer of the instance's q and r
- *                        rows (mp_shinv_batch: w), which the results then
- *                        overwrite; instances whose rows are shorter than 27
- *                        limbs make a small inverse in their own workgroup.
+ *                        inverse of one block's precision, which Newton steps
+ *                        on one wave compute; this bounds the iterate the last
+ *                        step starts from, in limbs (0..140; below 16 counts
+ *                        as 16), and with it the block: 257 limbs from 133 on.
  *                        MP_SMALL_LIMIT_AUTO (the default) is 136.
  * mp_set_knob returns MP_ERR_ARG for an unknown knob or a value out of range;
  * mp_get_knob returns the current value (-1 for an unknown knob).

@@ -5,36 +5,26 @@
 // width so that every linear pass handles at most 16 limbs per thread:
 //   width <= 2048 limbs -> 256 threads, <= 4096 -> 512, <= 8192 -> 1024.
 // All operands and intermediates of an instance live in dynamic LDS laid out
-// by plan_div (about 4h + 800 words: 36 KB at 2^16 bits, 134 KB at 2^18).
-//
-// A division or shifted inverse may run in two launches: the head kernels
-// (four waves per workgroup, one instance per wave) compute the initial
-// approximation and the Refine iterations with short operands and leave a
-// record in each instance's output row; the body kernels pick it up.
+// by plan_body (21 KB at 2^16 bits, 74 KB at most at 2^18).
 //
 // The build compiles this file once per kernel family and workgroup size
-// (MP_KFAMILY: 0 product, 1 shifted inverse, 2 division, 3 ragged division,
-// 4 heads; MP_KT: threads), each object holding one explicit instantiation
+// (MP_KFAMILY: 0 product, 1 shifted inverse, 2 division, 3 ragged division;
+// MP_KT: threads), each object holding one explicit instantiation
 // of a launcher, so the translation units compile in parallel.
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
-#include "mp_div.hpp"
+#include "mp_mul.hpp"
 #include "mp_block.hpp"
 
 namespace mp {
 
-// Division kernels ask the compiler for at most 128 registers per lane (four
-// waves per SIMD: four 256-thread workgroups per compute unit at 2^16 bits).
-// MP_BODY_WAVES=5 builds the 256-thread kernels for five (96 registers, a few
-// spills; the LDS plan at 2^16 bits also allows five): measured slower, as the
-// instances then contend for the same units.
-#ifndef MP_BODY_WAVES
-#define MP_BODY_WAVES 4
-#endif
-#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(T == 256 ? MP_BODY_WAVES : 4, 8)))
-// heads: four waves per SIMD (16 per compute unit, which is also what their LDS allows)
-#define MP_HEAD_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
-
+// Registers of the division kernels.  A 256-thread instance spends much of its
+// time in phases that one of its waves runs (Newton steps, a block's digits
+// and quotient product), so further resident instances fill the other waves'
+// issue slots: six waves per SIMD (80 registers; the LDS of a 2^16-bit
+// instance, 20 KB, allows seven) take 176 us for 4096 divisions of 2048 by 1024
+// limbs, five 203 us, four 205 us.  The wider workgroups are bound by their LDS.
+#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(T == 256 ? 6 : 4, 8)))
 // Workspace of a ragged batch (int32): [0, 4) instances per class, [4, 8)
 // queue heads, then one list of instance indices per class, each `count` long.
 constexpr int kClasses = 4;
@@ -48,34 +38,34 @@ MP_DEV int64_t uniform64(int64_t x)
 
 template <int T>
 __global__ __launch_bounds__(T) void k_mul(const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
-                                           Knobs kn)
+                                           int mfma_min)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
-    mul_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb), kn);
+    mul_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb), mfma_min);
 }
 
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_shinv(const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                                                          int32_t *status, int head)
+                                                          int32_t *status, int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *wj = w + j * nw;
     divide_instance<T>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
-                       head ? wj : nullptr);
+                       bmax);
 }
 
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, int nu, const uint32_t *v, int nv,
                                                            uint32_t *q, int nq, uint32_t *r, int32_t *status,
-                                                           int head)
+                                                           int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *qj = q + j * nq, *rj = r + j * nv;
     divide_instance<T>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
-                       head ? (nq >= nv ? qj : rj) : nullptr);
+                       bmax);
 }
 
 // persistent workgroups of one class: take the next instance of the class's
@@ -83,7 +73,7 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, in
 template <int T>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
                                                            const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
-                                                           int32_t *status, int32_t *ws, int cls, int count, int head)
+                                                           int32_t *status, int32_t *ws, int cls, int count, int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int n = ws[cls];
@@ -100,140 +90,52 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, c
                       ro = uniform64(d.r_off);
         const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
         divide_instance<T>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j,
-                           head ? (nq >= nv ? qp + qo : rp + ro) : nullptr);
+                           bmax);
     }
 }
 
 template <int T>
 hipError_t launch_mul(int grid, size_t lds, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb,
-                      uint32_t *c, Knobs kn)
+                      uint32_t *c, int mfma_min)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_mul<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mul<T>, dim3(grid), dim3(T), lds, st, a, na, b, nb, c, kn);
+    hipLaunchKernelGGL(k_mul<T>, dim3(grid), dim3(T), lds, st, a, na, b, nb, c, mfma_min);
     return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
-                        int32_t *status, int head)
+                        int32_t *status, int bmax)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_shinv<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_shinv<T>, dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, head);
+    hipLaunchKernelGGL(k_shinv<T>, dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, bmax);
     return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
-                         uint32_t *q, int nq, uint32_t *r, int32_t *status, int head)
+                         uint32_t *q, int nq, uint32_t *r, int32_t *status, int bmax)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_divrem<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_divrem<T>, dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, head);
+    hipLaunchKernelGGL(k_divrem<T>, dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, bmax);
     return hipGetLastError();
 }
 
 template <int T>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
-                         int count, int head)
+                         int count, int bmax)
 {
     if (!lds_attr(reinterpret_cast<const void *>(k_ragged<T>), lds)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_ragged<T>, dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count,
-                       head);
+                       bmax);
     return hipGetLastError();
 }
-
-#if defined(MP_KFAMILY) && MP_KFAMILY == 4
-// heads (not templates: compiled in their own translation unit only)
-
-// Heads: wave w of workgroup b owns instance b * kHeadWaves + w and the
-// `words` LDS words at lds + w * words (no workgroup barrier anywhere).
-__global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_divrem(const uint32_t *u, int nu, const uint32_t *v,
-                                                                      int nv, uint32_t *q, int nq,
-                                                                      uint32_t *r, int batch, int words, Knobs kn)
-{
-    extern __shared__ __align__(16) uint32_t lds[];
-    const int w = (int)(threadIdx.x / kLanes);
-    const size_t j = (size_t)blockIdx.x * kHeadWaves + w;
-    if (j >= (size_t)batch) return;
-    uint32_t *rec = nq >= nv ? q + j * nq : r + j * nv;
-    head_divrem(lds + w * words, u + j * nu, nu, v + j * nv, nv, rec, nq >= nv ? nq : nv, nq, kn);
-}
-
-__global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_shinv(const uint32_t *v, int nv, int h, uint32_t *w,
-                                                                     int nw, int batch, int words, Knobs kn)
-{
-    extern __shared__ __align__(16) uint32_t lds[];
-    const int wv = (int)(threadIdx.x / kLanes);
-    const size_t j = (size_t)blockIdx.x * kHeadWaves + wv;
-    if (j >= (size_t)batch) return;
-    head_shinv(lds + wv * words, h, v + j * nv, nv, w + j * nw, nw, kn);
-}
-
-// heads of a ragged batch: wave g takes the g-th valid instance of the class
-// lists (the preparation kernel's buckets, in class order)
-__global__ __launch_bounds__(kLanes * kHeadWaves) MP_HEAD_OCCUPANCY void k_head_ragged(const uint32_t *up, const uint32_t *vp,
-                                                                      const mp_desc_t *desc, uint32_t *qp,
-                                                                      uint32_t *rp, const int32_t *ws, int count,
-                                                                      int words, Knobs kn)
-{
-    extern __shared__ __align__(16) uint32_t lds[];
-    const int w = (int)(threadIdx.x / kLanes);
-    int idx = (int)blockIdx.x * kHeadWaves + w, c = 0;
-    while (c < kClasses && idx >= ws[c]) idx -= ws[c++];
-    if (c == kClasses) return;
-    const int j = uniform(ws[kWsHeader + (size_t)c * count + idx]);
-    const mp_desc_t &d = desc[j];
-    const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off),
-                  ro = uniform64(d.r_off);
-    const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-    head_divrem(lds + w * words, up + uo, nu, vp + vo, nv, nq >= nv ? qp + qo : rp + ro, nq >= nv ? nq : nv, nq, kn);
-}
-
-// LDS words of one head wave for the current knobs
-int head_words(const Knobs &kn) { return plan_head(kn.small_limit, 0).total; }
-
-hipError_t launch_head_divrem(hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv, uint32_t *q,
-                              int nq, uint32_t *r, int batch, Knobs kn)
-{
-    const int words = head_words(kn);
-    const size_t lds = (size_t)words * 4 * kHeadWaves;
-    if (!lds_attr(reinterpret_cast<const void *>(k_head_divrem), lds)) return hipErrorInvalidValue;
-    const int grid = (batch + kHeadWaves - 1) / kHeadWaves;
-    hipLaunchKernelGGL(k_head_divrem, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, u, nu, v, nv, q, nq, r, batch,
-                       words, kn);
-    return hipGetLastError();
-}
-
-hipError_t launch_head_shinv(hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw, int batch,
-                             Knobs kn)
-{
-    const int words = head_words(kn);
-    const size_t lds = (size_t)words * 4 * kHeadWaves;
-    if (!lds_attr(reinterpret_cast<const void *>(k_head_shinv), lds)) return hipErrorInvalidValue;
-    const int grid = (batch + kHeadWaves - 1) / kHeadWaves;
-    hipLaunchKernelGGL(k_head_shinv, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, v, nv, h, w, nw, batch, words,
-                       kn);
-    return hipGetLastError();
-}
-
-hipError_t launch_head_ragged(hipStream_t st, const uint32_t *up, const uint32_t *vp, const mp_desc_t *desc,
-                              uint32_t *qp, uint32_t *rp, const int32_t *ws, int count, Knobs kn)
-{
-    const int words = head_words(kn);
-    const size_t lds = (size_t)words * 4 * kHeadWaves;
-    if (!lds_attr(reinterpret_cast<const void *>(k_head_ragged), lds)) return hipErrorInvalidValue;
-    const int grid = (count + kHeadWaves - 1) / kHeadWaves;
-    hipLaunchKernelGGL(k_head_ragged, dim3(grid), dim3(kLanes * kHeadWaves), lds, st, up, vp, desc, qp, rp, ws, count,
-                       words, kn);
-    return hipGetLastError();
-}
-
-#endif
 
 #if defined(MP_KFAMILY) && defined(MP_KT)
 #if MP_KFAMILY == 0
 template hipError_t launch_mul<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
-                                      uint32_t *, Knobs);
+                                      uint32_t *, int);
 #elif MP_KFAMILY == 1
 template hipError_t launch_shinv<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
                                         int32_t *, int);
@@ -248,15 +150,6 @@ template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_
 #endif
 
 }  // namespace mp
-
-#if defined(MP_PHASE_TRACE) && MP_KFAMILY == 4
-// copies the head stamps of the first `waves` instances (32 per instance) to host memory
-extern "C" int mp_trace_read_head(uint64_t *dst, int waves)
-{
-    return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(mp_trace_buf), (size_t)waves * 32 * sizeof(uint64_t), 0,
-                                    hipMemcpyDeviceToHost);
-}
-#endif
 
 #if defined(MP_PHASE_TRACE) && MP_KFAMILY == 0 && MP_KT == 256
 // copies the stamps of the first `blocks` product workgroups (32 per workgroup) to host memory

@@ -1,23 +1,23 @@
 // Block division: one workgroup divides u by v in blocks of quotient limbs.
 //
-// The head leaves an approximation W of B^(k+dp+2) / v (dp at most 257 limbs
-// of precision, two guard limbs).  The quotient's d = h - k limbs are found in
-// nb blocks from the top, block i holding the limbs [o_i, o_(i-1)):
+// First W ~ B^(k+dp+2) / v is computed for a precision of dp <= 257 limbs (and
+// two guard limbs) by Newton steps on one wave.  Then the quotient's d = h - k
+// limbs are found in nb blocks from the top, block i holding the limbs
+// [o_i, o_(i-1)):
 //     q_i = floor(R_top W / B^(dp+3)),   R_top = floor(R / B^(o_i+k-1))
 //     R  <- R - v q_i B^(o_i)
-// with a signed remainder R that starts as u.  Both products run on the int8
+// with a signed remainder R that starts as u.  All products run on the int8
 // matrix cores over balanced radix-256 digits; the digits of v and of W are
 // made once per instance, those of R_top and of -q_i once per block, and R is
 // added to the accumulators of the second product, so the subtraction costs
 // no pass of its own.  After the last block r = R up to a few multiples of v.
 //
-// Against one full-precision inverse followed by u * shinv and v * q this
-// needs no Newton iteration beyond 257 limbs and about half the limb products
-// (a 2048 by 1024-limb division: 1.2e6 instead of 1.8e6), and every operand
-// converted to digits is at most one block long.
+// Against one full-precision inverse followed by u * shinv and v * q (Alg. 1
+// and 3 as printed) this needs no Newton step beyond 257 limbs and fewer limb
+// products (a 2048 by 1024-limb division: 1.2e6 instead of 1.8e6), and every
+// operand converted to digits is at most one block long.
 //
-// Error bounds (W = B^(k+dp+2)/v - E with |E| a few units; measured at most 2
-// over structured divisors, and clipping adds at most one per iteration):
+// Error bounds.  With W = B^(k+dp+2)/v - E and |E| <= 3 (see newton),
 // |R| < 2.1 v B^(o_(i-1)) gives R_top W / B^(dp+3) = R / (v B^(o_i)) + e with
 // |e| < 2^-20; the floor and the columns of R_top W below cA add at most one
 // unit each, so q_i is within (-2, 1] of the real ratio: after the block
@@ -26,21 +26,51 @@
 // whose top limb is its sign, and at most two corrections each way remain.
 #pragma once
 
-#include "mp_div.hpp"
+#include "launch.hpp"
 
 namespace mp {
+
+enum : int32_t { kInstOk = 0, kInstDivZero = 1, kInstQWidth = 2, kInstInternal = 3 };
+
+// The quotient's d limbs: nb blocks of bi limbs, the first (top) of
+// d - (nb - 1) bi; dp limbs of precision of W serve the longest of them.  bi
+// is a multiple of 4, so that every block starts at a 16-byte boundary of R.
+struct BlockSplit {
+    int nb, bi, dp;
+};
+
+// Longest block: W and one block's operands of up to 257 limbs keep every
+// Newton product within one 256-column strip (f = 131 -> 259 limbs is the last
+// step that does).
+constexpr int kBlockMax = 257;
+
+MP_HD BlockSplit block_split(int d, int bmax)
+{
+    if (d <= bmax) return BlockSplit{1, 0, d > 2 ? d : 2};
+    const int top = bmax & ~3, nb = 1 + (d - bmax + top - 1) / top;
+    const int even = r4((d + nb - 1) / nb), bi = even < top ? even : top, b0 = d - (nb - 1) * bi;
+    return BlockSplit{nb, bi, b0 > bi ? b0 : bi};
+}
+
+// longest block for a limit on the iterates of the Newton steps (the small_limit knob)
+MP_HD int block_limit(int limit)
+{
+    int b = 17;
+    while (2 * b - 1 <= kBlockMax && b + 3 < limit) b = 2 * b - 1;
+    return b;
+}
 
 // ---------------------------------------------------------------- LDS layout
 //
 // ctl | pad | V plane 0 | pad | V plane 1 | pad | R_top plane 0 | pad |
-// R_top plane 1 | pad | W reversed | -q reversed | P | R
+// R_top plane 1 | pad | W reversed | -q reversed | W | P | R
 // (pads of kYPadBlk zero blocks shared by their neighbours).  R holds the
 // dividend's h limbs and above them the quotient: limb j of q goes to
 // R[k + 2 + j], which the remainder has left by the time the block is done.
 struct BodyPlan {
     int nbV, lyV, offV;       // 8-limb blocks of the divisor's digits, distance of the planes, first word
     int nbT, lyT, offT;       // the same for R_top
-    int offW, offQ, offP, offR;
+    int offX, offQ, offW, offP, offR;   // W's reversed digits, -q's, W's limbs, q's columns, R
     int capR;
     int total;
 };
@@ -60,9 +90,10 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
     p.lyV = 4 * p.nbV + kPadWords;
     p.offT = p.offV + 2 * p.lyV;
     p.lyT = 4 * p.nbT + kPadWords;
-    p.offW = p.offT + 2 * p.lyT + kXPad;
-    p.offQ = r4(p.offW + dm + 4 + kXPad);
-    p.offP = r4(p.offQ + dm + 1 + kXPad);
+    p.offX = p.offT + 2 * p.lyT + kXPad;
+    p.offQ = r4(p.offX + dm + 4 + kXPad);
+    p.offW = r4(p.offQ + dm + 1 + kXPad);
+    p.offP = p.offW + r4(dm + 4);
     p.offR = p.offP + r4(dm + 16);
     p.capR = r4(nu + 8);
     p.total = p.offR + p.capR;
@@ -96,6 +127,7 @@ MP_DEV uint32_t row_carry_out(uint64_t G, uint64_t P)
 }
 
 constexpr uint32_t kBal = 0x80808080u;
+constexpr int kRowBatch = 5;   // rows read at once (a block's 257 + 3 limbs)
 
 // out(k, digit limb) for the limbs k of rows [r0, r1): the balanced radix-256
 // digits of the n-limb number x with carry-in cin0 at limb 0.  Limb n gets the
@@ -112,15 +144,15 @@ MP_DEV void balance_rows(int r0, int r1, int n, uint32_t cin0, const FX &x, cons
             break;
         }
     }
-    for (int r = r0; r < r1; r += 4) {
-        uint32_t xv[4];
+    for (int r = r0; r < r1; r += kRowBatch) {
+        uint32_t xv[kRowBatch];
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
+        for (int j = 0; j < kRowBatch; j++) {
             const int k = 64 * (r + j) + lane();
             xv[j] = r + j < r1 && k < n ? x(k) : 0u;
         }
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
+        for (int j = 0; j < kRowBatch; j++) {
             if (r + j < r1) {
                 const int k = 64 * (r + j) + lane();
                 const uint32_t a = k < n ? kBal : 0u, s = xv[j] + a;
@@ -236,16 +268,20 @@ MP_DEV MfmaAcc strip_sums(const Operands &o, int S0)
     int d = uniform(imax(0, S0 - o.nyblk + 1));
     const int dhi = uniform(imin(o.dmax, S0 + 31));
     const uint32_t *x = o.x - 8 * d, *y = o.y + 4 * (S0 - d);
-    for (; d + 3 <= dhi; d += 4) {
-        const XRaw r0 = xraw(x), r1 = xraw(x - 8), r2 = xraw(x - 16), r3 = xraw(x - 24);
-        const Limb4 y0 = load4(y), y1 = load4(y - 4), y2 = load4(y - 8), y3 = load4(y - 12);
-        acc = mfma_x(acc, xfrag(r0, o.sft), y0);
-        acc = mfma_x(acc, xfrag(r1, o.sft), y1);
-        acc = mfma_x(acc, xfrag(r2, o.sft), y2);
-        acc = mfma_x(acc, xfrag(r3, o.sft), y3);
+    constexpr int D = 2;   // diagonals whose operands are in flight (more cost registers, and with them resident waves)
+    for (; d + D - 1 <= dhi; d += D) {
+        XRaw r[D];
+        Limb4 yv[D];
+#pragma unroll
+        for (int j = 0; j < D; j++) {
+            r[j] = xraw(x - 8 * j);
+            yv[j] = load4(y - 4 * j);
+        }
+#pragma unroll
+        for (int j = 0; j < D; j++) acc = mfma_x(acc, xfrag(r[j], o.sft), yv[j]);
         sched_loads_first();
-        x -= 32;
-        y -= 16;
+        x -= 8 * D;
+        y -= 4 * D;
     }
     for (; d <= dhi; d++) {
         acc = mfma_x(acc, xfrag(xraw(x), o.sft), load4(y));
@@ -265,6 +301,39 @@ MP_DEV int64_t byte_sum(const MfmaAcc &a, int j, int64_t c)
     c += (int64_t)mfma_get(a, j + 2) * b2;
     c += (int64_t)mfma_get(a, j + 3) * b3;
     return c;
+}
+
+// adds the carries between the lanes' four-limb groups, given the groups that
+// generate one (G) and the carry into the lowest, by a lookahead over the 32
+// lane pairs (n, 0), (n, 1)
+MP_DEV void quad_carries(uint32_t (&z)[4], uint64_t G, uint32_t cin, uint32_t &cout)
+{
+    cout = 0;
+    if (G == 0 && cin == 0) return;
+    const uint64_t P = ballot((z[0] & z[1] & z[2] & z[3]) == 0xFFFFFFFFu);
+    const uint32_t Gl = (uint32_t)G, Gh = (uint32_t)(G >> 32), Pl = (uint32_t)P, Ph = (uint32_t)(P >> 32);
+    const uint32_t Gp = Gh | (Ph & Gl), X = Gp | (Ph & Pl);
+    const uint64_t s = (uint64_t)X + Gp + cin;
+    const uint32_t cl = (uint32_t)s ^ X ^ Gp, ch = Gl | (Pl & cl);
+    cout = (uint32_t)(s >> 32);
+    uint32_t co;
+    z[0] = __builtin_addc(z[0], 0u, inverse_ballot((uint64_t)ch << 32 | cl) ? 1u : 0u, &co);
+    z[1] = __builtin_addc(z[1], 0u, co, &co);
+    z[2] = __builtin_addc(z[2], 0u, co, &co);
+    z[3] += co;
+}
+
+// z += c in each lane's four limbs (lane (n, h): limbs 8n + 4h .. + 3 of one
+// number) with the carries between the lanes; cout: the carry out of the
+// number's 256 limbs
+MP_DEV void quad_add(uint32_t (&z)[4], uint32_t c, uint32_t &cout)
+{
+    uint32_t co;
+    z[0] = __builtin_addc(z[0], c, 0u, &co);
+    z[1] = __builtin_addc(z[1], 0u, co, &co);
+    z[2] = __builtin_addc(z[2], 0u, co, &co);
+    z[3] = __builtin_addc(z[3], 0u, co, &co);
+    quad_carries(z, ballot(co != 0u), 0u, cout);
 }
 
 // The limbs of a strip from its byte sums plus four addend limbs per lane:
@@ -290,28 +359,9 @@ MP_DEV uint64_t strip_limbs(const MfmaAcc &a, const Limb4 &add, uint32_t below, 
     half_swap(c, lo, hi);                 // lo: lane l gets c of lane l & 31; hi: of lane (l & 31) + 32
     const uint32_t up = shfl_up1(hi);
     const uint32_t prev = lane() >= 32 ? lo : (lane() == 0 ? below : up);
-    uint32_t co;
-    z[0] = __builtin_addc(z[0], prev, 0u, &co);
-    z[1] = __builtin_addc(z[1], 0u, co, &co);
-    z[2] = __builtin_addc(z[2], 0u, co, &co);
-    z[3] = __builtin_addc(z[3], 0u, co, &co);
-    const uint64_t G = ballot(co != 0u);
-    uint64_t e = readlane(c, kLanes - 1);
-    if (G) {
-        // lookahead over the 32 lane pairs (n, 0), (n, 1)
-        const uint64_t P = ballot((z[0] & z[1] & z[2] & z[3]) == 0xFFFFFFFFu);
-        const uint32_t Gl = (uint32_t)G, Gh = (uint32_t)(G >> 32), Pl = (uint32_t)P, Ph = (uint32_t)(P >> 32);
-        const uint32_t Gp = Gh | (Ph & Gl), X = Gp | (Ph & Pl);
-        const uint64_t s = (uint64_t)X + Gp;
-        const uint32_t cl = (uint32_t)s ^ X ^ Gp, ch = Gl | (Pl & cl);
-        e += s >> 32;
-        const uint32_t ci = inverse_ballot((uint64_t)ch << 32 | cl) ? 1u : 0u;
-        z[0] = __builtin_addc(z[0], ci, 0u, &co);
-        z[1] = __builtin_addc(z[1], 0u, co, &co);
-        z[2] = __builtin_addc(z[2], 0u, co, &co);
-        z[3] += co;
-    }
-    return e;
+    uint32_t cout;
+    quad_add(z, prev, cout);
+    return (uint64_t)readlane(c, kLanes - 1) + cout;
 }
 
 // dst[c] = limb of column c of x * y (+ R, when ADD: dst's own limbs) for c in
@@ -382,140 +432,222 @@ struct Shifted {
     }
 };
 
-// W for an instance without a head record, by one wave: the top limbs of v
-// (at pv) and the first Refine iterations in registers, for at most
-// kSmallBlock limbs of precision.  V and Wl are scratch for the divisor
-// prefix and the iterate (2 kSmallBlock + 8 words each).  Returns prec(W),
-// 0 if an iteration does not fit (never for dp <= kSmallBlock).
-MP_DEV int small_inverse(uint32_t *lds, int offV, int offW, int k, int dp, const Shifted &v)
+// number of significant limbs of x[0, n) (global memory), by one wave from the top
+MP_DEV int wave_prec(const uint32_t *x, int n)
 {
-    const int iters = refine_iters(dp), hh = k + dp;
-    Plan pl{};
-    pl.vbase = imax(0, k - 2 * refine_l(dp, iters - 1) - 1);
-    pl.capV = pl.capW = 2 * kSmallBlock + 8;
-    pl.offV = offV;
-    pl.offW = offW;
-    for (int i = lane(); i < k + 1 - pl.vbase; i += kLanes) lds[offV + i] = v(pl.vbase + i);
-    for (int i = lane(); i < pl.capW; i += kLanes) lds[offW + i] = 0u;
-    wave_sync();
-    int we = 0, nw = 0, l = 2;
-    head_init((uint64_t)uniform(v(k)) << 32 | uniform(v(k - 1)), lds + offW, we, nw);
-    for (int i = 0; i < iters; i++)
-        if (!iter_fits_wave(pl, hh, k, l, nw, we) || !refine_iter_wave(pl, lds, hh, k, i, l, we, nw)) return 0;
-    wave_sync();
-    return nw;
+    for (int top = n; top > 0; top -= kLanes) {
+        const int i = top - kLanes + lane();
+        const uint64_t m = ballot(i >= 0 && x[i] != 0u);
+        if (m) return top - kLanes + 64 - __builtin_clzll(m);
+    }
+    return 0;
 }
 
+// w[0, 5) ~ B^(k+4) / v from the top five limbs a[4] (v_k), a[3], .. of v: at
+// most max(2, 2^-111 of it) off.  1/D for the normalised top D in [1/2, 1) as
+// a double, then one step in integers with the second-order term:
+// R = R1 (1 + e + e^2), e = 1 - D R1 / 2^62.
+MP_DEV void newton_start(const uint32_t (&a)[5], uint32_t (&w)[5])
+{
+    typedef unsigned __int128 u128;
+    typedef __int128 i128;
+    const int lz = __builtin_clz(a[4]);
+    const uint64_t hi = (uint64_t)a[4] << 32 | a[3], lo = (uint64_t)a[2] << 32 | a[1];
+    const u128 n0 = (u128)hi << 64 | lo;
+    const u128 N = n0 << lz | (uint32_t)((uint64_t)a[0] << lz >> 32);
+    const uint64_t Nh = (uint64_t)(N >> 64), Nl = (uint64_t)N;
+    const double d = (double)(uint32_t)(Nh >> 32) * 0x1p-32 + (double)(uint32_t)Nh * 0x1p-64;
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    const double rs = r * 0x1p31;                                  // in (2^31, 2^32]
+    const uint32_t r1 = rs >= 0x1p32 ? 0xFFFFFFFFu : (uint32_t)rs;
+    const uint64_t R1 = ((uint64_t)r1 << 31) + (uint32_t)((rs - (double)r1) * 0x1p31);   // (at most 2^63)
+    // e 2^112 = (2^190 - N R1) / 2^78, |e| < 2^-50
+    const u128 p0 = (u128)Nl * R1, p1 = (u128)Nh * R1 + (uint64_t)(p0 >> 64);   // N R1 = p1 2^64 + lo(p0)
+    const int64_t e = (int64_t)((((i128)1 << 126) - (i128)p1) >> 14);
+    const i128 c1 = (i128)e * (i128)(u128)R1 >> 48;
+    const int64_t eh = e >> 32;
+    const uint64_t c2 = (uint64_t)((u128)(uint64_t)(eh * eh) * R1 >> 96);
+    const u128 F = ((u128)R1 << 64) + (u128)c1 + c2;               // R 2^126
+    const u128 t = lz < 31 ? F >> (30 - lz) : F << 1;
+    w[0] = (uint32_t)t;
+    w[1] = (uint32_t)(t >> 32);
+    w[2] = (uint32_t)(t >> 64);
+    w[3] = (uint32_t)(t >> 96);
+    w[4] = lz == 31 ? (uint32_t)(F >> 127) : 0u;
+}
+
+// limbs of the iterate a Newton step to f limbs starts from
+MP_HD int newton_from(int f) { return (f + 4) >> 1; }
+
+// W ~ B^(k+F) / v, F = dp + 2, by one wave: w[0, F] its limbs, xw the reversed
+// digits of its F + 2 digit limbs (with their pads).  vd: the planes (distance
+// lv) of v's digits, tv(i): limb i of v, td: planes (distance lt, nt blocks,
+// pads zero) for the residuals.
+//
+// The iterate for f limbs is w ~ B^(k+f)/v, the top of the final one: w[F - f,
+// F].  A step to f' <= 2f - 3 limbs takes the middle columns of v w as the
+// residual e = (v w - B^(k+f)) / B^c and adds -w e: both products fill one
+// 256-column strip.  With |E| the error of w in units of its last limb, the
+// new one is at most E^2 / B (quadratic term) + 1 (floor) + 0.1: limbs of v
+// below s are left out (but for those the strip reads anyway), s <= k - 1 -
+// f', which moves e by less than B^f, and columns of e below c = sh - f - 2,
+// of either sign and below 2^26 B^c.  (The first step, from newton_start, adds
+// at most 2 instead of E^2 / B.)  So |E| <= 3 at the end.
+template <class FV>
+MP_DEV void newton(const FV &tv, int k, int dp, const uint32_t *vd, int lv, uint32_t *td, int lt, int nt, uint32_t *w,
+                   uint32_t *xw)
+{
+    const int F = dp + 2, l = lane(), g = 8 * (l & 31) + 4 * (l >> 5);
+    {
+        uint32_t a[5], s[5];
+#pragma unroll
+        for (int j = 0; j < 5; j++) a[j] = k - 4 + j >= 0 ? tv(k - 4 + j) : 0u;
+        newton_start(a, s);
+        if (l == 0) {
+#pragma unroll
+            for (int j = 0; j < 5; j++) w[F - 4 + j] = s[j];
+        }
+    }
+    if (l < kXPad) xw[l - kXPad] = 0u;
+    for (int b = 32 + l; b < nt; b += kLanes)   // (blocks past the first strip are never residual)
+        for (int j = 0; j < 4; j++) td[4 * b + j] = td[lt + 4 * b + j] = 0u;
+    int f = 4;
+    for (;;) {
+        // digits of w, top digit first
+        wave_sync();
+        const int n = f + 1;
+        balance_rows(0, (n + 64) >> 6, n, 0u, Span{w + F - f, 0, n}, StoreRev{xw, n + 1});
+        if (l < kXPad) xw[n + 1 + l] = 0u;
+        if (f == F) break;
+        int fn = F;                              // the next step of the schedule that ends at F
+        while (fn > 7 && newton_from(fn) > f) fn = newton_from(fn);
+        const int s = imax(0, k - 1 - fn) & ~7;
+        const int sh = k - s + 2 * f - fn;       // w e / B^sh is the correction
+        const int c0 = imax(0, sh - f - 2) & ~7, L = k + 2 - s;
+        wave_sync();
+        // -e: the two's complement of the columns [c0, L) of v w (B^(k+f-s) vanishes mod B^L), as digits
+        uint32_t z[4], co;
+        strip_limbs(strip_sums(operands(xw, n + 1, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), Limb4{0u, 0u, 0u, 0u},
+                    0x80000000u, z);
+        const int nx = L - c0;
+        uint32_t cc = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t bal = g + j < nx ? kBal : 0u, y = g + j < nx ? ~z[j] : 0u;
+            z[j] = __builtin_addc(y, bal, cc, &cc);
+        }
+        quad_carries(z, ballot(cc != 0u), 1u, co);
+        if ((l & 31) < nt) {
+            uint32_t *p = td + (l >> 5) * lt + 4 * (l & 31);
+            store4(p, g < nx ? z[0] ^ kBal : 0u, g + 1 < nx ? z[1] ^ kBal : 0u, g + 2 < nx ? z[2] ^ kBal : 0u,
+                   g + 3 < nx ? z[3] ^ kBal : 0u);
+        }
+        wave_sync();
+        // the correction's limbs: columns [shc, shc + fn - f + 2) of w (-e)
+        const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f;
+        strip_limbs(strip_sums(operands(xw, n + 1, td, lt, nx), cB >> 3), Limb4{0u, 0u, 0u, 0u}, 0x80000000u, z);
+        uint32_t top[2] = {0u, 0u};              // limbs m and m + 1 (the sign), wherever they are
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int i = cB + g + j - shc;      // limb of the correction
+            if (i >= 0 && i < m) w[F - fn + i] = z[j];
+            const uint64_t b0 = ballot(i == m), b1 = ballot(i == m + 1);
+            if (b0) top[0] = readlane(z[j], __builtin_ctzll(b0));
+            if (b1) top[1] = readlane(z[j], __builtin_ctzll(b1));
+        }
+        wave_sync();
+        const uint32_t x = uniform(w[F - f]), y = x + top[0];
+        wave_sync();
+        if (l == 0) w[F - f] = y;
+        add_small(w + F - f + 1, f, (int)top[1] + (y < x ? 1 : 0));
+        f = fn;
+    }
+}
+
+// limbs of a dividend: an array (wave_prec reads it), or B^e
+MP_DEV int top_limb(const Span &u, int n) { return wave_prec(u.p, n); }
+MP_DEV int top_limb(const PowB &u, int) { return u.e + 1; }
+
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
-// U(i) is limb i of the dividend, which has at most nu limbs.  rec: the head's
-// record, or nullptr when no head ran.
+// U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
+// block.
 template <int T, class FU>
 MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *v, int nv, uint32_t *q, int nq,
-                            uint32_t *r, int32_t *status, const uint32_t *rec)
+                            uint32_t *r, int32_t *status, int bmax)
 {
     constexpr int W = T / kLanes;
     uint32_t *ctl = lds;
     const BodyPlan pl = plan_body(nu, nv);
-    uint32_t *Vd = lds + pl.offV, *Td = lds + pl.offT, *XW = lds + pl.offW, *XQ = lds + pl.offQ;
+    uint32_t *Vd = lds + pl.offV, *Td = lds + pl.offT, *XW = lds + pl.offX, *XQ = lds + pl.offQ;
     uint32_t *P = lds + pl.offP, *R = lds + pl.offR;
     const int w = wave_index(), t = tid<T>(), nr = r ? nv : 0;
-    int h = 0, k = 0, sv = 0, nw = 0, dp = 0, nb = 0, bi = 0;
-    const bool valid = rec && uniform(rec[0]) == kRecValid;
     MP_RSTAMP(14);
     MP_STAMP(0);
-    bar<T>();
-    if (valid) {
-        h = (int)uniform(rec[1]);
-        k = (int)uniform(rec[2]);
-        sv = (int)uniform(rec[3]);
-        nw = (int)uniform(rec[4]);
-        dp = (int)uniform(rec[5]);
-        nb = (int)uniform(rec[6]);
-        bi = (int)uniform(rec[7]);
-    } else {
-        // precisions, and the cases that need no division
-        int32_t st = kInstOk;
-        h = prec<T>(ctl, nu, U);
-        k = prec<T>(ctl, nv, Span{v, 0, nv}) - 1;
-        if (k < 0 || h <= k) {                        // v = 0, or u < v: (0, u)
-            for (int i = t; i < nq; i += T) q[i] = 0u;
-            for (int i = t; i < nr; i += T) r[i] = k >= 0 && i < h ? U(i) : 0u;
-            if (status && t == 0) *status = k < 0 ? kInstDivZero : kInstOk;
-            return;
-        }
-        const uint32_t vk = uniform(v[k]);
-        const bool pow = vk == 1u && prec<T>(ctl, k, Span{v, 0, nv}) == 0;
-        const int d0 = h - k;
-        if (d0 - 1 > nq) {                            // q >= B^(d-2): it needs more than nq limbs
-            st = kInstQWidth;
-        } else if (pow) {                             // v = B^k: q = u >> k, r the limbs below
-            if (d0 > nq && uniform(U(h - 1)) != 0u) {
-                st = kInstQWidth;
-            } else {
-                for (int i = t; i < nq; i += T) q[i] = i < d0 ? U(i + k) : 0u;
-                for (int i = t; i < nr; i += T) r[i] = i < k ? U(i) : 0u;
-                if (status && t == 0) *status = st;
-                return;
-            }
-        }
-        if (st != kInstOk) {
-            for (int i = t; i < nq; i += T) q[i] = 0u;
-            for (int i = t; i < nr; i += T) r[i] = 0u;
-            if (status && t == 0) *status = st;
-            return;
-        }
-        if (k == 0) {                                 // one limb: u B / (v B)
-            sv = 1;
-            k = 1;
-            h += 1;
-        }
-        const BlockSplit bs = block_split(h - k, kSmallBlock);
-        dp = bs.dp;
-        nb = bs.nb;
-        bi = bs.bi;
-        if (w == 0) {
-            const int nw0 = small_inverse(lds, pl.offP, pl.offQ, k, dp, Shifted{v, nv, sv});
-            if (lane() == 0) ctl[kCtlBcast] = (uint32_t)nw0;
-        }
-        bar<T>();
-        nw = (int)uniform(ctl[kCtlBcast]);
+    // precisions (every wave finds them by itself), and the cases that need no division
+    int h = top_limb(U, nu), k = wave_prec(v, nv) - 1;
+    if (k < 0 || h <= k) {                            // v = 0, or u < v: (0, u)
+        for (int i = t; i < nq; i += T) q[i] = 0u;
+        for (int i = t; i < nr; i += T) r[i] = k >= 0 && i < h ? U(i) : 0u;
+        if (status && t == 0) *status = k < 0 ? kInstDivZero : kInstOk;
+        return;
     }
-    MP_STAMP(1);
     const int d = h - k;
-    // the dividend's limbs and zeros above them; the divisor's digits; W's; zero pads
+    if (uniform(v[k]) == 1u && wave_prec(v, k) == 0) {   // v = B^k: q = u >> k, r the limbs below
+        const bool ok = d <= nq;                         // (limb h - 1 is not zero)
+        for (int i = t; i < nq; i += T) q[i] = ok && i < d ? U(i + k) : 0u;
+        for (int i = t; i < nr; i += T) r[i] = ok && i < k ? U(i) : 0u;
+        if (status && t == 0) *status = ok ? kInstOk : kInstQWidth;
+        return;
+    }
+    if (d - 1 > nq) {                                 // q >= B^(d-2): it needs more than nq limbs
+        for (int i = t; i < nq; i += T) q[i] = 0u;
+        for (int i = t; i < nr; i += T) r[i] = 0u;
+        if (status && t == 0) *status = kInstQWidth;
+        return;
+    }
+    const int sv = k == 0 ? 1 : 0;                    // a one-limb divisor: u B / (v B)
+    h += sv;
+    k += sv;
+    const Shifted Vv{v, nv, sv};
+    const BlockSplit bs = block_split(d, bmax);
+    const int dp = bs.dp, nb = bs.nb, bi = bs.bi;
+    MP_STAMP(1);
+    // the divisor's digits and the planes' zero pads
     {
-        for (int i0 = t; i0 < pl.capR; i0 += 8 * T) {
-            uint32_t a[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const int i = i0 + j * T - sv;
-                a[j] = i >= 0 && i < nu ? U(i) : 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (i0 + j * T < pl.capR) R[i0 + j * T] = a[j];
-        }
-        for (int i = t; i < 5 * kPadWords; i += T) {   // the planes' pads
+        for (int i = t; i < 5 * kPadWords; i += T) {
             const int b = i / kPadWords, j = i - b * kPadWords;
             const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * pl.lyT;
             lds[at - kPadWords + j] = 0u;
         }
         const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 1) / W;
         const int r0 = w * per, r1 = imin(rows, r0 + per);
-        if (r0 < r1)
-            balance_rows(r0, r1, k + 1, 0u, Shifted{v, nv, sv}, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
-        if (w == W - 1) {
-            // W's reversed digits (one digit limb more than its limbs)
-            const uint32_t *ws = valid ? rec + kRecHdr : lds + pl.offQ;
-            balance_rows(0, (nw + 64) >> 6, nw, 0u, Span{ws, 0, nw}, StoreRev{XW, nw + 1});
-            if (lane() < kXPad) XW[lane() - kXPad] = 0u;
-            else if (lane() < 2 * kXPad) XW[nw + 1 + lane() - kXPad] = 0u;
+        if (r0 < r1) balance_rows(r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
+    }
+    bar<T>();
+    MP_STAMP(9);
+    // W by the first wave, while the others read the dividend (zeros above it)
+    if (w == 0) {
+        newton(Vv, k, dp, Vd, pl.lyV, Td, pl.lyT, pl.nbT, lds + pl.offW, XW);
+        if (lane() < kXPad) XQ[lane() - kXPad] = 0u;
+    } else {
+        constexpr int S = T - kLanes;
+        for (int i0 = t - kLanes; i0 < pl.capR; i0 += 8 * S) {
+            uint32_t a[8];
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const int i = i0 + j * S - sv;
+                a[j] = i >= 0 && i < nu ? U(i) : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (i0 + j * S < pl.capR) R[i0 + j * S] = a[j];
         }
     }
     bar<T>();
-    if (w == 0 && lane() < kXPad) XQ[lane() - kXPad] = 0u;   // (after W's digits: an own W was in XQ)
     MP_STAMP(2);
-    bool good = nw > 0 && nw <= dp + 3;
+    bool good = true;
     const int n2 = k + 2, bs2 = (n2 + kStrip - 1) / kStrip, base2 = ((n2 + 7) & ~7) - bs2 * kStrip;
     int o = d;
     for (int i = 0; i < nb && good; i++) {
@@ -533,7 +665,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         MP_STAMP(16 + 4 * (i & 3));   // (trace build: the phases of the last four blocks)
         // q_i = R_top W / B^(dp+3): columns from cA up
         const int shA = dp + 3, cA = (shA - 2) & ~7, nA = shA + b + 1, sA = (nA - cA + kStrip - 1) / kStrip;
-        strips<T, false>(ctl, operands(XW, nw + 1, Td, pl.lyT, nt), P - cA, cA, nA, cA, sA);
+        strips<T, false>(ctl, operands(XW, dp + 4, Td, pl.lyT, nt), P - cA, cA, nA, cA, sA);
         bar<T>();
         MP_STAMP(17 + 4 * (i & 3));
         // its limbs to the quotient, the reversed digits of -q_i
@@ -542,9 +674,14 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             const uint32_t *src = P + (shA - cA);
             const int nd = b + 1;
             uint32_t *Q = R + k + 2 + o;
-            balance_rows(0, (nd + 63) >> 6, nd, 1u, [&](int j) { return ~src[j]; }, StoreRev{XQ, nd});
+            balance_rows(0, (nd + 63) >> 6, nd, 1u,
+                         [&](int j) {
+                             const uint32_t x = src[j];
+                             if (j < b) Q[j] = x;
+                             return ~x;
+                         },
+                         StoreRev{XQ, nd});
             if (lane() < kXPad) XQ[nd + lane()] = 0u;
-            for (int j = lane(); j < b; j += kLanes) Q[j] = src[j];
             const int s = (int)uniform(src[b]);       // q_i's sign limb
             wave_sync();
             if (i == 0) {
@@ -565,7 +702,6 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     MP_STAMP(6);
     // corrections: R is a signed (k + 2)-limb number in (-1.1 v, 2.1 v)
     uint32_t *Q = R + k + 2, *Ra = R, *Rb = Vd;       // (the divisor's digits are no longer needed)
-    const Shifted Vv{v, nv, sv};
     int delta = 0;
     for (int it = 0; good; it++) {
         bool neg = (int32_t)uniform(Ra[k + 1]) < 0, ge = uniform(Ra[k + 1]) != 0u;

@@ -28,7 +28,6 @@ constexpr int kRCol = 4;                 // product columns per lane
 constexpr int kStrip = kLanes * kRCol;   // product columns per wave pass
 constexpr int kPad = kStrip + 8;         // zero guard on both sides of a staged window operand
 constexpr int kCMax = 17;                // most limbs one thread handles in a linear operation
-constexpr int kHeadMaxLimbs = 9 * kLanes;   // longest operand of a one-wave addsub (9 limbs per lane)
 
 // control block at the start of the instance's LDS (32-bit words)
 constexpr int kCtlRed = 0;       // 3 x 16 per-wave reduction slots
@@ -39,8 +38,12 @@ constexpr int kCtlStrip = 96;    // 2 words per strip carry, up to 72 strips
 constexpr int kCtlBcast = 240;   // 16 broadcast scalars
 constexpr int kCtlWords = 256;
 constexpr int kMaxStrips = 72;
-constexpr int kHeadStrips = 4;  // strips of a head's products (one wave, short operands)
-constexpr int kHeadCtlWords = kCtlStrip + 2 * kHeadStrips;   // a head's control block (no broadcast slots)
+
+#define MP_HD __host__ __device__ __forceinline__
+
+MP_HD constexpr int r4(int x) { return (x + 3) & ~3; }
+MP_HD constexpr int hmax(int a, int b) { return a > b ? a : b; }
+MP_HD constexpr int hmin(int a, int b) { return a < b ? a : b; }
 
 // barrier of the T threads working on an instance: the workgroup, or (T = 64)
 // a single wave, which needs no hardware barrier
@@ -374,13 +377,8 @@ MP_DEV uint32_t addsub_nb(uint32_t *ctl, int n, bool sub, uint32_t cin,
     if (C == 1) return addsub_chunk<T, 1>(ctl, n, C, sub, cin, x, y, out, stk, scan);
     if (C == 3) return addsub_chunk<T, 3>(ctl, n, C, sub, cin, x, y, out, stk, scan);
     if (C <= 5) return addsub_chunk<T, 5>(ctl, n, C, sub, cin, x, y, out, stk, scan);
-    // a single wave (a head) handles at most kHeadMaxLimbs limbs per operation
-    if constexpr (T == kLanes) {
-        return addsub_chunk<T, 9>(ctl, n, C, sub, cin, x, y, out, stk, scan);
-    } else {
-        if (C <= 9) return addsub_chunk<T, 9>(ctl, n, C, sub, cin, x, y, out, stk, scan);
-        return addsub_chunk<T, kCMax>(ctl, n, C, sub, cin, x, y, out, stk, scan);
-    }
+    if (C <= 9) return addsub_chunk<T, 9>(ctl, n, C, sub, cin, x, y, out, stk, scan);
+    return addsub_chunk<T, kCMax>(ctl, n, C, sub, cin, x, y, out, stk, scan);
 }
 
 template <int T, class FX, class FY, class FO, class FS = NoSticky>
@@ -576,82 +574,6 @@ MP_DEV int mul(uint32_t *ctl, uint32_t *p, int ncols,
         strip_resolve(ctl, s, K0, lo, hi, p, c0, ncols);
     }
     return add_strip_carries<T>(ctl, p, c0, ncols, nstrips, base, want_prec);
-}
-
-// The same product for a single wave, one column per lane: for short
-// operands, where most lanes of a 256-column strip would be idle.  The wave
-// walks strips of 64 columns from the bottom; lane l of strip s sums column
-// K0 + l over the rows in four independent 96-bit accumulators (rows i, i+1,
-// i+2, i+3), reading window limb k - i of each row.  The column sums
-// S_l = s0 + s1 B + s2 B^2 become limbs as t_l = s0_l + s1_(l-1) + s2_(l-2)
-// (neighbour values by DPP lane shifts) plus, in lanes 0 and 1, the carry E
-// of the strip below; then y_l = lo(t_l) + hi(t_(l-1)) has a one-bit carry,
-// resolved by the ballot lookahead.  The carry leaving the strip (into its
-// next two columns) is kept in scalar registers for the next strip, so no
-// pass over the stored limbs follows; the top strip's carry lies above
-// ncols and is dropped.
-template <int T>
-MP_DEV int mul1(uint32_t *ctl, uint32_t *p, int ncols, const uint32_t *a, int na, const uint32_t *bw, int nb, int c0,
-                bool want_prec)
-{
-    static_assert(T == kLanes, "mul1 is the single-wave product");
-    (void)ctl;
-    wave_sync();
-    if (na == 0 || nb == 0 || ncols <= c0) {
-        for (int k = c0 + lane(); k < ncols; k += kLanes) p[k] = 0u;
-        return 0;
-    }
-    const int nstrips = (ncols - c0 + kLanes - 1) / kLanes;
-    const int base = strip_base(c0, ncols, na + nb, nstrips, kLanes);
-    const int l = lane();
-    uint64_t E = 0;        // carry into columns K0, K0 + 1 of the current strip
-    int top = 0;           // 1 + highest nonzero stored column
-    for (int s = 0; s < nstrips; s++) {
-        const int K0 = base + s * kLanes, k = K0 + l;
-        const int ilo = imax(0, K0 - nb + 1);
-        const int ihi = imin(na, imin(K0 + kLanes, ncols));
-        uint64_t lo[4] = {0, 0, 0, 0};
-        uint32_t hi[4] = {0, 0, 0, 0};
-        const uint32_t *wp = bw + k;
-        int i = ilo;
-        for (; i + 3 < ihi; i += 4) {
-            const uint32_t w0 = wp[-i], w1 = wp[-i - 1], w2 = wp[-i - 2], w3 = wp[-i - 3];
-            mac4x(lo, hi, a[i], w0, a[i + 1], w1, a[i + 2], w2, a[i + 3], w3);
-        }
-        if (i < ihi) {
-            const uint32_t a1 = i + 1 < ihi ? a[i + 1] : 0u, a2 = i + 2 < ihi ? a[i + 2] : 0u;
-            mac4x(lo, hi, a[i], wp[-i], a1, wp[-i - 1], a2, wp[-i - 2], 0u, 0u);
-        }
-        // the four partial sums of column k, added exactly (each below 2^(64 + 7))
-        uint64_t sl = lo[0];
-        uint32_t sh = hi[0];
-#pragma unroll
-        for (int r = 1; r < 4; r++) {
-            const uint64_t t = sl + lo[r];
-            sh += hi[r] + (t < sl ? 1u : 0u);
-            sl = t;
-        }
-        // limbs: t = s0 + s1 of the lane below + s2 of the lane two below (+ E at the bottom)
-        const uint32_t s1m = shfl_up1((uint32_t)(sl >> 32)), s2m = shfl_up2(sh);
-        const uint32_t e = l == 0 ? (uint32_t)E : l == 1 ? (uint32_t)(E >> 32) : 0u;
-        const uint64_t t = (uint64_t)(uint32_t)sl + s1m + s2m + e;     // < 4 B
-        const uint32_t cm = shfl_up1((uint32_t)(t >> 32));                // 0..3 from the lane below
-        const uint64_t y = (uint64_t)(uint32_t)t + cm;
-        uint32_t z = (uint32_t)y;
-        const bool g = (y >> 32) != 0, pr = z == 0xFFFFFFFFu;
-        const uint64_t G = ballot(g), P = ballot(pr), X = G | P;
-        const uint64_t sum = X + G;
-        z += (uint32_t)(((sum ^ X ^ G) >> l) & 1u);
-        const bool st = k >= c0 && k < ncols;
-        if (st) p[k] = z;
-        const uint64_t nz = ballot(st && z != 0u);
-        if (nz) top = K0 + kLanes - __builtin_clzll(nz);
-        // carry into the next strip: what lanes 62 and 63 pass upward plus the lookahead's carry out
-        const uint32_t s2_62 = readlane(sh, 62), s2_63 = readlane(sh, 63);
-        const uint32_t s1_63 = readlane((uint32_t)(sl >> 32), 63), c_63 = readlane((uint32_t)(t >> 32), 63);
-        E = (uint64_t)s1_63 + s2_62 + c_63 + (sum < X ? 1u : 0u) + ((uint64_t)s2_63 << 32);
-    }
-    return want_prec ? top : -1;
 }
 
 // ---------------------------------------------------- matrix-core product

@@ -3,7 +3,7 @@
 // kernels themselves are in kernels.hip.
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
-#include "mp_div.hpp"
+#include "mp_mul.hpp"
 #include "mp_block.hpp"
 #include "launch.hpp"
 
@@ -21,19 +21,14 @@ constexpr int kLdsWords = 160 * 1024 / 4;   // gfx950: 160 KB of LDS per workgro
 // run-time knobs (mp_set_knob)
 std::atomic<int32_t> g_mfma_min{64}, g_small_limit{MP_SMALL_LIMIT_AUTO};
 
-int device_cus();
+constexpr int kAutoLimit = 136, kMaxLimit = 140;
 
-// the knobs of a launch (the automatic head limit, and limits below the
-// smallest block, resolved)
-mp::Knobs knobs_now()
+// longest block of a launch's divisions
+int block_max()
 {
     const int sl = g_small_limit.load();
-    return mp::Knobs{g_mfma_min.load(), sl == MP_SMALL_LIMIT_AUTO ? 136 : mp::hmax(sl, mp::kHeadMinLimit)};
+    return mp::block_limit(sl == MP_SMALL_LIMIT_AUTO ? kAutoLimit : sl);
 }
-
-// a head kernel runs first when an output row can hold a record (otherwise the
-// instances are short and the bodies make their own inverses)
-int use_head(int row) { return mp::record_block(row) >= mp::kSmallBlock; }
 
 size_t body_bytes(int nu, int nv) { return (size_t)mp::plan_body(nu, nv).total * 4; }
 
@@ -191,12 +186,10 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
 {
     const int cus = device_cus();
     if (cus <= 0) return MP_ERR_DEVICE;
-    const mp::Knobs kn = knobs_now();
+    const int bmax = block_max();
     hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, u_limbs, v_limbs, q_limbs,
                        r_limbs, inst_status, ws);
     if (hipGetLastError() != hipSuccess) return MP_ERR_LAUNCH;
-    if (mp::launch_head_ragged(st, u_pool, v_pool, desc, q_pool, r_pool, ws, count, kn) != hipSuccess)
-        return MP_ERR_LAUNCH;
     if (fk && hipEventRecord(fk->ev_fork, st) != hipSuccess) return MP_ERR_LAUNCH;
     for (int c = 0; c < kClasses; c++) {
         hipStream_t fs = fk ? fk->fs[c] : st;
@@ -211,15 +204,15 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
         switch (T) {
         case 256:
             e = mp::launch_ragged<256>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, 1);
+                                       count, bmax);
             break;
         case 512:
             e = mp::launch_ragged<512>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, 1);
+                                       count, bmax);
             break;
         default:
             e = mp::launch_ragged<1024>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                        count, 1);
+                                        count, bmax);
             break;
         }
         if (e != hipSuccess) return MP_ERR_LAUNCH;
@@ -257,7 +250,7 @@ mp_status_t mp_set_knob(int32_t knob, int32_t value)
         g_mfma_min.store(value);
         return MP_OK;
     case MP_KNOB_SMALL_LIMIT:
-        if (value != MP_SMALL_LIMIT_AUTO && (value < 0 || value > mp::kHeadMaxLimit)) return MP_ERR_ARG;
+        if (value != MP_SMALL_LIMIT_AUTO && (value < 0 || value > kMaxLimit)) return MP_ERR_ARG;
         g_small_limit.store(value);
         return MP_OK;
     }
@@ -295,7 +288,7 @@ mp_status_t mp_mul_batch(const uint32_t *a, int32_t na, const uint32_t *b, int32
     if (words > kLdsWords) return MP_ERR_SIZE;
     const size_t bytes = (size_t)words * 4;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_now();
+    const int kn = g_mfma_min.load();
     switch (threads_for((na + nb + 1) / 2)) {
     case 256: return status_of(mp::launch_mul<256>(batch, bytes, st, a, na, b, nb, c, kn));
     case 512: return status_of(mp::launch_mul<512>(batch, bytes, st, a, na, b, nb, c, kn));
@@ -314,13 +307,11 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
     const size_t bytes = body_bytes(h + 1, nv);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_now();
-    const int head = use_head(nw);
-    if (head && mp::launch_head_shinv(st, v, nv, h, w, nw, batch, kn) != hipSuccess) return MP_ERR_LAUNCH;
+    const int bmax = block_max();
     switch (T) {
-    case 256: return status_of(mp::launch_shinv<256>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
-    case 512: return status_of(mp::launch_shinv<512>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
-    default: return status_of(mp::launch_shinv<1024>(batch, bytes, st, v, nv, h, w, nw, inst_status, head));
+    case 256: return status_of(mp::launch_shinv<256>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
+    case 512: return status_of(mp::launch_shinv<512>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
+    default: return status_of(mp::launch_shinv<1024>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
     }
 }
 
@@ -336,16 +327,14 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
     const size_t bytes = body_bytes(nu, nv);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
-    const mp::Knobs kn = knobs_now();
-    const int head = use_head(nq > nv ? nq : nv);
-    if (head && mp::launch_head_divrem(st, u, nu, v, nv, q, nq, r, batch, kn) != hipSuccess) return MP_ERR_LAUNCH;
+    const int bmax = block_max();
     switch (T) {
     case 256:
-        return status_of(mp::launch_divrem<256>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
+        return status_of(mp::launch_divrem<256>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
     case 512:
-        return status_of(mp::launch_divrem<512>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
+        return status_of(mp::launch_divrem<512>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
     default:
-        return status_of(mp::launch_divrem<1024>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, head));
+        return status_of(mp::launch_divrem<1024>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
     }
 }
 

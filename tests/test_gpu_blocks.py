@@ -2,10 +2,10 @@
 
 The quotient's d = h - k limbs are found in blocks of at most 257 limbs, the
 remainder is updated in strips of 256 columns of k + 2 limbs, digits are
-converted in rows of 64 limbs and 8-limb blocks, and the head's inverse lies
-in the longer of the q and r rows.  Quotient and divisor lengths on both sides
-of each of these, one-limb divisors, rows too short for a record and quotients
-one limb longer than their row; random and structured operands, bit-exact."""
+converted in rows of 64 limbs and 8-limb blocks, and the inverse's precision
+follows the longest block.  Quotient and divisor lengths on both sides of each
+of these, one-limb divisors, and quotients one limb longer than their row;
+random and structured operands, bit-exact."""
 import random
 
 import numpy as np
@@ -84,8 +84,8 @@ def test_divisor_lengths(mp, k):
 
 
 @pytest.mark.parametrize("nq,nv", [(257, 1024), (257, 257), (40, 12), (12, 40), (8, 8), (26, 20), (27, 20), (300, 3)])
-def test_record_rows(mp, nq, nv):
-    """The record in q, in r, in neither; quotients that fit nq limbs, that need one more, and that need many more."""
+def test_row_widths(mp, nq, nv):
+    """Long and short q and r rows; quotients that fit nq limbs, that need one more, and that need many more."""
     rng = random.Random(nq * 1000 + nv)
     k = nv - 1
     us, vs = [], []
