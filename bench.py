@@ -370,7 +370,7 @@ def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
 
 
 # the four stamps of a block of quotient limbs in the body
-BLOCK_PHASES = ["top_digits", "quotient_product", "quotient_digits", "remainder_update"]
+BLOCK_PHASES = ["quotient_top_digits", "quotient", "remainder_update"]
 
 
 RT_HZ = 100e6   # rate of the real-time counter (s_memrealtime)

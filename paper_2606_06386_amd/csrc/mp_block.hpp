@@ -1,6 +1,6 @@
 // Block division: one workgroup divides u by v in blocks of quotient limbs.
 //
-// First W ~ B^(k+dp+2) / v is computed for a precision of dp <= 257 limbs (and
+// First W ~ B^(k+dp+2) / v is computed for a precision of dp <= 255 limbs (and
 // two guard limbs) by Newton steps on one wave.  Then the quotient's d = h - k
 // limbs are found in nb blocks from the top, block i holding the limbs
 // [o_i, o_(i-1)):
@@ -34,48 +34,52 @@ enum : int32_t { kInstOk = 0, kInstDivZero = 1, kInstQWidth = 2, kInstInternal =
 
 // The quotient's d limbs: nb blocks of bi limbs, the first (top) of
 // d - (nb - 1) bi; dp limbs of precision of W serve the longest of them.  bi
-// is a multiple of 4, so that every block starts at a 16-byte boundary of R.
+// is a multiple of 4, so that every block starts at a 16-byte boundary of R;
+// dp + 1 is a multiple of 8, so that the quotient product starts two columns
+// below the quotient's limbs.
 struct BlockSplit {
     int nb, bi, dp;
 };
 
-// Longest block: W and one block's operands of up to 257 limbs keep every
-// Newton product within one 256-column strip (f = 131 -> 259 limbs is the last
-// step that does).
-constexpr int kBlockMax = 257;
+// Longest block: R_top (3 limbs more), the quotient's columns (3 more) and
+// every Newton product then fit the 256 limbs of one strip, which one wave
+// holds in registers, four limbs per lane, from the accumulators to the digits
+// of the next product.
+constexpr int kBlockMax = 252;
+
+MP_HD constexpr int block_precision(int b) { return ((b + 8) & ~7) - 1; }
 
 MP_HD BlockSplit block_split(int d, int bmax)
 {
-    if (d <= bmax) return BlockSplit{1, 0, d > 2 ? d : 2};
-    const int top = bmax & ~3, nb = 1 + (d - bmax + top - 1) / top;
-    const int even = r4((d + nb - 1) / nb), bi = even < top ? even : top, b0 = d - (nb - 1) * bi;
-    return BlockSplit{nb, bi, b0 > bi ? b0 : bi};
+    if (d <= bmax) return BlockSplit{1, 0, block_precision(d)};
+    const int nb = 1 + (d - 1) / bmax, even = r4((d + nb - 1) / nb), bi = even < bmax ? even : bmax;
+    const int b0 = d - (nb - 1) * bi;
+    return BlockSplit{nb, bi, block_precision(b0 > bi ? b0 : bi)};
 }
 
 // longest block for a limit on the iterates of the Newton steps (the small_limit knob)
-MP_HD int block_limit(int limit)
-{
-    int b = 17;
-    while (2 * b - 1 <= kBlockMax && b + 3 < limit) b = 2 * b - 1;
-    return b;
-}
+MP_HD int block_limit(int limit) { return hmax(16, hmin(kBlockMax, (2 * limit - 16) & ~3)); }
 
 // ---------------------------------------------------------------- LDS layout
 //
-// ctl | pad | V plane 0 | pad | V plane 1 | pad | R_top plane 0 | pad |
-// R_top plane 1 | pad | W reversed | -q reversed | W | P | R
-// (pads of kYPadBlk zero blocks shared by their neighbours).  R holds the
-// dividend's h limbs and above them the quotient: limb j of q goes to
-// R[k + 2 + j], which the remainder has left by the time the block is done.
+// ctl | pad | V plane 0 | pad | V plane 1 | pad | T plane 0 | pad | T plane 1 |
+// pad | W reversed | -q reversed | W | R
+// (pads of kYPadBlk zero blocks shared by their neighbours; T: R_top, and the
+// residuals of the Newton steps).  R holds the dividend's h limbs and above
+// them the quotient: limb j of q goes to R[k + 2 + j], which the remainder has
+// left by the time the block is done.
 struct BodyPlan {
     int nbV, lyV, offV;       // 8-limb blocks of the divisor's digits, distance of the planes, first word
-    int nbT, lyT, offT;       // the same for R_top
-    int offX, offQ, offW, offP, offR;   // W's reversed digits, -q's, W's limbs, q's columns, R
+    int offT;                 // the same planes for T: 32 blocks each
+    int offX, offQ, offW, offR;   // W's reversed digits, -q's, W's limbs, R
     int capR;
     int total;
 };
 
 constexpr int kPadWords = 4 * kYPadBlk;
+
+constexpr int kStripBlks = kStrip / 8;
+constexpr int kLyT = 4 * kStripBlks + kPadWords;   // distance of T's planes
 
 // a dividend of at most nu and a divisor of at most nv limbs (each one more
 // inside, for divisors of one limb, which are shifted up by one)
@@ -83,18 +87,15 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
 {
     BodyPlan p{};
     const int ny = (nv < nu ? nv : nu) + 2;            // digit limbs of the divisor
-    const int dm = hmin(kBlockMax, hmax(nu + 1, 40));  // longest block and inverse
+    const int dm = block_precision(hmin(kBlockMax, nu + 1));
     p.nbV = (ny + 7) >> 3;
-    p.nbT = (dm + 3 + 7) >> 3;
     p.offV = kCtlWords + kPadWords;
     p.lyV = 4 * p.nbV + kPadWords;
     p.offT = p.offV + 2 * p.lyV;
-    p.lyT = 4 * p.nbT + kPadWords;
-    p.offX = p.offT + 2 * p.lyT + kXPad;
-    p.offQ = r4(p.offX + dm + 4 + kXPad);
-    p.offW = r4(p.offQ + dm + 1 + kXPad);
-    p.offP = p.offW + r4(dm + 4);
-    p.offR = p.offP + r4(dm + 16);
+    p.offX = p.offT + 2 * kLyT + kXPad;
+    p.offQ = p.offX + dm + 4 + 2 * kXPad;
+    p.offW = p.offQ + dm + 1 + kXPad;
+    p.offR = r4(p.offW + dm + 4);
     p.capR = r4(nu + 8);
     p.total = p.offR + p.capR;
     return p;
@@ -303,6 +304,19 @@ MP_DEV int64_t byte_sum(const MfmaAcc &a, int j, int64_t c)
     return c;
 }
 
+// A number of up to 256 limbs in one wave's registers: lane (n, h) = n + 32 h
+// holds the limbs 8n + 4h .. 8n + 4h + 3, which is also the half-block h of
+// block n in the planes.
+MP_DEV int quad_limb() { return 8 * (lane() & 31) + 4 * (lane() >> 5); }
+
+// limb i (the same in every lane) of such a number
+MP_DEV uint32_t quad_get(const uint32_t (&z)[4], int i)
+{
+    const int j = i & 3;
+    const uint32_t x = j == 0 ? z[0] : j == 1 ? z[1] : j == 2 ? z[2] : z[3];
+    return readlane(x, ((i >> 3) & 31) + ((i & 4) << 3));
+}
+
 // adds the carries between the lanes' four-limb groups, given the groups that
 // generate one (G) and the carry into the lowest, by a lookahead over the 32
 // lane pairs (n, 0), (n, 1)
@@ -321,6 +335,15 @@ MP_DEV void quad_carries(uint32_t (&z)[4], uint64_t G, uint32_t cin, uint32_t &c
     z[1] = __builtin_addc(z[1], 0u, co, &co);
     z[2] = __builtin_addc(z[2], 0u, co, &co);
     z[3] += co;
+}
+
+// z += b + cin, b[j] in limb j of each lane's four
+MP_DEV void quad_add4(uint32_t (&z)[4], const uint32_t (&b)[4], uint32_t cin)
+{
+    uint32_t co = 0, cout;
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] = __builtin_addc(z[j], b[j], co, &co);
+    quad_carries(z, ballot(co != 0u), cin, cout);
 }
 
 // z += c in each lane's four limbs (lane (n, h): limbs 8n + 4h .. + 3 of one
@@ -364,29 +387,28 @@ MP_DEV uint64_t strip_limbs(const MfmaAcc &a, const Limb4 &add, uint32_t below, 
     return (uint64_t)readlane(c, kLanes - 1) + cout;
 }
 
-// dst[c] = limb of column c of x * y (+ R, when ADD: dst's own limbs) for c in
-// [c0, ncols), mod B^(ncols - c0) above c0, but for the strips' carries: the
-// carry of strip s goes to the control slots of s, and strip_carries adds it.
-// Strips are dealt to the workgroup's waves round robin; dst is 16-byte
-// aligned, c0 a multiple of 8 (0 with ADD).
-template <int T, bool ADD>
-MP_DEV void strips(uint32_t *ctl, const Operands &o, uint32_t *dst, int c0, int ncols, int base, int nstrips)
+// R[c] += column c of x * y for c in [0, ncols), mod B^ncols, but for the
+// strips' carries: the carry of strip s goes to the control slots of s, and
+// strip_carries adds it.  The strips end at ncols (rounded up to 8 limbs) and
+// are dealt to the workgroup's waves round robin; R is 16-byte aligned.
+template <int T>
+MP_DEV void strips(uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
 {
-    const int l = lane(), k = 8 * (l & 31) + 4 * (l >> 5);
+    const int l = lane(), k = quad_limb();
     for (int s = wave_index(); s < nstrips; s += T / kLanes) {
         const int k0 = base + s * kStrip + k;
         Limb4 add{0u, 0u, 0u, 0u};
-        if (ADD && k0 >= 0 && k0 < ncols) add = load4(dst + k0);
-        const MfmaAcc acc = strip_sums(o, (base >> 3) + s * (kStrip / 8));
+        if (k0 >= 0 && k0 < ncols) add = load4(R + k0);
+        const MfmaAcc acc = strip_sums(o, (base >> 3) + s * kStripBlks);
         uint32_t z[4];
         const uint64_t e = strip_limbs(acc, add, s == 0 ? 0x80000000u : 0u, z);
-        if (k0 >= c0) {
+        if (k0 >= 0) {
             if (k0 + 3 < ncols) {
-                store4(dst + k0, z[0], z[1], z[2], z[3]);
+                store4(R + k0, z[0], z[1], z[2], z[3]);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-                    if (k0 + j < ncols) dst[k0 + j] = z[j];
+                    if (k0 + j < ncols) R[k0 + j] = z[j];
             }
         }
         if (l == 0) {
@@ -482,86 +504,82 @@ MP_DEV void newton_start(const uint32_t (&a)[5], uint32_t (&w)[5])
 MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 
 // W ~ B^(k+F) / v, F = dp + 2, by one wave: w[0, F] its limbs, xw the reversed
-// digits of its F + 2 digit limbs (with their pads).  vd: the planes (distance
-// lv) of v's digits, tv(i): limb i of v, td: planes (distance lt, nt blocks,
-// pads zero) for the residuals.
+// digits of its F + 2 digit limbs (with their pads; all F + 2 + 2 kXPad words
+// from xw - kXPad on are zero before).  vd: the planes (distance lv) of v's
+// digits, td: T's planes (their pads zero), s: the five limbs newton_start gave.
 //
 // The iterate for f limbs is w ~ B^(k+f)/v, the top of the final one: w[F - f,
 // F].  A step to f' <= 2f - 3 limbs takes the middle columns of v w as the
 // residual e = (v w - B^(k+f)) / B^c and adds -w e: both products fill one
-// 256-column strip.  With |E| the error of w in units of its last limb, the
-// new one is at most E^2 / B (quadratic term) + 1 (floor) + 0.1: limbs of v
-// below s are left out (but for those the strip reads anyway), s <= k - 1 -
-// f', which moves e by less than B^f, and columns of e below c = sh - f - 2,
-// of either sign and below 2^26 B^c.  (The first step, from newton_start, adds
-// at most 2 instead of E^2 / B.)  So |E| <= 3 at the end.
-template <class FV>
-MP_DEV void newton(const FV &tv, int k, int dp, const uint32_t *vd, int lv, uint32_t *td, int lt, int nt, uint32_t *w,
+// 256-column strip, and both results go from the accumulators to the digits of
+// the next product in registers.  With |E| the error of w in units of its last
+// limb, the new one is at most E^2 / B (quadratic term) + 1 (floor) + 0.1:
+// limbs of v below s are left out (but for those the strip reads anyway), s <=
+// k - 1 - f', which moves e by less than B^f, and columns of e below c = sh - f
+// - 2, of either sign and below 2^26 B^c.  (The first step, from newton_start,
+// adds at most 2 instead of E^2 / B.)  So |E| <= 3 at the end.
+//
+// The correction ends in the old iterate's last limb, which the second product
+// takes as an addend.  As long as that limb neither overflows (it moves by a
+// few units) nor passes another balancing carry up than before, the digits
+// above it stay as they are and only the new limbs' are written; otherwise all
+// digits are made again from the limbs.
+MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint32_t *w,
                    uint32_t *xw)
 {
-    const int F = dp + 2, l = lane(), g = 8 * (l & 31) + 4 * (l >> 5);
-    {
-        uint32_t a[5], s[5];
+    const int F = dp + 2, l = lane(), g = quad_limb();
+    if (l == 0) {
 #pragma unroll
-        for (int j = 0; j < 5; j++) a[j] = k - 4 + j >= 0 ? tv(k - 4 + j) : 0u;
-        newton_start(a, s);
-        if (l == 0) {
-#pragma unroll
-            for (int j = 0; j < 5; j++) w[F - 4 + j] = s[j];
-        }
+        for (int j = 0; j < 5; j++) w[F - 4 + j] = s0[j];
     }
-    if (l < kXPad) xw[l - kXPad] = 0u;
-    for (int b = 32 + l; b < nt; b += kLanes)   // (blocks past the first strip are never residual)
-        for (int j = 0; j < 4; j++) td[4 * b + j] = td[lt + 4 * b + j] = 0u;
     int f = 4;
+    bool again = true;                           // the digits are to be made from the limbs
     for (;;) {
-        // digits of w, top digit first
         wave_sync();
-        const int n = f + 1;
-        balance_rows(0, (n + 64) >> 6, n, 0u, Span{w + F - f, 0, n}, StoreRev{xw, n + 1});
-        if (l < kXPad) xw[n + 1 + l] = 0u;
+        if (again) balance_rows(0, (f + 65) >> 6, f + 1, 0u, Span{w + F - f, 0, f + 1}, StoreRev{xw, f + 2});
         if (f == F) break;
+        const uint32_t last = uniform(w[F - f]);
         int fn = F;                              // the next step of the schedule that ends at F
         while (fn > 7 && newton_from(fn) > f) fn = newton_from(fn);
         const int s = imax(0, k - 1 - fn) & ~7;
         const int sh = k - s + 2 * f - fn;       // w e / B^sh is the correction
-        const int c0 = imax(0, sh - f - 2) & ~7, L = k + 2 - s;
+        const int c0 = imax(0, sh - f - 2) & ~7, nx = k + 2 - s - c0;
         wave_sync();
-        // -e: the two's complement of the columns [c0, L) of v w (B^(k+f-s) vanishes mod B^L), as digits
-        uint32_t z[4], co;
-        strip_limbs(strip_sums(operands(xw, n + 1, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), Limb4{0u, 0u, 0u, 0u},
+        // -e: the two's complement of the columns [c0, c0 + nx) of v w (B^(k+f-s) lies above them), as digits
+        uint32_t z[4], b[4];
+        strip_limbs(strip_sums(operands(xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), Limb4{0u, 0u, 0u, 0u},
                     0x80000000u, z);
-        const int nx = L - c0;
-        uint32_t cc = 0u;
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            const uint32_t bal = g + j < nx ? kBal : 0u, y = g + j < nx ? ~z[j] : 0u;
-            z[j] = __builtin_addc(y, bal, cc, &cc);
+            b[j] = g + j < nx ? kBal : 0u;
+            z[j] = g + j < nx ? ~z[j] : 0u;
         }
-        quad_carries(z, ballot(cc != 0u), 1u, co);
-        if ((l & 31) < nt) {
-            uint32_t *p = td + (l >> 5) * lt + 4 * (l & 31);
-            store4(p, g < nx ? z[0] ^ kBal : 0u, g + 1 < nx ? z[1] ^ kBal : 0u, g + 2 < nx ? z[2] ^ kBal : 0u,
-                   g + 3 < nx ? z[3] ^ kBal : 0u);
-        }
+        quad_add4(z, b, 1u);
+        store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nx ? z[0] ^ kBal : 0u, g + 1 < nx ? z[1] ^ kBal : 0u,
+               g + 2 < nx ? z[2] ^ kBal : 0u, g + 3 < nx ? z[3] ^ kBal : 0u);
         wave_sync();
-        // the correction's limbs: columns [shc, shc + fn - f + 2) of w (-e)
-        const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f;
-        strip_limbs(strip_sums(operands(xw, n + 1, td, lt, nx), cB >> 3), Limb4{0u, 0u, 0u, 0u}, 0x80000000u, z);
-        uint32_t top[2] = {0u, 0u};              // limbs m and m + 1 (the sign), wherever they are
+        // the new limbs: columns [shc, shc + m) of w (-e), and the old last limb at column shc + m
+        const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f, i0 = cB + g - shc, at = shc + m - cB;
+        Limb4 add{i0 == m ? last : 0u, i0 + 1 == m ? last : 0u, i0 + 2 == m ? last : 0u, i0 + 3 == m ? last : 0u};
+        strip_limbs(strip_sums(operands(xw, f + 2, td, kLyT, nx), cB >> 3), add, 0x80000000u, z);
+        const int over = (int)quad_get(z, at + 1);
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            const int i = cB + g + j - shc;      // limb of the correction
-            if (i >= 0 && i < m) w[F - fn + i] = z[j];
-            const uint64_t b0 = ballot(i == m), b1 = ballot(i == m + 1);
-            if (b0) top[0] = readlane(z[j], __builtin_ctzll(b0));
-            if (b1) top[1] = readlane(z[j], __builtin_ctzll(b1));
+            const bool in = (unsigned)(i0 + j) <= (unsigned)m;
+            if (in) w[F - fn + i0 + j] = z[j];
+            b[j] = in ? kBal : 0u;
+            z[j] = in ? z[j] : 0u;
         }
-        wave_sync();
-        const uint32_t x = uniform(w[F - f]), y = x + top[0];
-        wave_sync();
-        if (l == 0) w[F - f] = y;
-        add_small(w + F - f + 1, f, (int)top[1] + (y < x ? 1 : 0));
+        quad_add4(z, b, 0u);
+        const uint32_t up = quad_get(z, at + 1);             // the balancing carry out of the old last limb
+        again = over != 0 || up != (last >= 0u - kBal ? 1u : 0u);
+        if (again) {
+            add_small(w + F - f + 1, f, over);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if ((unsigned)(i0 + j) <= (unsigned)m) xw[fn + 1 - i0 - j] = bswap(z[j] ^ kBal);
+        }
         f = fn;
     }
 }
@@ -581,7 +599,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     uint32_t *ctl = lds;
     const BodyPlan pl = plan_body(nu, nv);
     uint32_t *Vd = lds + pl.offV, *Td = lds + pl.offT, *XW = lds + pl.offX, *XQ = lds + pl.offQ;
-    uint32_t *P = lds + pl.offP, *R = lds + pl.offR;
+    uint32_t *R = lds + pl.offR;
     const int w = wave_index(), t = tid<T>(), nr = r ? nv : 0;
     MP_RSTAMP(14);
     MP_STAMP(0);
@@ -614,13 +632,14 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     const BlockSplit bs = block_split(d, bmax);
     const int dp = bs.dp, nb = bs.nb, bi = bs.bi;
     MP_STAMP(1);
-    // the divisor's digits and the planes' zero pads
+    // the divisor's digits and the zero pads
     {
         for (int i = t; i < 5 * kPadWords; i += T) {
             const int b = i / kPadWords, j = i - b * kPadWords;
-            const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * pl.lyT;
+            const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * kLyT;
             lds[at - kPadWords + j] = 0u;
         }
+        for (int i = pl.offX - kXPad + t; i < pl.offW; i += T) lds[i] = 0u;
         const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 1) / W;
         const int r0 = w * per, r1 = imin(rows, r0 + per);
         if (r0 < r1) balance_rows(r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
@@ -629,8 +648,11 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     MP_STAMP(9);
     // W by the first wave, while the others read the dividend (zeros above it)
     if (w == 0) {
-        newton(Vv, k, dp, Vd, pl.lyV, Td, pl.lyT, pl.nbT, lds + pl.offW, XW);
-        if (lane() < kXPad) XQ[lane() - kXPad] = 0u;
+        uint32_t a[5], s[5];
+#pragma unroll
+        for (int j = 0; j < 5; j++) a[j] = k - 4 + j >= 0 ? Vv(k - 4 + j) : 0u;
+        newton_start(a, s);
+        newton(s, k, dp, Vd, pl.lyV, Td, lds + pl.offW, XW);
     } else {
         constexpr int S = T - kLanes;
         for (int i0 = t - kLanes; i0 < pl.capR; i0 += 8 * S) {
@@ -650,54 +672,60 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     bool good = true;
     const int n2 = k + 2, bs2 = (n2 + kStrip - 1) / kStrip, base2 = ((n2 + 7) & ~7) - bs2 * kStrip;
     int o = d;
-    for (int i = 0; i < nb && good; i++) {
+    for (int i = 0; i < nb; i++) {
         const int op = o;
         o = (nb - 1 - i) * bi;
         const int b = op - o, nt = b + 3;             // limbs of this block, of R_top
-        // R complete, R_top's digits
         if (w == 0) {
+            const int l = lane(), g = quad_limb();
+            uint32_t z[4], y[4];
+            // R complete; R_top's digits
             if (i) strip_carries(ctl, R + op, n2, base2, bs2);
-            const uint32_t *src = R + o + k - 1;
-            balance_rows(0, (8 * pl.nbT + 63) >> 6, nt, 0u, Span{src, 0, nt}, StorePlane{Td, imin(nt, 8 * pl.nbT), pl.lyT});
-            for (int j = nt + lane(); j < 8 * pl.nbT; j += kLanes) Td[plane_word(j, pl.lyT)] = 0u;
-        }
-        bar<T>();
-        MP_STAMP(16 + 4 * (i & 3));   // (trace build: the phases of the last four blocks)
-        // q_i = R_top W / B^(dp+3): columns from cA up
-        const int shA = dp + 3, cA = (shA - 2) & ~7, nA = shA + b + 1, sA = (nA - cA + kStrip - 1) / kStrip;
-        strips<T, false>(ctl, operands(XW, dp + 4, Td, pl.lyT, nt), P - cA, cA, nA, cA, sA);
-        bar<T>();
-        MP_STAMP(17 + 4 * (i & 3));
-        // its limbs to the quotient, the reversed digits of -q_i
-        if (w == 0) {
-            strip_carries(ctl, P - cA, nA, cA, sA);
-            const uint32_t *src = P + (shA - cA);
-            const int nd = b + 1;
-            uint32_t *Q = R + k + 2 + o;
-            balance_rows(0, (nd + 63) >> 6, nd, 1u,
-                         [&](int j) {
-                             const uint32_t x = src[j];
-                             if (j < b) Q[j] = x;
-                             return ~x;
-                         },
-                         StoreRev{XQ, nd});
-            if (lane() < kXPad) XQ[nd + lane()] = 0u;
-            const int s = (int)uniform(src[b]);       // q_i's sign limb
+            const uint32_t *src = R + o + k - 1 + g;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                z[j] = g + j < nt ? src[j] : 0u;
+                y[j] = g + j < nt ? kBal : 0u;
+            }
+            quad_add4(z, y, 0u);
+            store4(Td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] ^ kBal : 0u, g + 1 < nt ? z[1] ^ kBal : 0u,
+                   g + 2 < nt ? z[2] ^ kBal : 0u, g + 3 < nt ? z[3] ^ kBal : 0u);
             wave_sync();
+            MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
+            // q_i = R_top W / B^(dp+3), formed from column dp + 1 up: limb j of q_i is column dp + 3 + j
+            strip_limbs(strip_sums(operands(XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u},
+                        0x80000000u, z);
+            // to the quotient; the reversed digits of -q_i (limb b is its sign)
+            uint32_t *Q = R + k + 2 + o;
+            const int s = (int)quad_get(z, b + 2);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int e = g + j - 2;              // limb of q_i
+                if ((unsigned)e < (unsigned)b) Q[e] = z[j];
+                y[j] = (unsigned)e <= (unsigned)b ? kBal : 0u;
+                z[j] = e <= b ? (e < 0 ? 0xFFFFFFFFu : ~z[j]) : 0u;   // (the two columns below pass the +1 on)
+            }
+            quad_add4(z, y, 1u);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int e = g + j - 2;
+                if ((unsigned)e <= (unsigned)b) XQ[b - e] = bswap(z[j] ^ kBal);
+            }
+            if (l < kXPad) XQ[b + 1 + l] = 0u;
             if (i == 0) {
-                if (lane() == 0) Q[b] = (uint32_t)s;
+                if (l == 0) Q[b] = (uint32_t)s;
             } else {
                 add_small(Q + b, d + 1 - op, s);
             }
         }
         bar<T>();
-        MP_STAMP(18 + 4 * (i & 3));
+        MP_STAMP(17 + 3 * (i % 5));
         // R -= v q_i
-        strips<T, true>(ctl, operands(XQ, b + 1, Vd, pl.lyV, k + 2), R + o, 0, n2, base2, bs2);
+        strips<T>(ctl, operands(XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
         bar<T>();
-        MP_STAMP(19 + 4 * (i & 3));
+        MP_STAMP(18 + 3 * (i % 5));
     }
-    if (w == 0 && good) strip_carries(ctl, R, n2, base2, bs2);
+    if (w == 0) strip_carries(ctl, R, n2, base2, bs2);
     bar<T>();
     MP_STAMP(6);
     // corrections: R is a signed (k + 2)-limb number in (-1.1 v, 2.1 v)
