@@ -18,13 +18,14 @@
 
 namespace mp {
 
-// Registers of the division kernels.  A 256-thread instance spends much of its
-// time in phases that one of its waves runs (Newton steps, a block's digits
-// and quotient product), so further resident instances fill the other waves'
-// issue slots: six waves per SIMD (80 registers; the LDS of a 2^16-bit
-// instance, 20 KB, allows seven) take 176 us for 4096 divisions of 2048 by 1024
-// limbs, five 203 us, four 205 us.  The wider workgroups are bound by their LDS.
-#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(T == 256 ? 6 : 4, 8)))
+// Registers of the division kernels.  An instance spends much of its time in
+// phases that one of its waves runs (Newton steps, a block's digits and
+// quotient product), so further resident instances fill the other waves' issue
+// slots: eight waves per SIMD (64 vector and 96 scalar registers), which the LDS
+// of a 2^16-bit instance, 20 KB, also allows.  4096 divisions of 2048 by 1024
+// limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
+// 112 us.
+#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 // Workspace of a ragged batch (int32): [0, 4) instances per class, [4, 8)
 // queue heads, then one list of instance indices per class, each `count` long.
 constexpr int kClasses = 4;

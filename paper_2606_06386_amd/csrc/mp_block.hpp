@@ -32,6 +32,11 @@ namespace mp {
 
 enum : int32_t { kInstOk = 0, kInstDivZero = 1, kInstQWidth = 2, kInstInternal = 3 };
 
+#ifndef MP_DIAGS
+#define MP_DIAGS 2
+#endif
+constexpr int kDiags = MP_DIAGS;   // diagonals per step of a product
+
 // The quotient's d limbs: nb blocks of bi limbs, the first (top) of
 // d - (nb - 1) bi; dp limbs of precision of W serve the longest of them.  bi
 // is a multiple of 4, so that every block starts at a 16-byte boundary of R;
@@ -64,7 +69,7 @@ MP_HD int block_limit(int limit) { return hmax(16, hmin(kBlockMax, (2 * limit - 
 //
 // ctl | pad | V plane 0 | pad | V plane 1 | pad | T plane 0 | pad | T plane 1 |
 // pad | W reversed | -q reversed | W | R
-// (pads of kYPadBlk zero blocks shared by their neighbours; T: R_top, and the
+// (pads of kPadBlk zero blocks shared by their neighbours; T: R_top, and the
 // residuals of the Newton steps).  R holds the dividend's h limbs and above
 // them the quotient: limb j of q goes to R[k + 2 + j], which the remainder has
 // left by the time the block is done.
@@ -76,7 +81,8 @@ struct BodyPlan {
     int total;
 };
 
-constexpr int kPadWords = 4 * kYPadBlk;
+constexpr int kPadBlk = kYPadBlk + kDiags - 1, kPadWords = 4 * kPadBlk;
+constexpr int kXLow = kXPad + 8 * (kDiags - 1);   // zero words below the reversed digits
 
 constexpr int kStripBlks = kStrip / 8;
 constexpr int kLyT = 4 * kStripBlks + kPadWords;   // distance of T's planes
@@ -92,8 +98,8 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
     p.offV = kCtlWords + kPadWords;
     p.lyV = 4 * p.nbV + kPadWords;
     p.offT = p.offV + 2 * p.lyV;
-    p.offX = p.offT + 2 * kLyT + kXPad;
-    p.offQ = p.offX + dm + 4 + 2 * kXPad;
+    p.offX = r4(p.offT + 2 * kLyT + kXLow);
+    p.offQ = p.offX + dm + 4 + kXPad + kXLow;
     p.offW = p.offQ + dm + 1 + kXPad;
     p.offR = r4(p.offW + dm + 4);
     p.capR = r4(nu + 8);
@@ -127,18 +133,18 @@ MP_DEV uint32_t row_carry_out(uint64_t G, uint64_t P)
     return (uint32_t)(G >> (63 - __builtin_clzll(~P))) & 1u;
 }
 
-constexpr uint32_t kBal = 0x80808080u;
+constexpr uint32_t kBal = 0x80808080u, kBalTop = 0x7F7F7F7Fu;   // (limbs above kBalTop carry)
 constexpr int kRowBatch = 5;   // rows read at once (a block's 257 + 3 limbs)
 
 // out(k, digit limb) for the limbs k of rows [r0, r1): the balanced radix-256
 // digits of the n-limb number x with carry-in cin0 at limb 0.  Limb n gets the
 // top carry digit (0 or 1), limbs above it zero.
 template <class FX, class FO>
-MP_DEV void balance_rows(int r0, int r1, int n, uint32_t cin0, const FX &x, const FO &out)
+MP_DEV void balance_rows(int ln, int r0, int r1, int n, uint32_t cin0, const FX &x, const FO &out)
 {
     uint32_t c = cin0;
     for (int r = r0 - 1; r >= 0; r--) {          // (rows below r0 lie inside [0, n))
-        const uint32_t s = x(64 * r + lane()) + kBal;
+        const uint32_t s = x(64 * r + ln) + kBal;
         const uint64_t G = ballot(s < kBal), P = ballot(s == 0xFFFFFFFFu);
         if (~P) {
             c = row_carry_out(G, P);
@@ -149,13 +155,13 @@ MP_DEV void balance_rows(int r0, int r1, int n, uint32_t cin0, const FX &x, cons
         uint32_t xv[kRowBatch];
 #pragma unroll
         for (int j = 0; j < kRowBatch; j++) {
-            const int k = 64 * (r + j) + lane();
+            const int k = 64 * (r + j) + ln;
             xv[j] = r + j < r1 && k < n ? x(k) : 0u;
         }
 #pragma unroll
         for (int j = 0; j < kRowBatch; j++) {
             if (r + j < r1) {
-                const int k = 64 * (r + j) + lane();
+                const int k = 64 * (r + j) + ln;
                 const uint32_t a = k < n ? kBal : 0u, s = xv[j] + a;
                 const uint64_t cm = row_carries(ballot(s < a), ballot(s == 0xFFFFFFFFu), c);
                 out(k, (s + (inverse_ballot(cm) ? 1u : 0u)) ^ a);
@@ -186,11 +192,11 @@ struct StoreRev {
 
 // dst = x + y or x - y over limbs [0, n) (mod B^n), rows [r0, r1) by this wave; dst is neither operand
 template <class FX, class FY>
-MP_DEV void addsub_rows(int r0, int r1, int n, bool sub, const FX &x, const FY &y, uint32_t *dst)
+MP_DEV void addsub_rows(int ln, int r0, int r1, int n, bool sub, const FX &x, const FY &y, uint32_t *dst)
 {
     uint32_t c = 0;
     for (int r = r0 - 1; r >= 0; r--) {
-        const int k = 64 * r + lane();
+        const int k = 64 * r + ln;
         const uint32_t a = x(k), b = y(k), z = sub ? a - b : a + b;
         const uint64_t G = ballot(sub ? a < b : z < a), P = ballot(z == (sub ? 0u : 0xFFFFFFFFu));
         if (~P) {
@@ -199,7 +205,7 @@ MP_DEV void addsub_rows(int r0, int r1, int n, bool sub, const FX &x, const FY &
         }
     }
     for (int r = r0; r < r1; r++) {
-        const int k = 64 * r + lane();
+        const int k = 64 * r + ln;
         const uint32_t a = k < n ? x(k) : 0u, b = k < n ? y(k) : 0u, z = sub ? a - b : a + b;
         const uint64_t cm = row_carries(ballot(sub ? a < b : z < a), ballot(z == (sub ? 0u : 0xFFFFFFFFu)), c);
         const uint32_t ci = inverse_ballot(cm) ? 1u : 0u;
@@ -208,30 +214,30 @@ MP_DEV void addsub_rows(int r0, int r1, int n, bool sub, const FX &x, const FY &
 }
 
 // p[0, n) += 1 (up) or -= 1, by one wave: stops at the first limb that does not pass the carry on
-MP_DEV void ripple(uint32_t *p, int n, bool up)
+MP_DEV void ripple(int l, uint32_t *p, int n, bool up)
 {
     const uint32_t pass = up ? 0xFFFFFFFFu : 0u;
     for (int b = 0; b < n; b += kLanes) {
-        const int k = b + lane();
+        const int k = b + l;
         wave_sync();
         const uint32_t x = k < n ? p[k] : pass;
         const uint64_t m = ballot(x != pass);
-        if (k < n && (m == 0 || lane() <= __builtin_ctzll(m))) p[k] = up ? x + 1u : x - 1u;
+        if (k < n && (m == 0 || l <= __builtin_ctzll(m))) p[k] = up ? x + 1u : x - 1u;
         wave_sync();
         if (m) return;
     }
 }
 
 // p[0, n) += s for a small signed s, by one wave
-MP_DEV void add_small(uint32_t *p, int n, int s)
+MP_DEV void add_small(int l, uint32_t *p, int n, int s)
 {
     if (s == 0 || n <= 0) return;
     wave_sync();
     const uint32_t x = uniform(p[0]), z = x + (uint32_t)s;
     wave_sync();
-    if (lane() == 0) p[0] = z;
+    if (l == 0) p[0] = z;
     wave_sync();
-    if (s > 0 ? z < x : z > x) ripple(p + 1, n - 1, s > 0);
+    if (s > 0 ? z < x : z > x) ripple(l, p + 1, n - 1, s > 0);
 }
 
 // ---------------------------------------------------------------- products
@@ -247,67 +253,77 @@ MP_DEV void add_small(uint32_t *p, int n, int s)
 // between lanes is needed to form limbs.
 
 struct Operands {
-    const uint32_t *x;   // this lane's word of the reversed short digits at diagonal 0
+    uint32_t x;          // LDS byte address of this lane's word of the reversed short digits at diagonal 0
     uint32_t sft;        // and its byte shift
     int dmax;            // last diagonal that touches the short digits
-    const uint32_t *y;   // this lane's word of the long digits' planes for block 0
+    uint32_t y;          // LDS byte address of this lane's word of the long digits' planes for block 0
     int nyblk;           // blocks of the long digits
 };
 
 // xr: nx reversed digit limbs; yb: planes (distance ly) of ny digit limbs
-MP_DEV Operands operands(const uint32_t *xr, int nx, const uint32_t *yb, int ly, int ny)
+MP_DEV Operands operands(int l, const uint32_t *xr, int nx, const uint32_t *yb, int ly, int ny)
 {
-    const int l = lane(), p = l & 31, h = l >> 5;
-    const int ox = 4 * nx - 1 - (16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3)) + 16 * h;
-    return Operands{xr + (ox >> 2), (uint32_t)ox & 3u, (4 * nx + 30) >> 5, yb + h * ly + 4 * p, (ny + 7) >> 3};
+    const int p = l & 31, h = l >> 5;
+    const int ox = 16 * h - 1 - (16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3));   // (from the end of the digits)
+    return Operands{lds_address(xr + nx) + 4 * (ox >> 2), (uint32_t)ox & 3u, (4 * nx + 30) >> 5,
+                    lds_address(yb) + 4 * (h * ly + 4 * p), (ny + 7) >> 3};
 }
 
-// the accumulator of the strip whose first block is S0
+MP_DEV XRaw xraw_at(uint32_t a, int w)
+{
+    return XRaw{lds_word(a, w), lds_word(a, w + 1), lds_word(a, w + 2), lds_word(a, w + 3), lds_word(a, w + 4)};
+}
+
+// the accumulator of the strip whose first block is S0.  Steps of kDiags
+// diagonals; the last may pass the end: it reads zeros there (of the short
+// digits, or blocks below the long ones').
 MP_DEV MfmaAcc strip_sums(const Operands &o, int S0)
 {
     MfmaAcc acc = mfma_zero();
-    int d = uniform(imax(0, S0 - o.nyblk + 1));
-    const int dhi = uniform(imin(o.dmax, S0 + 31));
-    const uint32_t *x = o.x - 8 * d, *y = o.y + 4 * (S0 - d);
-    constexpr int D = 2;   // diagonals whose operands are in flight (more cost registers, and with them resident waves)
-    for (; d + D - 1 <= dhi; d += D) {
-        XRaw r[D];
-        Limb4 yv[D];
+    const int dlo = imax(0, S0 - o.nyblk + 1), dhi = imin(o.dmax, S0 + 31);
+    // (addresses of a step's last diagonal: the others lie at positive offsets)
+    uint32_t x = opaque(o.x - 32 * (dlo + kDiags - 1)), y = opaque(o.y + 16 * (S0 - dlo - (kDiags - 1)));
+    for (int n = uniform(dhi - dlo + 1); n > 0; n -= kDiags) {
+        XRaw r[kDiags];
+        Limb4 yv[kDiags];
 #pragma unroll
-        for (int j = 0; j < D; j++) {
-            r[j] = xraw(x - 8 * j);
-            yv[j] = load4(y - 4 * j);
+        for (int j = 0; j < kDiags; j++) {
+            r[j] = xraw_at(x, 8 * (kDiags - 1 - j));
+            yv[j] = lds_quad(y, kDiags - 1 - j);
         }
 #pragma unroll
-        for (int j = 0; j < D; j++) acc = mfma_x(acc, xfrag(r[j], o.sft), yv[j]);
+        for (int j = 0; j < kDiags; j++) acc = mfma_x(acc, xfrag(r[j], o.sft), yv[j]);
         sched_loads_first();
-        x -= 8 * D;
-        y -= 4 * D;
-    }
-    for (; d <= dhi; d++) {
-        acc = mfma_x(acc, xfrag(xraw(x), o.sft), load4(y));
-        x -= 8;
-        y -= 4;
+        x -= 32 * kDiags;
+        y -= 16 * kDiags;
     }
     return acc;
 }
 
-// sum of a[j] 256^j, j = 0..3, plus c (exact, signed)
-MP_DEV int64_t byte_sum(const MfmaAcc &a, int j, int64_t c)
+// the same for two strips at once over the diagonals [0, dmax], which both
+// must need in full (S0 >= dmax - 31): each X fragment serves both
+MP_DEV void strip_sums2(const Operands &o, int SA, int SB, MfmaAcc &accA, MfmaAcc &accB)
 {
-    int b1 = 256, b2 = 65536, b3 = 16777216;
-    asm("" : "+s"(b1), "+s"(b2), "+s"(b3));   // (keeps the products multiply-adds instead of 64-bit shifts)
-    c += mfma_get(a, j);
-    c += (int64_t)mfma_get(a, j + 1) * b1;
-    c += (int64_t)mfma_get(a, j + 2) * b2;
-    c += (int64_t)mfma_get(a, j + 3) * b3;
-    return c;
+    accA = mfma_zero();
+    accB = mfma_zero();
+    uint32_t x = opaque(o.x), ya = opaque(o.y + 16 * SA), yb = opaque(o.y + 16 * SB);
+    for (int n = uniform(o.dmax); n >= 0; n--) {
+        const XRaw r = xraw_at(x, 0);
+        const Limb4 va = lds_quad(ya, 0), vb = lds_quad(yb, 0);
+        const XFrag f = xfrag(r, o.sft);
+        accA = mfma_x(accA, f, va);
+        accB = mfma_x(accB, f, vb);
+        sched_loads_first();
+        x -= 32;
+        ya -= 16;
+        yb -= 16;
+    }
 }
 
 // A number of up to 256 limbs in one wave's registers: lane (n, h) = n + 32 h
 // holds the limbs 8n + 4h .. 8n + 4h + 3, which is also the half-block h of
 // block n in the planes.
-MP_DEV int quad_limb() { return 8 * (lane() & 31) + 4 * (lane() >> 5); }
+MP_DEV int quad_limb(int l) { return 8 * (l & 31) + 4 * (l >> 5); }
 
 // limb i (the same in every lane) of such a number
 MP_DEV uint32_t quad_get(const uint32_t (&z)[4], int i)
@@ -317,126 +333,167 @@ MP_DEV uint32_t quad_get(const uint32_t (&z)[4], int i)
     return readlane(x, ((i >> 3) & 31) + ((i & 4) << 3));
 }
 
-// adds the carries between the lanes' four-limb groups, given the groups that
-// generate one (G) and the carry into the lowest, by a lookahead over the 32
-// lane pairs (n, 0), (n, 1)
-MP_DEV void quad_carries(uint32_t (&z)[4], uint64_t G, uint32_t cin, uint32_t &cout)
+// the lanes next above those of mask m (in limb order), the lowest lane getting cin
+MP_DEV uint64_t quad_up(uint64_t m, uint32_t cin)
 {
-    cout = 0;
-    if (G == 0 && cin == 0) return;
-    const uint64_t P = ballot((z[0] & z[1] & z[2] & z[3]) == 0xFFFFFFFFu);
+    const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+    return (uint64_t)lo << 32 | (hi << 1 | cin);
+}
+
+// z += b + cin, b[j] in limb j of each lane's four; returns the carry out of
+// the 256 limbs.  The general case: a lookahead over the 32 lane pairs (n, 0),
+// (n, 1).
+MP_DEV uint32_t quad_add(uint32_t (&z)[4], const uint32_t (&b)[4], uint32_t cin)
+{
+    uint32_t co = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] = __builtin_addc(z[j], b[j], co, &co);
+    const uint64_t G = ballot(co != 0u), P = ballot((z[0] & z[1] & z[2] & z[3]) == 0xFFFFFFFFu);
     const uint32_t Gl = (uint32_t)G, Gh = (uint32_t)(G >> 32), Pl = (uint32_t)P, Ph = (uint32_t)(P >> 32);
     const uint32_t Gp = Gh | (Ph & Gl), X = Gp | (Ph & Pl);
     const uint64_t s = (uint64_t)X + Gp + cin;
     const uint32_t cl = (uint32_t)s ^ X ^ Gp, ch = Gl | (Pl & cl);
-    cout = (uint32_t)(s >> 32);
-    uint32_t co;
     z[0] = __builtin_addc(z[0], 0u, inverse_ballot((uint64_t)ch << 32 | cl) ? 1u : 0u, &co);
     z[1] = __builtin_addc(z[1], 0u, co, &co);
     z[2] = __builtin_addc(z[2], 0u, co, &co);
     z[3] += co;
+    return (uint32_t)(s >> 32);
 }
 
-// z += b + cin, b[j] in limb j of each lane's four
-MP_DEV void quad_add4(uint32_t (&z)[4], const uint32_t (&b)[4], uint32_t cin)
+// The balanced digits of the number in z, with carry-in cin.  A limb above
+// kBalTop carries, whatever comes in; a limb equal to it passes an incoming
+// carry on, which shows as a sum of 0: then (one limb in 2^32) the carries are
+// resolved in full.  Returns whether that was so.
+MP_DEV bool quad_balance(uint32_t (&z)[4], uint32_t cin)
 {
-    uint32_t co = 0, cout;
+    const uint32_t x[4] = {z[0], z[1], z[2], z[3]};
+    const uint64_t up = quad_up(add_above(z, kBal, kBalTop), cin);
+    z[0] = add_mask(z[0], kBal, up);
+    const uint32_t a = z[0] < z[1] ? z[0] : z[1], b = z[2] < z[3] ? z[2] : z[3];
+    const bool odd = ballot((a < b ? a : b) == 0u) != 0;
+    if (odd) {
+        const uint32_t bal[4] = {kBal, kBal, kBal, kBal};
 #pragma unroll
-    for (int j = 0; j < 4; j++) z[j] = __builtin_addc(z[j], b[j], co, &co);
-    quad_carries(z, ballot(co != 0u), cin, cout);
+        for (int j = 0; j < 4; j++) z[j] = x[j];
+        quad_add(z, bal, cin);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] ^= kBal;
+    return odd;
 }
 
-// z += c in each lane's four limbs (lane (n, h): limbs 8n + 4h .. + 3 of one
-// number) with the carries between the lanes; cout: the carry out of the
-// number's 256 limbs
-MP_DEV void quad_add(uint32_t (&z)[4], uint32_t c, uint32_t &cout)
+// The limbs of a strip from its accumulator plus (ADD) four addend limbs per
+// lane: z gets the limbs of columns 8n + 4h .. + 3 with the carries inside the
+// strip resolved; returns the strip's signed carry into its next column.
+// Every lane's four columns are chained exactly and pass a signed carry to the
+// next lane, where it is absorbed by the two lowest limbs; only if it is not
+// (about one lane in 2^40, or runs of zero or all-ones limbs) the carries are
+// resolved in full, biased by 2^31 to be non-negative.
+template <bool ADD>
+MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[4])
 {
-    uint32_t co;
-    z[0] = __builtin_addc(z[0], c, 0u, &co);
-    z[1] = __builtin_addc(z[1], 0u, co, &co);
-    z[2] = __builtin_addc(z[2], 0u, co, &co);
-    z[3] = __builtin_addc(z[3], 0u, co, &co);
-    quad_carries(z, ballot(co != 0u), 0u, cout);
-}
-
-// The limbs of a strip from its byte sums plus four addend limbs per lane:
-// z gets the limbs of columns 8n + 4h .. + 3 with every carry inside the strip
-// resolved.  A lane's four columns pass a signed carry on; it is biased by
-// 2^31 (subtracted again in the next lane's lowest column, or, below the first
-// column of the number, put in as `below` = 2^31) so that it is never
-// negative.  Returns the strip's carry into its next column, biased the same
-// way (0 <= carry < 2^33): the next strip's own bias takes the 2^31 off again.
-MP_DEV uint64_t strip_limbs(const MfmaAcc &a, const Limb4 &add, uint32_t below, uint32_t (&z)[4])
-{
-    int64_t t = byte_sum(a, 0, (int64_t)add.x - ((int64_t)1 << 31));
-    z[0] = (uint32_t)t;
-    t = byte_sum(a, 4, (t >> 32) + (int64_t)add.y);
-    z[1] = (uint32_t)t;
-    t = byte_sum(a, 8, (t >> 32) + (int64_t)add.z);
-    z[2] = (uint32_t)t;
-    t = byte_sum(a, 12, (t >> 32) + (int64_t)add.w);
-    z[3] = (uint32_t)t;
-    const uint32_t c = (uint32_t)(t >> 32) + 0x80000000u;
+    int w0 = 1, w1 = 256, w2 = 65536, w3 = 16777216;
+    asm("" : "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3));   // (every term one 64-bit multiply-add)
+    const uint32_t ad[4] = {add.x, add.y, add.z, add.w};
+    int64_t s[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        s[j] = (int64_t)mfma_get(a, 4 * j) * w0;
+        s[j] += (int64_t)mfma_get(a, 4 * j + 1) * w1;
+        s[j] += (int64_t)mfma_get(a, 4 * j + 2) * w2;
+        s[j] += (int64_t)mfma_get(a, 4 * j + 3) * w3;
+        if constexpr (ADD) s[j] = (int64_t)((uint64_t)ad[j] * (uint32_t)w0 + (uint64_t)s[j]);
+    }
+#pragma unroll
+    for (int j = 1; j < 4; j++) s[j] += (int64_t)(int32_t)(s[j - 1] >> 32) * w0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] = (uint32_t)s[j];
+    const uint32_t c = (uint32_t)(s[3] >> 32);
     // the lane below (n, 1) is (n, 0); below (n, 0) it is (n - 1, 1)
     uint32_t lo, hi;
     half_swap(c, lo, hi);                 // lo: lane l gets c of lane l & 31; hi: of lane (l & 31) + 32
-    const uint32_t up = shfl_up1(hi);
-    const uint32_t prev = lane() >= 32 ? lo : (lane() == 0 ? below : up);
-    uint32_t cout;
-    quad_add(z, prev, cout);
-    return (uint64_t)readlane(c, kLanes - 1) + cout;
+    const uint32_t up = shfl_up1(hi);     // (0 in lane 0)
+    const int prev = (int)(l >= 32 ? lo : up);
+    const uint64_t neg = ballot(prev < 0);
+    const uint64_t odd = add64_carry(z[0], z[1], prev) ^ neg;
+    int e = (int)readlane(c, kLanes - 1);
+    if (odd) {
+        // z + sum (c + 2^31) - sum 2^31, each sum over the lanes above the lowest
+        const bool first = l == 0;
+        const uint32_t b[4] = {first ? 0u : (uint32_t)prev + 0x80000000u, 0u, 0u, 0u};
+        const uint32_t m[4] = {first ? 0xFFFFFFFFu : 0x7FFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll
+        for (int j = 0; j < 4; j++) z[j] = (uint32_t)s[j];
+        e += (int)quad_add(z, b, 0u);
+        e += (int)quad_add(z, m, 1u) - 1;
+    }
+    return e;
+}
+
+// limbs of strip s (accumulator acc) into R, its carry into the control slot of s
+MP_DEV void strip_out(int l, uint32_t *ctl, const MfmaAcc &acc, uint32_t *R, int ncols, int base, int s)
+{
+    const int k0 = base + s * kStrip + quad_limb(l);
+    Limb4 add{0u, 0u, 0u, 0u};
+    if (k0 >= 0 && k0 < ncols) add = load4(R + k0);
+    uint32_t z[4];
+    const int e = strip_limbs<true>(l, acc, add, z);
+    if (k0 >= 0) {
+        if (k0 + 3 < ncols) {
+            store4(R + k0, z[0], z[1], z[2], z[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (k0 + j < ncols) R[k0 + j] = z[j];
+        }
+    }
+    if (l == 0) ctl[kCtlStrip + s] = (uint32_t)e;
 }
 
 // R[c] += column c of x * y for c in [0, ncols), mod B^ncols, but for the
 // strips' carries: the carry of strip s goes to the control slots of s, and
-// strip_carries adds it.  The strips end at ncols (rounded up to 8 limbs) and
-// are dealt to the workgroup's waves round robin; R is 16-byte aligned.
+// strip_carries adds it.  x has at most kBlockMax + 1 limbs, y at least ncols
+// digit limbs, and the strips end at ncols (rounded up to 8 limbs), so that
+// every strip but the lowest needs every diagonal of x: a wave takes two of
+// these at a time when it has more than one.  The lowest, partial strip goes to the
+// wave that has the fewest.  R is 16-byte aligned.
 template <int T>
-MP_DEV void strips(uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
+MP_DEV void strips(int l, uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
 {
-    const int l = lane(), k = quad_limb();
-    for (int s = wave_index(); s < nstrips; s += T / kLanes) {
-        const int k0 = base + s * kStrip + k;
-        Limb4 add{0u, 0u, 0u, 0u};
-        if (k0 >= 0 && k0 < ncols) add = load4(R + k0);
-        const MfmaAcc acc = strip_sums(o, (base >> 3) + s * kStripBlks);
-        uint32_t z[4];
-        const uint64_t e = strip_limbs(acc, add, s == 0 ? 0x80000000u : 0u, z);
-        if (k0 >= 0) {
-            if (k0 + 3 < ncols) {
-                store4(R + k0, z[0], z[1], z[2], z[3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    if (k0 + j < ncols) R[k0 + j] = z[j];
-            }
-        }
-        if (l == 0) {
-            ctl[kCtlStrip + 2 * s] = (uint32_t)e;
-            ctl[kCtlStrip + 2 * s + 1] = (uint32_t)(e >> 32);
-        }
+    constexpr int W = T / kLanes;
+    const int w = wave_index(), n = nstrips - 1, b = base >> 3;
+    int s = 1 + w;
+    for (; s + W <= n; s += 2 * W) {
+        MfmaAcc accA, accB;
+        strip_sums2(o, b + s * kStripBlks, b + (s + W) * kStripBlks, accA, accB);
+        strip_out(l, ctl, accA, R, ncols, base, s);
+        strip_out(l, ctl, accB, R, ncols, base, s + W);
+    }
+    bool low = w == n % W;
+    while (s <= n || low) {
+        const int i = s <= n ? s : 0;
+        if (s > n) low = false;
+        strip_out(l, ctl, strip_sums(o, b + i * kStripBlks), R, ncols, base, i);
+        s = n + 1;
     }
 }
 
 // adds the strips' carries to dst (see strips), by one wave after a barrier:
-// lane s adds the carry of strip s - 1 to the first two limbs of strip s; a
-// carry out of those (rare) ripples on
-MP_DEV void strip_carries(const uint32_t *ctl, uint32_t *dst, int ncols, int base, int nstrips)
+// lane s adds the signed carry of strip s - 1 to the first two limbs of strip
+// s; a carry or borrow out of those (rare) ripples on
+MP_DEV void strip_carries(int s, const uint32_t *ctl, uint32_t *dst, int ncols, int base, int nstrips)
 {
-    const int s = lane(), cb = base + s * kStrip;
+    const int cb = base + s * kStrip;
     const bool on = s >= 1 && s < nstrips, two = on && cb + 1 < ncols;
-    uint32_t co = 0;
-    if (on) {
-        const uint32_t z0 = __builtin_addc(dst[cb], ctl[kCtlStrip + 2 * s - 2], 0u, &co);
-        const uint32_t z1 = __builtin_addc(two ? dst[cb + 1] : 0u, ctl[kCtlStrip + 2 * s - 1], co, &co);
-        dst[cb] = z0;
-        if (two) dst[cb + 1] = z1;
-    }
-    uint64_t m = ballot(two && co != 0u);
+    const int e = on ? (int)ctl[kCtlStrip + s - 1] : 0;
+    const uint64_t x = ((uint64_t)(two ? dst[cb + 1] : 0u) << 32) | (on ? dst[cb] : 0u), y = x + (uint64_t)(int64_t)e;
+    if (on) dst[cb] = (uint32_t)y;
+    if (two) dst[cb + 1] = (uint32_t)(y >> 32);
+    uint64_t up = ballot(two && e > 0 && y < x), m = up | ballot(two && e < 0 && y > x);
     while (m) {
-        const int c = base + __builtin_ctzll(m) * kStrip + 2;
+        const int t = __builtin_ctzll(m), c = base + t * kStrip + 2;
         m &= m - 1;
-        if (c < ncols) ripple(dst + c, ncols - c, true);
+        if (c < ncols) ripple(s, dst + c, ncols - c, (up >> t) & 1u);
     }
     wave_sync();
 }
@@ -455,10 +512,10 @@ struct Shifted {
 };
 
 // number of significant limbs of x[0, n) (global memory), by one wave from the top
-MP_DEV int wave_prec(const uint32_t *x, int n)
+MP_DEV int wave_prec(int ln, const uint32_t *x, int n)
 {
     for (int top = n; top > 0; top -= kLanes) {
-        const int i = top - kLanes + lane();
+        const int i = top - kLanes + ln;
         const uint64_t m = ballot(i >= 0 && x[i] != 0u);
         if (m) return top - kLanes + 64 - __builtin_clzll(m);
     }
@@ -504,9 +561,9 @@ MP_DEV void newton_start(const uint32_t (&a)[5], uint32_t (&w)[5])
 MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 
 // W ~ B^(k+F) / v, F = dp + 2, by one wave: w[0, F] its limbs, xw the reversed
-// digits of its F + 2 digit limbs (with their pads; all F + 2 + 2 kXPad words
-// from xw - kXPad on are zero before).  vd: the planes (distance lv) of v's
-// digits, td: T's planes (their pads zero), s: the five limbs newton_start gave.
+// digits of its F + 2 digit limbs (all words from xw - kXLow to their upper pad
+// are zero before).  vd: the planes (distance lv) of v's digits, td: T's planes
+// (their pads zero), s0: the five limbs newton_start gave.
 //
 // The iterate for f limbs is w ~ B^(k+f)/v, the top of the final one: w[F - f,
 // F].  A step to f' <= 2f - 3 limbs takes the middle columns of v w as the
@@ -527,16 +584,17 @@ MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint32_t *w,
                    uint32_t *xw)
 {
-    const int F = dp + 2, l = lane(), g = quad_limb();
+    const int F = dp + 2, l = lane_at(k), g = quad_limb(l);
     if (l == 0) {
 #pragma unroll
         for (int j = 0; j < 5; j++) w[F - 4 + j] = s0[j];
     }
+    const Limb4 none{0u, 0u, 0u, 0u};
     int f = 4;
     bool again = true;                           // the digits are to be made from the limbs
     for (;;) {
         wave_sync();
-        if (again) balance_rows(0, (f + 65) >> 6, f + 1, 0u, Span{w + F - f, 0, f + 1}, StoreRev{xw, f + 2});
+        if (again) balance_rows(l, 0, (f + 65) >> 6, f + 1, 0u, Span{w + F - f, 0, f + 1}, StoreRev{xw, f + 2});
         if (f == F) break;
         const uint32_t last = uniform(w[F - f]);
         int fn = F;                              // the next step of the schedule that ends at F
@@ -546,47 +604,42 @@ MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, i
         const int c0 = imax(0, sh - f - 2) & ~7, nx = k + 2 - s - c0;
         wave_sync();
         // -e: the two's complement of the columns [c0, c0 + nx) of v w (B^(k+f-s) lies above them), as digits
-        uint32_t z[4], b[4];
-        strip_limbs(strip_sums(operands(xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), Limb4{0u, 0u, 0u, 0u},
-                    0x80000000u, z);
+        uint32_t z[4];
+        strip_limbs<false>(l, strip_sums(operands(l, xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), none, z);
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-            b[j] = g + j < nx ? kBal : 0u;
-            z[j] = g + j < nx ? ~z[j] : 0u;
-        }
-        quad_add4(z, b, 1u);
-        store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nx ? z[0] ^ kBal : 0u, g + 1 < nx ? z[1] ^ kBal : 0u,
-               g + 2 < nx ? z[2] ^ kBal : 0u, g + 3 < nx ? z[3] ^ kBal : 0u);
+        for (int j = 0; j < 4; j++) z[j] = g + j < nx ? ~z[j] : 0u;
+        quad_balance(z, 1u);
+        store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nx ? z[0] : 0u, g + 1 < nx ? z[1] : 0u,
+               g + 2 < nx ? z[2] : 0u, g + 3 < nx ? z[3] : 0u);
         wave_sync();
         // the new limbs: columns [shc, shc + m) of w (-e), and the old last limb at column shc + m
         const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f, i0 = cB + g - shc, at = shc + m - cB;
         Limb4 add{i0 == m ? last : 0u, i0 + 1 == m ? last : 0u, i0 + 2 == m ? last : 0u, i0 + 3 == m ? last : 0u};
-        strip_limbs(strip_sums(operands(xw, f + 2, td, kLyT, nx), cB >> 3), add, 0x80000000u, z);
+        strip_limbs<true>(l, strip_sums(operands(l, xw, f + 2, td, kLyT, nx), cB >> 3), add, z);
         const int over = (int)quad_get(z, at + 1);
+        const uint32_t nl = quad_get(z, at);                 // the old last limb, moved
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const bool in = (unsigned)(i0 + j) <= (unsigned)m;
             if (in) w[F - fn + i0 + j] = z[j];
-            b[j] = in ? kBal : 0u;
             z[j] = in ? z[j] : 0u;
         }
-        quad_add4(z, b, 0u);
-        const uint32_t up = quad_get(z, at + 1);             // the balancing carry out of the old last limb
-        again = over != 0 || up != (last >= 0u - kBal ? 1u : 0u);
+        const bool odd = quad_balance(z, 0u);                // (a limb that passes its carry on: look at all)
+        again = odd || over != 0 || (nl > kBalTop) != (last > kBalTop);
         if (again) {
-            add_small(w + F - f + 1, f, over);
+            add_small(l, w + F - f + 1, f, over);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; j++)
-                if ((unsigned)(i0 + j) <= (unsigned)m) xw[fn + 1 - i0 - j] = bswap(z[j] ^ kBal);
+                if ((unsigned)(i0 + j) <= (unsigned)m) xw[fn + 1 - i0 - j] = bswap(z[j]);
         }
         f = fn;
     }
 }
 
 // limbs of a dividend: an array (wave_prec reads it), or B^e
-MP_DEV int top_limb(const Span &u, int n) { return wave_prec(u.p, n); }
-MP_DEV int top_limb(const PowB &u, int) { return u.e + 1; }
+MP_DEV int top_limb(int l, const Span &u, int n) { return wave_prec(l, u.p, n); }
+MP_DEV int top_limb(int, const PowB &u, int) { return u.e + 1; }
 
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
 // U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
@@ -600,11 +653,11 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     const BodyPlan pl = plan_body(nu, nv);
     uint32_t *Vd = lds + pl.offV, *Td = lds + pl.offT, *XW = lds + pl.offX, *XQ = lds + pl.offQ;
     uint32_t *R = lds + pl.offR;
-    const int w = wave_index(), t = tid<T>(), nr = r ? nv : 0;
+    const int w = wave_index(), l0 = lane_at(nu), t = w * kLanes + l0, nr = r ? nv : 0;
     MP_RSTAMP(14);
     MP_STAMP(0);
     // precisions (every wave finds them by itself), and the cases that need no division
-    int h = top_limb(U, nu), k = wave_prec(v, nv) - 1;
+    int h = top_limb(l0, U, nu), k = wave_prec(l0, v, nv) - 1;
     if (k < 0 || h <= k) {                            // v = 0, or u < v: (0, u)
         for (int i = t; i < nq; i += T) q[i] = 0u;
         for (int i = t; i < nr; i += T) r[i] = k >= 0 && i < h ? U(i) : 0u;
@@ -612,7 +665,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         return;
     }
     const int d = h - k;
-    if (uniform(v[k]) == 1u && wave_prec(v, k) == 0) {   // v = B^k: q = u >> k, r the limbs below
+    if (uniform(v[k]) == 1u && wave_prec(l0, v, k) == 0) {   // v = B^k: q = u >> k, r the limbs below
         const bool ok = d <= nq;                         // (limb h - 1 is not zero)
         for (int i = t; i < nq; i += T) q[i] = ok && i < d ? U(i + k) : 0u;
         for (int i = t; i < nr; i += T) r[i] = ok && i < k ? U(i) : 0u;
@@ -639,10 +692,10 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * kLyT;
             lds[at - kPadWords + j] = 0u;
         }
-        for (int i = pl.offX - kXPad + t; i < pl.offW; i += T) lds[i] = 0u;
+        for (int i = pl.offX - kXLow + t; i < pl.offW; i += T) lds[i] = 0u;
         const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 1) / W;
         const int r0 = w * per, r1 = imin(rows, r0 + per);
-        if (r0 < r1) balance_rows(r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
+        if (r0 < r1) balance_rows(l0, r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
     }
     bar<T>();
     MP_STAMP(9);
@@ -676,25 +729,22 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         const int op = o;
         o = (nb - 1 - i) * bi;
         const int b = op - o, nt = b + 3;             // limbs of this block, of R_top
+        const int l = lane_at(i);
         if (w == 0) {
-            const int l = lane(), g = quad_limb();
-            uint32_t z[4], y[4];
+            const int g = quad_limb(l);
+            uint32_t z[4];
             // R complete; R_top's digits
-            if (i) strip_carries(ctl, R + op, n2, base2, bs2);
+            if (i) strip_carries(l, ctl, R + op, n2, base2, bs2);
             const uint32_t *src = R + o + k - 1 + g;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                z[j] = g + j < nt ? src[j] : 0u;
-                y[j] = g + j < nt ? kBal : 0u;
-            }
-            quad_add4(z, y, 0u);
-            store4(Td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] ^ kBal : 0u, g + 1 < nt ? z[1] ^ kBal : 0u,
-                   g + 2 < nt ? z[2] ^ kBal : 0u, g + 3 < nt ? z[3] ^ kBal : 0u);
+            for (int j = 0; j < 4; j++) z[j] = g + j < nt ? src[j] : 0u;
+            quad_balance(z, 0u);
+            store4(Td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] : 0u, g + 1 < nt ? z[1] : 0u,
+                   g + 2 < nt ? z[2] : 0u, g + 3 < nt ? z[3] : 0u);
             wave_sync();
             MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
             // q_i = R_top W / B^(dp+3), formed from column dp + 1 up: limb j of q_i is column dp + 3 + j
-            strip_limbs(strip_sums(operands(XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u},
-                        0x80000000u, z);
+            strip_limbs<false>(l, strip_sums(operands(l, XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u}, z);
             // to the quotient; the reversed digits of -q_i (limb b is its sign)
             uint32_t *Q = R + k + 2 + o;
             const int s = (int)quad_get(z, b + 2);
@@ -702,30 +752,29 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             for (int j = 0; j < 4; j++) {
                 const int e = g + j - 2;              // limb of q_i
                 if ((unsigned)e < (unsigned)b) Q[e] = z[j];
-                y[j] = (unsigned)e <= (unsigned)b ? kBal : 0u;
                 z[j] = e <= b ? (e < 0 ? 0xFFFFFFFFu : ~z[j]) : 0u;   // (the two columns below pass the +1 on)
             }
-            quad_add4(z, y, 1u);
+            quad_balance(z, 1u);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 const int e = g + j - 2;
-                if ((unsigned)e <= (unsigned)b) XQ[b - e] = bswap(z[j] ^ kBal);
+                if ((unsigned)e <= (unsigned)b) XQ[b - e] = bswap(z[j]);
             }
             if (l < kXPad) XQ[b + 1 + l] = 0u;
             if (i == 0) {
                 if (l == 0) Q[b] = (uint32_t)s;
             } else {
-                add_small(Q + b, d + 1 - op, s);
+                add_small(l, Q + b, d + 1 - op, s);
             }
         }
         bar<T>();
         MP_STAMP(17 + 3 * (i % 5));
         // R -= v q_i
-        strips<T>(ctl, operands(XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
+        strips<T>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
         bar<T>();
         MP_STAMP(18 + 3 * (i % 5));
     }
-    if (w == 0) strip_carries(ctl, R, n2, base2, bs2);
+    if (w == 0) strip_carries(lane_at(nb), ctl, R, n2, base2, bs2);
     bar<T>();
     MP_STAMP(6);
     // corrections: R is a signed (k + 2)-limb number in (-1.1 v, 2.1 v)
@@ -736,7 +785,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         if (!ge) {                                    // compare with v from the top, 64 limbs at a time
             ge = true;                                // (equal: R = v)
             for (int c = k; c >= 0; c -= kLanes) {
-                const int j = c - (kLanes - 1) + lane();
+                const int j = c - (kLanes - 1) + lane_at(it);
                 const uint32_t a = j >= 0 ? Ra[j] : 0u, x = j >= 0 ? Vv(j) : 0u;
                 const uint64_t ne = ballot(a != x), gt = ballot(a > x);
                 if (ne) {
@@ -752,7 +801,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         }
         const int rows = (n2 + 63) >> 6, per = (rows + W - 1) / W;
         const int r0 = w * per, r1 = imin(rows, r0 + per);
-        if (r0 < r1) addsub_rows(r0, r1, n2, !neg, Span{Ra, 0, n2}, Vv, Rb);
+        if (r0 < r1) addsub_rows(lane_at(it), r0, r1, n2, !neg, Span{Ra, 0, n2}, Vv, Rb);
         delta += neg ? -1 : 1;
         bar<T>();
         uint32_t *x = Ra;
@@ -760,7 +809,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         Rb = x;
     }
     if (good && delta) {
-        if (w == 0) add_small(Q, d + 1, delta);
+        if (w == 0) add_small(lane_at(delta), Q, d + 1, delta);
         bar<T>();
     }
     MP_STAMP(7);

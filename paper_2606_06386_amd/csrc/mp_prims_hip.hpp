@@ -60,6 +60,14 @@ namespace mp {
 constexpr int kLanes = 64;  // CDNA wavefront width
 
 MP_DEV int lane() { return (int)(threadIdx.x & (kLanes - 1)); }
+// the lane, computed anew where the scalar `at` changes: what follows from it is
+// not kept in registers across a loop in which `at` does
+MP_DEV int lane_at(int at)
+{
+    int l;
+    asm("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l) : "s"(at));
+    return l;
+}
 // index of the calling thread among the T threads working on one instance:
 // the workgroup's thread index, or the lane when a single wave owns the
 // instance (that wave may be any wave of its workgroup)
@@ -171,6 +179,46 @@ MP_DEV void mac4x(uint64_t (&lo)[4], uint32_t (&hi)[4], uint32_t a0, uint32_t b0
         : "v"(a0), "v"(b0), "v"(a1), "v"(b1), "v"(a2), "v"(b2), "v"(a3), "v"(b3));
 }
 
+// (hi:lo) += c (sign-extended) in every lane; returns the lanes whose addition
+// carried out of the 64 bits (of the unsigned value: for negative c, those that
+// did not borrow).  A VALU carry needs two wait states before a VALU reads it.
+MP_DEV uint64_t add64_carry(uint32_t &lo, uint32_t &hi, int c)
+{
+    uint64_t m;
+    asm("v_add_co_u32_e64 %0, %2, %0, %3\n\t"
+        "s_nop 1\n\t"
+        "v_addc_co_u32_e64 %1, %2, %1, %4, %2"
+        : "+&v"(lo), "+&v"(hi), "=&s"(m)
+        : "v"(c), "v"(c >> 31));
+    return m;
+}
+
+// z[j] = z[j] + a + carry from z[j-1] > t for j = 1..3 (a limb above t passes a
+// carry up); returns the lanes whose z[3] does.  z[0] is left to the caller.
+MP_DEV uint64_t add_above(uint32_t (&z)[4], uint32_t a, uint32_t t)
+{
+    uint64_t g0, g1, g2, g3, co;
+    asm("v_cmp_lt_u32_e64 %3, %9, %8\n\t"
+        "v_cmp_lt_u32_e64 %4, %9, %0\n\t"
+        "v_cmp_lt_u32_e64 %5, %9, %1\n\t"
+        "v_cmp_lt_u32_e64 %6, %9, %2\n\t"
+        "v_addc_co_u32_e64 %0, %7, %0, %10, %3\n\t"
+        "v_addc_co_u32_e64 %1, %7, %1, %10, %4\n\t"
+        "v_addc_co_u32_e64 %2, %7, %2, %10, %5"
+        : "+&v"(z[1]), "+&v"(z[2]), "+&v"(z[3]), "=&s"(g0), "=&s"(g1), "=&s"(g2), "=&s"(g3), "=&s"(co)
+        : "v"(z[0]), "v"(t), "v"(a));
+    return g3;
+}
+
+// x + a + (bit of m for the lane), m from the scalar unit
+MP_DEV uint32_t add_mask(uint32_t x, uint32_t a, uint64_t m)
+{
+    uint32_t r;
+    uint64_t co;
+    asm("v_addc_co_u32_e64 %0, %1, %2, %3, %4" : "=v"(r), "=&s"(co) : "v"(x), "v"(a), "s"(m));
+    return r;
+}
+
 // bytes [sel, sel + 4) of the 8-byte value hi:lo (sel in 0..3)
 MP_DEV uint32_t alignbyte(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_alignbyte(hi, lo, sel); }
 
@@ -211,6 +259,26 @@ MP_DEV Limb4 load4(const uint32_t *p)
 MP_DEV void store4(uint32_t *p, uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {
     *reinterpret_cast<uint4 *>(__builtin_assume_aligned(p, 16)) = make_uint4(a, b, c, d);
+}
+
+// LDS by byte address: the products' loops step plain 32-bit addresses and
+// reach a step's operands by constant offsets
+typedef __attribute__((address_space(3))) const uint32_t LdsWord;
+typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const Vec4 LdsQuad;
+
+MP_DEV uint32_t lds_address(const uint32_t *p) { return (uint32_t)(uintptr_t)(LdsWord *)p; }
+MP_DEV uint32_t lds_word(uint32_t a, int w) { return ((LdsWord *)(uintptr_t)a)[w]; }
+MP_DEV Limb4 lds_quad(uint32_t a, int q)
+{
+    const Vec4 v = ((LdsQuad *)(uintptr_t)a)[q];
+    return Limb4{v.x, v.y, v.z, v.w};
+}
+// the same value, whose origin the compiler does not see
+MP_DEV uint32_t opaque(uint32_t x)
+{
+    asm("" : "+v"(x));
+    return x;
 }
 
 }  // namespace mp
