@@ -458,8 +458,8 @@ def phase_trace(args):
 
 def phase_trace_mul(args, na=2048, nb=2048, batch=4096):
     """Per-phase cycle breakdown of one mp_mul_batch launch (the trace build):
-    clearing, digit conversion, the first wave's matrix-core strips, strip
-    carries, the copy out.  Prints one JSON line."""
+    digit conversion, the first wave's two groups of matrix-core strips,
+    limbs, store.  Prints one JSON line."""
     import ctypes
     import torch
     from paper_2606_06386_amd import build as hb
@@ -483,13 +483,13 @@ def phase_trace_mul(args, na=2048, nb=2048, batch=4096):
     st = np.zeros((batch, 32), dtype=np.uint64)
     assert L.mp_trace_read_mul(st.ctypes.data, batch) == 0
     st = st.astype(np.float64)
-    rows = st[(st[:, [0, 1, 2, 3, 4, 5, 10]] > 0).all(axis=1)]
-    ph = {"clear": (0, 1), "digit_conversion": (1, 2), "strips_first_wave": (2, 10), "strips_wait_and_carries": (10, 3),
-          "sync": (3, 4), "copy_out": (4, 5)}
+    rows = st[(st[:, [0, 1, 2, 3, 4, 5]] > 0).all(axis=1)]
+    ph = {"digit_conversion": (0, 1), "first_four_strips": (1, 2), "second_four_strips": (2, 3),
+          "limbs_and_wait": (3, 4), "store": (4, 5)}
     res = {k: float(np.mean(rows[:, b_] - rows[:, a_])) for k, (a_, b_) in ph.items()}
     total = float(np.mean(rows[:, 5] - rows[:, 0]))
     clk = clock_stats(st[:, 0], st[:, 5], st[:, 6], st[:, 7], e0.elapsed_time(e1))
-    print(json.dumps({"phase_trace": "mul %dx%d batch %d" % (na, nb, batch), "kernel": "k_mul<256>",
+    print(json.dumps({"phase_trace": "mul %dx%d batch %d" % (na, nb, batch), "kernel": "k_mul<128, 4, 2>",
                       "workgroups": len(rows), "total_cycles": total, "cycles": res,
                       "share": {k: v / total for k, v in res.items()}, "clock": clk}), flush=True)
 

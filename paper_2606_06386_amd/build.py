@@ -19,14 +19,14 @@ TRACE_LIB = os.path.join(HERE, "libmpdiv_trace.so")
 # instruction issue-rate probe (calibrates the integer-multiply roofline)
 PROBE_LIB = os.path.join(HERE, "libmpprobe.so")
 PROBE_SOURCES = [os.path.join(CSRC, "probe_rates.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("mp_prims_hip.hpp", "mp_core.hpp", "mp_mul.hpp", "mp_block.hpp", "launch.hpp")]
+HEADERS = [os.path.join(CSRC, f) for f in ("mp_prims_hip.hpp", "mp_core.hpp", "mp_strip.hpp", "mp_mul.hpp", "mp_block.hpp", "launch.hpp")]
 
 # (object name, source, defines): one object per kernel family x workgroup size
 FAMILIES = {0: "mul", 1: "shinv", 2: "divrem", 3: "ragged"}
 THREADS = (256, 512, 1024)
 UNITS = [("api", "mpdiv.hip", [])] + [
     (f"k_{name}_{t}", "kernels.hip", [f"-DMP_KFAMILY={fam}", f"-DMP_KT={t}"])
-    for fam, name in FAMILIES.items() for t in THREADS]
+    for fam, name in FAMILIES.items() for t in ((128,) if fam == 0 else ()) + THREADS]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -13,6 +13,7 @@
 // of a launcher, so the translation units compile in parallel.
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
+#include "mp_strip.hpp"
 #include "mp_mul.hpp"
 #include "mp_block.hpp"
 
@@ -26,6 +27,9 @@ namespace mp {
 // limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
 // 112 us.
 #define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
+// products: four waves per SIMD (four accumulators and a window of four fragments per wave)
+#define MP_MUL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
+
 // Workspace of a ragged batch (int32): [0, 4) instances per class, [4, 8)
 // queue heads, then one list of instance indices per class, each `count` long.
 constexpr int kClasses = 4;
@@ -37,13 +41,21 @@ MP_DEV int64_t uniform64(int64_t x)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-template <int T>
-__global__ __launch_bounds__(T) void k_mul(const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
-                                           int mfma_min)
+template <int T, int G, int K>
+__global__ __launch_bounds__(T) MP_MUL_OCCUPANCY void k_mul(const uint32_t *a, int na, const uint32_t *b, int nb,
+                                                            uint32_t *c)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
-    mul_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb), mfma_min);
+    mul_instance<T, G, K>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb));
+}
+
+template <int T>
+__global__ __launch_bounds__(T) void k_mul_valu(const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c)
+{
+    extern __shared__ __align__(16) uint32_t lds[];
+    const size_t j = blockIdx.x;
+    mul_valu_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb));
 }
 
 template <int T>
@@ -96,11 +108,17 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, c
 }
 
 template <int T>
-hipError_t launch_mul(int grid, size_t lds, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb,
-                      uint32_t *c, int mfma_min)
+hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
+                      MulKind kind)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(k_mul<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mul<T>, dim3(grid), dim3(T), lds, st, a, na, b, nb, c, mfma_min);
+    auto *fn = kind == MulKind::kStrip   ? k_mul<T, 1, 1>
+               : kind == MulKind::kPair  ? k_mul<T, 2, 1>
+               : kind == MulKind::kQuad  ? k_mul<T, 4, 1>
+               : kind == MulKind::kQuads ? k_mul<T, 4, 2>
+                                         : k_mul_valu<T>;
+    const size_t lds = (size_t)4 * (kind == MulKind::kValu ? mul_valu_lds_words(na, nb) : plan_mul(na, nb).total);
+    if (!lds_attr(reinterpret_cast<const void *>(fn), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(T), lds, st, a, na, b, nb, c);
     return hipGetLastError();
 }
 
@@ -135,8 +153,8 @@ hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *u
 
 #if defined(MP_KFAMILY) && defined(MP_KT)
 #if MP_KFAMILY == 0
-template hipError_t launch_mul<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
-                                      uint32_t *, int);
+template hipError_t launch_mul<MP_KT>(int, hipStream_t, const uint32_t *, int, const uint32_t *, int, uint32_t *,
+                                      MulKind);
 #elif MP_KFAMILY == 1
 template hipError_t launch_shinv<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
                                         int32_t *, int);
@@ -152,7 +170,7 @@ template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_
 
 }  // namespace mp
 
-#if defined(MP_PHASE_TRACE) && MP_KFAMILY == 0 && MP_KT == 256
+#if defined(MP_PHASE_TRACE) && MP_KFAMILY == 0 && MP_KT == 128
 // copies the stamps of the first `blocks` product workgroups (32 per workgroup) to host memory
 extern "C" int mp_trace_read_mul(uint64_t *dst, int blocks)
 {

@@ -14,9 +14,13 @@ namespace mp {
 // (cached: no runtime call once the limit is high enough)
 bool lds_attr(const void *kernel, size_t bytes);
 
+// Products on the matrix cores, a wave taking one strip of 256 columns, two
+// adjacent ones, four, or twice four; or on the vector ALU
+enum class MulKind { kStrip, kPair, kQuad, kQuads, kValu };
+
 template <int T>
-hipError_t launch_mul(int grid, size_t lds, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb,
-                      uint32_t *c, int mfma_min);
+hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
+                      MulKind kind);
 
 // division kernels; bmax: longest block of quotient limbs
 template <int T>

@@ -3,6 +3,7 @@
 // kernels themselves are in kernels.hip.
 #include "mp_prims_hip.hpp"
 #include "mp_core.hpp"
+#include "mp_strip.hpp"
 #include "mp_mul.hpp"
 #include "mp_block.hpp"
 #include "launch.hpp"
@@ -85,6 +86,39 @@ int threads_for(int width)
     return width <= 2048 ? 256 : width <= 4096 ? 512 : 1024;
 }
 
+// How a batch of products splits its strips of 256 columns over waves.  Few
+// products leave compute units idle: the more waves share one the better, down
+// to one strip each.  Many are bound by LDS reads (18 cycles per matrix-core
+// product where one strip reads its own fragments, 9 for a pair of strips, 4.5
+// for four), and then by uneven waves: four strips at either end of a product
+// have a third of the work of four in the middle, which two groups per wave
+// (w and w + W) even out, at the price of fewer waves.  us for lo x hi limbs,
+// batch: strip / pair / four / two fours per wave
+//   1024 x 1024:  256: 10 / 16 / 23 / 42;   1024: 27 / 29 / 28 / 44;   4096: 98 / 95 / 85 / 110
+//   2048 x 2048:  128: 18 / 23 / 34 / 52;    512: 43 / 40 / 46 / 67;   4096: 327 / 284 / 276 / 264
+//   4096 x 4096:  128: 59 / 46 / 58 / 74;    512: 154 / 131 / 117 / 128; 1024: 304 / 259 / 229 / 233
+//   8192 x 8192:  128: 218 / - / 143 / 167;  256: 294 / - / 210 / 227
+//   8192 x 2000:  256: 78 / - / 62 / 66;    1024: 298 / - / 242 / 221
+//   2048 x 300:   256: 10 / - / 11 / 14;    4096: 65 / - / 60 / 63
+// (A short operand below 1016 limbs leaves four strips no window of fragments:
+// they share single ones, evenly.)
+struct MulShape {
+    int threads;
+    mp::MulKind kind;
+};
+
+MulShape mul_shape(int lo, int nc, int64_t batch)
+{
+    const int ns = (nc + mp::kStrip - 1) / mp::kStrip;
+    const int64_t strips = batch * ns;
+    if (ns <= 6 || (ns <= 16 && strips <= 6144)) return {ns <= 4 ? 256 : ns <= 8 ? 512 : 1024, mp::MulKind::kStrip};
+    if (ns > 8 && ns <= 32 && lo >= 1016 && strips <= (ns <= 16 ? 16384 : 8192))
+        return {ns <= 16 ? 512 : 1024, mp::MulKind::kPair};
+    if (lo >= 1016 && ((ns > 8 && ns <= 16) || (ns > 32 && strips > 16384)))
+        return {ns <= 16 ? 128 : 512, mp::MulKind::kQuads};
+    return {ns <= 8 ? 128 : ns <= 16 ? 256 : ns <= 32 ? 512 : 1024, mp::MulKind::kQuad};
+}
+
 // the current device is gfx950 (checked once per device)
 bool device_ok()
 {
@@ -131,6 +165,17 @@ bool mp::lds_attr(const void *fn, size_t bytes)
 namespace {
 
 mp_status_t status_of(hipError_t e) { return e == hipSuccess ? MP_OK : MP_ERR_LAUNCH; }
+
+mp_status_t launch_mul_threads(int T, int grid, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb,
+                               uint32_t *c, mp::MulKind kind)
+{
+    switch (T) {
+    case 128: return status_of(mp::launch_mul<128>(grid, st, a, na, b, nb, c, kind));
+    case 256: return status_of(mp::launch_mul<256>(grid, st, a, na, b, nb, c, kind));
+    case 512: return status_of(mp::launch_mul<512>(grid, st, a, na, b, nb, c, kind));
+    default: return status_of(mp::launch_mul<1024>(grid, st, a, na, b, nb, c, kind));
+    }
+}
 
 // compute units of the current device (queried once per device)
 int device_cus()
@@ -270,7 +315,8 @@ int64_t mp_lds_bytes(int32_t op, int32_t n1, int32_t n2)
 {
     if (n1 <= 0 || n2 <= 0 || n1 > kMaxLimbs || n2 > kMaxLimbs) return -1;
     switch (op) {
-    case MP_OP_MUL: return (int64_t)4 * mp::mul_lds_words(n1, n2);
+    case MP_OP_MUL: return (int64_t)4 * (mp::hmin(n1, n2) < g_mfma_min.load() ? mp::mul_valu_lds_words(n1, n2)
+                                                                        : mp::plan_mul(n1, n2).total);
     case MP_OP_DIVREM: return (int64_t)body_bytes(n1, n2);
     case MP_OP_SHINV: return (int64_t)body_bytes(n2 + 1, n1);
     }
@@ -284,16 +330,12 @@ mp_status_t mp_mul_batch(const uint32_t *a, int32_t na, const uint32_t *b, int32
     if (na > kMaxLimbs || nb > kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
-    const int words = mp::mul_lds_words(na, nb);
-    if (words > kLdsWords) return MP_ERR_SIZE;
-    const size_t bytes = (size_t)words * 4;
     hipStream_t st = (hipStream_t)stream;
-    const int kn = g_mfma_min.load();
-    switch (threads_for((na + nb + 1) / 2)) {
-    case 256: return status_of(mp::launch_mul<256>(batch, bytes, st, a, na, b, nb, c, kn));
-    case 512: return status_of(mp::launch_mul<512>(batch, bytes, st, a, na, b, nb, c, kn));
-    default: return status_of(mp::launch_mul<1024>(batch, bytes, st, a, na, b, nb, c, kn));
-    }
+    const int lo = na < nb ? na : nb;
+    if (lo < g_mfma_min.load())
+        return launch_mul_threads(threads_for((na + nb + 1) / 2), batch, st, a, na, b, nb, c, mp::MulKind::kValu);
+    const MulShape m = mul_shape(lo, na + nb, batch);
+    return launch_mul_threads(m.threads, batch, st, a, na, b, nb, c, m.kind);
 }
 
 mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w, int32_t nw,
