@@ -427,10 +427,10 @@ def phase_trace(args):
     e1.record()
     torch.cuda.synchronize()
     L = binding.lib()
-    L.mp_trace_read_divrem.argtypes = [ctypes.c_void_p, ctypes.c_int]
-    L.mp_trace_read_divrem.restype = ctypes.c_int
+    L.mp_trace_read_divrem_256.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    L.mp_trace_read_divrem_256.restype = ctypes.c_int
     st = np.zeros((batch, 32), dtype=np.uint64)
-    assert L.mp_trace_read_divrem(st.ctypes.data, batch) == 0
+    assert L.mp_trace_read_divrem_256(st.ctypes.data, batch) == 0
     st = st.astype(np.float64)
     order = [0, 1, 9, 2, 6, 7, 8]                    # stamps of every instance that is divided in blocks
     full = (st[:, order] > 0).all(axis=1) & (np.diff(st[:, order], axis=1) >= 0).all(axis=1)

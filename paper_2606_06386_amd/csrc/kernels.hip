@@ -26,7 +26,7 @@ namespace mp {
 // of a 2^16-bit instance, 20 KB, also allows.  4096 divisions of 2048 by 1024
 // limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
 // 112 us.
-#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
+#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(FAST ? 4 : 8, 8)))
 // products: four waves per SIMD (four accumulators and a window of four fragments per wave)
 #define MP_MUL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
 
@@ -58,18 +58,18 @@ __global__ __launch_bounds__(T) void k_mul_valu(const uint32_t *a, int na, const
     mul_valu_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb));
 }
 
-template <int T>
+template <int T, bool FAST>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_shinv(const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                                                           int32_t *status, int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *wj = w + j * nw;
-    divide_instance<T>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
+    divide_instance<T, FAST>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
                        bmax);
 }
 
-template <int T>
+template <int T, bool FAST>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, int nu, const uint32_t *v, int nv,
                                                            uint32_t *q, int nq, uint32_t *r, int32_t *status,
                                                            int bmax)
@@ -77,13 +77,13 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, in
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *qj = q + j * nq, *rj = r + j * nv;
-    divide_instance<T>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
+    divide_instance<T, FAST>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
                        bmax);
 }
 
 // persistent workgroups of one class: take the next instance of the class's
 // queue until it is empty
-template <int T>
+template <int T, bool FAST>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
                                                            const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
                                                            int32_t *status, int32_t *ws, int cls, int count, int bmax)
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, c
         const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off),
                       ro = uniform64(d.r_off);
         const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-        divide_instance<T>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j,
+        divide_instance<T, FAST>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j,
                            bmax);
     }
 }
@@ -122,31 +122,31 @@ hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const
     return hipGetLastError();
 }
 
-template <int T>
+template <int T, bool FAST>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                         int32_t *status, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(k_shinv<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_shinv<T>, dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, bmax);
+    if (!lds_attr(reinterpret_cast<const void *>(&k_shinv<T, FAST>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_shinv<T, FAST>), dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, bmax);
     return hipGetLastError();
 }
 
-template <int T>
+template <int T, bool FAST>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
                          uint32_t *q, int nq, uint32_t *r, int32_t *status, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(k_divrem<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_divrem<T>, dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, bmax);
+    if (!lds_attr(reinterpret_cast<const void *>(&k_divrem<T, FAST>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_divrem<T, FAST>), dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, bmax);
     return hipGetLastError();
 }
 
-template <int T>
+template <int T, bool FAST>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
                          int count, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(k_ragged<T>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ragged<T>, dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count,
+    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged<T, FAST>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_ragged<T, FAST>), dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count,
                        bmax);
     return hipGetLastError();
 }
@@ -156,13 +156,20 @@ hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *u
 template hipError_t launch_mul<MP_KT>(int, hipStream_t, const uint32_t *, int, const uint32_t *, int, uint32_t *,
                                       MulKind);
 #elif MP_KFAMILY == 1
-template hipError_t launch_shinv<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
+template hipError_t launch_shinv<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
+                                        int32_t *, int);
+template hipError_t launch_shinv<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
                                         int32_t *, int);
 #elif MP_KFAMILY == 2
-template hipError_t launch_divrem<MP_KT>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
+template hipError_t launch_divrem<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
+                                         uint32_t *, int, uint32_t *, int32_t *, int);
+template hipError_t launch_divrem<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
                                          uint32_t *, int, uint32_t *, int32_t *, int);
 #elif MP_KFAMILY == 3
-template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
+template hipError_t launch_ragged<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
+                                         const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
+                                         int);
+template hipError_t launch_ragged<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
                                          const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
                                          int);
 #endif
@@ -179,9 +186,11 @@ extern "C" int mp_trace_read_mul(uint64_t *dst, int blocks)
 }
 #endif
 
-#if defined(MP_PHASE_TRACE) && MP_KFAMILY == 2 && MP_KT == 256
+#if defined(MP_PHASE_TRACE) && MP_KFAMILY == 2
+#define MP_TRACE_NAME2(t) mp_trace_read_divrem_##t
+#define MP_TRACE_NAME(t) MP_TRACE_NAME2(t)
 // copies the stamps of the first `blocks` workgroups (32 per workgroup) to host memory
-extern "C" int mp_trace_read_divrem(uint64_t *dst, int blocks)
+extern "C" int MP_TRACE_NAME(MP_KT)(uint64_t *dst, int blocks)
 {
     return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(mp_trace_buf), (size_t)blocks * 32 * sizeof(uint64_t), 0,
                                     hipMemcpyDeviceToHost);

@@ -22,16 +22,17 @@ template <int T>
 hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
                       MulKind kind);
 
-// division kernels; bmax: longest block of quotient limbs
-template <int T>
+// Division kernels; bmax: longest block of quotient limbs.  FAST: built for four
+// waves per SIMD instead of eight, with products that keep more reads in flight.
+template <int T, bool FAST>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                         int32_t *status, int bmax);
 
-template <int T>
+template <int T, bool FAST>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
                          uint32_t *q, int nq, uint32_t *r, int32_t *status, int bmax);
 
-template <int T>
+template <int T, bool FAST>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
                          int count, int bmax);

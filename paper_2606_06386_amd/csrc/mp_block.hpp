@@ -124,26 +124,26 @@ MP_DEV void strip_out(int l, uint32_t *ctl, const MfmaAcc &acc, uint32_t *R, int
 // strip_carries adds it.  x has at most kBlockMax + 1 limbs, y at least ncols
 // digit limbs, and the strips end at ncols (rounded up to 8 limbs), so that
 // every strip but the lowest needs every diagonal of x: a wave takes two of
-// these at a time when it has more than one.  The lowest, partial strip goes to the
-// wave that has the fewest.  R is 16-byte aligned.
-template <int T>
+// these at a time, which share each fragment of x (a wave's step of one
+// diagonal is bound by its instructions, not by the matrix core: two products
+// take little longer than one).  FAST: one each as long as there are waves.
+// The lowest, partial strip comes last.  R is 16-byte aligned.
+template <int T, bool FAST>
 MP_DEV void strips(int l, uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
 {
     constexpr int W = T / kLanes;
     const int w = wave_index(), n = nstrips - 1, b = base >> 3;
-    int s = 1 + w;
-    for (; s + W <= n; s += 2 * W) {
-        MfmaAcc accA, accB;
-        strip_sums2(o, b + s * kStripBlks, b + (s + W) * kStripBlks, accA, accB);
-        strip_out(l, ctl, accA, R, ncols, base, s);
-        strip_out(l, ctl, accB, R, ncols, base, s + W);
-    }
-    bool low = w == n % W;
-    while (s <= n || low) {
-        const int i = s <= n ? s : 0;
-        if (s > n) low = false;
-        strip_out(l, ctl, strip_sums(o, b + i * kStripBlks), R, ncols, base, i);
-        s = n + 1;
+    const int step = FAST && n <= W ? 1 : 2, units = (n + step - 1) / step;
+    for (int u = w; u <= units; u += W) {          // (unit `units`: the lowest strip)
+        const int i = u < units ? 1 + u * step : 0;
+        if (step == 2 && u < units && i < n) {
+            MfmaAcc accA, accB;
+            strip_sums2(o, b + i * kStripBlks, b + (i + 1) * kStripBlks, accA, accB);
+            strip_out(l, ctl, accA, R, ncols, base, i);
+            strip_out(l, ctl, accB, R, ncols, base, i + 1);
+        } else {
+            strip_out(l, ctl, strip_sums<FAST>(o, b + i * kStripBlks), R, ncols, base, i);
+        }
     }
 }
 
@@ -180,13 +180,24 @@ struct Shifted {
     }
 };
 
-// number of significant limbs of x[0, n) (global memory), by one wave from the top
+// number of significant limbs of x[0, n) (global memory), by one wave from the
+// top: 64 limbs first (most numbers fill their row), then 1024 per step
 MP_DEV int wave_prec(int ln, const uint32_t *x, int n)
 {
-    for (int top = n; top > 0; top -= kLanes) {
-        const int i = top - kLanes + ln;
-        const uint64_t m = ballot(i >= 0 && x[i] != 0u);
-        if (m) return top - kLanes + 64 - __builtin_clzll(m);
+    uint64_t m = ballot(n - kLanes + ln >= 0 && x[n - kLanes + ln] != 0u);
+    if (m) return n - __builtin_clzll(m);
+    for (int top = n - kLanes; top > 0; top -= 16 * kLanes) {
+        uint32_t v[16];
+#pragma unroll
+        for (int j = 0; j < 16; j++) {
+            const int i = top - (j + 1) * kLanes + ln;
+            v[j] = i >= 0 ? x[i] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; j++) {
+            m = ballot(v[j] != 0u);
+            if (m) return top - j * kLanes - __builtin_clzll(m);
+        }
     }
     return 0;
 }
@@ -250,6 +261,7 @@ MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 // few units) nor passes another balancing carry up than before, the digits
 // above it stay as they are and only the new limbs' are written; otherwise all
 // digits are made again from the limbs.
+template <bool FAST>
 MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint32_t *w,
                    uint32_t *xw)
 {
@@ -274,7 +286,7 @@ MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, i
         wave_sync();
         // -e: the two's complement of the columns [c0, c0 + nx) of v w (B^(k+f-s) lies above them), as digits
         uint32_t z[4];
-        strip_limbs<false>(l, strip_sums(operands(l, xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), none, z);
+        strip_limbs<false>(l, strip_sums<FAST>(operands(l, xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), none, z);
 #pragma unroll
         for (int j = 0; j < 4; j++) z[j] = g + j < nx ? ~z[j] : 0u;
         quad_balance(z, 1u);
@@ -284,7 +296,7 @@ MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, i
         // the new limbs: columns [shc, shc + m) of w (-e), and the old last limb at column shc + m
         const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f, i0 = cB + g - shc, at = shc + m - cB;
         Limb4 add{i0 == m ? last : 0u, i0 + 1 == m ? last : 0u, i0 + 2 == m ? last : 0u, i0 + 3 == m ? last : 0u};
-        strip_limbs<true>(l, strip_sums(operands(l, xw, f + 2, td, kLyT, nx), cB >> 3), add, z);
+        strip_limbs<true>(l, strip_sums<FAST>(operands(l, xw, f + 2, td, kLyT, nx), cB >> 3), add, z);
         const int over = (int)quad_get(z, at + 1);
         const uint32_t nl = quad_get(z, at);                 // the old last limb, moved
 #pragma unroll
@@ -312,8 +324,8 @@ MP_DEV int top_limb(int, const PowB &u, int) { return u.e + 1; }
 
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
 // U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
-// block.
-template <int T, class FU>
+// block; FAST: see strip_sums.
+template <int T, bool FAST, class FU>
 MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *v, int nv, uint32_t *q, int nq,
                             uint32_t *r, int32_t *status, int bmax)
 {
@@ -374,7 +386,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
 #pragma unroll
         for (int j = 0; j < 5; j++) a[j] = k - 4 + j >= 0 ? Vv(k - 4 + j) : 0u;
         newton_start(a, s);
-        newton(s, k, dp, Vd, pl.lyV, Td, lds + pl.offW, XW);
+        newton<FAST>(s, k, dp, Vd, pl.lyV, Td, lds + pl.offW, XW);
     } else {
         constexpr int S = T - kLanes;
         for (int i0 = t - kLanes; i0 < pl.capR; i0 += 8 * S) {
@@ -413,7 +425,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             wave_sync();
             MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
             // q_i = R_top W / B^(dp+3), formed from column dp + 1 up: limb j of q_i is column dp + 3 + j
-            strip_limbs<false>(l, strip_sums(operands(l, XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u}, z);
+            strip_limbs<false>(l, strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u}, z);
             // to the quotient; the reversed digits of -q_i (limb b is its sign)
             uint32_t *Q = R + k + 2 + o;
             const int s = (int)quad_get(z, b + 2);
@@ -439,7 +451,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         bar<T>();
         MP_STAMP(17 + 3 * (i % 5));
         // R -= v q_i
-        strips<T>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
+        strips<T, FAST>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
         bar<T>();
         MP_STAMP(18 + 3 * (i % 5));
     }

@@ -231,28 +231,64 @@ MP_DEV XRaw xraw_at(uint32_t a, int w)
     return XRaw{lds_word(a, w), lds_word(a, w + 1), lds_word(a, w + 2), lds_word(a, w + 3), lds_word(a, w + 4)};
 }
 
-// the accumulator of the strip whose first block is S0.  Steps of kDiags
+// the operands of N diagonals, the last at the addresses x and y
+template <int N>
+struct Diagonals {
+    XRaw r[N];
+    Limb4 y[N];
+    MP_DEV void load(uint32_t xa, uint32_t ya)
+    {
+#pragma unroll
+        for (int j = 0; j < N; j++) {
+            r[j] = xraw_at(xa, 8 * (N - 1 - j));
+            y[j] = lds_quad(ya, N - 1 - j);
+        }
+    }
+    MP_DEV void add(MfmaAcc &acc, uint32_t sft) const
+    {
+#pragma unroll
+        for (int j = 0; j < N; j++) acc = mfma_x(acc, xfrag(r[j], sft), y[j]);
+    }
+};
+
+// The accumulator of the strip whose first block is S0.  Steps of kDiags
 // diagonals; the last may pass the end: it reads zeros there (of the short
-// digits, or blocks below the long ones').
+// digits, or blocks below the long ones').  FAST, for kernels with registers to
+// spare and few waves per SIMD to hide LDS reads behind: the next step's
+// operands in flight.
+template <bool FAST>
 MP_DEV MfmaAcc strip_sums(const Operands &o, int S0)
 {
+    constexpr int D = kDiags;
     MfmaAcc acc = mfma_zero();
     const int dlo = imax(0, S0 - o.nyblk + 1), dhi = imin(o.dmax, S0 + 31);
+    int n = uniform(dhi - dlo + D) / D;          // steps
+    if (n <= 0) return acc;
     // (addresses of a step's last diagonal: the others lie at positive offsets)
-    uint32_t x = opaque(o.x - 32 * (dlo + kDiags - 1)), y = opaque(o.y + 16 * (S0 - dlo - (kDiags - 1)));
-    for (int n = uniform(dhi - dlo + 1); n > 0; n -= kDiags) {
-        XRaw r[kDiags];
-        Limb4 yv[kDiags];
-#pragma unroll
-        for (int j = 0; j < kDiags; j++) {
-            r[j] = xraw_at(x, 8 * (kDiags - 1 - j));
-            yv[j] = lds_quad(y, kDiags - 1 - j);
+    uint32_t x = opaque(o.x - 32 * (dlo + D - 1)), y = opaque(o.y + 16 * (S0 - dlo - (D - 1)));
+    if constexpr (FAST) {
+        Diagonals<D> a, b;
+        a.load(x, y);
+        for (; n >= 2; n -= 2) {                 // (the reads past the last step are not used)
+            b.load(x - 32 * D, y - 16 * D);
+            a.add(acc, o.sft);
+            sched_loads_first();
+            x -= 64 * D;
+            y -= 32 * D;
+            a.load(x, y);
+            b.add(acc, o.sft);
+            sched_loads_first();
         }
-#pragma unroll
-        for (int j = 0; j < kDiags; j++) acc = mfma_x(acc, xfrag(r[j], o.sft), yv[j]);
-        sched_loads_first();
-        x -= 32 * kDiags;
-        y -= 16 * kDiags;
+        if (n) a.add(acc, o.sft);
+    } else {
+        for (; n > 0; n--) {
+            Diagonals<D> a;
+            a.load(x, y);
+            a.add(acc, o.sft);
+            sched_loads_first();
+            x -= 32 * D;
+            y -= 16 * D;
+        }
     }
     return acc;
 }

@@ -13,6 +13,7 @@
 #include <atomic>
 #include <mutex>
 #include <string.h>
+#include <stdlib.h>
 
 namespace {
 
@@ -191,6 +192,15 @@ int device_cus()
     return cus[dev];
 }
 
+// whether `batch` workgroups of T threads all fit the device at four waves per
+// SIMD: then the kernels built for that finish sooner
+bool fast_fits(int T, int64_t batch)
+{
+    static const char *e = getenv("MP_FAST");
+    if (e) return atoi(e);
+    return batch * (T / 64) <= (int64_t)16 * device_cus();
+}
+
 // The work queue of mp_divrem_ragged_static: a library-owned array of one
 // ragged workspace for MP_STATIC_MAX_COUNT instances (1 MiB), one copy per
 // GPU, kept until the process ends.  Host code never uses the array's name as
@@ -232,6 +242,7 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
     const int cus = device_cus();
     if (cus <= 0) return MP_ERR_DEVICE;
     const int bmax = block_max();
+    const bool fast = fast_fits(1024, count);
     hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, u_limbs, v_limbs, q_limbs,
                        r_limbs, inst_status, ws);
     if (hipGetLastError() != hipSuccess) return MP_ERR_LAUNCH;
@@ -245,21 +256,11 @@ mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_
         const int fit = (int)(((size_t)kLdsWords * 4) / bytes);
         const int wpc = g_ragged.wgs_per_cu[c] < fit ? g_ragged.wgs_per_cu[c] : fit;
         const int grid = cus * wpc;
-        hipError_t e;
-        switch (T) {
-        case 256:
-            e = mp::launch_ragged<256>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, bmax);
-            break;
-        case 512:
-            e = mp::launch_ragged<512>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                       count, bmax);
-            break;
-        default:
-            e = mp::launch_ragged<1024>(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                        count, bmax);
-            break;
-        }
+        const auto launch = T == 256   ? (fast ? mp::launch_ragged<256, true> : mp::launch_ragged<256, false>)
+                            : T == 512 ? (fast ? mp::launch_ragged<512, true> : mp::launch_ragged<512, false>)
+                                       : (fast ? mp::launch_ragged<1024, true> : mp::launch_ragged<1024, false>);
+        const hipError_t e = launch(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c, count,
+                                    bmax);
         if (e != hipSuccess) return MP_ERR_LAUNCH;
         if (fk && (hipEventRecord(fk->ev_join[c], fs) != hipSuccess ||
                    hipStreamWaitEvent(st, fk->ev_join[c], 0) != hipSuccess))
@@ -350,11 +351,11 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
-    switch (T) {
-    case 256: return status_of(mp::launch_shinv<256>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
-    case 512: return status_of(mp::launch_shinv<512>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
-    default: return status_of(mp::launch_shinv<1024>(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
-    }
+    const bool fast = fast_fits(T, batch);
+    const auto launch = T == 256   ? (fast ? mp::launch_shinv<256, true> : mp::launch_shinv<256, false>)
+                        : T == 512 ? (fast ? mp::launch_shinv<512, true> : mp::launch_shinv<512, false>)
+                                   : (fast ? mp::launch_shinv<1024, true> : mp::launch_shinv<1024, false>);
+    return status_of(launch(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
 }
 
 mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, int32_t nv,
@@ -370,14 +371,11 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
-    switch (T) {
-    case 256:
-        return status_of(mp::launch_divrem<256>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
-    case 512:
-        return status_of(mp::launch_divrem<512>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
-    default:
-        return status_of(mp::launch_divrem<1024>(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
-    }
+    const bool fast = fast_fits(T, batch);
+    const auto launch = T == 256   ? (fast ? mp::launch_divrem<256, true> : mp::launch_divrem<256, false>)
+                        : T == 512 ? (fast ? mp::launch_divrem<512, true> : mp::launch_divrem<512, false>)
+                                   : (fast ? mp::launch_divrem<1024, true> : mp::launch_divrem<1024, false>);
+    return status_of(launch(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
 }
 
 int64_t mp_ragged_workspace_bytes(int32_t count)
