@@ -13,7 +13,6 @@
 #include <atomic>
 #include <mutex>
 #include <string.h>
-#include <stdlib.h>
 
 namespace {
 
@@ -196,8 +195,6 @@ int device_cus()
 // SIMD: then the kernels built for that finish sooner
 bool fast_fits(int T, int64_t batch)
 {
-    static const char *e = getenv("MP_FAST");
-    if (e) return atoi(e);
     return batch * (T / 64) <= (int64_t)16 * device_cus();
 }
 
