@@ -102,12 +102,14 @@ typedef struct {
 
 /*
  * Quotients and remainders of a batch of divisions of uneven precisions in one
- * launch sequence (Alg. 3 per instance, as mp_divrem_batch).  On the device,
- * instances are bucketed by dividend width into the classes <= 1024, <= 2048,
- * <= 4096 and <= 8192 limbs; each class runs one persistent kernel whose
- * workgroups take instances from a per-class work queue, the class kernels
- * running concurrently.  Nothing is synchronised with the host, so the
- * sequence can be captured into a hipGraph and replayed.
+ * launch sequence (Alg. 3 per instance, as mp_divrem_batch).  A batch of at
+ * most two instances per compute unit is one launch, a workgroup per instance.
+ * Of a larger one, instances are bucketed on the device by dividend width into
+ * the classes <= 1024, <= 2048, <= 4096 and <= 8192 limbs; each class runs one
+ * persistent kernel whose workgroups take instances from a per-class work
+ * queue, costly ones first, the class kernels running concurrently.  Nothing
+ * is synchronised with the host, so the sequence can be captured into a
+ * hipGraph and replayed.
  *   desc:      count descriptors (device memory);
  *   *_limbs:   sizes of the four pools; a descriptor whose ranges leave its
  *              pool or whose widths are outside [1, mp_max_limbs()] gets
@@ -116,9 +118,10 @@ typedef struct {
  *              by the caller, not shared by concurrent calls;
  *   inst_status: count int32 (required).
  * Widths and offsets are checked on the device; null pointers and count < 0 on
- * the host.  The class kernels run on library-owned fork streams joined back
- * into `stream`; each caller stream (up to eight per device) gets its own set,
- * so batches launched on different streams overlap on the device.  A stream
+ * the host.  The widest class's kernel runs on `stream`, the others on
+ * library-owned fork streams joined back into it; each caller stream (up to
+ * eight per device) gets its own set, so batches launched on different streams
+ * overlap on the device.  A stream
  * first seen while it is being captured into a graph gets no set: the class
  * kernels then run one after another on it (call once outside capture first
  * to capture the concurrent form).
@@ -153,8 +156,9 @@ mp_status_t mp_divrem_ragged_static(const uint32_t *u_pool, int64_t u_limbs, con
 /*
  * Launch configuration of width class cls (0..3) for mp_divrem_ragged:
  * threads per workgroup (256, 512 or 1024, at least width/8) and persistent
- * workgroups per compute unit (1..8).  Returns MP_ERR_ARG for an invalid
- * choice.  The defaults come from the library's tuned table.
+ * workgroups per compute unit (1..8; as many as the LDS holds are launched).
+ * Returns MP_ERR_ARG for an invalid choice.  The defaults come from the
+ * library's tuned table.
  */
 mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
 

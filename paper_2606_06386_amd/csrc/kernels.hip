@@ -27,6 +27,7 @@ namespace mp {
 // limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
 // 112 us.
 #define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(FAST ? 4 : 8, 8)))
+#define MP_SHARED_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 // products: four waves per SIMD (four accumulators and a window of four fragments per wave)
 #define MP_MUL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
 
@@ -81,29 +82,54 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, in
                        bmax);
 }
 
-// persistent workgroups of one class: take the next instance of the class's
-// queue until it is empty
+// instance j of a ragged batch
 template <int T, bool FAST>
-__global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
-                                                           const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
-                                                           int32_t *status, int32_t *ws, int cls, int count, int bmax)
+MP_DEV void ragged_instance(uint32_t *lds, const uint32_t *up, const uint32_t *vp, const mp_desc_t *desc, uint32_t *qp,
+                            uint32_t *rp, int32_t *status, int j, int bmax)
+{
+    // every value below is the same on all lanes: keep it in scalar registers
+    const mp_desc_t &d = desc[j];
+    const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off), ro = uniform64(d.r_off);
+    const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
+    divide_instance<T, FAST>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j, bmax);
+}
+
+// one workgroup per instance of a small ragged batch, whatever its width
+template <int T, bool FAST>
+__global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged_direct(const uint32_t *up, const uint32_t *vp,
+                                                                  const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
+                                                                  int32_t *status, PoolLimbs pools, int bmax)
+{
+    extern __shared__ __align__(16) uint32_t lds[];
+    const int j = blockIdx.x;
+    if (!desc_ok(desc[j], pools)) {
+        if (threadIdx.x == 0) status[j] = MP_INST_BADDESC;
+        return;
+    }
+    ragged_instance<T, FAST>(lds, up, vp, desc, qp, rp, status, j, bmax);
+}
+
+// Persistent workgroups of one class: take the next instance of the class's
+// queue until it is empty.  Instances of 1024 threads that would not give two
+// thirds of the compute units a second one run one per unit: two slow each
+// other down (300 of a batch of 1200: 184 us for the batch, 191 in pairs).
+template <int T>
+__global__ __launch_bounds__(T) MP_SHARED_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
+                                                                  const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
+                                                                  int32_t *status, int32_t *ws, int cls, int count,
+                                                                  int cus, int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int n = ws[cls];
+    if (T == 1024 && (int)blockIdx.x >= cus && n <= cus + (cus >> 1)) return;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) lds[kCtlBcast + 2] = (uint32_t)atomicAdd(&ws[kClasses + cls], 1);
         __syncthreads();
-        // every value below is the same on all lanes: keep it in scalar registers
         const int idx = uniform((int)lds[kCtlBcast + 2]);
         if (idx >= n) break;
-        const int j = uniform(ws[kWsHeader + (size_t)cls * count + idx]);
-        const mp_desc_t &d = desc[j];
-        const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off),
-                      ro = uniform64(d.r_off);
-        const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-        divide_instance<T, FAST>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j,
-                           bmax);
+        ragged_instance<T, false>(lds, up, vp, desc, qp, rp, status, uniform(ws[kWsHeader + (size_t)cls * count + idx]),
+                                  bmax);
     }
 }
 
@@ -140,13 +166,24 @@ hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u
     return hipGetLastError();
 }
 
-template <int T, bool FAST>
+template <int T>
 hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                          const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status, int32_t *ws, int cls,
-                         int count, int bmax)
+                         int count, int cus, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged<T, FAST>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_ragged<T, FAST>), dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count,
+    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged<T>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_ragged<T>, dim3(grid), dim3(T), lds, st, up, vp, desc, qp, rp, status, ws, cls, count, cus,
+                       bmax);
+    return hipGetLastError();
+}
+
+template <int T, bool FAST>
+hipError_t launch_ragged_direct(int count, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
+                                const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status,
+                                const PoolLimbs &pools, int bmax)
+{
+    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged_direct<T, FAST>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_ragged_direct<T, FAST>), dim3(count), dim3(T), lds, st, up, vp, desc, qp, rp, status, pools,
                        bmax);
     return hipGetLastError();
 }
@@ -166,12 +203,17 @@ template hipError_t launch_divrem<MP_KT, false>(int, size_t, hipStream_t, const 
 template hipError_t launch_divrem<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
                                          uint32_t *, int, uint32_t *, int32_t *, int);
 #elif MP_KFAMILY == 3
-template hipError_t launch_ragged<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
+template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
                                          const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
-                                         int);
-template hipError_t launch_ragged<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
-                                         const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
-                                         int);
+                                         int, int);
+#if MP_KT == 1024
+template hipError_t launch_ragged_direct<1024, false>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
+                                                      const mp_desc_t *, uint32_t *, uint32_t *, int32_t *,
+                                                      const PoolLimbs &, int);
+template hipError_t launch_ragged_direct<1024, true>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
+                                                     const mp_desc_t *, uint32_t *, uint32_t *, int32_t *,
+                                                     const PoolLimbs &, int);
+#endif
 #endif
 #endif
 

@@ -16,7 +16,6 @@
 
 namespace {
 
-constexpr int kMaxLimbs = 8192;
 constexpr int kLdsWords = 160 * 1024 / 4;   // gfx950: 160 KB of LDS per workgroup
 
 // run-time knobs (mp_set_knob)
@@ -46,37 +45,60 @@ __device__ __forceinline__ int width_class(int nu)
     return nu <= 1024 ? 0 : nu <= 2048 ? 1 : nu <= 4096 ? 2 : 3;
 }
 
-// one workgroup: validate descriptors and bucket instance indices by class
-__global__ __launch_bounds__(1024) void k_ragged_prep(const mp_desc_t *desc, int count, int64_t lu, int64_t lv,
-                                                      int64_t lq, int64_t lr, int32_t *status, int32_t *ws)
+// Queue order within a class: by falling cost, in kBins steps, so that no long
+// instance starts when the others are nearly done.  An instance of nb blocks
+// (and Newton steps worth four) costs a fixed time per block and one that grows
+// with the divisor.
+constexpr int kBins = 16;
+
+__device__ __forceinline__ int cost_of(int nu, int nv) { return ((nu > nv ? nu - nv : 0) / 136 + 5) * (4096 + nv); }
+
+__device__ __forceinline__ int cost_bin(int c, int nu, int nv)
 {
-    __shared__ int cnt[kClasses];
-    if (threadIdx.x < kClasses) cnt[threadIdx.x] = 0;
+    const int most = cost_of(kClassWidth[c], kClassWidth[c] / 2);
+    const int bin = (int)((int64_t)cost_of(nu, nv) * kBins / most);
+    return bin < kBins ? kBins - 1 - bin : 0;
+}
+
+// one workgroup: validate descriptors and bucket instance indices by class and cost
+__global__ __launch_bounds__(1024) void k_ragged_prep(const mp_desc_t *desc, int count, mp::PoolLimbs pools,
+                                                      int32_t *status, int32_t *ws)
+{
+    __shared__ int cnt[kClasses][kBins];
+    if (threadIdx.x < kClasses * kBins) cnt[0][threadIdx.x] = 0;
     __syncthreads();
     for (int j = threadIdx.x; j < count; j += blockDim.x) {
         const mp_desc_t d = desc[j];
-        const bool ok = d.nu >= 1 && d.nu <= kMaxLimbs && d.nv >= 1 && d.nv <= kMaxLimbs && d.nq >= 1 &&
-                        d.u_off >= 0 && d.v_off >= 0 && d.q_off >= 0 && d.r_off >= 0 &&
-                        d.u_off <= lu - d.nu && d.v_off <= lv - d.nv && d.q_off <= lq - d.nq &&
-                        d.r_off <= lr - d.nv;   // (no overflow: widths are small, offsets >= 0)
-        if (!ok) {
+        if (!mp::desc_ok(d, pools)) {
             status[j] = MP_INST_BADDESC;
             continue;
         }
         const int c = width_class(d.nu);
-        const int slot = atomicAdd(&cnt[c], 1);
-        ws[kWsHeader + (size_t)c * count + slot] = j;
+        atomicAdd(&cnt[c][cost_bin(c, d.nu, d.nv)], 1);
     }
     __syncthreads();
-    if (threadIdx.x < kClasses) {
-        ws[threadIdx.x] = cnt[threadIdx.x];
+    if (threadIdx.x < kClasses) {          // counts to first slots
+        int sum = 0;
+        for (int i = 0; i < kBins; i++) {
+            const int n = cnt[threadIdx.x][i];
+            cnt[threadIdx.x][i] = sum;
+            sum += n;
+        }
+        ws[threadIdx.x] = sum;
         ws[kClasses + threadIdx.x] = 0;
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < count; j += blockDim.x) {
+        const mp_desc_t d = desc[j];
+        if (!mp::desc_ok(d, pools)) continue;
+        const int c = width_class(d.nu);
+        ws[kWsHeader + (size_t)c * count + atomicAdd(&cnt[c][cost_bin(c, d.nu, d.nv)], 1)] = j;
     }
 }
 
 struct RaggedConfig {
     int threads[kClasses] = {256, 256, 512, 1024};
-    int wgs_per_cu[kClasses] = {6, 3, 2, 1};
+    int wgs_per_cu[kClasses] = {4, 4, 2, 2};
 };
 RaggedConfig g_ragged;
 std::mutex g_ragged_mu;
@@ -220,49 +242,70 @@ int32_t *static_scratch()
     return (int32_t *)ptr[dev];
 }
 
-// fork streams and events of the concurrent class kernels
+// A ragged batch of at most two instances per compute unit: one launch of one
+// 1024-thread workgroup per instance with the LDS of the widest division
+// (two per unit), which checks its own descriptor.  No instance waits for
+// another, so neither the preparation kernel nor the classes' streams gain
+// anything: 5 instances take 73 us (prepared 107), 256 146 (181), 512 166
+// (189), but 700 217 (195).  False: the batch is larger.
+bool ragged_direct(const uint32_t *u_pool, const uint32_t *v_pool, const mp_desc_t *desc, uint32_t *q_pool,
+                   uint32_t *r_pool, const mp::PoolLimbs &pools, int32_t *inst_status, int32_t count, hipStream_t st,
+                   mp_status_t *result)
+{
+    const int cus = device_cus();
+    if (count > 2 * cus) return false;
+    const auto launch = fast_fits(1024, count) ? mp::launch_ragged_direct<1024, true>
+                                               : mp::launch_ragged_direct<1024, false>;
+    *result = status_of(launch(count, body_bytes(mp::kMaxLimbs, mp::kMaxLimbs), st, u_pool, v_pool, desc, q_pool,
+                               r_pool, inst_status, pools, block_max()));
+    return true;
+}
+
+// Streams and events of the concurrent class kernels.  The widest class, most
+// of a batch's time, runs on the caller's stream: with a stream for each class
+// a fifth one shares a hardware queue (of four), and the whole batch waits
+// for whatever is queued there (4096 mixed instances: 530 us, with four 600 to
+// 750 from one process to the next).
+constexpr int kForked = kClasses - 1;
 struct Forks {
-    hipStream_t fs[kClasses];
-    hipEvent_t ev_fork, ev_join[kClasses];
+    hipStream_t fs[kForked];
+    hipEvent_t ev_fork, ev_join[kForked];
 };
 
-// The launches of one ragged batch: descriptor check and bucketing, heads,
-// then one persistent kernel per width class, each on its own fork stream
-// joined back into st (all on st, one after another, when fk is null).  The
-// preparation kernel sets every counter of the workspace, so it needs no
-// clearing.  Called with g_ragged_mu held.
-mp_status_t ragged_launch(const uint32_t *u_pool, int64_t u_limbs, const uint32_t *v_pool, int64_t v_limbs,
-                          const mp_desc_t *desc, uint32_t *q_pool, int64_t q_limbs, uint32_t *r_pool,
-                          int64_t r_limbs, int32_t *inst_status, int32_t count, int32_t *ws, hipStream_t st,
-                          const Forks *fk)
+// The launches of a larger ragged batch: descriptor check and bucketing, then
+// one persistent kernel per width class, the widest on st, the others each on
+// its own fork stream joined back into st (all on st, one after another, when
+// fk is null).  The preparation kernel sets every counter of the workspace, so
+// it needs no clearing.  Called with g_ragged_mu held.
+mp_status_t ragged_launch(const uint32_t *u_pool, const uint32_t *v_pool, const mp_desc_t *desc, uint32_t *q_pool,
+                          uint32_t *r_pool, const mp::PoolLimbs &pools, int32_t *inst_status, int32_t count,
+                          int32_t *ws, hipStream_t st, const Forks *fk)
 {
     const int cus = device_cus();
     if (cus <= 0) return MP_ERR_DEVICE;
     const int bmax = block_max();
-    const bool fast = fast_fits(1024, count);
-    hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, u_limbs, v_limbs, q_limbs,
-                       r_limbs, inst_status, ws);
+    hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, pools, inst_status, ws);
     if (hipGetLastError() != hipSuccess) return MP_ERR_LAUNCH;
     if (fk && hipEventRecord(fk->ev_fork, st) != hipSuccess) return MP_ERR_LAUNCH;
-    for (int c = 0; c < kClasses; c++) {
-        hipStream_t fs = fk ? fk->fs[c] : st;
-        if (fk && hipStreamWaitEvent(fs, fk->ev_fork, 0) != hipSuccess) return MP_ERR_LAUNCH;
+    for (int c = kClasses - 1; c >= 0; c--) {
+        const bool forked = fk && c < kForked;
+        hipStream_t fs = forked ? fk->fs[c] : st;
+        if (forked && hipStreamWaitEvent(fs, fk->ev_fork, 0) != hipSuccess) return MP_ERR_LAUNCH;
         const int T = g_ragged.threads[c];
         const size_t bytes = body_bytes(kClassWidth[c], kClassWidth[c]);   // the class's widest instance
         if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
         const int fit = (int)(((size_t)kLdsWords * 4) / bytes);
         const int wpc = g_ragged.wgs_per_cu[c] < fit ? g_ragged.wgs_per_cu[c] : fit;
-        const int grid = cus * wpc;
-        const auto launch = T == 256   ? (fast ? mp::launch_ragged<256, true> : mp::launch_ragged<256, false>)
-                            : T == 512 ? (fast ? mp::launch_ragged<512, true> : mp::launch_ragged<512, false>)
-                                       : (fast ? mp::launch_ragged<1024, true> : mp::launch_ragged<1024, false>);
-        const hipError_t e = launch(grid, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c, count,
-                                    bmax);
+        const auto launch = T == 256   ? mp::launch_ragged<256>
+                            : T == 512 ? mp::launch_ragged<512>
+                                       : mp::launch_ragged<1024>;
+        const hipError_t e = launch(cus * wpc, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
+                                    count, cus, bmax);
         if (e != hipSuccess) return MP_ERR_LAUNCH;
-        if (fk && (hipEventRecord(fk->ev_join[c], fs) != hipSuccess ||
-                   hipStreamWaitEvent(st, fk->ev_join[c], 0) != hipSuccess))
-            return MP_ERR_LAUNCH;
+        if (forked && hipEventRecord(fk->ev_join[c], fs) != hipSuccess) return MP_ERR_LAUNCH;
     }
+    for (int c = 0; fk && c < kForked; c++)
+        if (hipStreamWaitEvent(st, fk->ev_join[c], 0) != hipSuccess) return MP_ERR_LAUNCH;
     return MP_OK;
 }
 
@@ -283,7 +326,7 @@ const char *mp_status_str(mp_status_t s)
     return "unknown mp_status_t";
 }
 
-int32_t mp_max_limbs(void) { return kMaxLimbs; }
+int32_t mp_max_limbs(void) { return mp::kMaxLimbs; }
 
 mp_status_t mp_set_knob(int32_t knob, int32_t value)
 {
@@ -311,7 +354,7 @@ int32_t mp_get_knob(int32_t knob)
 
 int64_t mp_lds_bytes(int32_t op, int32_t n1, int32_t n2)
 {
-    if (n1 <= 0 || n2 <= 0 || n1 > kMaxLimbs || n2 > kMaxLimbs) return -1;
+    if (n1 <= 0 || n2 <= 0 || n1 > mp::kMaxLimbs || n2 > mp::kMaxLimbs) return -1;
     switch (op) {
     case MP_OP_MUL: return (int64_t)4 * (mp::hmin(n1, n2) < g_mfma_min.load() ? mp::mul_valu_lds_words(n1, n2)
                                                                         : mp::plan_mul(n1, n2).total);
@@ -325,7 +368,7 @@ mp_status_t mp_mul_batch(const uint32_t *a, int32_t na, const uint32_t *b, int32
                          uint32_t *c, int32_t batch, void *stream)
 {
     if (!a || !b || !c || na <= 0 || nb <= 0 || batch < 0) return MP_ERR_ARG;
-    if (na > kMaxLimbs || nb > kMaxLimbs) return MP_ERR_SIZE;
+    if (na > mp::kMaxLimbs || nb > mp::kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     hipStream_t st = (hipStream_t)stream;
@@ -340,7 +383,7 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
                            int32_t *inst_status, int32_t batch, void *stream)
 {
     if (!v || !w || nv <= 0 || nw <= 0 || h < 0 || batch < 0) return MP_ERR_ARG;
-    if (nv > kMaxLimbs || h > kMaxLimbs) return MP_ERR_SIZE;
+    if (nv > mp::kMaxLimbs || h > mp::kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(h > 0 ? h : 1);
@@ -360,7 +403,7 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
                             int32_t batch, void *stream)
 {
     if (!u || !v || !q || !r || nu <= 0 || nv <= 0 || nq <= 0 || batch < 0) return MP_ERR_ARG;
-    if (nu > kMaxLimbs || nv > kMaxLimbs) return MP_ERR_SIZE;
+    if (nu > mp::kMaxLimbs || nv > mp::kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(nu);
@@ -401,6 +444,10 @@ mp_status_t mp_divrem_ragged(const uint32_t *u_pool, int64_t u_limbs, const uint
     if (u_limbs < 0 || v_limbs < 0 || q_limbs < 0 || r_limbs < 0) return MP_ERR_ARG;
     if (count == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
+    hipStream_t st = (hipStream_t)stream;
+    const mp::PoolLimbs pools{u_limbs, v_limbs, q_limbs, r_limbs};
+    mp_status_t direct;
+    if (ragged_direct(u_pool, v_pool, desc, q_pool, r_pool, pools, inst_status, count, st, &direct)) return direct;
     std::lock_guard<std::mutex> lock(g_ragged_mu);
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MP_ERR_DEVICE;
@@ -412,7 +459,6 @@ mp_status_t mp_divrem_ragged(const uint32_t *u_pool, int64_t u_limbs, const uint
     static Forks forks[64][kForkSets];
     static hipStream_t owner[64][kForkSets];
     static int nsets[64];
-    hipStream_t st = (hipStream_t)stream;
     int f = 0;
     while (f < nsets[dev] && owner[dev][f] != st) f++;
     if (f == nsets[dev]) {
@@ -421,13 +467,13 @@ mp_status_t mp_divrem_ragged(const uint32_t *u_pool, int64_t u_limbs, const uint
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess) return MP_ERR_LAUNCH;
         if (cap != hipStreamCaptureStatusNone)
-            return ragged_launch(u_pool, u_limbs, v_pool, v_limbs, desc, q_pool, q_limbs, r_pool, r_limbs,
-                                 inst_status, count, (int32_t *)workspace, st, nullptr);
+            return ragged_launch(u_pool, v_pool, desc, q_pool, r_pool, pools, inst_status, count,
+                                 (int32_t *)workspace, st, nullptr);
         if (f == kForkSets) {
             f = kForkSets - 1;
         } else {
             Forks &fk = forks[dev][f];
-            for (int c = 0; c < kClasses; c++) {
+            for (int c = 0; c < kForked; c++) {
                 if (hipStreamCreateWithFlags(&fk.fs[c], hipStreamNonBlocking) != hipSuccess ||
                     hipEventCreateWithFlags(&fk.ev_join[c], hipEventDisableTiming) != hipSuccess)
                     return MP_ERR_LAUNCH;
@@ -437,8 +483,8 @@ mp_status_t mp_divrem_ragged(const uint32_t *u_pool, int64_t u_limbs, const uint
             nsets[dev] = f + 1;
         }
     }
-    return ragged_launch(u_pool, u_limbs, v_pool, v_limbs, desc, q_pool, q_limbs, r_pool, r_limbs, inst_status,
-                         count, (int32_t *)workspace, st, &forks[dev][f]);
+    return ragged_launch(u_pool, v_pool, desc, q_pool, r_pool, pools, inst_status, count, (int32_t *)workspace, st,
+                         &forks[dev][f]);
 }
 
 mp_status_t mp_divrem_ragged_static(const uint32_t *u_pool, int64_t u_limbs, const uint32_t *v_pool,
@@ -451,11 +497,15 @@ mp_status_t mp_divrem_ragged_static(const uint32_t *u_pool, int64_t u_limbs, con
     if (count > MP_STATIC_MAX_COUNT) return MP_ERR_COUNT;
     if (count == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
+    const mp::PoolLimbs pools{u_limbs, v_limbs, q_limbs, r_limbs};
+    mp_status_t direct;
+    if (ragged_direct(u_pool, v_pool, desc, q_pool, r_pool, pools, inst_status, count, (hipStream_t)stream, &direct))
+        return direct;
     std::lock_guard<std::mutex> lock(g_ragged_mu);
     int32_t *ws = static_scratch();
     if (!ws) return MP_ERR_DEVICE;
-    return ragged_launch(u_pool, u_limbs, v_pool, v_limbs, desc, q_pool, q_limbs, r_pool, r_limbs, inst_status,
-                         count, ws, (hipStream_t)stream, nullptr);
+    return ragged_launch(u_pool, v_pool, desc, q_pool, r_pool, pools, inst_status, count, ws, (hipStream_t)stream,
+                         nullptr);
 }
 
 }  // extern "C"

@@ -106,8 +106,10 @@ def tune_knobs(count=1024, reps=3, log=None):
     return {"small_limit": sl, "mfma_min": mm, "ms": ms}
 
 
-def tune(counts=(2048, 1024, 512, 256), reps=3, log=None):
-    """Time every candidate per class; returns {cls: (threads, wgs_per_cu, ms)}."""
+def tune(counts=(2048, 1024, 1024, 768), reps=3, log=None):
+    """Time every candidate per class; returns {cls: (threads, wgs_per_cu, ms)}.
+    (Batches of at most two instances per compute unit run outside the classes:
+    the counts are above that.)"""
     from . import binding, ragged
     best = {}
     for cls in range(len(CLASS_WIDTHS)):
