@@ -202,48 +202,91 @@ MP_DEV int wave_prec(int ln, const uint32_t *x, int n)
     return 0;
 }
 
-// w[0, 5) ~ B^(k+4) / v from the top five limbs a[4] (v_k), a[3], .. of v: at
-// most max(2, 2^-111 of it) off.  1/D for the normalised top D in [1/2, 1) as
-// a double, then one step in integers with the second-order term:
-// R = R1 (1 + e + e^2), e = 1 - D R1 / 2^62.
-MP_DEV void newton_start(const uint32_t (&a)[5], uint32_t (&w)[5])
+// limbs a Newton step to f limbs starts from
+MP_HD int newton_from(int f) { return (f + 4) >> 1; }
+
+constexpr int kStartLimbs = 40;   // longest iterate of newton_start
+
+// limbs of the iterate the Newton steps to F limbs start from
+MP_HD int start_limbs(int F)
 {
-    typedef unsigned __int128 u128;
-    typedef __int128 i128;
-    const int lz = __builtin_clz(a[4]);
-    const uint64_t hi = (uint64_t)a[4] << 32 | a[3], lo = (uint64_t)a[2] << 32 | a[1];
-    const u128 n0 = (u128)hi << 64 | lo;
-    const u128 N = n0 << lz | (uint32_t)((uint64_t)a[0] << lz >> 32);
-    const uint64_t Nh = (uint64_t)(N >> 64), Nl = (uint64_t)N;
-    const double d = (double)(uint32_t)(Nh >> 32) * 0x1p-32 + (double)(uint32_t)Nh * 0x1p-64;
-    double r = __builtin_amdgcn_rcp(d);
-    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    const double rs = r * 0x1p31;                                  // in (2^31, 2^32]
-    const uint32_t r1 = rs >= 0x1p32 ? 0xFFFFFFFFu : (uint32_t)rs;
-    const uint64_t R1 = ((uint64_t)r1 << 31) + (uint32_t)((rs - (double)r1) * 0x1p31);   // (at most 2^63)
-    // e 2^112 = (2^190 - N R1) / 2^78, |e| < 2^-50
-    const u128 p0 = (u128)Nl * R1, p1 = (u128)Nh * R1 + (uint64_t)(p0 >> 64);   // N R1 = p1 2^64 + lo(p0)
-    const int64_t e = (int64_t)((((i128)1 << 126) - (i128)p1) >> 14);
-    const i128 c1 = (i128)e * (i128)(u128)R1 >> 48;
-    const int64_t eh = e >> 32;
-    const uint64_t c2 = (uint64_t)((u128)(uint64_t)(eh * eh) * R1 >> 96);
-    const u128 F = ((u128)R1 << 64) + (u128)c1 + c2;               // R 2^126
-    const u128 t = lz < 31 ? F >> (30 - lz) : F << 1;
-    w[0] = (uint32_t)t;
-    w[1] = (uint32_t)(t >> 32);
-    w[2] = (uint32_t)(t >> 64);
-    w[3] = (uint32_t)(t >> 96);
-    w[4] = lz == 31 ? (uint32_t)(F >> 127) : 0u;
+    while (F > kStartLimbs) F = newton_from(F);
+    return F;
 }
 
-// limbs of the iterate a Newton step to f limbs starts from
-MP_HD int newton_from(int f) { return (f + 4) >> 1; }
+// lane j >= 1: bits [24 (j - 1), 24 j) below the leading bit of v, which is lz
+// bits below the top of limb k (lane 0: 0)
+template <class FV>
+MP_DEV uint32_t start_digits(int l, const FV &v, int k, int lz)
+{
+    const int p = 32 * (k + 1) - lz - 24 * l, i = p >> 5;
+    const uint32_t lo = i >= 0 ? v(i) : 0u, hi = i >= -1 ? v(i + 1) : 0u;
+    return l ? alignbit(hi, lo, (uint32_t)p & 31u) & 0xFFFFFFu : 0u;
+}
+
+// w[0, f] = floor(B^(k+f) / v) or one less, 4 <= f <= kStartLimbs, by one wave
+// from the start_digits V of v: a division of 2^(e-48) by v' = v / 2^(32(k+1)-lz)
+// in signed digits of 48 bits.  Lane j holds weight 2^(-24j): the remainder r in
+// signed 25-bit parts a, and v' shifted down to the next digit's place (the
+// upper and the lower half of the digit: vA, vB).  A step takes the digit from
+// the leading lanes of r (as an integer modulo 2^64, which drops the lanes
+// above: they cancel) times 1 / v' in double precision, to within 2^-2 of r/v':
+// |r| stays below 0.8 v' 2^(-48 t).  It costs about 200 cycles, nearly all of
+// it one dependent chain of 20 instructions; a Newton step on the matrix core
+// costs 4000 to 5000 however short its operands (its LDS round trips and carry
+// passes), so 25 steps here (37 limbs) beat the five Newton steps from the 112
+// bits of one reciprocal.  scratch: 64 words.
+MP_DEV void newton_start(int l, uint32_t V, int lz, int f, uint32_t *scratch, uint32_t *w)
+{
+    constexpr double kRound = 0x1.8p52;          // (adding it leaves the integer in the low mantissa bits)
+    const int e = 39 + ((lz + 1) & 7);           // (the result ends at a byte)
+    const int n = (32 * (f - 1) + lz - e + 8 + 47) / 48 + 1, x = 48 * (n - 1) + e - 32 * (f - 1) - lz;
+    const double d = (double)(int)readlane(V, 1) * 0x1p-24 + (double)(int)readlane(V, 2) * 0x1p-48 +
+                     (double)(int)readlane(V, 3) * 0x1p-72;
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    r = -__builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    uint32_t vA = shfl_up1(V), vB = shfl_up1(vA);
+    int a = l == 1 ? 1 << (e - 24) : 0, digit = 0;
+    for (int t = 0; t < n; t++) {
+        const int a0 = (int)readlane((uint32_t)a, 2 * t), a1 = (int)readlane((uint32_t)a, 2 * t + 1),
+                  a2 = (int)readlane((uint32_t)a, 2 * t + 2), a3 = (int)readlane((uint32_t)a, 2 * t + 3);
+        const int64_t S = (int64_t)((uint64_t)(int64_t)a0 << 48) + ((int64_t)a1 * (1 << 24) + a2);
+        const double rem = __builtin_fma((double)a3, 0x1p-24, __builtin_bit_cast(double, 0x4338000000000000ll + S) - kRound);
+        const uint64_t b = __builtin_bit_cast(uint64_t, __builtin_fma(rem, r, kRound + 0x1p23));
+        // minus the digit's halves, the lower one in [-2^23, 2^23)
+        const int ql = (int)((uint32_t)b & 0xFFFFFFu) - (1 << 23);
+        const int qh = (int)(alignbit((uint32_t)(b >> 32), (uint32_t)b, 24) << 5) >> 5;
+        const int64_t P = (int64_t)qh * (int)vA + (a + (1 << 23)) + (int64_t)ql * (int)vB;
+        a = (int)((uint32_t)P & 0xFFFFFFu) - (1 << 23) +
+            (int)shfl_down1(alignbit((uint32_t)((uint64_t)P >> 32), (uint32_t)P, 24));
+        digit = l == 2 * t + 1 ? -qh : l == 2 * t + 2 ? -ql : digit;
+        vA = shfl_up1(vB);
+        vB = shfl_up1(vA);
+    }
+    // the borrows of the digits (lane 1 the highest), their bytes, and the limbs
+    const uint64_t G = __builtin_bitreverse64(ballot(digit < 0)), X = G | __builtin_bitreverse64(ballot(digit == 0));
+    const uint32_t z = (uint32_t)digit - (inverse_ballot(__builtin_bitreverse64((X + G) ^ X ^ G)) ? 1u : 0u);
+    scratch[l] = 0u;
+    wave_sync();
+    if (l >= 1 && l <= 2 * n) {
+        uint8_t *at = reinterpret_cast<uint8_t *>(scratch) + 3 * (2 * n - l);
+        at[0] = (uint8_t)z;
+        at[1] = (uint8_t)(z >> 8);
+        at[2] = (uint8_t)(z >> 16);
+    }
+    wave_sync();
+    if (l <= f) {
+        const int o = (x >> 3) + 4 * l;
+        w[l] = alignbyte(scratch[(o >> 2) + 1], scratch[o >> 2], (uint32_t)o & 3u);
+    }
+    wave_sync();
+}
 
 // W ~ B^(k+F) / v, F = dp + 2, by one wave: w[0, F] its limbs, xw the reversed
 // digits of its F + 2 digit limbs (all words from xw - kXLow to their upper pad
 // are zero before).  vd: the planes (distance lv) of v's digits, td: T's planes
-// (their pads zero), s0: the five limbs newton_start gave.
+// (their pads zero).  w holds newton_start's start_limbs(F) limbs below its top.
 //
 // The iterate for f limbs is w ~ B^(k+f)/v, the top of the final one: w[F - f,
 // F].  A step to f' <= 2f - 3 limbs takes the middle columns of v w as the
@@ -253,8 +296,7 @@ MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 // limb, the new one is at most E^2 / B (quadratic term) + 1 (floor) + 0.1:
 // limbs of v below s are left out (but for those the strip reads anyway), s <=
 // k - 1 - f', which moves e by less than B^f, and columns of e below c = sh - f
-// - 2, of either sign and below 2^26 B^c.  (The first step, from newton_start,
-// adds at most 2 instead of E^2 / B.)  So |E| <= 3 at the end.
+// - 2, of either sign and below 2^26 B^c.  So |E| <= 3 at the end.
 //
 // The correction ends in the old iterate's last limb, which the second product
 // takes as an addend.  As long as that limb neither overflows (it moves by a
@@ -262,16 +304,12 @@ MP_HD int newton_from(int f) { return (f + 4) >> 1; }
 // above it stay as they are and only the new limbs' are written; otherwise all
 // digits are made again from the limbs.
 template <bool FAST>
-MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint32_t *w,
+MP_DEV void newton(int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint32_t *w,
                    uint32_t *xw)
 {
     const int F = dp + 2, l = lane_at(k), g = quad_limb(l);
-    if (l == 0) {
-#pragma unroll
-        for (int j = 0; j < 5; j++) w[F - 4 + j] = s0[j];
-    }
     const Limb4 none{0u, 0u, 0u, 0u};
-    int f = 4;
+    int f = start_limbs(F);
     bool again = true;                           // the digits are to be made from the limbs
     for (;;) {
         wave_sync();
@@ -279,7 +317,7 @@ MP_DEV void newton(const uint32_t (&s0)[5], int k, int dp, const uint32_t *vd, i
         if (f == F) break;
         const uint32_t last = uniform(w[F - f]);
         int fn = F;                              // the next step of the schedule that ends at F
-        while (fn > 7 && newton_from(fn) > f) fn = newton_from(fn);
+        while (newton_from(fn) > f) fn = newton_from(fn);
         const int s = imax(0, k - 1 - fn) & ~7;
         const int sh = k - s + 2 * f - fn;       // w e / B^sh is the correction
         const int c0 = imax(0, sh - f - 2) & ~7, nx = k + 2 - s - c0;
@@ -366,27 +404,28 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     const BlockSplit bs = block_split(d, bmax);
     const int dp = bs.dp, nb = bs.nb, bi = bs.bi;
     MP_STAMP(1);
-    // the divisor's digits and the zero pads
-    {
-        for (int i = t; i < 5 * kPadWords; i += T) {
+    // the first wave: the start of the inverse; the others: the divisor's digits and the zero pads
+    if (w == 0) {
+        const int l = lane_at(k), lz = __builtin_clz(uniform(Vv(k)));
+        const int f = start_limbs(dp + 2);
+        newton_start(l, start_digits(l, Vv, k, lz), lz, f, Td, lds + pl.offW + dp + 2 - f);
+    } else {
+        const int t1 = t - kLanes;
+        for (int i = t1; i < 5 * kPadWords; i += T - kLanes) {
             const int b = i / kPadWords, j = i - b * kPadWords;
             const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * kLyT;
             lds[at - kPadWords + j] = 0u;
         }
-        for (int i = pl.offX - kXLow + t; i < pl.offW; i += T) lds[i] = 0u;
-        const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 1) / W;
-        const int r0 = w * per, r1 = imin(rows, r0 + per);
+        for (int i = pl.offX - kXLow + t1; i < pl.offW; i += T - kLanes) lds[i] = 0u;
+        const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 2) / (W - 1);
+        const int r0 = (w - 1) * per, r1 = imin(rows, r0 + per);
         if (r0 < r1) balance_rows(l0, r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
     }
     bar<T>();
     MP_STAMP(9);
     // W by the first wave, while the others read the dividend (zeros above it)
     if (w == 0) {
-        uint32_t a[5], s[5];
-#pragma unroll
-        for (int j = 0; j < 5; j++) a[j] = k - 4 + j >= 0 ? Vv(k - 4 + j) : 0u;
-        newton_start(a, s);
-        newton<FAST>(s, k, dp, Vd, pl.lyV, Td, lds + pl.offW, XW);
+        newton<FAST>(k, dp, Vd, pl.lyV, Td, lds + pl.offW, XW);
     } else {
         constexpr int S = T - kLanes;
         for (int i0 = t - kLanes; i0 < pl.capR; i0 += 8 * S) {

@@ -91,6 +91,7 @@ MP_DEV int wave_index() { return (int)__builtin_amdgcn_readfirstlane(threadIdx.x
 // from another lane of the same wave, no LDS round trip)
 constexpr int kDppQuadSwap1 = 0xB1;      // quad_perm [1, 0, 3, 2]
 constexpr int kDppQuadSwap2 = 0x4E;      // quad_perm [2, 3, 0, 1]
+constexpr int kDppWaveShl1 = 0x130;      // lane i reads lane i + 1
 constexpr int kDppWaveShr1 = 0x138;      // lane i reads lane i - 1
 constexpr int kDppRowMirror = 0x140;     // lane i of a 16-lane row reads lane 15 - i
 constexpr int kDppRowHalfMirror = 0x141; // lane i of an 8-lane half row reads lane 7 - i
@@ -107,6 +108,9 @@ MP_DEV uint32_t dpp(uint32_t x)
 
 // value held by lane-1 (lane 0 receives 0)
 MP_DEV uint32_t shfl_up1(uint32_t x) { return dpp<kDppWaveShr1>(x); }
+
+// value held by lane+1 (lane 63 receives 0)
+MP_DEV uint32_t shfl_down1(uint32_t x) { return dpp<kDppWaveShl1>(x); }
 
 // value held by lane-2 (lanes 0 and 1 receive 0)
 MP_DEV uint32_t shfl_up2(uint32_t x) { return dpp<kDppWaveShr1>(dpp<kDppWaveShr1>(x)); }
@@ -221,6 +225,9 @@ MP_DEV uint32_t add_mask(uint32_t x, uint32_t a, uint64_t m)
 
 // bytes [sel, sel + 4) of the 8-byte value hi:lo (sel in 0..3)
 MP_DEV uint32_t alignbyte(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_alignbyte(hi, lo, sel); }
+
+// bits [n, n + 32) of the 8-byte value hi:lo (n in 0..31)
+MP_DEV uint32_t alignbit(uint32_t hi, uint32_t lo, uint32_t n) { return __builtin_amdgcn_alignbit(hi, lo, n); }
 
 MP_DEV uint32_t bswap(uint32_t x) { return __builtin_bswap32(x); }
 
