@@ -26,7 +26,7 @@ namespace mp {
 // of a 2^16-bit instance, 20 KB, also allows.  4096 divisions of 2048 by 1024
 // limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
 // 112 us.
-#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(FAST ? 4 : 8, 8)))
+#define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(M == Mode::kPacked ? 8 : 4, 8)))
 #define MP_SHARED_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 // products: four waves per SIMD (four accumulators and a window of four fragments per wave)
 #define MP_MUL_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4, 8)))
@@ -59,18 +59,18 @@ __global__ __launch_bounds__(T) void k_mul_valu(const uint32_t *a, int na, const
     mul_valu_instance<T>(lds, a + j * na, na, b + j * nb, nb, c + j * (size_t)(na + nb));
 }
 
-template <int T, bool FAST>
+template <int T, Mode M>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_shinv(const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                                                           int32_t *status, int bmax)
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *wj = w + j * nw;
-    divide_instance<T, FAST>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
+    divide_instance<T, M>(lds, PowB{h}, h + 1, v + j * nv, nv, wj, nw, nullptr, status ? status + j : nullptr,
                        bmax);
 }
 
-template <int T, bool FAST>
+template <int T, Mode M>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, int nu, const uint32_t *v, int nv,
                                                            uint32_t *q, int nq, uint32_t *r, int32_t *status,
                                                            int bmax)
@@ -78,12 +78,12 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_divrem(const uint32_t *u, in
     extern __shared__ __align__(16) uint32_t lds[];
     const size_t j = blockIdx.x;
     uint32_t *qj = q + j * nq, *rj = r + j * nv;
-    divide_instance<T, FAST>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
+    divide_instance<T, M>(lds, Span{u + j * nu, 0, nu}, nu, v + j * nv, nv, qj, nq, rj, status ? status + j : nullptr,
                        bmax);
 }
 
 // instance j of a ragged batch
-template <int T, bool FAST>
+template <int T, Mode M>
 MP_DEV void ragged_instance(uint32_t *lds, const uint32_t *up, const uint32_t *vp, const mp_desc_t *desc, uint32_t *qp,
                             uint32_t *rp, int32_t *status, int j, int bmax)
 {
@@ -91,11 +91,11 @@ MP_DEV void ragged_instance(uint32_t *lds, const uint32_t *up, const uint32_t *v
     const mp_desc_t &d = desc[j];
     const int64_t uo = uniform64(d.u_off), vo = uniform64(d.v_off), qo = uniform64(d.q_off), ro = uniform64(d.r_off);
     const int nu = uniform(d.nu), nv = uniform(d.nv), nq = uniform(d.nq);
-    divide_instance<T, FAST>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j, bmax);
+    divide_instance<T, M>(lds, Span{up + uo, 0, nu}, nu, vp + vo, nv, qp + qo, nq, rp + ro, status + j, bmax);
 }
 
 // one workgroup per instance of a small ragged batch, whatever its width
-template <int T, bool FAST>
+template <int T, Mode M>
 __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged_direct(const uint32_t *up, const uint32_t *vp,
                                                                   const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
                                                                   int32_t *status, PoolLimbs pools, int bmax)
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged_direct(const uint32_t
         if (threadIdx.x == 0) status[j] = MP_INST_BADDESC;
         return;
     }
-    ragged_instance<T, FAST>(lds, up, vp, desc, qp, rp, status, j, bmax);
+    ragged_instance<T, M>(lds, up, vp, desc, qp, rp, status, j, bmax);
 }
 
 // Persistent workgroups of one class: take the next instance of the class's
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(T) MP_SHARED_OCCUPANCY void k_ragged(const uint32_t
         __syncthreads();
         const int idx = uniform((int)lds[kCtlBcast + 2]);
         if (idx >= n) break;
-        ragged_instance<T, false>(lds, up, vp, desc, qp, rp, status, uniform(ws[kWsHeader + (size_t)cls * count + idx]),
+        ragged_instance<T, Mode::kPacked>(lds, up, vp, desc, qp, rp, status, uniform(ws[kWsHeader + (size_t)cls * count + idx]),
                                   bmax);
     }
 }
@@ -148,21 +148,21 @@ hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const
     return hipGetLastError();
 }
 
-template <int T, bool FAST>
+template <int T, Mode M>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                         int32_t *status, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(&k_shinv<T, FAST>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_shinv<T, FAST>), dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, bmax);
+    if (!lds_attr(reinterpret_cast<const void *>(&k_shinv<T, M>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_shinv<T, M>), dim3(grid), dim3(T), lds, st, v, nv, h, w, nw, status, bmax);
     return hipGetLastError();
 }
 
-template <int T, bool FAST>
+template <int T, Mode M>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
                          uint32_t *q, int nq, uint32_t *r, int32_t *status, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(&k_divrem<T, FAST>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_divrem<T, FAST>), dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, bmax);
+    if (!lds_attr(reinterpret_cast<const void *>(&k_divrem<T, M>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_divrem<T, M>), dim3(grid), dim3(T), lds, st, u, nu, v, nv, q, nq, r, status, bmax);
     return hipGetLastError();
 }
 
@@ -177,42 +177,51 @@ hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *u
     return hipGetLastError();
 }
 
-template <int T, bool FAST>
+template <int T, Mode M>
 hipError_t launch_ragged_direct(int count, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                                 const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status,
                                 const PoolLimbs &pools, int bmax)
 {
-    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged_direct<T, FAST>), lds)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_ragged_direct<T, FAST>), dim3(count), dim3(T), lds, st, up, vp, desc, qp, rp, status, pools,
+    if (!lds_attr(reinterpret_cast<const void *>(&k_ragged_direct<T, M>), lds)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_ragged_direct<T, M>), dim3(count), dim3(T), lds, st, up, vp, desc, qp, rp, status, pools,
                        bmax);
     return hipGetLastError();
 }
 
 #if defined(MP_KFAMILY) && defined(MP_KT)
+// (Mode::kFast serves workgroups of 256 threads only, see division_mode)
 #if MP_KFAMILY == 0
 template hipError_t launch_mul<MP_KT>(int, hipStream_t, const uint32_t *, int, const uint32_t *, int, uint32_t *,
                                       MulKind);
 #elif MP_KFAMILY == 1
-template hipError_t launch_shinv<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
-                                        int32_t *, int);
-template hipError_t launch_shinv<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *, int,
-                                        int32_t *, int);
+#define MP_SHINV(M)                                                                                                 \
+    template hipError_t launch_shinv<MP_KT, M>(int, size_t, hipStream_t, const uint32_t *, int, int, uint32_t *,    \
+                                               int, int32_t *, int);
+MP_SHINV(Mode::kPacked)
+MP_SHINV(Mode::kShared)
+#if MP_KT == 256
+MP_SHINV(Mode::kFast)
+#endif
 #elif MP_KFAMILY == 2
-template hipError_t launch_divrem<MP_KT, false>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
-                                         uint32_t *, int, uint32_t *, int32_t *, int);
-template hipError_t launch_divrem<MP_KT, true>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *, int,
-                                         uint32_t *, int, uint32_t *, int32_t *, int);
+#define MP_DIVREM(M)                                                                                                \
+    template hipError_t launch_divrem<MP_KT, M>(int, size_t, hipStream_t, const uint32_t *, int, const uint32_t *,  \
+                                                int, uint32_t *, int, uint32_t *, int32_t *, int);
+MP_DIVREM(Mode::kPacked)
+MP_DIVREM(Mode::kShared)
+#if MP_KT == 256
+MP_DIVREM(Mode::kFast)
+#endif
 #elif MP_KFAMILY == 3
 template hipError_t launch_ragged<MP_KT>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
                                          const mp_desc_t *, uint32_t *, uint32_t *, int32_t *, int32_t *, int, int,
                                          int, int);
 #if MP_KT == 1024
-template hipError_t launch_ragged_direct<1024, false>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
-                                                      const mp_desc_t *, uint32_t *, uint32_t *, int32_t *,
+#define MP_DIRECT(M)                                                                                                \
+    template hipError_t launch_ragged_direct<1024, M>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *, \
+                                                      const mp_desc_t *, uint32_t *, uint32_t *, int32_t *,         \
                                                       const PoolLimbs &, int);
-template hipError_t launch_ragged_direct<1024, true>(int, size_t, hipStream_t, const uint32_t *, const uint32_t *,
-                                                     const mp_desc_t *, uint32_t *, uint32_t *, int32_t *,
-                                                     const PoolLimbs &, int);
+MP_DIRECT(Mode::kPacked)
+MP_DIRECT(Mode::kShared)
 #endif
 #endif
 #endif

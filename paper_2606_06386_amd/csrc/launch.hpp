@@ -38,13 +38,17 @@ template <int T>
 hipError_t launch_mul(int grid, hipStream_t st, const uint32_t *a, int na, const uint32_t *b, int nb, uint32_t *c,
                       MulKind kind);
 
-// Division kernels; bmax: longest block of quotient limbs.  FAST: built for four
-// waves per SIMD instead of eight, with products that keep more reads in flight.
-template <int T, bool FAST>
+// Division kernels, by the room the batch leaves them: eight waves per SIMD; or
+// built for four, with products that keep more reads in flight; the latter with
+// four waves sharing a block's quotient product
+enum class Mode { kPacked, kFast, kShared };
+
+// bmax: longest block of quotient limbs
+template <int T, Mode M>
 hipError_t launch_shinv(int grid, size_t lds, hipStream_t st, const uint32_t *v, int nv, int h, uint32_t *w, int nw,
                         int32_t *status, int bmax);
 
-template <int T, bool FAST>
+template <int T, Mode M>
 hipError_t launch_divrem(int grid, size_t lds, hipStream_t st, const uint32_t *u, int nu, const uint32_t *v, int nv,
                          uint32_t *q, int nq, uint32_t *r, int32_t *status, int bmax);
 
@@ -54,7 +58,7 @@ hipError_t launch_ragged(int grid, size_t lds, hipStream_t st, const uint32_t *u
                          int count, int cus, int bmax);
 
 // one workgroup per instance, descriptors checked by the workgroup (no workspace)
-template <int T, bool FAST>
+template <int T, Mode M>
 hipError_t launch_ragged_direct(int count, size_t lds, hipStream_t st, const uint32_t *up, const uint32_t *vp,
                                 const mp_desc_t *desc, uint32_t *qp, uint32_t *rp, int32_t *status,
                                 const PoolLimbs &pools, int bmax);

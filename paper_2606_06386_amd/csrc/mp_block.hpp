@@ -48,6 +48,10 @@ struct BlockSplit {
 // of the next product.
 constexpr int kBlockMax = 252;
 
+// Longest block whose R_top lies above the two lowest limbs of the remainder's
+// top strip.
+constexpr int kBlockInTop = 244;
+
 MP_HD constexpr int block_precision(int b) { return ((b + 8) & ~7) - 1; }
 
 MP_HD BlockSplit block_split(int d, int bmax)
@@ -76,6 +80,9 @@ struct BodyPlan {
     int capR;
     int total;
 };
+
+// behind the plan, Mode::kShared: partial sums of the quotient products, by the waves [1, kShares)
+constexpr int kShares = 4, kPartWords = (kShares - 1) * 1024;
 
 constexpr int kLyT = 4 * kStripBlks + kPadWords;   // distance of T's planes
 
@@ -127,14 +134,16 @@ MP_DEV void strip_out(int l, uint32_t *ctl, const MfmaAcc &acc, uint32_t *R, int
 // these at a time, which share each fragment of x (a wave's step of one
 // diagonal is bound by its instructions, not by the matrix core: two products
 // take little longer than one).  FAST: one each as long as there are waves.
-// The lowest, partial strip comes last.  R is 16-byte aligned.
-template <int T, bool FAST>
+// The lowest, partial strip comes last.  Shared quotient products: the first
+// wave, which stores the quotient's limbs before, takes the last share.  R is 16-byte aligned.
+template <int T, Mode M>
 MP_DEV void strips(int l, uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
 {
     constexpr int W = T / kLanes;
+    constexpr bool FAST = M != Mode::kPacked;
     const int w = wave_index(), n = nstrips - 1, b = base >> 3;
     const int step = FAST && n <= W ? 1 : 2, units = (n + step - 1) / step;
-    for (int u = w; u <= units; u += W) {          // (unit `units`: the lowest strip)
+    for (int u = M == Mode::kShared ? (w ? w : W) - 1 : w; u <= units; u += W) {          // (unit `units`: the lowest strip)
         const int i = u < units ? 1 + u * step : 0;
         if (step == 2 && u < units && i < n) {
             MfmaAcc accA, accB;
@@ -356,22 +365,68 @@ MP_DEV void newton(int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint
     }
 }
 
+// the digits of R_top, nt limbs at src, to T's planes td
+MP_DEV void top_digits(int l, const uint32_t *src, int nt, uint32_t *td)
+{
+    const int g = quad_limb(l);
+    uint32_t z[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] = g + j < nt ? src[g + j] : 0u;
+    quad_balance(z, 0u);
+    store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] : 0u, g + 1 < nt ? z[1] : 0u, g + 2 < nt ? z[2] : 0u,
+           g + 3 < nt ? z[3] : 0u);
+}
+
+// the reversed digits of -q_i to xq; q: limbs of R_top W / B^(dp+1), limb 2 + j is limb j of q_i, 2 + b its sign
+MP_DEV void quotient_digits(int l, const uint32_t (&q)[4], int b, uint32_t *xq)
+{
+    const int g = quad_limb(l) - 2;
+    uint32_t z[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) z[j] = g + j <= b ? (g + j < 0 ? 0xFFFFFFFFu : ~q[j]) : 0u;   // (the two columns below pass the +1 on)
+    quad_balance(z, 1u);
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        if ((unsigned)(g + j) <= (unsigned)b) xq[b - g - j] = bswap(z[j]);
+    if (l < kXPad) xq[b + 1 + l] = 0u;
+}
+
+// the b limbs of q_i (see quotient_digits) to the quotient's limbs Q
+MP_DEV void quotient_limbs(int l, uint32_t *Q, const uint32_t (&q)[4], int b)
+{
+    const int g = quad_limb(l) - 2;
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        if ((unsigned)(g + j) < (unsigned)b) Q[g + j] = q[j];
+}
+
+// its sign to the n limbs above them (or, for the first block, one more limb)
+MP_DEV void quotient_sign(int l, uint32_t *Q, int sign, int n)
+{
+    if (n == 0) {
+        if (l == 0) Q[0] = (uint32_t)sign;
+    } else {
+        add_small(l, Q, n + 1, sign);
+    }
+}
+
 // limbs of a dividend: an array (wave_prec reads it), or B^e
 MP_DEV int top_limb(int l, const Span &u, int n) { return wave_prec(l, u.p, n); }
 MP_DEV int top_limb(int, const PowB &u, int) { return u.e + 1; }
 
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
 // U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
-// block; FAST: see strip_sums.
-template <int T, bool FAST, class FU>
+// block.
+template <int T, Mode M, class FU>
 MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *v, int nv, uint32_t *q, int nq,
                             uint32_t *r, int32_t *status, int bmax)
 {
     constexpr int W = T / kLanes;
+    constexpr bool FAST = M != Mode::kPacked, SHARED = M == Mode::kShared;
     uint32_t *ctl = lds;
     const BodyPlan pl = plan_body(nu, nv);
     uint32_t *Vd = lds + pl.offV, *Td = lds + pl.offT, *XW = lds + pl.offX, *XQ = lds + pl.offQ;
-    uint32_t *R = lds + pl.offR;
+    uint32_t *R = lds + pl.offR, *part = lds + r4(pl.total);
     const int w = wave_index(), l0 = lane_at(nu), t = w * kLanes + l0, nr = r ? nv : 0;
     MP_RSTAMP(14);
     MP_STAMP(0);
@@ -444,53 +499,62 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     MP_STAMP(2);
     bool good = true;
     const int n2 = k + 2, bs2 = (n2 + kStrip - 1) / kStrip, base2 = ((n2 + 7) & ~7) - bs2 * kStrip;
+    const Limb4 none{0u, 0u, 0u, 0u};
     int o = d;
     for (int i = 0; i < nb; i++) {
         const int op = o;
         o = (nb - 1 - i) * bi;
         const int b = op - o, nt = b + 3;             // limbs of this block, of R_top
         const int l = lane_at(i);
-        if (w == 0) {
-            const int g = quad_limb(l);
-            uint32_t z[4];
-            // R complete; R_top's digits
+        uint32_t q[4];                                // (the first wave's) q_i
+        const int cq = (dp + 1) >> 3;                 // block of the product's first column
+        if constexpr (SHARED) {
+            // R_top is read before the strips' carries are added, which the last
+            // wave does meanwhile: they lie below R_top (unless the block is
+            // longer than kBlockInTop) but for a ripple of one unit into its
+            // lowest limb, which the quotient's error bound has room for.
+            const bool late = b <= kBlockInTop;
+            if (w == 0) {
+                if (i && !late) strip_carries(l, ctl, R + op, n2, base2, bs2);
+                top_digits(l, R + o + k - 1, nt, Td);
+                MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
+            }
+            bar<T>();
+            MfmaAcc acc;
+            if (w < kShares) {
+                acc = strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), cq, w, kShares);
+                if (w) acc_store(l, acc, part + (w - 1) * 1024);
+            }
+            bar<T>();
+            if (w == 0) {
+#pragma unroll
+                for (int j = 0; j < kShares - 1; j++) acc_add(l, acc, part + j * 1024);
+                strip_limbs<false>(l, acc, none, q);
+                quotient_digits(l, q, b, XQ);
+            } else if (w == W - 1 && i && late) {
+                strip_carries(l, ctl, R + op, n2, base2, bs2);
+            }
+        } else if (w == 0) {
             if (i) strip_carries(l, ctl, R + op, n2, base2, bs2);
-            const uint32_t *src = R + o + k - 1 + g;
-#pragma unroll
-            for (int j = 0; j < 4; j++) z[j] = g + j < nt ? src[j] : 0u;
-            quad_balance(z, 0u);
-            store4(Td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] : 0u, g + 1 < nt ? z[1] : 0u,
-                   g + 2 < nt ? z[2] : 0u, g + 3 < nt ? z[3] : 0u);
+            top_digits(l, R + o + k - 1, nt, Td);
             wave_sync();
-            MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
-            // q_i = R_top W / B^(dp+3), formed from column dp + 1 up: limb j of q_i is column dp + 3 + j
-            strip_limbs<false>(l, strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), (dp + 1) >> 3), Limb4{0u, 0u, 0u, 0u}, z);
-            // to the quotient; the reversed digits of -q_i (limb b is its sign)
+            MP_STAMP(16 + 3 * (i % 5));
+            strip_limbs<false>(l, strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), cq), none, q);
             uint32_t *Q = R + k + 2 + o;
-            const int s = (int)quad_get(z, b + 2);
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int e = g + j - 2;              // limb of q_i
-                if ((unsigned)e < (unsigned)b) Q[e] = z[j];
-                z[j] = e <= b ? (e < 0 ? 0xFFFFFFFFu : ~z[j]) : 0u;   // (the two columns below pass the +1 on)
-            }
-            quad_balance(z, 1u);
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int e = g + j - 2;
-                if ((unsigned)e <= (unsigned)b) XQ[b - e] = bswap(z[j]);
-            }
-            if (l < kXPad) XQ[b + 1 + l] = 0u;
-            if (i == 0) {
-                if (l == 0) Q[b] = (uint32_t)s;
-            } else {
-                add_small(l, Q + b, d + 1 - op, s);
-            }
+            const int sign = (int)quad_get(q, b + 2);
+            quotient_limbs(l, Q, q, b);
+            quotient_digits(l, q, b, XQ);
+            quotient_sign(l, Q + b, sign, d - op);
         }
         bar<T>();
         MP_STAMP(17 + 3 * (i % 5));
+        if (SHARED && w == 0) {
+            uint32_t *Q = R + k + 2 + o;
+            quotient_limbs(l, Q, q, b);
+            quotient_sign(l, Q + b, (int)quad_get(q, b + 2), d - op);
+        }
         // R -= v q_i
-        strips<T, FAST>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
+        strips<T, M>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
         bar<T>();
         MP_STAMP(18 + 3 * (i % 5));
     }

@@ -251,21 +251,24 @@ struct Diagonals {
     }
 };
 
-// The accumulator of the strip whose first block is S0.  Steps of kDiags
+// The accumulator of the strip whose first block is S0, or the share `part` of
+// `parts` of its diagonals (the first share the smallest).  Steps of kDiags
 // diagonals; the last may pass the end: it reads zeros there (of the short
 // digits, or blocks below the long ones').  FAST, for kernels with registers to
 // spare and few waves per SIMD to hide LDS reads behind: the next step's
 // operands in flight.
 template <bool FAST>
-MP_DEV MfmaAcc strip_sums(const Operands &o, int S0)
+MP_DEV MfmaAcc strip_sums(const Operands &o, int S0, int part = 0, int parts = 1)
 {
     constexpr int D = kDiags;
     MfmaAcc acc = mfma_zero();
     const int dlo = imax(0, S0 - o.nyblk + 1), dhi = imin(o.dmax, S0 + 31);
     int n = uniform(dhi - dlo + D) / D;          // steps
     if (n <= 0) return acc;
+    const int first = n * part / parts, d0 = dlo + D * first;
+    n = n * (part + 1) / parts - first;
     // (addresses of a step's last diagonal: the others lie at positive offsets)
-    uint32_t x = opaque(o.x - 32 * (dlo + D - 1)), y = opaque(o.y + 16 * (S0 - dlo - (D - 1)));
+    uint32_t x = opaque(o.x - 32 * (d0 + D - 1)), y = opaque(o.y + 16 * (S0 - d0 - (D - 1)));
     if constexpr (FAST) {
         Diagonals<D> a, b;
         a.load(x, y);
@@ -310,6 +313,27 @@ MP_DEV void strip_sums2(const Operands &o, int SA, int SB, MfmaAcc &accA, MfmaAc
         x -= 32;
         ya -= 16;
         yb -= 16;
+    }
+}
+
+// an accumulator through LDS, 1024 words from p, and its sum with another
+MP_DEV void acc_store(int l, const MfmaAcc &a, uint32_t *p)
+{
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        store4(p + 256 * j + 4 * l, (uint32_t)a[4 * j], (uint32_t)a[4 * j + 1], (uint32_t)a[4 * j + 2],
+               (uint32_t)a[4 * j + 3]);
+}
+
+MP_DEV void acc_add(int l, MfmaAcc &a, const uint32_t *p)
+{
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const Limb4 v = load4(p + 256 * j + 4 * l);
+        a[4 * j] += (int)v.x;
+        a[4 * j + 1] += (int)v.y;
+        a[4 * j + 2] += (int)v.z;
+        a[4 * j + 3] += (int)v.w;
     }
 }
 

@@ -30,7 +30,12 @@ int block_max()
     return mp::block_limit(sl == MP_SMALL_LIMIT_AUTO ? kAutoLimit : sl);
 }
 
-size_t body_bytes(int nu, int nv) { return (size_t)mp::plan_body(nu, nv).total * 4; }
+// LDS of a division kernel
+size_t body_bytes(int nu, int nv, mp::Mode mode = mp::Mode::kPacked)
+{
+    const int n = mp::plan_body(nu, nv).total;
+    return (size_t)4 * (mode == mp::Mode::kShared ? mp::r4(n) + mp::kPartWords : n);
+}
 
 // ------------------------------------------------------------ ragged batches
 //
@@ -213,11 +218,19 @@ int device_cus()
     return cus[dev];
 }
 
-// whether `batch` workgroups of T threads all fit the device at four waves per
-// SIMD: then the kernels built for that finish sooner
-bool fast_fits(int T, int64_t batch)
+// The division kernel of a batch of `batch` workgroups of T threads.  Those
+// built for four waves per SIMD finish sooner as long as the device holds the
+// batch at that; and up to three instances per compute unit are faster if four
+// waves share each quotient product (us, one wave and four: 1 of 1024 by 512
+// limbs 22.8 and 21.3, 768 26.7 and 26.1, 1024 27.4 and 28.1; 512 of 4096 by
+// 2048 73.5 and 70.2; 256 of 8192 by 4096 135 and 124), which is every such
+// batch of more than 256 threads per instance.
+mp::Mode division_mode(int T, int64_t batch)
 {
-    return batch * (T / 64) <= (int64_t)16 * device_cus();
+    const int cus = device_cus();
+    return batch * (T / 64) > (int64_t)16 * cus ? mp::Mode::kPacked
+           : batch <= (int64_t)3 * cus          ? mp::Mode::kShared
+                                                : mp::Mode::kFast;
 }
 
 // The work queue of mp_divrem_ragged_static: a library-owned array of one
@@ -254,9 +267,10 @@ bool ragged_direct(const uint32_t *u_pool, const uint32_t *v_pool, const mp_desc
 {
     const int cus = device_cus();
     if (count > 2 * cus) return false;
-    const auto launch = fast_fits(1024, count) ? mp::launch_ragged_direct<1024, true>
-                                               : mp::launch_ragged_direct<1024, false>;
-    *result = status_of(launch(count, body_bytes(mp::kMaxLimbs, mp::kMaxLimbs), st, u_pool, v_pool, desc, q_pool,
+    const mp::Mode mode = division_mode(1024, count);
+    const auto launch = mode == mp::Mode::kPacked ? mp::launch_ragged_direct<1024, mp::Mode::kPacked>
+                                                  : mp::launch_ragged_direct<1024, mp::Mode::kShared>;
+    *result = status_of(launch(count, body_bytes(mp::kMaxLimbs, mp::kMaxLimbs, mode), st, u_pool, v_pool, desc, q_pool,
                                r_pool, inst_status, pools, block_max()));
     return true;
 }
@@ -387,14 +401,20 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(h > 0 ? h : 1);
-    const size_t bytes = body_bytes(h + 1, nv);
+    const mp::Mode mode = division_mode(T, batch);
+    const size_t bytes = body_bytes(h + 1, nv, mode);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
-    const bool fast = fast_fits(T, batch);
-    const auto launch = T == 256   ? (fast ? mp::launch_shinv<256, true> : mp::launch_shinv<256, false>)
-                        : T == 512 ? (fast ? mp::launch_shinv<512, true> : mp::launch_shinv<512, false>)
-                                   : (fast ? mp::launch_shinv<1024, true> : mp::launch_shinv<1024, false>);
+    using mp::Mode;
+    const auto launch =
+        mode == Mode::kFast     ? mp::launch_shinv<256, Mode::kFast>
+        : mode == Mode::kShared ? (T == 256   ? mp::launch_shinv<256, Mode::kShared>
+                                   : T == 512 ? mp::launch_shinv<512, Mode::kShared>
+                                              : mp::launch_shinv<1024, Mode::kShared>)
+                                : (T == 256   ? mp::launch_shinv<256, Mode::kPacked>
+                                   : T == 512 ? mp::launch_shinv<512, Mode::kPacked>
+                                              : mp::launch_shinv<1024, Mode::kPacked>);
     return status_of(launch(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
 }
 
@@ -407,14 +427,20 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
     const int T = threads_for(nu);
-    const size_t bytes = body_bytes(nu, nv);
+    const mp::Mode mode = division_mode(T, batch);
+    const size_t bytes = body_bytes(nu, nv, mode);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
-    const bool fast = fast_fits(T, batch);
-    const auto launch = T == 256   ? (fast ? mp::launch_divrem<256, true> : mp::launch_divrem<256, false>)
-                        : T == 512 ? (fast ? mp::launch_divrem<512, true> : mp::launch_divrem<512, false>)
-                                   : (fast ? mp::launch_divrem<1024, true> : mp::launch_divrem<1024, false>);
+    using mp::Mode;
+    const auto launch =
+        mode == Mode::kFast     ? mp::launch_divrem<256, Mode::kFast>
+        : mode == Mode::kShared ? (T == 256   ? mp::launch_divrem<256, Mode::kShared>
+                                   : T == 512 ? mp::launch_divrem<512, Mode::kShared>
+                                              : mp::launch_divrem<1024, Mode::kShared>)
+                                : (T == 256   ? mp::launch_divrem<256, Mode::kPacked>
+                                   : T == 512 ? mp::launch_divrem<512, Mode::kPacked>
+                                              : mp::launch_divrem<1024, Mode::kPacked>);
     return status_of(launch(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
 }
 

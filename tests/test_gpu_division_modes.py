@@ -1,0 +1,47 @@
+"""The division kernels of small, middle and large batches give the same results.
+
+Up to three instances per compute unit share their quotient products among four
+waves, batches of one round of 256-thread workgroups run kernels with more
+registers, larger ones a third kind.  The same operands, at the lengths where
+blocks and strips end, repeated to batches of each kind, against the oracle."""
+import random
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2606_06386_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+B = 1 << 32
+
+
+def _operands(d, k):
+    rng = random.Random(1000 * d + k)
+    h = d + k
+    us, vs = [], []
+    for v in (rng.getrandbits(32 * k + 32) | 1 << (32 * k + 31), B ** k + 1, B ** (k + 1) - 1, B ** k + rng.getrandbits(32 * k)):
+        w = rng.getrandbits(32 * max(d - 1, 1)) | 1
+        for u in (rng.getrandbits(32 * h) | 1 << (32 * h - 1), B ** h - 1, v * w + v - 1, v * w, v - 1):
+            us.append(min(u, B ** h - 1))
+            vs.append(v)
+    return us, vs, h
+
+
+# quotient limbs at the ends of one and two blocks (and of those whose carries may be late), divisors of one to three strips
+@pytest.mark.parametrize("d,k", [(1, 1), (8, 3), (39, 60), (132, 254), (243, 255), (244, 247), (245, 300), (252, 260),
+                                 (253, 510), (504, 247), (505, 520), (1030, 700), (1, 1020)])
+@pytest.mark.parametrize("per_cu", [0, 3, 4, 5])
+def test_every_kind_of_batch(d, k, per_cu):
+    import torch
+    from paper_2606_06386_amd import binding
+    us, vs, h = _operands(d, k)
+    n = max(len(us), per_cu * torch.cuda.get_device_properties(0).multi_processor_count)
+    u, v = (np.stack([I.from_int(x, w) for x in xs]) for xs, w in ((us, h), (vs, k + 1)))
+    rows = torch.arange(n, device="cuda") % len(us)
+    dev = [torch.from_numpy(x.view(np.int32)).cuda()[rows].contiguous() for x in (u, v)]
+    got = [x.cpu().numpy().view(np.uint32) for x in binding.divrem(dev[0], dev[1], nq=d + 1)]
+    want = oracle.divrem(u, v, nq=d + 1, nr=k + 1)
+    rows = rows.cpu().numpy()
+    for g, w, name in zip(got, want, ("quotient", "remainder", "status")):
+        assert (g == np.asarray(w).view(np.uint32)[rows]).all(), name
