@@ -147,7 +147,7 @@ MP_DEV void strips(int l, uint32_t *ctl, const Operands &o, uint32_t *R, int nco
         const int i = u < units ? 1 + u * step : 0;
         if (step == 2 && u < units && i < n) {
             MfmaAcc accA, accB;
-            strip_sums2(o, b + i * kStripBlks, b + (i + 1) * kStripBlks, accA, accB);
+            strip_sums2(o, b + i * kStripBlks, accA, accB);
             strip_out(l, ctl, accA, R, ncols, base, i);
             strip_out(l, ctl, accB, R, ncols, base, i + 1);
         } else {

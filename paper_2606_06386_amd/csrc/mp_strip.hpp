@@ -296,23 +296,35 @@ MP_DEV MfmaAcc strip_sums(const Operands &o, int S0, int part = 0, int parts = 1
     return acc;
 }
 
-// the same for two strips at once over the diagonals [0, dmax], which both
-// must need in full (S0 >= dmax - 31): each X fragment serves both
-MP_DEV void strip_sums2(const Operands &o, int SA, int SB, MfmaAcc &accA, MfmaAcc &accB)
+// The same for two adjacent strips at once over the diagonals [0, dmax], which
+// both must need in full (SA >= dmax - 31): each X fragment serves both, and one
+// address steps over two diagonals.
+MP_DEV void strip_sums2(const Operands &o, int SA, MfmaAcc &accA, MfmaAcc &accB)
 {
     accA = mfma_zero();
     accB = mfma_zero();
-    uint32_t x = opaque(o.x), ya = opaque(o.y + 16 * SA), yb = opaque(o.y + 16 * SB);
-    for (int n = uniform(o.dmax); n >= 0; n--) {
-        const XRaw r = xraw_at(x, 0);
-        const Limb4 va = lds_quad(ya, 0), vb = lds_quad(yb, 0);
+    uint32_t x = o.x, y = o.y + 16 * SA;
+    const auto one = [&](int j) {                // diagonal j below the addresses
+        const XRaw r = xraw_at(x, -8 * j);
+        const Limb4 va = lds_quad(y, -j), vb = lds_quad(y, kStripBlks - j);
         const XFrag f = xfrag(r, o.sft);
         accA = mfma_x(accA, f, va);
         accB = mfma_x(accB, f, vb);
         sched_loads_first();
+    };
+    const int n = uniform(o.dmax) + 1;
+    if (n & 1) {
+        one(0);
         x -= 32;
-        ya -= 16;
-        yb -= 16;
+        y -= 16;
+    }
+    x = opaque(x - 32);                          // (offsets from an address are not negative)
+    y = opaque(y - 16);
+    for (int i = n >> 1; i > 0; i--) {
+        one(-1);
+        one(0);
+        x -= 64;
+        y -= 32;
     }
 }
 
@@ -409,8 +421,10 @@ MP_DEV bool quad_balance(uint32_t (&z)[4], uint32_t cin)
 template <bool ADD>
 MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[4])
 {
-    int w0 = 1, w1 = 256, w2 = 65536, w3 = 16777216;
-    asm("" : "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3));   // (every term one 64-bit multiply-add)
+    // every term one 64-bit multiply-add (the carry's weight hidden apart from
+    // w0, or the compiler adds before it multiplies, in 64 bits)
+    int w0 = 1, w1 = 256, w2 = 65536, w3 = 16777216, wc = 1;
+    asm("" : "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3), "+s"(wc));
     const uint32_t ad[4] = {add.x, add.y, add.z, add.w};
     int64_t s[4];
 #pragma unroll
@@ -422,7 +436,7 @@ MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[
         if constexpr (ADD) s[j] = (int64_t)((uint64_t)ad[j] * (uint32_t)w0 + (uint64_t)s[j]);
     }
 #pragma unroll
-    for (int j = 1; j < 4; j++) s[j] += (int64_t)(int32_t)(s[j - 1] >> 32) * w0;
+    for (int j = 1; j < 4; j++) s[j] += (int64_t)(int32_t)(s[j - 1] >> 32) * wc;
 #pragma unroll
     for (int j = 0; j < 4; j++) z[j] = (uint32_t)s[j];
     const uint32_t c = (uint32_t)(s[3] >> 32);
