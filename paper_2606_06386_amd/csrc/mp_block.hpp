@@ -211,10 +211,11 @@ MP_DEV int wave_prec(int ln, const uint32_t *x, int n)
     return 0;
 }
 
-// limbs a Newton step to f limbs starts from
-MP_HD int newton_from(int f) { return (f + 4) >> 1; }
+constexpr int kStartLimbs = 46;   // longest iterate of newton_start
 
-constexpr int kStartLimbs = 40;   // longest iterate of newton_start
+// limbs a Newton step to f limbs starts from: the first step's are exact to one
+// unit, so it needs one limb less (see newton)
+MP_HD int newton_from(int f) { return (f + (f <= 2 * kStartLimbs - 2 ? 3 : 4)) >> 1; }
 
 // limbs of the iterate the Newton steps to F limbs start from
 MP_HD int start_limbs(int F)
@@ -244,7 +245,8 @@ MP_DEV uint32_t start_digits(int l, const FV &v, int k, int lz)
 // it one dependent chain of 20 instructions; a Newton step on the matrix core
 // costs 4000 to 5000 however short its operands (its LDS round trips and carry
 // passes), so 25 steps here (37 limbs) beat the five Newton steps from the 112
-// bits of one reciprocal.  scratch: 64 words.
+// bits of one reciprocal.  (46 limbs are what 63 lanes of 24 bits leave exact to
+// one unit.)  scratch: 64 words.
 MP_DEV void newton_start(int l, uint32_t V, int lz, int f, uint32_t *scratch, uint32_t *w)
 {
     constexpr double kRound = 0x1.8p52;          // (adding it leaves the integer in the low mantissa bits)
@@ -254,24 +256,26 @@ MP_DEV void newton_start(int l, uint32_t V, int lz, int f, uint32_t *scratch, ui
                      (double)(int)readlane(V, 3) * 0x1p-72;
     double r = __builtin_amdgcn_rcp(d);
     r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    r = -__builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
-    uint32_t vA = shfl_up1(V), vB = shfl_up1(vA);
-    int a = l == 1 ? 1 << (e - 24) : 0, digit = 0;
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    constexpr int kHalf = 1 << 23;
+    int vA = -(int)shfl_up1(V), vB = (int)shfl_up1((uint32_t)vA);
+    int a = (l == 1 ? 1 << (e - 24) : 0) + kHalf, digit = 0;   // (a: the part plus kHalf)
     for (int t = 0; t < n; t++) {
         const int a0 = (int)readlane((uint32_t)a, 2 * t), a1 = (int)readlane((uint32_t)a, 2 * t + 1),
-                  a2 = (int)readlane((uint32_t)a, 2 * t + 2), a3 = (int)readlane((uint32_t)a, 2 * t + 3);
+                  a2 = (int)readlane((uint32_t)a, 2 * t + 2), a3 = (int)readlane((uint32_t)a, 2 * t + 3) - kHalf;
+        // (as a double: the bits of kRound, less the three kHalf)
         const int64_t S = (int64_t)((uint64_t)(int64_t)a0 << 48) + ((int64_t)a1 * (1 << 24) + a2);
-        const double rem = __builtin_fma((double)a3, 0x1p-24, __builtin_bit_cast(double, 0x4338000000000000ll + S) - kRound);
-        const uint64_t b = __builtin_bit_cast(uint64_t, __builtin_fma(rem, r, kRound + 0x1p23));
-        // minus the digit's halves, the lower one in [-2^23, 2^23)
-        const int ql = (int)((uint32_t)b & 0xFFFFFFu) - (1 << 23);
+        const int64_t bits = 0x4338000000000000ll - (int64_t)((uint64_t)kHalf * ((1ull << 48) + (1ull << 24) + 1)) + S;
+        const double rem = __builtin_fma((double)a3, 0x1p-24, __builtin_bit_cast(double, bits) - kRound);
+        const uint64_t b = __builtin_bit_cast(uint64_t, __builtin_fma(rem, r, kRound + kHalf));
+        // the digit's halves, the lower one in [-2^23, 2^23)
+        const int ql = (int)((uint32_t)b & 0xFFFFFFu) - kHalf;
         const int qh = (int)(alignbit((uint32_t)(b >> 32), (uint32_t)b, 24) << 5) >> 5;
-        const int64_t P = (int64_t)qh * (int)vA + (a + (1 << 23)) + (int64_t)ql * (int)vB;
-        a = (int)((uint32_t)P & 0xFFFFFFu) - (1 << 23) +
-            (int)shfl_down1(alignbit((uint32_t)((uint64_t)P >> 32), (uint32_t)P, 24));
-        digit = l == 2 * t + 1 ? -qh : l == 2 * t + 2 ? -ql : digit;
-        vA = shfl_up1(vB);
-        vB = shfl_up1(vA);
+        const int64_t P = (int64_t)qh * vA + (a + (int64_t)ql * vB);
+        a = (int)((uint32_t)P & 0xFFFFFFu) + (int)shfl_down1(alignbit((uint32_t)((uint64_t)P >> 32), (uint32_t)P, 24));
+        digit = l == 2 * t + 1 ? qh : l == 2 * t + 2 ? ql : digit;
+        vA = (int)shfl_up1((uint32_t)vB);
+        vB = (int)shfl_up1((uint32_t)vA);
     }
     // the borrows of the digits (lane 1 the highest), their bytes, and the limbs
     const uint64_t G = __builtin_bitreverse64(ballot(digit < 0)), X = G | __builtin_bitreverse64(ballot(digit == 0));
@@ -302,7 +306,8 @@ MP_DEV void newton_start(int l, uint32_t V, int lz, int f, uint32_t *scratch, ui
 // residual e = (v w - B^(k+f)) / B^c and adds -w e: both products fill one
 // 256-column strip, and both results go from the accumulators to the digits of
 // the next product in registers.  With |E| the error of w in units of its last
-// limb, the new one is at most E^2 / B (quadratic term) + 1 (floor) + 0.1:
+// limb, the new one is at most E^2 / B (quadratic term; E^2 in the first step,
+// to 2f - 2 limbs, where newton_start's |E| is 1) + 1 (floor) + 0.1:
 // limbs of v below s are left out (but for those the strip reads anyway), s <=
 // k - 1 - f', which moves e by less than B^f, and columns of e below c = sh - f
 // - 2, of either sign and below 2^26 B^c.  So |E| <= 3 at the end.

@@ -103,7 +103,7 @@ constexpr int kDppRowBcast31 = 0x143;    // lane 31 to rows 2 and 3
 template <int CTRL, int ROWS = 0xF>
 MP_DEV uint32_t dpp(uint32_t x)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, ROWS == 0xF);
 }
 
 // value held by lane-1 (lane 0 receives 0)
