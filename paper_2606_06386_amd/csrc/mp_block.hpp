@@ -189,26 +189,56 @@ struct Shifted {
     }
 };
 
-// number of significant limbs of x[0, n) (global memory), by one wave from the
-// top: 64 limbs first (most numbers fill their row), then 1024 per step
-MP_DEV int wave_prec(int ln, const uint32_t *x, int n)
+// limb n - 64 + l of x (zero below its first): most numbers fill their row
+MP_DEV uint32_t top_limb(int l, const uint32_t *x, int n) { return n - kLanes + l >= 0 ? x[n - kLanes + l] : 0u; }
+
+// Number of significant limbs of x[0, n) (global memory), the same in all waves:
+// by every wave from its top_limb, or else by all of them together, 8 limbs per
+// thread and step (one wave by itself took eight steps of 5000 cycles for 8192
+// limbs).  slot: two words per wave.
+template <int T>
+MP_DEV int precision(int l, int w, const uint32_t *x, int n, uint32_t top, uint32_t *slot)
 {
-    uint64_t m = ballot(n - kLanes + ln >= 0 && x[n - kLanes + ln] != 0u);
+    constexpr int W = T / kLanes, R = 8;
+    const uint64_t m = ballot(top != 0u);
     if (m) return n - __builtin_clzll(m);
-    for (int top = n - kLanes; top > 0; top -= 16 * kLanes) {
-        uint32_t v[16];
+    for (int s = (n - 1) / (R * T); s >= 0; s--) {
+        const int r0 = (s * W + w) * R;
+        uint32_t v[R];
 #pragma unroll
-        for (int j = 0; j < 16; j++) {
-            const int i = top - (j + 1) * kLanes + ln;
-            v[j] = i >= 0 ? x[i] : 0u;
+        for (int j = 0; j < R; j++) {
+            const int i = (r0 + j) * kLanes + l;
+            v[j] = i < n ? x[i] : 0u;
         }
+        int found = 0;
 #pragma unroll
-        for (int j = 0; j < 16; j++) {
-            m = ballot(v[j] != 0u);
-            if (m) return top - j * kLanes - __builtin_clzll(m);
+        for (int j = 0; j < R; j++) {
+            const uint64_t mj = ballot(v[j] != 0u);
+            if (mj) found = (r0 + j + 1) * kLanes - __builtin_clzll(mj);
         }
+        uint32_t *sl = slot + (s & 1) * W;       // (the step before may still be read)
+        if (l == 0) sl[w] = (uint32_t)found;
+        bar<T>();
+        const uint32_t f = l < W ? sl[l] : 0u;
+        const uint64_t mf = ballot(f != 0u);
+        if (mf) return (int)readlane(f, 63 - __builtin_clzll(mf));
     }
     return 0;
+}
+
+// whether x[0, n) is zero, by one wave, 1024 limbs at a time
+MP_DEV bool all_zero(int l, const uint32_t *x, int n)
+{
+    for (int b = n; b > 0; b -= 16 * kLanes) {
+        uint32_t any = 0;
+#pragma unroll
+        for (int j = 0; j < 16; j++) {
+            const int i = b - (j + 1) * kLanes + l;
+            any |= i >= 0 ? x[i] : 0u;
+        }
+        if (ballot(any != 0u)) return false;
+    }
+    return true;
 }
 
 constexpr int kStartLimbs = 46;   // longest iterate of newton_start
@@ -241,8 +271,8 @@ MP_DEV uint32_t start_digits(int l, const FV &v, int k, int lz)
 // upper and the lower half of the digit: vA, vB).  A step takes the digit from
 // the leading lanes of r (as an integer modulo 2^64, which drops the lanes
 // above: they cancel) times 1 / v' in double precision, to within 2^-2 of r/v':
-// |r| stays below 0.8 v' 2^(-48 t).  It costs about 200 cycles, nearly all of
-// it one dependent chain of 20 instructions; a Newton step on the matrix core
+// |r| stays below 0.8 v' 2^(-48 t).  It costs about 270 cycles, nearly all of
+// it one dependent chain through scalar and vector units; a Newton step on the matrix core
 // costs 4000 to 5000 however short its operands (its LDS round trips and carry
 // passes), so 25 steps here (37 limbs) beat the five Newton steps from the 112
 // bits of one reciprocal.  (46 limbs are what 63 lanes of 24 bits leave exact to
@@ -415,9 +445,19 @@ MP_DEV void quotient_sign(int l, uint32_t *Q, int sign, int n)
     }
 }
 
-// limbs of a dividend: an array (wave_prec reads it), or B^e
-MP_DEV int top_limb(int l, const Span &u, int n) { return wave_prec(l, u.p, n); }
-MP_DEV int top_limb(int, const PowB &u, int) { return u.e + 1; }
+// limbs of a dividend: an array, or B^e
+MP_DEV uint32_t top_limb(int l, const Span &u, int n) { return top_limb(l, u.p, n); }
+MP_DEV uint32_t top_limb(int, const PowB &, int) { return 0u; }
+template <int T>
+MP_DEV int precision(int l, int w, const Span &u, int n, uint32_t top, uint32_t *slot)
+{
+    return precision<T>(l, w, u.p, n, top, slot);
+}
+template <int T>
+MP_DEV int precision(int, int, const PowB &u, int, uint32_t, uint32_t *)
+{
+    return u.e + 1;
+}
 
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
 // U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
@@ -435,8 +475,9 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     const int w = wave_index(), l0 = lane_at(nu), t = w * kLanes + l0, nr = r ? nv : 0;
     MP_RSTAMP(14);
     MP_STAMP(0);
-    // precisions (every wave finds them by itself), and the cases that need no division
-    int h = top_limb(l0, U, nu), k = wave_prec(l0, v, nv) - 1;
+    // precisions, and the cases that need no division
+    const uint32_t tu = top_limb(l0, U, nu), tv = top_limb(l0, v, nv);
+    int h = precision<T>(l0, w, U, nu, tu, ctl + kCtlPrec), k = precision<T>(l0, w, v, nv, tv, ctl + kCtlPrec + 2 * W) - 1;
     if (k < 0 || h <= k) {                            // v = 0, or u < v: (0, u)
         for (int i = t; i < nq; i += T) q[i] = 0u;
         for (int i = t; i < nr; i += T) r[i] = k >= 0 && i < h ? U(i) : 0u;
@@ -444,7 +485,8 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         return;
     }
     const int d = h - k;
-    if (uniform(v[k]) == 1u && wave_prec(l0, v, k) == 0) {   // v = B^k: q = u >> k, r the limbs below
+    const uint32_t vk = k >= nv - kLanes ? readlane(tv, k - nv + kLanes) : uniform(v[k]);
+    if (vk == 1u && all_zero(l0, v, k)) {   // v = B^k: q = u >> k, r the limbs below
         const bool ok = d <= nq;                         // (limb h - 1 is not zero)
         for (int i = t; i < nq; i += T) q[i] = ok && i < d ? U(i + k) : 0u;
         for (int i = t; i < nr; i += T) r[i] = ok && i < k ? U(i) : 0u;
@@ -466,7 +508,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     MP_STAMP(1);
     // the first wave: the start of the inverse; the others: the divisor's digits and the zero pads
     if (w == 0) {
-        const int l = lane_at(k), lz = __builtin_clz(uniform(Vv(k)));
+        const int l = lane_at(k), lz = __builtin_clz(vk);
         const int f = start_limbs(dp + 2);
         newton_start(l, start_digits(l, Vv, k, lz), lz, f, Td, lds + pl.offW + dp + 2 - f);
     } else {
