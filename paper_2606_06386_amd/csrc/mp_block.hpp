@@ -67,24 +67,28 @@ MP_HD int block_limit(int limit) { return hmax(16, hmin(kBlockMax, (2 * limit - 
 
 // ---------------------------------------------------------------- LDS layout
 //
-// ctl | pad | V plane 0 | pad | V plane 1 | pad | T plane 0 | pad | T plane 1 |
-// pad | W reversed | -q reversed | W | R
-// (pads of kPadBlk zero blocks shared by their neighbours; T: R_top, and the
-// residuals of the Newton steps).  R holds the dividend's h limbs and above
+// ctl | pad | V planes 0 .. 3 | T planes 0, 1 | W reversed | -q reversed | W | R
+// (pads of zero half-blocks before the first plane and after each; T: R_top, and
+// the residuals of the Newton steps).  R holds the dividend's h limbs and above
 // them the quotient: limb j of q goes to R[k + 2 + j], which the remainder has
 // left by the time the block is done.
 struct BodyPlan {
-    int nbV, lyV, offV;       // 8-limb blocks of the divisor's digits, distance of the planes, first word
-    int offT;                 // the same planes for T: 32 blocks each
+    int nV, lyV, offV;        // limbs of the divisor's planes, distance of the planes, first word
+    int offT;                 // T's two planes of 32 blocks
     int offX, offQ, offW, offR;   // W's reversed digits, -q's, W's limbs, R
     int capR;
     int total;
 };
 
+constexpr int kPad4 = kPadWords / 2;             // zero words a strip reads on each side of one of four planes
+constexpr int kPlaneT = 4 * kStripBlks;          // words of T's planes
+constexpr int kLyT = kPlaneT + kPadWords;        // distance of T's planes
+
+// distance of V's planes of n words: a pad between them, and 16 modulo 32
+MP_HD constexpr int plane_distance(int n) { return ((n + kPad4 + 15) & ~31) + 16; }
+
 // behind the plan, Mode::kShared: partial sums of the quotient products, by the waves [1, kShares)
 constexpr int kShares = 4, kPartWords = (kShares - 1) * 1024;
-
-constexpr int kLyT = 4 * kStripBlks + kPadWords;   // distance of T's planes
 
 // a dividend of at most nu and a divisor of at most nv limbs (each one more
 // inside, for divisors of one limb, which are shifted up by one)
@@ -93,10 +97,10 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
     BodyPlan p{};
     const int ny = (nv < nu ? nv : nu) + 2;            // digit limbs of the divisor
     const int dm = block_precision(hmin(kBlockMax, nu + 1));
-    p.nbV = (ny + 7) >> 3;
-    p.offV = kCtlWords + kPadWords;
-    p.lyV = 4 * p.nbV + kPadWords;
-    p.offT = p.offV + 2 * p.lyV;
+    p.nV = (ny + 15) & ~15;
+    p.offV = kCtlWords + kPad4;
+    p.lyV = plane_distance(p.nV >> 2);
+    p.offT = p.offV + 4 * p.lyV + kPadWords - kPad4;
     p.offX = r4(p.offT + 2 * kLyT + kXLow);
     p.offQ = p.offX + dm + 4 + kXPad + kXLow;
     p.offW = p.offQ + dm + 1 + kXPad;
@@ -106,24 +110,30 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
     return p;
 }
 
-// limbs of strip s (accumulator acc) into R, its carry into the control slot of s
-MP_DEV void strip_out(int l, uint32_t *ctl, const MfmaAcc &acc, uint32_t *R, int ncols, int base, int s)
+// the quad of limbs of each lane (see quad_limb) to T's planes, zeros from limb n on
+MP_DEV void store_T(int l, uint32_t *td, const uint32_t (&z)[4], int n)
 {
-    const int k0 = base + s * kStrip + quad_limb(l);
-    Limb4 add{0u, 0u, 0u, 0u};
-    if (k0 >= 0 && k0 < ncols) add = load4(R + k0);
-    uint32_t z[4];
-    const int e = strip_limbs<true>(l, acc, add, z);
-    if (k0 >= 0) {
-        if (k0 + 3 < ncols) {
-            store4(R + k0, z[0], z[1], z[2], z[3]);
-        } else {
+    const int g = quad_limb(l);
+    store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < n ? z[0] : 0u, g + 1 < n ? z[1] : 0u, g + 2 < n ? z[2] : 0u,
+           g + 3 < n ? z[3] : 0u);
+}
+
+// R's quad of limbs at k0, its columns in [0, ncols)
+MP_DEV Limb4 quad_in(const uint32_t *R, int ncols, int k0)
+{
+    return k0 >= 0 && k0 < ncols ? load4(R + k0) : Limb4{0u, 0u, 0u, 0u};
+}
+
+MP_DEV void quad_out(uint32_t *R, int ncols, int k0, const uint32_t (&z)[4])
+{
+    if (k0 < 0) return;
+    if (k0 + 3 < ncols) {
+        store4(R + k0, z[0], z[1], z[2], z[3]);
+    } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++)
-                if (k0 + j < ncols) R[k0 + j] = z[j];
-        }
+        for (int j = 0; j < 4; j++)
+            if (k0 + j < ncols) R[k0 + j] = z[j];
     }
-    if (l == 0) ctl[kCtlStrip + s] = (uint32_t)e;
 }
 
 // R[c] += column c of x * y for c in [0, ncols), mod B^ncols, but for the
@@ -131,27 +141,40 @@ MP_DEV void strip_out(int l, uint32_t *ctl, const MfmaAcc &acc, uint32_t *R, int
 // strip_carries adds it.  x has at most kBlockMax + 1 limbs, y at least ncols
 // digit limbs, and the strips end at ncols (rounded up to 8 limbs), so that
 // every strip but the lowest needs every diagonal of x: a wave takes two of
-// these at a time, which share each fragment of x (a wave's step of one
-// diagonal is bound by its instructions, not by the matrix core: two products
-// take little longer than one).  FAST: one each as long as there are waves.
-// The lowest, partial strip comes last.  Shared quotient products: the first
-// wave, which stores the quotient's limbs before, takes the last share.  R is 16-byte aligned.
-template <int T, Mode M>
-MP_DEV void strips(int l, uint32_t *ctl, const Operands &o, uint32_t *R, int ncols, int base, int nstrips)
+// these at a time (strip_sums2).  FAST, few strips: one each, which takes less
+// time as long as there are waves and LDS reads do not bind (4096 by 1024 limbs,
+// four strips on eight waves: 55 us, in pairs 61; four on four waves of up to
+// four instances, 700 divisions of 2048 by 1024: 42 us, in pairs 39).  The
+// lowest, partial strip comes last.  Shared quotient products: the first wave,
+// which stores the quotient's limbs before, takes the last share.  R is 16-byte
+// aligned.
+template <int T, Mode M, class FX, class FY>
+MP_DEV void strips(uint32_t *ctl, const FX &xs, const FY &ys, uint32_t *R, int ncols, int base, int nstrips)
 {
     constexpr int W = T / kLanes;
     constexpr bool FAST = M != Mode::kPacked;
     const int w = wave_index(), n = nstrips - 1, b = base >> 3;
-    const int step = FAST && n <= W ? 1 : 2, units = (n + step - 1) / step;
-    for (int u = M == Mode::kShared ? (w ? w : W) - 1 : w; u <= units; u += W) {          // (unit `units`: the lowest strip)
-        const int i = u < units ? 1 + u * step : 0;
+    const int step = FAST && n <= (T == 256 ? 2 : 4) ? 1 : 2, units = (n + step - 1) / step;
+    for (int u = M == Mode::kShared ? (w ? w : W) - 1 : w; u <= units; u += W) {   // (unit `units`: the lowest strip)
+        const int i = u < units ? 1 + u * step : 0, l = lane_at(u);
+        const ShortDigits x = xs(l);
+        const Planes4 y = ys(l);
         if (step == 2 && u < units && i < n) {
-            MfmaAcc accA, accB;
-            strip_sums2(o, b + i * kStripBlks, accA, accB);
-            strip_out(l, ctl, accA, R, ncols, base, i);
-            strip_out(l, ctl, accB, R, ncols, base, i + 1);
+            MfmaAcc accE, accO;
+            strip_sums2<FAST>(x, y, b + i * kStripBlks, accE, accO);
+            const int k0 = base + i * kStrip + 16 * (l & 31) + 4 * (l >> 5);
+            uint32_t zE[4], zO[4];
+            const int e = strip_limbs2(l, accE, accO, [&](int odd) { return quad_in(R, ncols, k0 + 8 * odd); }, zE, zO);
+            quad_out(R, ncols, k0, zE);
+            quad_out(R, ncols, k0 + 8, zO);
+            if (l < 2) ctl[kCtlStrip + i + l] = l ? (uint32_t)e : 0u;
         } else {
-            strip_out(l, ctl, strip_sums<FAST>(o, b + i * kStripBlks), R, ncols, base, i);
+            const MfmaAcc acc = strip_sums<FAST>(x, y, b + i * kStripBlks);
+            const int k0 = base + i * kStrip + quad_limb(l);
+            uint32_t z[4];
+            const int e = strip_limbs<true>(l, acc, quad_in(R, ncols, k0), z);
+            quad_out(R, ncols, k0, z);
+            if (l == 0) ctl[kCtlStrip + i] = (uint32_t)e;
         }
     }
 }
@@ -362,23 +385,22 @@ MP_DEV void newton(int k, int dp, const uint32_t *vd, int lv, uint32_t *td, uint
         const uint32_t last = uniform(w[F - f]);
         int fn = F;                              // the next step of the schedule that ends at F
         while (newton_from(fn) > f) fn = newton_from(fn);
-        const int s = imax(0, k - 1 - fn) & ~7;
+        const int s = imax(0, k - 1 - fn) & ~15;
         const int sh = k - s + 2 * f - fn;       // w e / B^sh is the correction
         const int c0 = imax(0, sh - f - 2) & ~7, nx = k + 2 - s - c0;
         wave_sync();
         // -e: the two's complement of the columns [c0, c0 + nx) of v w (B^(k+f-s) lies above them), as digits
         uint32_t z[4];
-        strip_limbs<false>(l, strip_sums<FAST>(operands(l, xw, f + 2, vd + (s >> 1), lv, k + 2 - s), c0 >> 3), none, z);
+        strip_limbs<false>(l, strip_sums<FAST>(short_digits(l, xw, f + 2), planes4(l, vd + (s >> 2), lv, k + 2 - s), c0 >> 3), none, z);
 #pragma unroll
         for (int j = 0; j < 4; j++) z[j] = g + j < nx ? ~z[j] : 0u;
         quad_balance(z, 1u);
-        store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nx ? z[0] : 0u, g + 1 < nx ? z[1] : 0u,
-               g + 2 < nx ? z[2] : 0u, g + 3 < nx ? z[3] : 0u);
+        store_T(l, td, z, nx);
         wave_sync();
         // the new limbs: columns [shc, shc + m) of w (-e), and the old last limb at column shc + m
         const int shc = sh - c0, cB = (shc - 2) & ~7, m = fn - f, i0 = cB + g - shc, at = shc + m - cB;
         Limb4 add{i0 == m ? last : 0u, i0 + 1 == m ? last : 0u, i0 + 2 == m ? last : 0u, i0 + 3 == m ? last : 0u};
-        strip_limbs<true>(l, strip_sums<FAST>(operands(l, xw, f + 2, td, kLyT, nx), cB >> 3), add, z);
+        strip_limbs<true>(l, strip_sums<FAST>(short_digits(l, xw, f + 2), planes(l, td, kLyT, nx), cB >> 3), add, z);
         const int over = (int)quad_get(z, at + 1);
         const uint32_t nl = quad_get(z, at);                 // the old last limb, moved
 #pragma unroll
@@ -408,8 +430,7 @@ MP_DEV void top_digits(int l, const uint32_t *src, int nt, uint32_t *td)
 #pragma unroll
     for (int j = 0; j < 4; j++) z[j] = g + j < nt ? src[g + j] : 0u;
     quad_balance(z, 0u);
-    store4(td + (l >> 5) * kLyT + 4 * (l & 31), g < nt ? z[0] : 0u, g + 1 < nt ? z[1] : 0u, g + 2 < nt ? z[2] : 0u,
-           g + 3 < nt ? z[3] : 0u);
+    store_T(l, td, z, nt);
 }
 
 // the reversed digits of -q_i to xq; q: limbs of R_top W / B^(dp+1), limb 2 + j is limb j of q_i, 2 + b its sign
@@ -513,15 +534,17 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         newton_start(l, start_digits(l, Vv, k, lz), lz, f, Td, lds + pl.offW + dp + 2 - f);
     } else {
         const int t1 = t - kLanes;
-        for (int i = t1; i < 5 * kPadWords; i += T - kLanes) {
-            const int b = i / kPadWords, j = i - b * kPadWords;
-            const int at = b < 3 ? pl.offV + b * pl.lyV : pl.offT + (b - 2) * kLyT;
-            lds[at - kPadWords + j] = 0u;
+        const int nw = pl.nV >> 2;                    // words of V's planes
+        for (int i = t1; i < pl.lyV - nw; i += T - kLanes) {
+            if (i < kPad4) lds[pl.offV - kPad4 + i] = 0u;
+#pragma unroll
+            for (int p = 0; p < 4; p++) Vd[p * pl.lyV + nw + i] = 0u;
         }
+        for (int i = t1; i < kPadWords; i += T - kLanes) Td[i - kPadWords] = Td[i + kPlaneT] = Td[i + kLyT + kPlaneT] = 0u;
         for (int i = pl.offX - kXLow + t1; i < pl.offW; i += T - kLanes) lds[i] = 0u;
-        const int rows = (8 * pl.nbV + 63) >> 6, per = (rows + W - 2) / (W - 1);
+        const int rows = (pl.nV + 63) >> 6, per = (rows + W - 2) / (W - 1);
         const int r0 = (w - 1) * per, r1 = imin(rows, r0 + per);
-        if (r0 < r1) balance_rows(l0, r0, r1, k + 1, 0u, Vv, StorePlane{Vd, 8 * pl.nbV, pl.lyV});
+        if (r0 < r1) balance_rows(l0, r0, r1, k + 1, 0u, Vv, StorePlane4{Vd, pl.nV, pl.lyV});
     }
     bar<T>();
     MP_STAMP(9);
@@ -547,6 +570,11 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     bool good = true;
     const int n2 = k + 2, bs2 = (n2 + kStrip - 1) / kStrip, base2 = ((n2 + 7) & ~7) - bs2 * kStrip;
     const Limb4 none{0u, 0u, 0u, 0u};
+    // the lanes' addresses of the products' operands, where registers allow
+    const int lf = lane_at(nb);
+    const ShortDigits xw0 = short_digits(lf, XW, dp + 4), xq0 = short_digits(lf, XQ, 0);
+    const Planes4 yv0 = planes4(lf, Vd, pl.lyV, n2);
+    Planes yt0 = planes(lf, Td, kLyT, 0);
     int o = d;
     for (int i = 0; i < nb; i++) {
         const int op = o;
@@ -569,7 +597,8 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             bar<T>();
             MfmaAcc acc;
             if (w < kShares) {
-                acc = strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), cq, w, kShares);
+                yt0.ny = nt;
+                acc = strip_sums<FAST>(xw0, yt0, cq, w, kShares);
                 if (w) acc_store(l, acc, part + (w - 1) * 1024);
             }
             bar<T>();
@@ -586,7 +615,13 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             top_digits(l, R + o + k - 1, nt, Td);
             wave_sync();
             MP_STAMP(16 + 3 * (i % 5));
-            strip_limbs<false>(l, strip_sums<FAST>(operands(l, XW, dp + 4, Td, kLyT, nt), cq), none, q);
+            if constexpr (FAST) {
+                yt0.ny = nt;
+                strip_limbs<false>(l, strip_sums<FAST>(xw0, yt0, cq), none, q);
+            } else {
+                strip_limbs<false>(
+                    l, strip_sums<FAST>(short_digits(l, XW, dp + 4), planes(l, Td, kLyT, nt), cq), none, q);
+            }
             uint32_t *Q = R + k + 2 + o;
             const int sign = (int)quad_get(q, b + 2);
             quotient_limbs(l, Q, q, b);
@@ -601,7 +636,9 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             quotient_sign(l, Q + b, (int)quad_get(q, b + 2), d - op);
         }
         // R -= v q_i
-        strips<T, M>(l, ctl, operands(l, XQ, b + 1, Vd, pl.lyV, k + 2), R + o, n2, base2, bs2);
+        strips<T, M>(
+            ctl, [&](int lu) { return FAST ? short_digits(xq0, b + 1) : short_digits(lu, XQ, b + 1); },
+            [&](int lu) { return FAST ? yv0 : planes4(lu, Vd, pl.lyV, n2); }, R + o, n2, base2, bs2);
         bar<T>();
         MP_STAMP(18 + 3 * (i % 5));
     }
@@ -650,9 +687,10 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         if (uniform(Q[d - 1]) != 0u) st = kInstQWidth;
     }
     const bool ok = st == kInstOk;
-    for (int i = t; i < nq; i += T) q[i] = ok && i < d ? Q[i] : 0u;
-    for (int i = t; i < nr; i += T) r[i] = ok && i <= k - sv ? Ra[i + sv] : 0u;
-    if (status && t == 0) *status = st;
+    const int te = w * kLanes + lane_at(st);
+    for (int i = te; i < nq; i += T) q[i] = ok && i < d ? Q[i] : 0u;
+    for (int i = te; i < nr; i += T) r[i] = ok && i <= k - sv ? Ra[i + sv] : 0u;
+    if (status && te == 0) *status = st;
     MP_STAMP(8);
     MP_RSTAMP(15);
 }

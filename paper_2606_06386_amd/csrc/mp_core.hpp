@@ -22,11 +22,10 @@ constexpr int kPad = kStrip + 8;         // zero guard on both sides of a staged
 
 // control block at the start of the instance's LDS (32-bit words)
 constexpr int kCtlOver = 0;      // 16 per-wave carries that run through a wave's columns
-constexpr int kCtlStrip = 16;    // strip carries: one word per strip, or two (vector ALU), up to 72 strips
-constexpr int kCtlPrec = 96;     // precisions: four words per wave
-constexpr int kCtlBcast = 240;   // 16 broadcast scalars
-constexpr int kCtlWords = 256;
-constexpr int kMaxStrips = 72;
+constexpr int kCtlStrip = 16;    // strip carries: one word per strip, or two (vector ALU: up to 64 strips)
+constexpr int kCtlPrec = 16;     // before them, precisions: four words per wave
+constexpr int kCtlBcast = 144;   // 16 broadcast scalars
+constexpr int kCtlWords = 160;
 
 #define MP_HD __host__ __device__ __forceinline__
 

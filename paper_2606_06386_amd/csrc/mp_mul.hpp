@@ -49,6 +49,20 @@ MP_HD int mul_valu_lds_words(int na, int nb)
     return kCtlWords + r4(lo + 1) + 4 + kPad + r4(hi + 1) + kPad + r4(na + nb) + 4;
 }
 
+struct Operands {
+    uint32_t x, sft;     // the short digits (see ShortDigits)
+    int dmax;
+    uint32_t y;          // LDS byte address of this lane's word of the long digits' planes for block 0
+    int nyblk;           // blocks of the long digits
+};
+
+// xr: nx reversed digit limbs; yb: planes (distance ly) of ny digit limbs
+MP_DEV Operands operands(int l, const uint32_t *xr, int nx, const uint32_t *yb, int ly, int ny)
+{
+    const ShortDigits s = short_digits(l, xr, nx);
+    return Operands{s.x, s.sft, s.dmax, lds_address(yb) + 4 * ((l >> 5) * ly + 4 * (l & 31)), (ny + 7) >> 3};
+}
+
 // acc += the diagonals [d, dhi] of the strip whose first block is S0
 MP_DEV void diagonal_sums(const Operands &o, int S0, int d, int dhi, MfmaAcc &acc)
 {

@@ -13,16 +13,9 @@
 
 namespace mp {
 
-constexpr int kYPadBlk = 31;   // zero blocks a strip reads on each side of a digit plane
-constexpr int kXPad = 16;      // zero words it reads on each side of the reversed short operand
-
-#ifndef MP_DIAGS
-#define MP_DIAGS 2
-#endif
-constexpr int kDiags = MP_DIAGS;   // diagonals per step of a product
-
-constexpr int kPadBlk = kYPadBlk + kDiags - 1, kPadWords = 4 * kPadBlk;
-constexpr int kXLow = kXPad + 8 * (kDiags - 1);   // zero words below the reversed digits
+constexpr int kPadBlk = 32, kPadWords = 4 * kPadBlk;   // zero blocks a strip may read on each side of a digit plane
+constexpr int kXPad = 16;            // zero words it reads on each side of the reversed short operand
+constexpr int kXLow = kXPad + 8;     // and below it where diagonals are taken in pairs
 
 constexpr int kStripBlks = kStrip / 8;
 
@@ -32,6 +25,16 @@ constexpr int kStripBlks = kStrip / 8;
 // operand's lie byte-reversed, so that a Toeplitz row is 16 consecutive bytes.
 // word of the planes holding limb k: block k / 8, plane (k / 4) % 2, word k % 4
 MP_DEV int plane_word(int k, int ly) { return ((k >> 1) & ~3) + (k & 3) + ((k >> 2) & 1) * ly; }
+
+// A divisor's lie in four, 2r + h holding the half-blocks h of the even (r = 0)
+// or odd blocks, so that every second of 64 blocks is read in consecutive chunks
+// (see strip_sums2).  Planes 16 words apart modulo 32 keep the even and odd
+// lanes of a read of 32 consecutive blocks on different banks (if the first is
+// an odd one, all but three in sixteen).
+MP_DEV int plane4_word(int k, int ly)
+{
+    return (((k >> 3) & 1) * 2 + ((k >> 2) & 1)) * ly + ((k >> 4) << 2) + (k & 3);
+}
 
 // ------------------------------------------------------------- row passes
 //
@@ -103,6 +106,15 @@ struct StorePlane {
     MP_DEV void operator()(int k, uint32_t z) const
     {
         if (k < n) p[plane_word(k, ly)] = z;
+    }
+};
+
+struct StorePlane4 {
+    uint32_t *p;
+    int n, ly;
+    MP_DEV void operator()(int k, uint32_t z) const
+    {
+        if (k < n) p[plane4_word(k, ly)] = z;
     }
 };
 
@@ -209,21 +221,24 @@ MP_DEV MfmaAcc mfma_x(MfmaAcc acc, const XFrag &x, const Limb4 &y)
     return mfma_i8(acc, x.a, x.b, x.c, x.d, y.x, y.y, y.z, y.w);
 }
 
-struct Operands {
+struct ShortDigits {
     uint32_t x;          // LDS byte address of this lane's word of the reversed short digits at diagonal 0
     uint32_t sft;        // and its byte shift
-    int dmax;            // last diagonal that touches the short digits
-    uint32_t y;          // LDS byte address of this lane's word of the long digits' planes for block 0
-    int nyblk;           // blocks of the long digits
+    int dmax;            // last diagonal that touches them
 };
 
-// xr: nx reversed digit limbs; yb: planes (distance ly) of ny digit limbs
-MP_DEV Operands operands(int l, const uint32_t *xr, int nx, const uint32_t *yb, int ly, int ny)
+// xr: nx reversed digit limbs
+MP_DEV ShortDigits short_digits(int l, const uint32_t *xr, int nx)
 {
     const int p = l & 31, h = l >> 5;
     const int ox = 16 * h - 1 - (16 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3));   // (from the end of the digits)
-    return Operands{lds_address(xr + nx) + 4 * (ox >> 2), (uint32_t)ox & 3u, (4 * nx + 30) >> 5,
-                    lds_address(yb) + 4 * (h * ly + 4 * p), (ny + 7) >> 3};
+    return ShortDigits{lds_address(xr + nx) + 4 * (ox >> 2), (uint32_t)ox & 3u, (4 * nx + 30) >> 5};
+}
+
+// those of nx limbs, from those of none
+MP_DEV ShortDigits short_digits(const ShortDigits &none, int nx)
+{
+    return ShortDigits{none.x + 4 * nx, none.sft, (4 * nx + 30) >> 5};
 }
 
 MP_DEV XRaw xraw_at(uint32_t a, int w)
@@ -231,100 +246,167 @@ MP_DEV XRaw xraw_at(uint32_t a, int w)
     return XRaw{lds_word(a, w), lds_word(a, w + 1), lds_word(a, w + 2), lds_word(a, w + 3), lds_word(a, w + 4)};
 }
 
-// the operands of N diagonals, the last at the addresses x and y
-template <int N>
-struct Diagonals {
-    XRaw r[N];
-    Limb4 y[N];
-    MP_DEV void load(uint32_t xa, uint32_t ya)
+// ny digit limbs in two planes at p: LDS byte address of this lane's half of the
+// 32 blocks from B on
+struct Planes {
+    static constexpr int kStep = 32;   // (two blocks)
+    uint32_t y;
+    int ny;
+    MP_DEV uint32_t at(int B) const { return y + 16 * B; }
+};
+
+MP_DEV Planes planes(int l, const uint32_t *p, int ly, int ny)
+{
+    return Planes{lds_address(p) + 4 * (l >> 5) * ly + 16 * (l & 31), ny};
+}
+
+// the same in four planes, and of the 32 blocks B, B + 2, ..
+struct Planes4 {
+    static constexpr int kStep = 16;
+    uint32_t even, odd;   // from block 0 and from block 1 on
+    uint32_t alt;         // the blocks 0, 2, ..
+    int ly, ny;
+    MP_DEV uint32_t at(int B) const
     {
-#pragma unroll
-        for (int j = 0; j < N; j++) {
-            r[j] = xraw_at(xa, 8 * (N - 1 - j));
-            y[j] = lds_quad(ya, N - 1 - j);
-        }
+        const uint32_t e = even, o = odd;
+        return (B & 1 ? o : e) + 16 * (B >> 1);
+    }
+    MP_DEV uint32_t alternate(int B) const { return alt + 8 * (B & 1) * ly + 16 * (B >> 1); }
+};
+
+MP_DEV Planes4 planes4(int l, const uint32_t *p, int ly, int ny)
+{
+    const uint32_t a = lds_address(p) + 4 * (l >> 5) * ly;
+    const int n = l & 31, r = 8 * ly;
+    return Planes4{a + 16 * (n >> 1) + (n & 1 ? r : 0), a + 16 * ((n + 1) >> 1) + (n & 1 ? 0 : r), a + 16 * n, ly, ny};
+}
+
+// the operands of two diagonals, the second at the addresses x and y1
+struct Diagonals {
+    XRaw r0, r1;
+    Limb4 v0, v1;
+    MP_DEV void load(uint32_t x, uint32_t y0, uint32_t y1)
+    {
+        r0 = xraw_at(x, 8);
+        v0 = lds_quad(y0, 0);
+        r1 = xraw_at(x, 0);
+        v1 = lds_quad(y1, 0);
     }
     MP_DEV void add(MfmaAcc &acc, uint32_t sft) const
     {
-#pragma unroll
-        for (int j = 0; j < N; j++) acc = mfma_x(acc, xfrag(r[j], sft), y[j]);
+        acc = mfma_x(acc, xfrag(r0, sft), v0);
+        acc = mfma_x(acc, xfrag(r1, sft), v1);
     }
 };
 
 // The accumulator of the strip whose first block is S0, or the share `part` of
-// `parts` of its diagonals (the first share the smallest).  Steps of kDiags
+// `parts` of its diagonals (the first share the smallest).  Steps of two
 // diagonals; the last may pass the end: it reads zeros there (of the short
 // digits, or blocks below the long ones').  FAST, for kernels with registers to
 // spare and few waves per SIMD to hide LDS reads behind: the next step's
 // operands in flight.
-template <bool FAST>
-MP_DEV MfmaAcc strip_sums(const Operands &o, int S0, int part = 0, int parts = 1)
+template <bool FAST, class Y>
+MP_DEV MfmaAcc strip_sums(const ShortDigits &o, const Y &q, int S0, int part = 0, int parts = 1)
 {
-    constexpr int D = kDiags;
     MfmaAcc acc = mfma_zero();
-    const int dlo = imax(0, S0 - o.nyblk + 1), dhi = imin(o.dmax, S0 + 31);
-    int n = uniform(dhi - dlo + D) / D;          // steps
+    const int dlo = imax(0, S0 - ((q.ny + 7) >> 3) + 1), dhi = imin(o.dmax, S0 + 31);
+    int n = uniform(dhi - dlo + 2) >> 1;         // steps
     if (n <= 0) return acc;
-    const int first = n * part / parts, d0 = dlo + D * first;
+    const int first = n * part / parts, d0 = dlo + 2 * first;
     n = n * (part + 1) / parts - first;
-    // (addresses of a step's last diagonal: the others lie at positive offsets)
-    uint32_t x = opaque(o.x - 32 * (d0 + D - 1)), y = opaque(o.y + 16 * (S0 - d0 - (D - 1)));
+    // (address of a step's second diagonal: the first lies at a positive offset)
+    uint32_t x = opaque(o.x - 32 * (d0 + 1)), y0 = opaque(q.at(S0 - d0)), y1 = opaque(q.at(S0 - d0 - 1));
+    constexpr int S = Y::kStep;
     if constexpr (FAST) {
-        Diagonals<D> a, b;
-        a.load(x, y);
+        Diagonals a, b;
+        a.load(x, y0, y1);
         for (; n >= 2; n -= 2) {                 // (the reads past the last step are not used)
-            b.load(x - 32 * D, y - 16 * D);
+            b.load(x - 64, y0 - S, y1 - S);
             a.add(acc, o.sft);
             sched_loads_first();
-            x -= 64 * D;
-            y -= 32 * D;
-            a.load(x, y);
+            x -= 128;
+            y0 -= 2 * S;
+            y1 -= 2 * S;
+            a.load(x, y0, y1);
             b.add(acc, o.sft);
             sched_loads_first();
         }
         if (n) a.add(acc, o.sft);
     } else {
         for (; n > 0; n--) {
-            Diagonals<D> a;
-            a.load(x, y);
+            Diagonals a;
+            a.load(x, y0, y1);
             a.add(acc, o.sft);
             sched_loads_first();
-            x -= 32 * D;
-            y -= 16 * D;
+            x -= 64;
+            y0 -= S;
+            y1 -= S;
         }
     }
     return acc;
 }
 
-// The same for two adjacent strips at once over the diagonals [0, dmax], which
-// both must need in full (SA >= dmax - 31): each X fragment serves both, and one
-// address steps over two diagonals.
-MP_DEV void strip_sums2(const Operands &o, int SA, MfmaAcc &accA, MfmaAcc &accB)
+// Two adjacent strips at once, of every second block each: accE holds the sums of
+// the blocks P0, P0 + 2, .., accO those between.  Both must need all diagonals
+// [0, dmax] (P0 >= dmax - 31).  What the even blocks multiply by diagonal m the
+// odd ones multiply by m + 1, so a step reads one fragment of each operand for
+// two products (18 LDS cycles; two fragments of the long operand, for strips one
+// behind the other, 26: LDS reads bind a compute unit full of instances).
+template <bool FAST>
+MP_DEV void strip_sums2(const ShortDigits &o, const Planes4 &q, int P0, MfmaAcc &accE, MfmaAcc &accO)
 {
-    accA = mfma_zero();
-    accB = mfma_zero();
-    uint32_t x = o.x, y = o.y + 16 * SA;
-    const auto one = [&](int j) {                // diagonal j below the addresses
-        const XRaw r = xraw_at(x, -8 * j);
-        const Limb4 va = lds_quad(y, -j), vb = lds_quad(y, kStripBlks - j);
-        const XFrag f = xfrag(r, o.sft);
-        accA = mfma_x(accA, f, va);
-        accB = mfma_x(accB, f, vb);
-        sched_loads_first();
+    accE = mfma_zero();
+    accO = mfma_zero();
+    const int dmax = uniform(o.dmax), odd = dmax & 1;
+    XFrag w = xfrag(xraw_at(o.x, 0), o.sft);     // X_m
+    accO = mfma_x(accO, w, lds_quad(q.alternate(P0 + 1), 0));
+    const auto step = [&](const XRaw &r, const Limb4 &v) {
+        accE = mfma_x(accE, w, v);
+        w = xfrag(r, o.sft);
+        accO = mfma_x(accO, w, v);
     };
-    const int n = uniform(o.dmax) + 1;
-    if (n & 1) {
-        one(0);
-        x -= 32;
-        y -= 16;
-    }
-    x = opaque(x - 32);                          // (offsets from an address are not negative)
-    y = opaque(y - 16);
-    for (int i = n >> 1; i > 0; i--) {
-        one(-1);
-        one(0);
-        x -= 64;
-        y -= 32;
+    if (odd) step(xraw_at(o.x - 32, 0), lds_quad(q.alternate(P0), 0));
+    // (m, m + 1) per step
+    uint32_t x = opaque(o.x - 32 * (odd + 2)), y0 = opaque(q.alternate(P0 - odd)),
+             y1 = opaque(q.alternate(P0 - odd - 1));
+    int n = dmax >> 1;
+    if constexpr (FAST) {
+        Diagonals a, b;
+        a.load(x, y0, y1);
+        for (; n >= 2; n -= 2) {                 // (the reads past the last step are not used)
+            b.load(x - 64, y0 - 16, y1 - 16);
+            step(a.r0, a.v0);
+            step(a.r1, a.v1);
+            sched_loads_first();
+            x -= 128;
+            y0 -= 32;
+            y1 -= 32;
+            a.load(x, y0, y1);
+            step(b.r0, b.v0);
+            step(b.r1, b.v1);
+            sched_loads_first();
+        }
+        if (n) {
+            step(a.r0, a.v0);
+            step(a.r1, a.v1);
+            a.v0 = lds_quad(y0 - 16, 0);
+        }
+        accE = mfma_x(accE, w, a.v0);            // (m = dmax)
+    } else {
+        for (; n > 0; n--) {
+            const XRaw r0 = xraw_at(x, 8);
+            const Limb4 v0 = lds_quad(y0, 0);
+            step(r0, v0);
+            sched_loads_first();
+            const XRaw r1 = xraw_at(x, 0);
+            const Limb4 v1 = lds_quad(y1, 0);
+            step(r1, v1);
+            sched_loads_first();
+            x -= 64;
+            y0 -= 16;
+            y1 -= 16;
+        }
+        accE = mfma_x(accE, w, lds_quad(y0, 0));
     }
 }
 
@@ -411,15 +493,10 @@ MP_DEV bool quad_balance(uint32_t (&z)[4], uint32_t cin)
     return odd;
 }
 
-// The limbs of a strip from its accumulator plus (ADD) four addend limbs per
-// lane: z gets the limbs of columns 8n + 4h .. + 3 with the carries inside the
-// strip resolved; returns the strip's signed carry into its next column.
-// Every lane's four columns are chained exactly and pass a signed carry to the
-// next lane, where it is absorbed by the two lowest limbs; only if it is not
-// (about one lane in 2^40, or runs of zero or all-ones limbs) the carries are
-// resolved in full, biased by 2^31 to be non-negative.
+// The four limbs of a lane's columns from its accumulator plus (ADD) four
+// addend limbs, and their signed carry into the next lane.
 template <bool ADD>
-MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[4])
+MP_DEV uint32_t quad_sums(const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[4])
 {
     // every term one 64-bit multiply-add (the carry's weight hidden apart from
     // w0, or the compiler adds before it multiplies, in 64 bits)
@@ -439,24 +516,101 @@ MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[
     for (int j = 1; j < 4; j++) s[j] += (int64_t)(int32_t)(s[j - 1] >> 32) * wc;
 #pragma unroll
     for (int j = 0; j < 4; j++) z[j] = (uint32_t)s[j];
-    const uint32_t c = (uint32_t)(s[3] >> 32);
+    return (uint32_t)(s[3] >> 32);
+}
+
+// The limbs of a strip from its accumulator plus (ADD) four addend limbs per
+// lane: z gets the limbs of columns 8n + 4h .. + 3 with the carries inside the
+// strip resolved; returns the strip's signed carry into its next column.
+// Every lane's four columns are chained exactly and pass a signed carry to the
+// next lane, where it is absorbed by the two lowest limbs; only if it is not
+// (about one lane in 2^40, or runs of zero or all-ones limbs) the carries are
+// resolved in full, biased by 2^31 to be non-negative.
+template <bool ADD>
+MP_DEV int strip_limbs(int l, const MfmaAcc &a, const Limb4 &add, uint32_t (&z)[4])
+{
+    const uint32_t c = quad_sums<ADD>(a, add, z);
+    const uint32_t z0 = z[0], z1 = z[1];
     // the lane below (n, 1) is (n, 0); below (n, 0) it is (n - 1, 1)
     uint32_t lo, hi;
     half_swap(c, lo, hi);                 // lo: lane l gets c of lane l & 31; hi: of lane (l & 31) + 32
     const uint32_t up = shfl_up1(hi);     // (0 in lane 0)
     const int prev = (int)(l >= 32 ? lo : up);
-    const uint64_t neg = ballot(prev < 0);
-    const uint64_t odd = add64_carry(z[0], z[1], prev) ^ neg;
+    const uint64_t odd = add64_carry(z[0], z[1], prev) ^ ballot(prev < 0);
     int e = (int)readlane(c, kLanes - 1);
     if (odd) {
         // z + sum (c + 2^31) - sum 2^31, each sum over the lanes above the lowest
         const bool first = l == 0;
         const uint32_t b[4] = {first ? 0u : (uint32_t)prev + 0x80000000u, 0u, 0u, 0u};
         const uint32_t m[4] = {first ? 0xFFFFFFFFu : 0x7FFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-#pragma unroll
-        for (int j = 0; j < 4; j++) z[j] = (uint32_t)s[j];
+        z[0] = z0;
+        z[1] = z1;
         e += (int)quad_add(z, b, 0u);
         e += (int)quad_add(z, m, 1u) - 1;
+    }
+    return e;
+}
+
+// z += b + cin for a number of 512 limbs, zE the lanes' quads of its even
+// blocks and zO those of its odd ones (in limb order: E of (n, 0), E of (n, 1), O
+// of (n, 0), O of (n, 1)); returns the carry out
+MP_DEV uint32_t quad2_add(uint32_t (&zE)[4], uint32_t (&zO)[4], const uint32_t (&bE)[4], const uint32_t (&bO)[4],
+                          uint32_t cin)
+{
+    uint32_t cE = 0, cO = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        zE[j] = __builtin_addc(zE[j], bE[j], cE, &cE);
+        zO[j] = __builtin_addc(zO[j], bO[j], cO, &cO);
+    }
+    const uint64_t GE = ballot(cE != 0u), GO = ballot(cO != 0u);
+    const uint64_t PE = ballot((zE[0] & zE[1] & zE[2] & zE[3]) == 0xFFFFFFFFu),
+                   PO = ballot((zO[0] & zO[1] & zO[2] & zO[3]) == 0xFFFFFFFFu);
+    const uint32_t g0 = (uint32_t)GE, g1 = (uint32_t)(GE >> 32), g2 = (uint32_t)GO, g3 = (uint32_t)(GO >> 32);
+    const uint32_t p0 = (uint32_t)PE, p1 = (uint32_t)(PE >> 32), p2 = (uint32_t)PO, p3 = (uint32_t)(PO >> 32);
+    const uint32_t G = g3 | (p3 & (g2 | (p2 & (g1 | (p1 & g0))))), X = G | (p0 & p1 & p2 & p3);
+    const uint64_t s = (uint64_t)X + G + cin;
+    const uint32_t c0 = (uint32_t)s ^ X ^ G, c1 = g0 | (p0 & c0), c2 = g1 | (p1 & c1), c3 = g2 | (p2 & c2);
+    cE = inverse_ballot((uint64_t)c1 << 32 | c0) ? 1u : 0u;
+    cO = inverse_ballot((uint64_t)c3 << 32 | c2) ? 1u : 0u;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        zE[j] = __builtin_addc(zE[j], 0u, cE, &cE);
+        zO[j] = __builtin_addc(zO[j], 0u, cO, &cO);
+    }
+    return (uint32_t)(s >> 32);
+}
+
+// the same as strip_limbs<true> for the 512 limbs of strip_sums2 (add(0): the
+// addend quad of the even blocks, add(1): of the odd ones)
+template <class FA>
+MP_DEV int strip_limbs2(int l, const MfmaAcc &aE, const MfmaAcc &aO, const FA &add, uint32_t (&zE)[4],
+                        uint32_t (&zO)[4])
+{
+    const uint32_t cE = quad_sums<true>(aE, add(0), zE);
+    wave_sync();                          // (one addend at a time: registers)
+    const uint32_t cO = quad_sums<true>(aO, add(1), zO);
+    const uint32_t xE[2] = {zE[0], zE[1]}, xO[2] = {zO[0], zO[1]};
+    uint32_t loE, hiE, loO, hiO;
+    half_swap(cE, loE, hiE);
+    half_swap(cO, loO, hiO);
+    const uint32_t up = shfl_up1(hiO);    // (0 in lane 0)
+    const int pE = (int)(l >= 32 ? loE : up), pO = (int)(l >= 32 ? loO : hiE);
+    const uint64_t odd = (add64_carry(zE[0], zE[1], pE) ^ ballot(pE < 0)) | (add64_carry(zO[0], zO[1], pO) ^ ballot(pO < 0));
+    int e = (int)readlane(cO, kLanes - 1);
+    if (odd) {
+        const bool first = l == 0;
+        const uint32_t bE[4] = {first ? 0u : (uint32_t)pE + 0x80000000u, 0u, 0u, 0u};
+        const uint32_t bO[4] = {(uint32_t)pO + 0x80000000u, 0u, 0u, 0u};
+        const uint32_t mE[4] = {first ? 0xFFFFFFFFu : 0x7FFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+        const uint32_t mO[4] = {0x7FFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            zE[j] = xE[j];
+            zO[j] = xO[j];
+        }
+        e += (int)quad2_add(zE, zO, bE, bO, 0u);
+        e += (int)quad2_add(zE, zO, mE, mO, 1u) - 1;
     }
     return e;
 }
