@@ -84,6 +84,13 @@ MP_DEV void sync() { __syncthreads(); }
 MP_DEV void wave_sync() { asm volatile("" ::: "memory"); }
 MP_DEV uint64_t ballot(bool p) { return __ballot(p); }
 
+// this wave's claim on its SIMD's issue slots, 0 (all waves at first) to 3
+template <int P>
+MP_DEV void wave_priority()
+{
+    __builtin_amdgcn_s_setprio(P);
+}
+
 // index of the wave in its workgroup
 MP_DEV int wave_index() { return (int)__builtin_amdgcn_readfirstlane(threadIdx.x / kLanes); }
 
