@@ -189,7 +189,7 @@ hipError_t launch_ragged_direct(int count, size_t lds, hipStream_t st, const uin
 }
 
 #if defined(MP_KFAMILY) && defined(MP_KT)
-// (Mode::kFast serves workgroups of 256 threads only, see division_mode)
+// (Mode::kFast serves workgroups of 256 and 512 threads only, see division_shape)
 #if MP_KFAMILY == 0
 template hipError_t launch_mul<MP_KT>(int, hipStream_t, const uint32_t *, int, const uint32_t *, int, uint32_t *,
                                       MulKind);
@@ -199,7 +199,7 @@ template hipError_t launch_mul<MP_KT>(int, hipStream_t, const uint32_t *, int, c
                                                int, int32_t *, int);
 MP_SHINV(Mode::kPacked)
 MP_SHINV(Mode::kShared)
-#if MP_KT == 256
+#if MP_KT <= 512
 MP_SHINV(Mode::kFast)
 #endif
 #elif MP_KFAMILY == 2
@@ -208,7 +208,7 @@ MP_SHINV(Mode::kFast)
                                                 int, uint32_t *, int, uint32_t *, int32_t *, int);
 MP_DIVREM(Mode::kPacked)
 MP_DIVREM(Mode::kShared)
-#if MP_KT == 256
+#if MP_KT <= 512
 MP_DIVREM(Mode::kFast)
 #endif
 #elif MP_KFAMILY == 3

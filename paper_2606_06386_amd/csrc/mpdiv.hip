@@ -233,6 +233,26 @@ mp::Mode division_mode(int T, int64_t batch)
                                                 : mp::Mode::kFast;
 }
 
+struct DivShape {
+    int threads;
+    mp::Mode mode;
+};
+
+// In large batches of wide operands LDS allows few instances per compute unit:
+// half the waves with twice the registers each do better if they still take
+// the remainder update's strips in one round (pairs, and the lowest), that is if
+// the divisor is short enough (us, whole and half: 600 divisions of 4096 by 1638
+// limbs 77.6 and 72.9, 2000 of 2500 by 1500 89.0 and 86.0, by 1875 72.9 and 73.6,
+// 2000 of 4096 by 3072 131 and 137; 1000 of 8192 by 1228 340 and 301, by 4915 308
+// and 311).
+DivShape division_shape(int nu, int nv, int64_t batch)
+{
+    const int T = threads_for(nu);
+    const mp::Mode mode = division_mode(T, batch);
+    if (mode == mp::Mode::kPacked && T >= 512 && nv + 2 <= (T / 64 - 1) * mp::kStrip) return {T / 2, mp::Mode::kFast};
+    return {T, mode};
+}
+
 // The work queue of mp_divrem_ragged_static: a library-owned array of one
 // ragged workspace for MP_STATIC_MAX_COUNT instances (1 MiB), one copy per
 // GPU, kept until the process ends.  Host code never uses the array's name as
@@ -400,21 +420,21 @@ mp_status_t mp_shinv_batch(const uint32_t *v, int32_t nv, int32_t h, uint32_t *w
     if (nv > mp::kMaxLimbs || h > mp::kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
-    const int T = threads_for(h > 0 ? h : 1);
-    const mp::Mode mode = division_mode(T, batch);
-    const size_t bytes = body_bytes(h + 1, nv, mode);
+    const DivShape shape = division_shape(h > 0 ? h : 1, nv, batch);
+    const size_t bytes = body_bytes(h + 1, nv, shape.mode);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
     using mp::Mode;
     const auto launch =
-        mode == Mode::kFast     ? mp::launch_shinv<256, Mode::kFast>
-        : mode == Mode::kShared ? (T == 256   ? mp::launch_shinv<256, Mode::kShared>
-                                   : T == 512 ? mp::launch_shinv<512, Mode::kShared>
-                                              : mp::launch_shinv<1024, Mode::kShared>)
-                                : (T == 256   ? mp::launch_shinv<256, Mode::kPacked>
-                                   : T == 512 ? mp::launch_shinv<512, Mode::kPacked>
-                                              : mp::launch_shinv<1024, Mode::kPacked>);
+        shape.mode == Mode::kFast     ? (shape.threads == 256 ? mp::launch_shinv<256, Mode::kFast>
+                                                              : mp::launch_shinv<512, Mode::kFast>)
+        : shape.mode == Mode::kShared ? (shape.threads == 256   ? mp::launch_shinv<256, Mode::kShared>
+                                         : shape.threads == 512 ? mp::launch_shinv<512, Mode::kShared>
+                                                                : mp::launch_shinv<1024, Mode::kShared>)
+                                      : (shape.threads == 256   ? mp::launch_shinv<256, Mode::kPacked>
+                                         : shape.threads == 512 ? mp::launch_shinv<512, Mode::kPacked>
+                                                                : mp::launch_shinv<1024, Mode::kPacked>);
     return status_of(launch(batch, bytes, st, v, nv, h, w, nw, inst_status, bmax));
 }
 
@@ -426,21 +446,21 @@ mp_status_t mp_divrem_batch(const uint32_t *u, int32_t nu, const uint32_t *v, in
     if (nu > mp::kMaxLimbs || nv > mp::kMaxLimbs) return MP_ERR_SIZE;
     if (batch == 0) return MP_OK;
     if (!device_ok()) return MP_ERR_DEVICE;
-    const int T = threads_for(nu);
-    const mp::Mode mode = division_mode(T, batch);
-    const size_t bytes = body_bytes(nu, nv, mode);
+    const DivShape shape = division_shape(nu, nv, batch);
+    const size_t bytes = body_bytes(nu, nv, shape.mode);
     if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
     hipStream_t st = (hipStream_t)stream;
     const int bmax = block_max();
     using mp::Mode;
     const auto launch =
-        mode == Mode::kFast     ? mp::launch_divrem<256, Mode::kFast>
-        : mode == Mode::kShared ? (T == 256   ? mp::launch_divrem<256, Mode::kShared>
-                                   : T == 512 ? mp::launch_divrem<512, Mode::kShared>
-                                              : mp::launch_divrem<1024, Mode::kShared>)
-                                : (T == 256   ? mp::launch_divrem<256, Mode::kPacked>
-                                   : T == 512 ? mp::launch_divrem<512, Mode::kPacked>
-                                              : mp::launch_divrem<1024, Mode::kPacked>);
+        shape.mode == Mode::kFast     ? (shape.threads == 256 ? mp::launch_divrem<256, Mode::kFast>
+                                                              : mp::launch_divrem<512, Mode::kFast>)
+        : shape.mode == Mode::kShared ? (shape.threads == 256   ? mp::launch_divrem<256, Mode::kShared>
+                                         : shape.threads == 512 ? mp::launch_divrem<512, Mode::kShared>
+                                                                : mp::launch_divrem<1024, Mode::kShared>)
+                                      : (shape.threads == 256   ? mp::launch_divrem<256, Mode::kPacked>
+                                         : shape.threads == 512 ? mp::launch_divrem<512, Mode::kPacked>
+                                                                : mp::launch_divrem<1024, Mode::kPacked>);
     return status_of(launch(batch, bytes, st, u, nu, v, nv, q, nq, r, inst_status, bmax));
 }
 

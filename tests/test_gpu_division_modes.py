@@ -45,3 +45,10 @@ def test_every_kind_of_batch(d, k, per_cu):
     rows = rows.cpu().numpy()
     for g, w, name in zip(got, want, ("quotient", "remainder", "status")):
         assert (g == np.asarray(w).view(np.uint32)[rows]).all(), name
+
+
+# wide operands: divisors on both sides of the length up to which large batches take half the waves
+@pytest.mark.parametrize("d,k", [(1990, 300), (300, 1789), (300, 1790), (260, 3837), (260, 3838), (4000, 500)])
+@pytest.mark.parametrize("per_cu", [1, 3])
+def test_wide_batches(d, k, per_cu):
+    test_every_kind_of_batch(d, k, per_cu)
