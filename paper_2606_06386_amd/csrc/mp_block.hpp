@@ -48,10 +48,6 @@ struct BlockSplit {
 // of the next product.
 constexpr int kBlockMax = 252;
 
-// Longest block whose R_top lies above the two lowest limbs of the remainder's
-// top strip.
-constexpr int kBlockInTop = 244;
-
 MP_HD constexpr int block_precision(int b) { return ((b + 8) & ~7) - 1; }
 
 MP_HD BlockSplit block_split(int d, int bmax)
@@ -102,8 +98,8 @@ MP_HD constexpr BodyPlan plan_body(int nu, int nv)
     p.lyV = plane_distance(p.nV >> 2);
     p.offT = p.offV + 4 * p.lyV + kPadWords - kPad4;
     p.offX = r4(p.offT + 2 * kLyT + kXLow);
-    p.offQ = p.offX + dm + 4 + kXPad + kXLow;
-    p.offW = p.offQ + dm + 1 + kXPad;
+    p.offQ = r4(p.offX + dm + 4 + kXPad + kXLow);
+    p.offW = p.offQ + 3 + dm + 1 + kXPad;
     p.offR = r4(p.offW + dm + 4);
     p.capR = r4(nu + 8);
     p.total = p.offR + p.capR;
@@ -433,18 +429,23 @@ MP_DEV void top_digits(int l, const uint32_t *src, int nt, uint32_t *td)
     store_T(l, td, z, nt);
 }
 
-// the reversed digits of -q_i to xq; q: limbs of R_top W / B^(dp+1), limb 2 + j is limb j of q_i, 2 + b its sign
+// word of the 16-byte aligned place of -q's digits where those of a block of b limbs start: a lane's quad ends there on an aligned word
+MP_DEV int quotient_at(int b) { return (1 - b) & 3; }
+
+// the reversed digits of -q_i to xq + quotient_at(b); q: limbs of R_top W /
+// B^(dp+1), limb 2 + j is limb j of q_i, 2 + b its sign
 MP_DEV void quotient_digits(int l, const uint32_t (&q)[4], int b, uint32_t *xq)
 {
-    const int g = quad_limb(l) - 2;
+    const int g = quad_limb(l) - 2, at = quotient_at(b);
     uint32_t z[4];
 #pragma unroll
-    for (int j = 0; j < 4; j++) z[j] = g + j <= b ? (g + j < 0 ? 0xFFFFFFFFu : ~q[j]) : 0u;   // (the two columns below pass the +1 on)
+    for (int j = 0; j < 4; j++) z[j] = g + j < 0 ? 0xFFFFFFFFu : ~q[j];   // (the two columns below pass the +1 on)
     quad_balance(z, 1u);
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-        if ((unsigned)(g + j) <= (unsigned)b) xq[b - g - j] = bswap(z[j]);
-    if (l < kXPad) xq[b + 1 + l] = 0u;
+    if (g <= b) {                                 // (digits below limb 0 are zero)
+        store4(xq + at + b - g - 3, g + 3 <= b ? bswap(z[3]) : 0u, g + 2 <= b ? bswap(z[2]) : 0u,
+               g + 1 <= b ? bswap(z[1]) : 0u, bswap(z[0]));
+    }
+    if (l < kXPad - 2) xq[at + b + 3 + l] = 0u;
 }
 
 // the b limbs of q_i (see quotient_digits) to the quotient's limbs Q
@@ -588,18 +589,20 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         const int l = lane_at(i);
         uint32_t q[4];                                // (the first wave's) q_i
         const int cq = (dp + 1) >> 3;                 // block of the product's first column
+        // R_top is read before the strips' carries are added, which the last wave
+        // does during the product, if those lie below R_top (the top strip starts
+        // three limbs below it): but for a ripple of one unit into R_top's
+        // lowest limb, which the quotient's error bound has room for.  The limbs
+        // from k + 2 + o on are R_top's by then, and the quotient's next.
+        const bool late = bs2 == 1 || b + ((n2 + 7) & ~7) <= k + 253;
+        if (w == 0) {
+            if (i && !late) strip_carries(l, ctl, R + op, n2, base2, bs2);
+            top_digits(l, R + o + k - 1, nt, Td);
+            MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
+        }
+        bar<T>();
+        const bool carries = w == W - 1 && i && late;
         if constexpr (SHARED) {
-            // R_top is read before the strips' carries are added, which the last
-            // wave does meanwhile: they lie below R_top (unless the block is
-            // longer than kBlockInTop) but for a ripple of one unit into its
-            // lowest limb, which the quotient's error bound has room for.
-            const bool late = b <= kBlockInTop;
-            if (w == 0) {
-                if (i && !late) strip_carries(l, ctl, R + op, n2, base2, bs2);
-                top_digits(l, R + o + k - 1, nt, Td);
-                MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
-            }
-            bar<T>();
             MfmaAcc acc;
             if (w < kShares) {
                 yt0.ny = nt;
@@ -612,14 +615,12 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
                 for (int j = 0; j < kShares - 1; j++) acc_add(l, acc, part + j * 1024);
                 strip_limbs<false>(l, acc, none, q);
                 quotient_digits(l, q, b, XQ);
-            } else if (w == W - 1 && i && late) {
-                strip_carries(l, ctl, R + op, n2, base2, bs2);
+            } else if (carries) {
+                strip_carries(l, ctl, R + op, n2 - b, base2, bs2);
             }
+        } else if (carries) {
+            strip_carries(l, ctl, R + op, n2 - b, base2, bs2);
         } else if (w == 0) {
-            if (i) strip_carries(l, ctl, R + op, n2, base2, bs2);
-            top_digits(l, R + o + k - 1, nt, Td);
-            wave_sync();
-            MP_STAMP(16 + 3 * (i % 5));
             if constexpr (FAST) {
                 yt0.ny = nt;
                 strip_limbs<false>(l, strip_sums<FAST>(xw0, yt0, cq), none, q);
@@ -643,7 +644,10 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         // R -= v q_i
         if (w == 0) wave_priority<0>();
         strips<T, M>(
-            ctl, [&](int lu) { return FAST ? short_digits(xq0, b + 1) : short_digits(lu, XQ, b + 1); },
+            ctl, [&](int lu) {
+                return FAST ? short_digits(xq0, quotient_at(b), b + 1)
+                            : short_digits(lu, XQ + quotient_at(b), b + 1);
+            },
             [&](int lu) { return FAST ? yv0 : planes4(lu, Vd, pl.lyV, n2); }, R + o, n2, base2, bs2);
         if (w == 0) wave_priority<3>();
         bar<T>();

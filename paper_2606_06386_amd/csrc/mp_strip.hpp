@@ -235,10 +235,10 @@ MP_DEV ShortDigits short_digits(int l, const uint32_t *xr, int nx)
     return ShortDigits{lds_address(xr + nx) + 4 * (ox >> 2), (uint32_t)ox & 3u, (4 * nx + 30) >> 5};
 }
 
-// those of nx limbs, from those of none
-MP_DEV ShortDigits short_digits(const ShortDigits &none, int nx)
+// those of nx limbs from word `at` on, from those of none at word 0
+MP_DEV ShortDigits short_digits(const ShortDigits &none, int at, int nx)
 {
-    return ShortDigits{none.x + 4 * nx, none.sft, (4 * nx + 30) >> 5};
+    return ShortDigits{none.x + 4 * (at + nx), none.sft, (4 * nx + 30) >> 5};
 }
 
 MP_DEV XRaw xraw_at(uint32_t a, int w)
