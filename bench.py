@@ -58,7 +58,7 @@ def workload(name):
 
 def limb_products(u, v, clipped=True):
     """Algorithmic limb products of one launch over the batch: the cost model's
-    W_clipped (what the kernels compute), or the method's W with full
+    W_clipped (only the columns that are needed), or the method's W with full
     quotient and remainder products (clipped=False)."""
     from paper_2606_06386_amd import costmodel as cm
     cost = cm.division_cost_clipped if clipped else cm.division_cost
@@ -100,16 +100,17 @@ def measured_traffic(workload_name):
 
 
 TRAFFIC_SOURCES = ["paper_2606_06386_amd/csrc/mp_prims_hip.hpp", "paper_2606_06386_amd/csrc/mp_core.hpp",
-                   "paper_2606_06386_amd/csrc/mp_div.hpp", "paper_2606_06386_amd/csrc/launch.hpp",
+                   "paper_2606_06386_amd/csrc/mp_strip.hpp", "paper_2606_06386_amd/csrc/mp_block.hpp",
+                   "paper_2606_06386_amd/csrc/launch.hpp",
                    "paper_2606_06386_amd/csrc/kernels.hip", "paper_2606_06386_amd/csrc/mpdiv.hip"]
 
 
 def write_traffic(fetch_csv, write_csv, workload_name, kernels=("k_head_divrem", "k_divrem<")):
     """profiles/k_divrem_<workload>_traffic.json from two rocprofv3 --pmc
     counter files (FETCH_SIZE, WRITE_SIZE) of `bench.py --copy-calibration`:
-    the mean KiB per dispatch of each kernel of one launch (the head and the
-    per-instance kernel of mp_divrem_batch), summed, each counter scaled by
-    what it reads for the 256 MiB device copy."""
+    the mean KiB per dispatch of each of `kernels` that the file holds (every
+    kernel of one launch), summed, each counter scaled by what it reads for the
+    256 MiB device copy."""
     import csv
     import hashlib
 
@@ -125,8 +126,8 @@ def write_traffic(fetch_csv, write_csv, workload_name, kernels=("k_head_divrem",
                     kern[hit[0]].append(v)
                 elif "copyBuffer" in row["Kernel_Name"]:
                     copy.append(v)
-        assert all(kern.values()) and copy, (path, counter, {k: len(x) for k, x in kern.items()}, len(copy))
-        return sum(sum(x) / len(x) for x in kern.values()), max(copy)   # the 256 MiB copy is the largest
+        assert any(kern.values()) and copy, (path, counter, {k: len(x) for k, x in kern.items()}, len(copy))
+        return sum(sum(x) / len(x) for x in kern.values() if x), max(copy)   # the 256 MiB copy is the largest
 
     f_k, f_c = read(fetch_csv, "FETCH_SIZE")
     w_k, w_c = read(write_csv, "WRITE_SIZE")
@@ -246,7 +247,8 @@ def settle(fn, stream, min_ms=SETTLE_MS):
 def roofline(W, W_clipped, ms, kernel, traffic, algo_bytes):
     """Roofline object of a launch of ms milliseconds.  W is the method's
     algorithmic work (limb products of Alg. 1-3 at exact operand sizes, full
-    quotient and remainder products); W_clipped is what the kernels form.
+    quotient and remainder products); W_clipped counts only the columns that are
+    needed of each.
     The products run on the int8 matrix cores (32 int8 operations per limb
     product), so achieved and peak are int8 operations per second; the
     fraction of the vector-ALU multiply peak is given beside them."""
@@ -363,7 +365,7 @@ def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
     return {"workload": c["name"], "batch": batch, "kernel_ms": {"mean": kmean, "median": ms[len(ms) // 2],
                                                                  "min": ms[0]},
             "div_per_s": batch * steps / elapsed, "div_per_s_kernel": batch / (kmean * 1e-3),
-            "roofline": roofline(W, Wc, kmean, "k_head_divrem + k_divrem<%d>" % threads_for(n),
+            "roofline": roofline(W, Wc, kmean, "k_divrem<%d>" % threads_for(n),
                                  measured_traffic(c["name"]), algo_bytes),
             "full_mult_equivalents_per_s": batch / (kmean * 1e-3) * (W / batch) / (n * n / 2),
             "status_ok": int((status == 0).sum())}
@@ -595,7 +597,7 @@ def run_mixed(args):
         "limb_products_per_launch": W,
         "limb_products_per_launch_full_products": ragged_limb_products(us, vs, clipped=False),
         "roofline": roofline(ragged_limb_products(us, vs, clipped=False), W, kmean,
-                             "k_ragged_prep + k_head_ragged + k_ragged (4 width classes)", None, algo_bytes),
+                             "k_ragged_prep + k_ragged (4 width classes)", None, algo_bytes),
         "status_ok": int((status == 0).sum()),
     }
     if not args.no_cpu_baseline:

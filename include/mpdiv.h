@@ -174,7 +174,7 @@ mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
  *                        inverse of one block's precision, which Newton steps
  *                        on one wave compute; this bounds the iterate the last
  *                        step starts from, in limbs (0..140; below 16 counts
- *                        as 16), and with it the block: 257 limbs from 133 on.
+ *                        as 16), and with it the block: 252 limbs from 134 on.
  *                        MP_SMALL_LIMIT_AUTO (the default) is 136.
  * mp_set_knob returns MP_ERR_ARG for an unknown knob or a value out of range;
  * mp_get_knob returns the current value (-1 for an unknown knob).
@@ -188,7 +188,8 @@ int32_t mp_get_knob(int32_t knob);
 /*
  * Dynamic LDS bytes per workgroup that a launch needs (host-side query, no
  * device call): MP_OP_MUL with (na, nb), MP_OP_DIVREM with (nu, nv),
- * MP_OP_SHINV with (nv, h).  Returns -1 for an unknown op or a width outside
+ * MP_OP_SHINV with (nv, h); divisions in batches of up to three per compute unit
+ * take 12 KB more.  Returns -1 for an unknown op or a width outside
  * [1, mp_max_limbs()].  A launch whose figure exceeds the 160 KB of one
  * gfx950 workgroup returns MP_ERR_SIZE.
  */

@@ -42,7 +42,6 @@ MP_DEV void bar()
     else wave_sync();
 }
 
-MP_DEV int round4(int x) { return (x + 3) & ~3; }
 MP_DEV int imin(int a, int b) { return a < b ? a : b; }
 MP_DEV int imax(int a, int b) { return a > b ? a : b; }
 

@@ -5,10 +5,10 @@ limbs) it times a one-class batch of seeded random divisions under every
 valid (threads per workgroup, hence limbs per thread in the linear passes;
 persistent workgroups per compute unit) and installs the fastest with
 mp_ragged_config.  Then, on a seeded mixed batch, it times the two
-process-wide knobs of the method's schedule and product engine: where the
-Newton precision-doubling schedule hands over from the one-wave head to the
-per-instance workgroups (MP_KNOB_SMALL_LIMIT) and from which operand length
-products move from the vector ALU to the matrix cores (MP_KNOB_MFMA_MIN),
+process-wide knobs of the method's schedule and product engine: how long the
+blocks of quotient limbs are (MP_KNOB_SMALL_LIMIT, in limbs of the inverse's
+last Newton step) and from which operand length mp_mul_batch moves from the
+vector ALU to the matrix cores (MP_KNOB_MFMA_MIN),
 and installs the fastest pair.  Results are cached in a JSON file keyed by
 the device (architecture name and compute-unit count) and by a hash of the
 kernel sources, so a cache entry is never applied to a different chip or to
@@ -74,7 +74,7 @@ def _time(rb, reps):
     return e0.elapsed_time(e1) / reps
 
 
-AUTO = -2           # the library's per-launch head limit (MP_SMALL_LIMIT_AUTO)
+AUTO = -2           # the library's own limit (MP_SMALL_LIMIT_AUTO)
 SMALL_LIMITS = (AUTO, 32, 48, 64, 80, 96, 112, 128, 136)
 MFMA_MINS = (32, 64, 96, 128)
 AUTO_SLACK = 1.01    # the per-launch setting is kept unless a fixed one is >1% faster
@@ -83,8 +83,7 @@ AUTO_SLACK = 1.01    # the per-launch setting is kept unless a fixed one is >1% 
 def tune_knobs(count=1024, reps=3, log=None):
     """Time every (small_limit, mfma_min) pair on a seeded mixed batch (all four
     width classes); installs and returns the fastest as {knob: value, 'ms': ms}.
-    The per-launch head limit (AUTO) adapts to each batch's size, so it is
-    preferred over a fixed limit that is not clearly faster on this batch."""
+    The library's own limit (AUTO) is preferred over a fixed limit that is not clearly faster on this batch."""
     from . import binding, ragged
     m = I.config_c4(index=np.arange(0, 8 * count, 8))
     rb = binding.Ragged(ragged.pack(m["u"], m["v"]))
