@@ -95,6 +95,8 @@ def measured_traffic(workload_name):
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
+    if not all(os.path.exists(os.path.join(ROOT, s_)) for s_ in rec["sources"]):
+        return None
     h = hashlib.sha256(b"".join(open(os.path.join(ROOT, s_), "rb").read() for s_ in rec["sources"])).hexdigest()
     return rec["traffic_bytes_per_dispatch"] if h == rec["source_sha256"] else None
 

@@ -52,3 +52,20 @@ def test_every_kind_of_batch(d, k, per_cu):
 @pytest.mark.parametrize("per_cu", [1, 3])
 def test_wide_batches(d, k, per_cu):
     test_every_kind_of_batch(d, k, per_cu)
+
+
+@pytest.mark.parametrize("nu,nv,batch", [(100, 8192, 2), (2048, 8192, 1100), (600, 2100, 3)])
+def test_divisor_rows_wider_than_the_dividend(nu, nv, batch):
+    import torch
+    from paper_2606_06386_amd import binding
+    rng = random.Random(nv)
+    us = [rng.getrandbits(32 * nu) | 1 for _ in range(3)]
+    vs = [rng.getrandbits(32 * n) | 1 << (32 * n - 1) for n in (5, nu // 2, min(nv, nu + 1))]
+    rows = np.arange(batch) % 3
+    u, v = (np.stack([I.from_int(x, w) for x in xs])[rows] for xs, w in ((us, nu), (vs, nv)))
+    q, r, st = (x.cpu().numpy().view(np.uint32) for x in binding.divrem(
+        torch.from_numpy(u.view(np.int32)).cuda(), torch.from_numpy(v.view(np.int32)).cuda()))
+    for j in range(3):
+        want = divmod(us[j], vs[j])
+        for row in (np.nonzero(rows == j)[0][[0, -1]] if batch > j else []):
+            assert st[row] == 0 and (q[row] == I.from_int(want[0], nu)).all() and (r[row] == I.from_int(want[1], nv)).all()
