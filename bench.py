@@ -56,12 +56,12 @@ def workload(name):
     return {"c1": I.config_c1, "c2": I.config_c2, "c3": I.config_c3}[name]()
 
 
-def limb_products(u, v, clipped=True):
+def limb_products(u, v, clipped=True, cost=None):
     """Algorithmic limb products of one launch over the batch: the cost model's
     W_clipped (only the columns that are needed), or the method's W with full
-    quotient and remainder products (clipped=False)."""
+    quotient and remainder products (clipped=False), or by another of its counts."""
     from paper_2606_06386_amd import costmodel as cm
-    cost = cm.division_cost_clipped if clipped else cm.division_cost
+    cost = cost or (cm.division_cost_clipped if clipped else cm.division_cost)
     hs, nvs = prec_rows(u), prec_rows(v)
     total = 0
     cache = {}
@@ -73,9 +73,9 @@ def limb_products(u, v, clipped=True):
     return total
 
 
-def ragged_limb_products(us, vs, clipped=True):
+def ragged_limb_products(us, vs, clipped=True, cost=None):
     from paper_2606_06386_amd import costmodel as cm
-    cost = cm.division_cost_clipped if clipped else cm.division_cost
+    cost = cost or (cm.division_cost_clipped if clipped else cm.division_cost)
     cache, total = {}, 0
     for u, v in zip(us, vs):
         key = (len(u), len(v) - 1)          # top limbs are nonzero in the mixed workload
@@ -246,11 +246,12 @@ def settle(fn, stream, min_ms=SETTLE_MS):
     return n
 
 
-def roofline(W, W_clipped, ms, kernel, traffic, algo_bytes):
+def roofline(W, W_clipped, ms, kernel, traffic, algo_bytes, W_formed=None):
     """Roofline object of a launch of ms milliseconds.  W is the method's
     algorithmic work (limb products of Alg. 1-3 at exact operand sizes, full
     quotient and remainder products); W_clipped counts only the columns that are
-    needed of each.
+    needed of each.  The block division forms W_formed, fewer than either: frac,
+    which counts the method's work, can pass 1, frac_formed cannot.
     The products run on the int8 matrix cores (32 int8 operations per limb
     product), so achieved and peak are int8 operations per second; the
     fraction of the vector-ALU multiply peak is given beside them."""
@@ -262,6 +263,9 @@ def roofline(W, W_clipped, ms, kernel, traffic, algo_bytes):
             "work": "limb products of Alg. 1-3 at exact sizes (full u*shinv, v*q), 32 int8 ops each",
             "limb_products_per_launch": W, "limb_products_per_s": rate,
             "frac_clipped": OPS_PER_LIMB_PRODUCT * W_clipped / (ms * 1e-3) / PEAK_INT8_OPS,
+            **({} if W_formed is None else
+               {"limb_products_per_launch_formed": W_formed,
+                "frac_formed": OPS_PER_LIMB_PRODUCT * W_formed / (ms * 1e-3) / PEAK_INT8_OPS}),
             "limb_products_per_launch_clipped": W_clipped,
             "frac_valu_peak": rate / PEAK_LIMB_PRODUCTS, "valu_mad_peak_limb_products_per_s": PEAK_LIMB_PRODUCTS}
 
@@ -357,6 +361,7 @@ def time_mul(binding, na, nb, batch, steps, warmup, stream):
 
 def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
     """Per-configuration figures of a timed plain batch."""
+    from paper_2606_06386_amd import costmodel as cm
     u_h, v_h = c["u"], c["v"]
     batch = len(u_h)
     kmean = sum(ms) / len(ms)
@@ -368,7 +373,8 @@ def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
                                                                  "min": ms[0]},
             "div_per_s": batch * steps / elapsed, "div_per_s_kernel": batch / (kmean * 1e-3),
             "roofline": roofline(W, Wc, kmean, "k_divrem<%d>" % threads_for(n),
-                                 measured_traffic(c["name"]), algo_bytes),
+                                 measured_traffic(c["name"]), algo_bytes,
+                                 limb_products(u_h, v_h, cost=cm.division_cost_blocks)),
             "full_mult_equivalents_per_s": batch / (kmean * 1e-3) * (W / batch) / (n * n / 2),
             "status_ok": int((status == 0).sum())}
 
@@ -518,7 +524,7 @@ def run_mixed(args):
     """The mixed-precision batch: one mp_divrem_ragged call per step."""
     import torch
     import oracle
-    from paper_2606_06386_amd import binding, inputs as I, ragged as R, tune
+    from paper_2606_06386_amd import binding, costmodel as cm, inputs as I, ragged as R, tune
     c = I.config_c4()
     us, vs = c["u"], c["v"]
     count = len(us)
@@ -599,7 +605,8 @@ def run_mixed(args):
         "limb_products_per_launch": W,
         "limb_products_per_launch_full_products": ragged_limb_products(us, vs, clipped=False),
         "roofline": roofline(ragged_limb_products(us, vs, clipped=False), W, kmean,
-                             "k_ragged_prep + k_ragged (4 width classes)", None, algo_bytes),
+                             "k_ragged_prep + k_ragged (4 width classes)", None, algo_bytes,
+                             ragged_limb_products(us, vs, cost=cm.division_cost_blocks)),
         "status_ok": int((status == 0).sum()),
     }
     if not args.no_cpu_baseline:
