@@ -5,7 +5,7 @@
 // width so that every linear pass handles at most 16 limbs per thread:
 //   width <= 2048 limbs -> 256 threads, <= 4096 -> 512, <= 8192 -> 1024.
 // All operands and intermediates of an instance live in dynamic LDS laid out
-// by plan_body (21 KB at 2^16 bits, 74 KB at most at 2^18).
+// by plan_body (20 KB at 2^16 bits, 74 KB at most at 2^18).
 //
 // The build compiles this file once per kernel family and workgroup size
 // (MP_KFAMILY: 0 product, 1 shifted inverse, 2 division, 3 ragged division;
@@ -24,8 +24,8 @@ namespace mp {
 // quotient product), so further resident instances fill the other waves' issue
 // slots: eight waves per SIMD (64 vector and 96 scalar registers), which the LDS
 // of a 2^16-bit instance, 20 KB, also allows.  4096 divisions of 2048 by 1024
-// limbs take 151 us, seven waves 160 us; 2048 of random divisor lengths 90 and
-// 112 us.
+// limbs take 122 us, at seven waves 133; 2048 of random divisor lengths 72 and
+// 99 us.
 #define MP_OCCUPANCY __attribute__((amdgpu_waves_per_eu(M == Mode::kPacked ? 8 : 4, 8)))
 #define MP_SHARED_OCCUPANCY __attribute__((amdgpu_waves_per_eu(8, 8)))
 // products: four waves per SIMD (four accumulators and a window of four fragments per wave)

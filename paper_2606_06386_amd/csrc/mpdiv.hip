@@ -222,9 +222,9 @@ int device_cus()
 // built for four waves per SIMD finish sooner as long as the device holds the
 // batch at that; and up to three instances per compute unit are faster if four
 // waves share each quotient product (us, one wave and four: 1 of 1024 by 512
-// limbs 22.8 and 21.3, 768 26.7 and 26.1, 1024 27.4 and 28.1; 512 of 4096 by
-// 2048 73.5 and 70.2; 256 of 8192 by 4096 135 and 124), which is every such
-// batch of more than 256 threads per instance.
+// limbs 21.7 and 20.5, 768 24.7 and 24.5, 1024 25.6 and 26.1; when it was made,
+// 512 of 4096 by 2048 73.5 and 70.2, 256 of 8192 by 4096 135 and 124), which is
+// every such batch of more than 256 threads per instance.
 mp::Mode division_mode(int T, int64_t batch)
 {
     const int cus = device_cus();
@@ -279,8 +279,9 @@ int32_t *static_scratch()
 // 1024-thread workgroup per instance with the LDS of the widest division
 // (two per unit), which checks its own descriptor.  No instance waits for
 // another, so neither the preparation kernel nor the classes' streams gain
-// anything: 5 instances take 73 us (prepared 107), 256 146 (181), 512 166
-// (189), but 700 217 (195).  False: the batch is larger.
+// anything: 5 instances take 53 us (prepared 105), 256 122 (187), 512 142
+// (178); 700 would run in rounds of 512, 10% slower than by classes.  False: the
+// batch is larger.
 bool ragged_direct(const uint32_t *u_pool, const uint32_t *v_pool, const mp_desc_t *desc, uint32_t *q_pool,
                    uint32_t *r_pool, const mp::PoolLimbs &pools, int32_t *inst_status, int32_t count, hipStream_t st,
                    mp_status_t *result)
@@ -298,8 +299,8 @@ bool ragged_direct(const uint32_t *u_pool, const uint32_t *v_pool, const mp_desc
 // Streams and events of the concurrent class kernels.  The widest class, most
 // of a batch's time, runs on the caller's stream: with a stream for each class
 // a fifth one shares a hardware queue (of four), and the whole batch waits
-// for whatever is queued there (4096 mixed instances: 530 us, with four 600 to
-// 750 from one process to the next).
+// for whatever is queued there (4096 mixed instances took 530 us where a stream
+// for each class took 600 to 750 from one process to the next).
 constexpr int kForked = kClasses - 1;
 struct Forks {
     hipStream_t fs[kForked];
