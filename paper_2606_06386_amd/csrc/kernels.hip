@@ -110,9 +110,13 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged_direct(const uint32_t
 }
 
 // Persistent workgroups of one class: take the next instance of the class's
-// queue until it is empty.  Instances of 1024 threads that would not give two
-// thirds of the compute units a second one run one per unit: two slow each
-// other down (300 of a batch of 1200: 184 us for the batch, 191 in pairs).
+// queue until it is empty.  Of 1024 threads, only some of the workgroups launched
+// (two per compute unit) stay: one per unit if the instances would not give half
+// the units a second one, since two slow each other down (300 of a batch of 1200:
+// 184 us for the batch, in pairs 191); and three on two units beside a class of
+// the next width, whose workgroups then find LDS on every other unit (4096 of
+// mixed widths 417 -> 413 us, of widths spread evenly in their logarithm 419 ->
+// 394).
 template <int T>
 __global__ __launch_bounds__(T) MP_SHARED_OCCUPANCY void k_ragged(const uint32_t *up, const uint32_t *vp,
                                                                   const mp_desc_t *desc, uint32_t *qp, uint32_t *rp,
@@ -121,7 +125,11 @@ __global__ __launch_bounds__(T) MP_SHARED_OCCUPANCY void k_ragged(const uint32_t
 {
     extern __shared__ __align__(16) uint32_t lds[];
     const int n = ws[cls];
-    if (T == 1024 && (int)blockIdx.x >= cus && n <= cus + (cus >> 1)) return;
+    if (T == 1024) {
+        const int some = cus + (cus >> 1);
+        const bool beside = cls == kClasses - 1 && ws[cls - 1] >= cus;
+        if ((int)blockIdx.x >= (n <= some ? cus : beside ? some : 2 * cus)) return;
+    }
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) lds[kCtlBcast + 2] = (uint32_t)atomicAdd(&ws[kClasses + cls], 1);

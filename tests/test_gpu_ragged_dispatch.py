@@ -21,11 +21,11 @@ def _limbs(x, n):
     return np.frombuffer(x.to_bytes(4 * n, "little"), dtype="<u4").astype(np.uint32)
 
 
-def _batch(count):
+def _batch(count, widths=WIDTHS):
     rng = random.Random(count)
     us, vs, want = [], [], []
     for j in range(count):
-        n = WIDTHS[j % 4] - rng.choice((0, 1, 500))
+        n = widths[j % len(widths)] - rng.choice((0, 1, 500))
         k, d = rng.randint(1, 60), rng.randint(1, 40) if j % 31 else rng.randint(200, 450)
         m = rng.randint(k, n)
         u = rng.getrandbits(32 * (k + d))
@@ -89,3 +89,20 @@ def test_ragged_both_sides_of_each_launch_rule(per_cu, extra, entry):
         torch.arange(1 << 16, device="cuda").sum().item()      # unrelated eager work
         g.replay()
         check(f"replay {rep}")
+
+
+@pytest.mark.parametrize("widths", [(8192,), (4096, 8192, 8192, 8192)])
+def test_ragged_batches_of_the_widest_class(widths):
+    """(with no or few instances of the next class beside)"""
+    import torch
+    from paper_2606_06386_amd import binding
+    us, vs, want = _batch(800, widths)
+    packed = R.pack(us, vs)
+    rb = binding.Ragged(packed)
+    rb.run()
+    torch.cuda.synchronize()
+    q, r, st = (x.cpu().numpy().view(np.uint32) for x in (rb.q, rb.r, rb.status))
+    qs, rs = R.unpack(q, packed["desc"], "q"), R.unpack(r, packed["desc"], "r")
+    bad = [j for j in range(800) if st[j] != want[j][2] or (qs[j] != _limbs(want[j][0], len(qs[j]))).any()
+           or (rs[j] != _limbs(want[j][1], len(rs[j]))).any()]
+    assert not bad, f"{len(bad)} mismatching instances, first {bad[:8]}"
