@@ -83,8 +83,12 @@ def _limbs(t, name):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """The HIP stream handle of `stream`, or of the current device's current one
+    (read without making a Stream object, 0.3 us instead of 2.9 per call: the
+    smallest products take 10 us from call to call, most of it on the host)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _raise(code, what):
