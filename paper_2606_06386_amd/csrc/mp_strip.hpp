@@ -63,7 +63,7 @@ MP_DEV uint32_t row_carry_out(uint64_t G, uint64_t P)
 }
 
 constexpr uint32_t kBal = 0x80808080u, kBalTop = 0x7F7F7F7Fu;   // (limbs above kBalTop carry)
-constexpr int kRowBatch = 5;   // rows read at once (a block's 257 + 3 limbs)
+constexpr int kRowBatch = 5;   // rows read at once (an iterate's 257 + 2 limbs)
 
 // out(k, digit limb) for the limbs k of rows [r0, r1): the balanced radix-256
 // digits of the n-limb number x with carry-in cin0 at limb 0.  Limb n gets the

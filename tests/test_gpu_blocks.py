@@ -1,6 +1,6 @@
 """Block division at the sizes where its splits change, against the oracle.
 
-The quotient's d = h - k limbs are found in blocks of at most 257 limbs, the
+The quotient's d = h - k limbs are found in blocks of at most 252 limbs, the
 remainder is updated in strips of 256 columns of k + 2 limbs, digits are
 converted in rows of 64 limbs and 8-limb blocks, and the inverse's precision
 follows the longest block.  Quotient and divisor lengths on both sides of each
