@@ -260,6 +260,19 @@ MP_DEV bool all_zero(int l, const uint32_t *x, int n)
     return true;
 }
 
+// x >= y for numbers of n limbs, by one wave, 64 limbs at a time from the top
+template <class FX, class FY>
+MP_DEV bool not_less(int l, int n, const FX &x, const FY &y)
+{
+    for (int c = n - 1; c >= 0; c -= kLanes) {
+        const int j = c - (kLanes - 1) + l;
+        const uint32_t a = j >= 0 ? x(j) : 0u, b = j >= 0 ? y(j) : 0u;
+        const uint64_t ne = ballot(a != b), gt = ballot(a > b);
+        if (ne) return (gt >> (63 - __builtin_clzll(ne))) & 1u;
+    }
+    return true;
+}
+
 constexpr int kStartLimbs = 46;   // longest iterate of newton_start
 
 // limbs a Newton step to f limbs starts from: the first step's are exact to one
@@ -481,6 +494,74 @@ MP_DEV int precision(int, int, const PowB &u, int, uint32_t, uint32_t *)
     return u.e + 1;
 }
 
+// Whether a comparison shows the quotient to be 0 or 1: u has h limbs, d - 1 more
+// than v, whose top limb k is vk (v is not B^k).
+MP_DEV bool quotient_below_two(int l, const Span &u, int h, int d, uint32_t vk, const uint32_t *v, int)
+{
+    return d == 1 && (vk >> 31 || !not_less(l, h, u, Span{v, 0, h}));   // (vk >= 2^31: u < B^h <= 2v)
+}
+
+// (B^e of v's length is less than v, of one limb more than 2v if v > B^e / 2)
+MP_DEV bool quotient_below_two(int l, const PowB &, int, int d, uint32_t vk, const uint32_t *v, int k)
+{
+    return d == 1 || (d == 2 && (vk > 0x80000000u || (vk == 0x80000000u && !all_zero(l, v, k))));
+}
+
+// The n <= 3 limbs of U by the limb v: the quotient's limbs to a, the remainder
+// returned.  The digits are chosen in double precision, a relative 2^-40 low (at
+// most 2^-8 of a unit), so they are exact or one too small.
+template <class FU>
+MP_DEV uint32_t short_division(const FU &U, int n, uint32_t v, uint32_t (&a)[3])
+{
+    const double d = (double)v;
+    double r = __builtin_amdgcn_rcp(d);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+    r -= r * 0x1p-40;
+    uint32_t rem = 0;
+#pragma unroll 1
+    for (int i = n - 1; i >= 0; i--) {
+        const uint64_t x = (uint64_t)rem << 32 | U(i);
+        const uint32_t q = (uint32_t)((double)x * r);
+        const uint64_t m = x - (uint64_t)q * v;
+        a[2] = a[1];
+        a[1] = a[0];
+        a[0] = q + (m >= v ? 1u : 0u);
+        rem = (uint32_t)(m >= v ? m - v : m);
+    }
+    return rem;
+}
+
+// Divisions that need no inverse, by all waves: of up to three limbs by one (k =
+// 0), and those of quotient_below_two.  A call, made once nothing else is
+// live: inlined, its registers pass the 64 of the packed kernels (one spilled,
+// random divisor lengths 1 to 2% slower).
+template <int T, class FU>
+__device__ __attribute__((noinline)) void divide_without_inverse(FU U, int h, int k, uint32_t vk, const uint32_t *v,
+                                                                 uint32_t *q, int nq, uint32_t *r, int nr,
+                                                                 int32_t *status)
+{
+    constexpr int W = T / kLanes;
+    const int l = lane(), w = wave_index(), t = w * kLanes + l;
+    bool ok = true;
+    if (k == 0) {
+        uint32_t a[3] = {0u, 0u, 0u};
+        const uint32_t rem = short_division(U, h, vk, a);
+        ok = (nq > 2 || a[2] == 0u) && (nq > 1 || a[1] == 0u);
+        for (int i = t; i < nq; i += T) q[i] = !ok ? 0u : i == 0 ? a[0] : i == 1 ? a[1] : i == 2 ? a[2] : 0u;
+        for (int i = t; i < nr; i += T) r[i] = ok && i == 0 ? rem : 0u;
+    } else {
+        const bool one = not_less(l, h, U, Span{v, 0, k + 1});
+        for (int i = t; i < nq; i += T) q[i] = one && i == 0 ? 1u : 0u;
+        if (nr) {                                     // r = u - q v, both of k + 1 limbs
+            const int rows = (k + 64) >> 6, per = (rows + W - 1) / W, r0 = w * per, r1 = imin(rows, r0 + per);
+            if (r0 < r1) addsub_rows(l, r0, r1, k + 1, true, U, Span{v, 0, one ? k + 1 : 0}, r);
+            for (int i = k + 1 + t; i < nr; i += T) r[i] = 0u;
+        }
+    }
+    if (status && t == 0) *status = ok ? kInstOk : kInstQWidth;
+}
+
 // (q, r) with u = q v + r, 0 <= r < v: q has nq limbs, r (unless null) nv.
 // U(i) is limb i of the dividend, which has at most nu limbs; bmax: longest
 // block.
@@ -519,6 +600,13 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         for (int i = t; i < nq; i += T) q[i] = 0u;
         for (int i = t; i < nr; i += T) r[i] = 0u;
         if (status && t == 0) *status = kInstQWidth;
+        return;
+    }
+    // Without the inverse they take (us; with it): 4096 of 64 by 64 limbs and a
+    // quotient of 0 or 1 6.8 (19.8), of 1 by 1 limb 5.7 (18.7), 4096 inverses of B^7
+    // by 8 limbs 5.4 (17.9), any one of these 4.4 (6.6).
+    if (__builtin_expect(d <= 3, 0) && (k == 0 || quotient_below_two(l0, U, h, d, vk, v, k))) {
+        divide_without_inverse<T>(U, h, k, vk, v, q, nq, r, nr, status);
         return;
     }
     const int sv = k == 0 ? 1 : 0;                    // a one-limb divisor: u B / (v B)
@@ -664,18 +752,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
     int delta = 0;
     for (int it = 0; good; it++) {
         bool neg = (int32_t)uniform(Ra[k + 1]) < 0, ge = uniform(Ra[k + 1]) != 0u;
-        if (!ge) {                                    // compare with v from the top, 64 limbs at a time
-            ge = true;                                // (equal: R = v)
-            for (int c = k; c >= 0; c -= kLanes) {
-                const int j = c - (kLanes - 1) + lane_at(it);
-                const uint32_t a = j >= 0 ? Ra[j] : 0u, x = j >= 0 ? Vv(j) : 0u;
-                const uint64_t ne = ballot(a != x), gt = ballot(a > x);
-                if (ne) {
-                    ge = (gt >> (63 - __builtin_clzll(ne))) & 1u;
-                    break;
-                }
-            }
-        }
+        if (!ge) ge = not_less(lane_at(it), k + 1, [&](int j) { return Ra[j]; }, Vv);   // (equal: R = v)
         if (!neg && !ge) break;
         if (it == 4) {
             good = false;
