@@ -44,6 +44,8 @@ size_t body_bytes(int nu, int nv, mp::Mode mode = mp::Mode::kPacked)
 constexpr int kClasses = 4;
 constexpr int kClassWidth[kClasses] = {1024, 2048, 4096, 8192};
 constexpr int kWsHeader = 16;
+static_assert(mp::plan_body(kClassWidth[kClasses - 1], kClassWidth[kClasses - 1]).total <= kLdsWords,
+              "an instance of the widest class fits the LDS of a workgroup");
 
 __device__ __forceinline__ int width_class(int nu)
 {
@@ -322,26 +324,31 @@ mp_status_t ragged_launch(const uint32_t *u_pool, const uint32_t *v_pool, const 
     hipLaunchKernelGGL(k_ragged_prep, dim3(1), dim3(1024), 0, st, desc, count, pools, inst_status, ws);
     if (hipGetLastError() != hipSuccess) return MP_ERR_LAUNCH;
     if (fk && hipEventRecord(fk->ev_fork, st) != hipSuccess) return MP_ERR_LAUNCH;
-    for (int c = kClasses - 1; c >= 0; c--) {
+    mp_status_t result = MP_OK;
+    int forks = kForked;                              // the fork streams [forks, kForked) hold work
+    for (int c = kClasses - 1; c >= 0 && result == MP_OK; c--) {
         const bool forked = fk && c < kForked;
         hipStream_t fs = forked ? fk->fs[c] : st;
-        if (forked && hipStreamWaitEvent(fs, fk->ev_fork, 0) != hipSuccess) return MP_ERR_LAUNCH;
+        if (forked && hipStreamWaitEvent(fs, fk->ev_fork, 0) != hipSuccess) {
+            result = MP_ERR_LAUNCH;
+            break;
+        }
+        if (forked) forks = c;
         const int T = g_ragged.threads[c];
         const size_t bytes = body_bytes(kClassWidth[c], kClassWidth[c]);   // the class's widest instance
-        if (bytes > (size_t)kLdsWords * 4) return MP_ERR_SIZE;
         const int fit = (int)(((size_t)kLdsWords * 4) / bytes);
         const int wpc = g_ragged.wgs_per_cu[c] < fit ? g_ragged.wgs_per_cu[c] : fit;
         const auto launch = T == 256   ? mp::launch_ragged<256>
                             : T == 512 ? mp::launch_ragged<512>
                                        : mp::launch_ragged<1024>;
-        const hipError_t e = launch(cus * wpc, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
-                                    count, cus, bmax);
-        if (e != hipSuccess) return MP_ERR_LAUNCH;
-        if (forked && hipEventRecord(fk->ev_join[c], fs) != hipSuccess) return MP_ERR_LAUNCH;
+        result = status_of(launch(cus * wpc, bytes, fs, u_pool, v_pool, desc, q_pool, r_pool, inst_status, ws, c,
+                                  count, cus, bmax));
+        if (forked && hipEventRecord(fk->ev_join[c], fs) != hipSuccess) result = MP_ERR_LAUNCH;
     }
-    for (int c = 0; fk && c < kForked; c++)
-        if (hipStreamWaitEvent(st, fk->ev_join[c], 0) != hipSuccess) return MP_ERR_LAUNCH;
-    return MP_OK;
+    // (also after a failure: what runs on a fork stream must not outlive the caller's order)
+    for (int c = forks; c < kForked; c++)
+        if (hipStreamWaitEvent(st, fk->ev_join[c], 0) != hipSuccess) result = MP_ERR_LAUNCH;
+    return result;
 }
 
 }  // namespace
