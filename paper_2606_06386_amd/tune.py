@@ -4,20 +4,21 @@ For each dividend width class of mp_divrem_ragged (<= 1024, 2048, 4096, 8192
 limbs) it times a one-class batch of seeded random divisions under every
 valid (threads per workgroup, hence limbs per thread in the linear passes;
 persistent workgroups per compute unit) and installs the fastest with
-mp_ragged_config.  Then, on a seeded mixed batch, it times the two
-process-wide knobs of the method's schedule and product engine: how long the
-blocks of quotient limbs are (MP_KNOB_SMALL_LIMIT, in limbs of the inverse's
-last Newton step) and from which operand length mp_mul_batch moves from the
-vector ALU to the matrix cores (MP_KNOB_MFMA_MIN),
-and installs the fastest pair.  Results are cached in a JSON file keyed by
+mp_ragged_config.  Then it times the two process-wide knobs, each on the calls
+that read it: how long the blocks of quotient limbs are (MP_KNOB_SMALL_LIMIT,
+in limbs of the inverse's last Newton step) on a seeded mixed batch, and from
+which operand length mp_mul_batch moves from the vector ALU to the matrix cores
+(MP_KNOB_MFMA_MIN) on products with short operands of the lengths in question;
+and installs the fastest of each.  Results are cached in a JSON file keyed by
 the device (architecture name and compute-unit count) and by a hash of the
-kernel sources, so a cache entry is never applied to a different chip or to
-changed kernels.  Timing runs on the GPU; nothing here computes any part of
+kernel sources and of this file, so a cache entry is never applied to a
+different chip, to changed kernels or if it was chosen another way.  Timing runs on the GPU; nothing here computes any part of
 a division, and every setting gives the same bits.
 """
 import hashlib
 import json
 import os
+import time
 
 import numpy as np
 
@@ -32,9 +33,9 @@ _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 
 def source_hash():
     h = hashlib.sha256()
-    for f in sorted(os.listdir(_CSRC)):
-        with open(os.path.join(_CSRC, f), "rb") as fh:
-            h.update(f.encode() + b"\0" + fh.read())
+    for f in [os.path.join(_CSRC, f) for f in sorted(os.listdir(_CSRC))] + [os.path.abspath(__file__)]:
+        with open(f, "rb") as fh:
+            h.update(os.path.basename(f).encode() + b"\0" + fh.read())
     return h.hexdigest()[:16]
 
 
@@ -61,14 +62,14 @@ def class_batch(cls, count):
     return us, vs
 
 
-def _time(rb, reps):
+def _time(call, reps):
     import torch
-    rb.run()
+    call()
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record()
     for _ in range(reps):
-        rb.run()
+        call()
     e1.record()
     torch.cuda.synchronize()
     return e0.elapsed_time(e1) / reps
@@ -77,31 +78,57 @@ def _time(rb, reps):
 AUTO = -2           # the library's own limit (MP_SMALL_LIMIT_AUTO)
 SMALL_LIMITS = (AUTO, 32, 48, 64, 80, 96, 112, 128, 136)
 MFMA_MINS = (32, 64, 96, 128)
-AUTO_SLACK = 1.01    # the per-launch setting is kept unless a fixed one is >1% faster
+MFMA_MIN_DEFAULT = 64
+AUTO_SLACK = 1.01    # the library's own settings are kept unless another is >1% faster
+
+
+def product_calls(batch=2048, hi=1024):
+    """Products whose short operand lies between two of MFMA_MINS, one call for each gap."""
+    import torch
+    from . import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(I.SEED_C4)
+    limbs = lambda n: torch.randint(-2 ** 31, 2 ** 31, (batch, n), dtype=torch.int32, device="cuda", generator=gen)
+    pairs = [(limbs((a + b) // 2), limbs(hi)) for a, b in zip(MFMA_MINS, MFMA_MINS[1:])]
+    return [lambda a=a, b=b: binding.mul(a, b) for a, b in pairs]
+
+
+ROUNDS = 3          # over all values in turn
+WARM_S = 0.06       # before them: from idle the clock rises for some 25 ms
+
+
+def _tune_knob(knob, name, values, default, time_ms, log=None):
+    """Set the knob to the value of the shortest time, or to the default where that is
+    within AUTO_SLACK of it; returns (value, ms)."""
+    from . import binding
+    start = time.perf_counter()
+    while time.perf_counter() - start < WARM_S:
+        time_ms()
+    best = dict.fromkeys(values, float("inf"))
+    for _ in range(ROUNDS):
+        for x in values:
+            binding.set_knob(knob, x)
+            best[x] = min(best[x], time_ms())
+    if log:
+        for x, ms in best.items():
+            log("knob %s %s: %.3f ms" % (name, "auto" if x == AUTO else x, ms))
+    x = min(values, key=best.get)
+    x = default if best[default] <= best[x] * AUTO_SLACK else x
+    binding.set_knob(knob, x)
+    return x, best[x]
 
 
 def tune_knobs(count=1024, reps=3, log=None):
-    """Time every (small_limit, mfma_min) pair on a seeded mixed batch (all four
-    width classes); installs and returns the fastest as {knob: value, 'ms': ms}.
-    The library's own limit (AUTO) is preferred over a fixed limit that is not clearly faster on this batch."""
+    """Time every small_limit on a seeded mixed batch (all four width classes) and
+    every mfma_min on products (divisions do not read it); installs the fastest of
+    each and returns them as {knob: value, 'ms': ms of the mixed batch}."""
     from . import binding, ragged
     m = I.config_c4(index=np.arange(0, 8 * count, 8))
     rb = binding.Ragged(ragged.pack(m["u"], m["v"]))
-    times = []
-    for sl in SMALL_LIMITS:
-        for mm in MFMA_MINS:
-            binding.set_knob(binding.MP_KNOB_SMALL_LIMIT, sl)
-            binding.set_knob(binding.MP_KNOB_MFMA_MIN, mm)
-            ms = _time(rb, reps)
-            times.append((ms, sl, mm))
-            if log:
-                log("knobs small_limit %s, mfma_min %d: %.3f ms" % ("auto" if sl == AUTO else sl, mm, ms))
-    ms, sl, mm = min(times)
-    auto_ms, _, auto_mm = min(t for t in times if t[1] == AUTO)
-    if auto_ms <= ms * AUTO_SLACK:
-        ms, sl, mm = auto_ms, AUTO, auto_mm
-    binding.set_knob(binding.MP_KNOB_SMALL_LIMIT, sl)
-    binding.set_knob(binding.MP_KNOB_MFMA_MIN, mm)
+    sl, ms = _tune_knob(binding.MP_KNOB_SMALL_LIMIT, "small_limit", SMALL_LIMITS, AUTO, lambda: _time(rb.run, reps), log)
+    calls = product_calls()
+    mm, _ = _tune_knob(binding.MP_KNOB_MFMA_MIN, "mfma_min", MFMA_MINS, MFMA_MIN_DEFAULT,
+                       lambda: sum(_time(f, 10 * reps) for f in calls), log)
     return {"small_limit": sl, "mfma_min": mm, "ms": ms}
 
 
@@ -117,7 +144,7 @@ def tune(counts=(2048, 1024, 1024, 768), reps=3, log=None):
         times = []
         for t, g in candidates(cls):
             binding.ragged_config(cls, t, g)
-            ms = _time(rb, reps)
+            ms = _time(rb.run, reps)
             times.append((ms, t, g))
             if log:
                 log("class %d (<= %d limbs): threads %d, %d WG/CU: %.3f ms" % (cls, CLASS_WIDTHS[cls], t, g, ms))
