@@ -132,14 +132,20 @@ def tune_knobs(count=1024, reps=3, log=None):
     return {"small_limit": sl, "mfma_min": mm, "ms": ms}
 
 
+def smallest_classed_batch():
+    """Instances from which mp_divrem_ragged runs its class kernels: up to two per
+    compute unit take one launch that reads no class configuration."""
+    import torch
+    return 2 * torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count + 1
+
+
 def tune(counts=(2048, 1024, 1024, 768), reps=3, log=None):
-    """Time every candidate per class; returns {cls: (threads, wgs_per_cu, ms)}.
-    (Batches of at most two instances per compute unit run outside the classes:
-    the counts are above that.)"""
+    """Time every candidate per class on a batch of `counts` instances (at least
+    as many as reach the class kernels); returns {cls: (threads, wgs_per_cu, ms)}."""
     from . import binding, ragged
-    best = {}
+    best, least = {}, smallest_classed_batch()
     for cls in range(len(CLASS_WIDTHS)):
-        us, vs = class_batch(cls, counts[cls])
+        us, vs = class_batch(cls, max(counts[cls], least))
         rb = binding.Ragged(ragged.pack(us, vs))
         times = []
         for t, g in candidates(cls):

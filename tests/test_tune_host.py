@@ -43,3 +43,14 @@ def test_small_limit_clearly_faster_than_the_librarys_own(host):
     host.setattr(tune, "_time", lambda call, reps: 0.9 if binding.get_knob(binding.MP_KNOB_SMALL_LIMIT) == 96 else 1.0)
     host.setattr(tune, "product_calls", lambda: [lambda: None], raising=False)
     assert tune.tune_knobs(count=4)["small_limit"] == 96 == binding.get_knob(binding.MP_KNOB_SMALL_LIMIT)
+
+
+def test_class_configurations_are_timed_where_they_are_read(host):
+    """Batches of at most two instances per compute unit run outside the classes."""
+    seen = {}
+    host.setattr(tune, "class_batch", lambda cls, count: seen.setdefault(cls, count) and ([[1]], [[1]]))
+    host.setattr(tune, "_time", lambda call, reps: 1.0)
+    host.setattr(tune, "smallest_classed_batch", lambda: 513, raising=False)
+    host.setattr(binding, "ragged_config", lambda cls, threads, wgs: None)
+    best = tune.tune(counts=(32, 16, 600, 4), reps=1)
+    assert set(best) == {0, 1, 2, 3} and seen == {0: 513, 1: 513, 2: 600, 3: 513}
