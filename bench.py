@@ -107,36 +107,39 @@ TRAFFIC_SOURCES = ["paper_2606_06386_amd/csrc/mp_prims_hip.hpp", "paper_2606_063
                    "paper_2606_06386_amd/csrc/kernels.hip", "paper_2606_06386_amd/csrc/mpdiv.hip"]
 
 
-def write_traffic(fetch_csv, write_csv, workload_name, kernels=("k_head_divrem", "k_divrem<")):
+def write_traffic(fetch_csv, write_csv, workload_name, kernels=("k_divrem<",)):
     """profiles/k_divrem_<workload>_traffic.json from two rocprofv3 --pmc
     counter files (FETCH_SIZE, WRITE_SIZE) of `bench.py --copy-calibration`:
-    the mean KiB per dispatch of each of `kernels` that the file holds (every
-    kernel of one launch), summed, each counter scaled by what it reads for the
-    256 MiB device copy."""
+    the mean KiB per dispatch of every division kernel of a launch, summed, each
+    counter scaled by what it reads for the 256 MiB device copy.  Each of
+    `kernels` has to be in both files, and both have to hold the same ones."""
     import csv
     import hashlib
 
     def read(path, counter):
-        kern, copy = {k: [] for k in kernels}, []
+        kern, copy = {}, []
         with open(path) as fh:
             for row in csv.DictReader(fh):
                 if row["Counter_Name"] != counter:
                     continue
                 v = float(row["Counter_Value"])
-                hit = [k for k in kernels if k in row["Kernel_Name"]]
-                if hit:
-                    kern[hit[0]].append(v)
+                if "divrem" in row["Kernel_Name"]:
+                    kern.setdefault(row["Kernel_Name"], []).append(v)
                 elif "copyBuffer" in row["Kernel_Name"]:
                     copy.append(v)
-        assert any(kern.values()) and copy, (path, counter, {k: len(x) for k, x in kern.items()}, len(copy))
-        return sum(sum(x) / len(x) for x in kern.values() if x), max(copy)   # the 256 MiB copy is the largest
+        missing = [k for k in kernels if not any(k in name for name in kern)]
+        assert not missing and copy, (path, counter, {k: len(x) for k, x in kern.items()}, len(copy))
+        names.append(sorted(kern))
+        return sum(sum(x) / len(x) for x in kern.values()), max(copy)   # the 256 MiB copy is the largest
 
+    names = []
     f_k, f_c = read(fetch_csv, "FETCH_SIZE")
     w_k, w_c = read(write_csv, "WRITE_SIZE")
+    assert names[0] == names[1], names
     nbytes = 256 << 20
     ff, wf = nbytes / 1024 / f_c, nbytes / 1024 / w_c
     h = hashlib.sha256(b"".join(open(os.path.join(ROOT, s_), "rb").read() for s_ in TRAFFIC_SOURCES)).hexdigest()
-    rec = {"kernels": list(kernels), "workload": workload_name, "fetch_size_kib_per_dispatch": f_k,
+    rec = {"kernels": names[0], "workload": workload_name, "fetch_size_kib_per_dispatch": f_k,
            "write_size_kib_per_dispatch": w_k,
            "copy_calibration": {"bytes": nbytes, "fetch_size_kib": f_c, "write_size_kib": w_c},
            "fetch_factor": ff, "write_factor": wf, "traffic_bytes_per_dispatch": 1024 * (f_k * ff + w_k * wf),
