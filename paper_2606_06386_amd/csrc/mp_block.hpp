@@ -237,7 +237,7 @@ MP_DEV int precision(int l, int w, const uint32_t *x, int n, uint32_t top, uint3
         }
         uint32_t *sl = slot + (s & 1) * W;       // (the step before may still be read)
         if (l == 0) sl[w] = (uint32_t)found;
-        bar<T>();
+        sync();
         const uint32_t f = l < W ? sl[l] : 0u;
         const uint64_t mf = ballot(f != 0u);
         if (mf) return (int)readlane(f, 63 - __builtin_clzll(mf));
@@ -640,7 +640,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         const int r0 = (w - 1) * per, r1 = imin(rows, r0 + per);
         if (r0 < r1) balance_rows(l0, r0, r1, k + 1, 0u, Vv, StorePlane4{Vd, pl.nV, pl.lyV});
     }
-    bar<T>();
+    sync();
     MP_STAMP(9);
     // W by the first wave, while the others read the dividend (zeros above it)
     if (w == 0) {
@@ -659,7 +659,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
                 if (i0 + j * S < pl.capR) R[i0 + j * S] = a[j];
         }
     }
-    bar<T>();
+    sync();
     MP_STAMP(2);
     bool good = true;
     const int n2 = k + 2, bs2 = (n2 + kStrip - 1) / kStrip, base2 = ((n2 + 7) & ~7) - bs2 * kStrip;
@@ -688,7 +688,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             top_digits(l, R + o + k - 1, nt, Td);
             MP_STAMP(16 + 3 * (i % 5));   // (trace build: the phases of the last five blocks)
         }
-        bar<T>();
+        sync();
         const bool carries = w == W - 1 && i && late;
         if constexpr (SHARED) {
             MfmaAcc acc;
@@ -697,7 +697,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
                 acc = strip_sums<FAST>(xw0, yt0, cq, w, kShares);
                 if (w) acc_store(l, acc, part + (w - 1) * 1024);
             }
-            bar<T>();
+            sync();
             if (w == 0) {
 #pragma unroll
                 for (int j = 0; j < kShares - 1; j++) acc_add(l, acc, part + j * 1024);
@@ -722,7 +722,7 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             quotient_digits(l, q, b, XQ);
             quotient_sign(l, Q + b, sign, d - op);
         }
-        bar<T>();
+        sync();
         MP_STAMP(17 + 3 * (i % 5));
         if (SHARED && w == 0) {
             uint32_t *Q = R + k + 2 + o;
@@ -738,14 +738,14 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
             },
             [&](int lu) { return FAST ? yv0 : planes4(lu, Vd, pl.lyV, n2); }, R + o, n2, base2, bs2);
         if (w == 0) wave_priority<3>();
-        bar<T>();
+        sync();
         MP_STAMP(18 + 3 * (i % 5));
     }
     if (w == 0) {
         strip_carries(lane_at(nb), ctl, R, n2, base2, bs2);
         wave_priority<0>();
     }
-    bar<T>();
+    sync();
     MP_STAMP(6);
     // corrections: R is a signed (k + 2)-limb number in (-1.1 v, 2.1 v)
     uint32_t *Q = R + k + 2, *Ra = R, *Rb = Vd;       // (the divisor's digits are no longer needed)
@@ -762,14 +762,14 @@ MP_DEV void divide_instance(uint32_t *lds, const FU &U, int nu, const uint32_t *
         const int r0 = w * per, r1 = imin(rows, r0 + per);
         if (r0 < r1) addsub_rows(lane_at(it), r0, r1, n2, !neg, Span{Ra, 0, n2}, Vv, Rb);
         delta += neg ? -1 : 1;
-        bar<T>();
+        sync();
         uint32_t *x = Ra;
         Ra = Rb;
         Rb = x;
     }
     if (good && delta) {
         if (w == 0) add_small(lane_at(delta), Q, d + 1, delta);
-        bar<T>();
+        sync();
     }
     MP_STAMP(7);
     int32_t st = good ? kInstOk : kInstInternal;

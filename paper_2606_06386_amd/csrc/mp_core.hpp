@@ -2,12 +2,12 @@
 //
 // One workgroup of T threads (T/64 wavefronts) owns one multi-precision
 // instance.  Operands live in LDS (or are read straight from global memory
-// through a view); every primitive below is called by all T threads with the
-// same (uniform) arguments, begins with a workgroup barrier so that it sees
-// every earlier write, and leaves its results unsynchronised (the next
-// primitive's opening barrier publishes them).
+// through a view).
 //
-// Here: the views operands are read through, and the vector-ALU product.
+// Here: the views operands are read through, and the vector-ALU product, whose
+// two passes (copy, mul) are called by all T threads with the same arguments,
+// begin with a workgroup barrier so that they see every earlier write, and leave
+// their results unsynchronised.
 // The primitives header (mp_prims_hip.hpp) must be included first.
 #pragma once
 
@@ -33,15 +33,6 @@ MP_HD constexpr int r4(int x) { return (x + 3) & ~3; }
 MP_HD constexpr int hmax(int a, int b) { return a > b ? a : b; }
 MP_HD constexpr int hmin(int a, int b) { return a < b ? a : b; }
 
-// barrier of the T threads working on an instance: the workgroup, or (T = 64)
-// a single wave, which needs no hardware barrier
-template <int T>
-MP_DEV void bar()
-{
-    if constexpr (T > kLanes) sync();
-    else wave_sync();
-}
-
 MP_DEV int imin(int a, int b) { return a < b ? a : b; }
 MP_DEV int imax(int a, int b) { return a > b ? a : b; }
 
@@ -61,10 +52,6 @@ struct Span {
     }
 };
 
-struct Zero {
-    MP_DEV uint32_t operator()(int) const { return 0u; }
-};
-
 // B^e
 struct PowB {
     int e;
@@ -75,9 +62,9 @@ struct PowB {
 template <int T, class FS>
 MP_DEV void copy(uint32_t *dst, int n, int clear, const FS &src)
 {
-    bar<T>();
+    sync();
     const int e = imax(n, clear);
-    int k = tid<T>();
+    int k = (int)threadIdx.x;
     for (; k + 3 * T < e; k += 4 * T) {
         const uint32_t y0 = k < n ? src(k) : 0u, y1 = k + T < n ? src(k + T) : 0u;
         const uint32_t y2 = k + 2 * T < n ? src(k + 2 * T) : 0u, y3 = k + 3 * T < n ? src(k + 3 * T) : 0u;
@@ -145,8 +132,8 @@ MP_DEV void strip_resolve(uint32_t *ctl, int s, int K0, const uint64_t (&lo)[4],
 }
 
 
-// p[0, na + nb) = a * b but for the carries between strips (in the strip slots,
-// see valu_strip_carries).  `a` (na limbs, readable up to 3 limbs past its end)
+// p[0, na + nb) = a * b but for the carries between strips (in the strip slots;
+// mul_valu_instance adds them).  `a` (na limbs, readable up to 3 limbs past its end)
 // is the row operand, read with wave-uniform addresses; `bw` points at limb 0
 // of the window operand (nb limbs) staged in LDS with kPad zero limbs on both
 // sides, 16-byte aligned.  The shorter operand should be the rows: the waste of
@@ -163,9 +150,9 @@ template <int T>
 MP_DEV void mul(uint32_t *ctl, uint32_t *p, const uint32_t *a, int na, const uint32_t *bw, int nb)
 {
     constexpr int W = T / kLanes;
-    bar<T>();
+    sync();
     const int ncols = na + nb, nstrips = (ncols + kStrip - 1) / kStrip;
-    const int w = uniform(tid<T>() / kLanes), l = lane();
+    const int w = wave_index(), l = lane();
     for (int s = w; s < nstrips; s += W) {
         const int K0 = s * kStrip, k0 = K0 + l * kRCol;
         const int ilo = imax(0, K0 - nb + 1) & ~3;

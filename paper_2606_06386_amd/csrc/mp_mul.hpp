@@ -251,7 +251,7 @@ MP_DEV void mul_instance(uint32_t *lds, const uint32_t *a, int na, const uint32_
         if (r1 > ry && r0 < ry + rx)
             balance_rows(l, imax(0, r0 - ry), imin(rx, r1 - ry), nx, 0u, Span{x, 0, nx}, StoreRev{X, nx + 1});
     }
-    bar<T>();
+    sync();
     MP_STAMP(1);
     const int ns = (nc + kStrip - 1) / kStrip;
     uint32_t z[K][G][4];
@@ -277,7 +277,7 @@ MP_DEV void mul_instance(uint32_t *lds, const uint32_t *a, int na, const uint32_
         }
         if (l == 0) ctl[kCtlStrip + g] = (uint32_t)e;
     }
-    bar<T>();
+    sync();
     MP_STAMP(4);
     const bool quads = ((nc | (int)((uintptr_t)c >> 2)) & 3) == 0;
 #pragma unroll
@@ -305,7 +305,7 @@ MP_DEV void mul_instance(uint32_t *lds, const uint32_t *a, int na, const uint32_
         }
         if (l == 0) ctl[kCtlOver + g] = (uint32_t)over;
     }
-    bar<T>();
+    sync();
     if (w == 0) {
         const int v = l < K * W ? (int)ctl[kCtlOver + l] : 0;
         for (uint64_t m = ballot(v != 0); m; m &= m - 1) {
@@ -330,7 +330,7 @@ MP_DEV void mul_valu_instance(uint32_t *lds, const uint32_t *a, int na, const ui
     copy<T>(A, nlo, r4(nlo) + 4, Span{sht, 0, nlo});
     copy<T>(SB - kPad, kPad + nhi, 2 * kPad + r4(nhi), Span{lng, kPad, nhi});
     mul<T>(ctl, P, A, nlo, SB, nhi);
-    bar<T>();
+    sync();
     if (wave_index() == 0) {
         // lane s adds the 64-bit carry of strip s - 1 to the first two limbs of strip s (a carry out of those ripples on)
         const int nc = na + nb, ns = (nc + kStrip - 1) / kStrip, s = lane(), at = s * kStrip;
@@ -345,8 +345,8 @@ MP_DEV void mul_valu_instance(uint32_t *lds, const uint32_t *a, int na, const ui
             if (k < nc) ripple(lane(), P + k, nc - k, true);
         }
     }
-    bar<T>();
-    for (int i = tid<T>(); i < na + nb; i += T) c[i] = P[i];
+    sync();
+    for (int i = (int)threadIdx.x; i < na + nb; i += T) c[i] = P[i];
 }
 
 }  // namespace mp

@@ -49,15 +49,6 @@ MP_DEV int lane_at(int at)
     asm("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l) : "s"(at));
     return l;
 }
-// index of the calling thread among the T threads working on one instance:
-// the workgroup's thread index, or the lane when a single wave owns the
-// instance (that wave may be any wave of its workgroup)
-template <int T>
-MP_DEV int tid()
-{
-    if constexpr (T == kLanes) return lane();
-    else return (int)threadIdx.x;
-}
 MP_DEV void sync() { __syncthreads(); }
 // orders this wave's LDS accesses before and after it (a wave runs in
 // lockstep and the LDS serves one wave's requests in order; only the
