@@ -382,7 +382,7 @@ def plain_result(c, elapsed, ms, q_h, r_h, status, steps):
             "status_ok": int((status == 0).sum())}
 
 
-# the four stamps of a block of quotient limbs in the body
+# the three phases of a block of quotient limbs, each ending at a stamp
 BLOCK_PHASES = ["quotient_top_digits", "quotient", "remainder_update"]
 
 

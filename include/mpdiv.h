@@ -154,11 +154,13 @@ mp_status_t mp_divrem_ragged_static(const uint32_t *u_pool, int64_t u_limbs, con
                                     void *stream);
 
 /*
- * Launch configuration of width class cls (0..3) for mp_divrem_ragged:
- * threads per workgroup (256, 512 or 1024, at least width/8) and persistent
- * workgroups per compute unit (1..8; as many as the LDS holds are launched).
- * Returns MP_ERR_ARG for an invalid choice.  The defaults come from the
- * library's tuned table.
+ * Launch configuration of width class cls (0..3) for mp_divrem_ragged and
+ * mp_divrem_ragged_static: threads per workgroup (256, 512 or 1024, at least
+ * width/8) and persistent workgroups per compute unit (1..8; at most as many as
+ * the LDS holds are launched, and of 1024 threads at most two take instances,
+ * the waves of a unit, fewer where two would slow each other down).  Batches of
+ * at most two instances per compute unit run outside the classes and do not
+ * read it.  Returns MP_ERR_ARG for an invalid choice.
  */
 mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
 
@@ -180,7 +182,7 @@ mp_status_t mp_ragged_config(int32_t cls, int32_t threads, int32_t wgs_per_cu);
  * mp_get_knob returns the current value (-1 for an unknown knob).
  */
 enum { MP_KNOB_MFMA_MIN = 0, MP_KNOB_SMALL_LIMIT = 1 };
-/* MP_KNOB_SMALL_LIMIT value: chosen per launch (see above) */
+/* MP_KNOB_SMALL_LIMIT value: the library's own choice (see above) */
 #define MP_SMALL_LIMIT_AUTO (-2)
 mp_status_t mp_set_knob(int32_t knob, int32_t value);
 int32_t mp_get_knob(int32_t knob);
@@ -188,8 +190,9 @@ int32_t mp_get_knob(int32_t knob);
 /*
  * Dynamic LDS bytes per workgroup that a launch needs (host-side query, no
  * device call): MP_OP_MUL with (na, nb), MP_OP_DIVREM with (nu, nv),
- * MP_OP_SHINV with (nv, h); divisions in batches of up to three per compute unit
- * take 12 KB more.  Returns -1 for an unknown op or a width outside
+ * MP_OP_SHINV with (nv, h), as in large batches; divisions and inverses in
+ * batches of up to three per compute unit take 12 KB more (86 KB at most), and
+ * ragged batches what the widest instance of a class takes.  Returns -1 for an unknown op or a width outside
  * [1, mp_max_limbs()].  A launch whose figure exceeds the 160 KB of one
  * gfx950 workgroup returns MP_ERR_SIZE.
  */

@@ -111,7 +111,7 @@ __global__ __launch_bounds__(T) MP_OCCUPANCY void k_ragged_direct(const uint32_t
 
 // Persistent workgroups of one class: take the next instance of the class's
 // queue until it is empty.  Of 1024 threads, only some of the workgroups launched
-// (two per compute unit) stay: one per unit if the instances would not give half
+// stay, at most two per compute unit, which hold all its waves: one per unit if the instances would not give half
 // the units a second one, since two slow each other down (300 of a batch of 1200:
 // 184 us for the batch, in pairs 191); and three on two units beside a class of
 // the next width, whose workgroups then find LDS on every other unit (4096 of

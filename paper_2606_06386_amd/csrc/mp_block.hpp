@@ -14,7 +14,7 @@
 //
 // Against one full-precision inverse followed by u * shinv and v * q (Alg. 1
 // and 3 as printed) this needs no Newton step beyond 257 limbs and fewer limb
-// products (a 2048 by 1024-limb division: 1.2e6 instead of 1.8e6), and every
+// products (a 2048 by 1024-limb division: 1.08e6 instead of 1.78e6), and every
 // operand converted to digits is at most one block long.
 //
 // Error bounds.  With W = B^(k+dp+2)/v - E and |E| <= 3 (see newton),
@@ -305,7 +305,7 @@ MP_DEV uint32_t start_digits(int l, const FV &v, int k, int lz)
 // above: they cancel) times 1 / v' in double precision, to within 2^-2 of r/v':
 // |r| stays below 0.8 v' 2^(-48 t).  It costs about 270 cycles, nearly all of
 // it one dependent chain through scalar and vector units; a Newton step on the matrix core
-// costs 4000 to 5000 however short its operands (its LDS round trips and carry
+// costs 4700 to 5600 however short its operands (its LDS round trips and carry
 // passes), so 25 steps here (37 limbs) beat the five Newton steps from the 112
 // bits of one reciprocal.  (46 limbs are what 63 lanes of 24 bits leave exact to
 // one unit.)  scratch: 64 words.

@@ -10,7 +10,7 @@
 // cycles per fragment pair against 8 matrix-core cycles of a compute unit's
 // four): G = 4 reads 4.5 cycles' worth per product, pairs of strips with one
 // shared fragment 13.  4096 products of 2048 x 2048 limbs: 301 -> 264 us (the
-// matrix cores busy 70% of the time at the 1.65 GHz the chip holds under them),
+// matrix cores busy 67% of the time, at the 1.7 GHz the chip holds under them),
 // 256 of 8192 x 8192: 254 -> 210 us, 2000 of 1531 x 333: 34 -> 25 us.
 //
 // The limbs go from the accumulators to global memory in registers; a strip's

@@ -130,7 +130,8 @@ int threads_for(int width)
 //   8192 x 2000:  256: 78 / - / 62 / 66;    1024: 298 / - / 242 / 221
 //   2048 x 300:   256: 10 / - / 11 / 14;    4096: 65 / - / 60 / 63
 // (A short operand below 1016 limbs leaves four strips no window of fragments:
-// they share single ones, evenly.)
+// they share single ones, evenly.)  The batches' limits are in strips: 24, 32 and
+// 64 for each of the 256 compute units.
 struct MulShape {
     int threads;
     mp::MulKind kind;
